@@ -1,0 +1,229 @@
+// Device helpers shared by the quantization and the GEMM translation units: 16-element units of an
+// activation row, the quantizer's exact quotient and cast, the epilogue's activations.
+#pragma once
+
+#include "qc_internal.h"
+
+namespace qc {
+namespace {
+
+constexpr int kUnit = 16;  // elements handled as one unit: 16 codes = one 16 B store
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+template <bool NT>
+__device__ inline uint4 load16(const void *p) {
+    if constexpr (NT) {
+        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        return make_uint4(v.x, v.y, v.z, v.w);
+    } else {
+        return *reinterpret_cast<const uint4 *>(p);
+    }
+}
+
+template <bool NT>
+__device__ inline void store16(void *p, const uint4 &v) {
+    if constexpr (NT) __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
+    else *reinterpret_cast<uint4 *>(p) = v;
+}
+
+__device__ inline float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
+
+// Eight lanes' share of 128 consecutive columns of a row: 16 elements per lane.  Every load
+// instruction covers whole 128 B lines (8 lanes x 16 B, consecutive), so a lane's elements are pieces
+// of 16 B that lie 128 B apart: bf16 columns 64 j + 8 sub .. + 7 (j = 0, 1), binary32 columns
+// 32 j + 4 sub .. + 3 (j = 0 .. 3), sub the lane's index among the eight.  (With 16 consecutive
+// elements per lane instead, every load instruction touches each line in part, which costs 32 % of
+// the time once the loads are non-temporal: binary32 16384 x 4608, 102 against 70 us.)
+//   load()         columns col0 .. of a row of K (a multiple of 16); past its end the row's last piece
+//                  is read again, which changes no maximum or minimum and is not stored
+//   get(i)         element i of the lane, i = 0 .. 15 in that order, widened to float
+//   gather_codes() turns dwords of four codes each, in that order, into the 16 codes of one unit of
+//                  16 consecutive columns; lane sub gets unit unit_of(sub) of the eight.
+//   absmax_into()  folds the elements' magnitudes into a running maximum, absmax_value() reads it.
+//                  For bf16 it stays two packed 16-bit patterns (magnitudes order like their bit
+//                  patterns): one v_and and one v_pk_max_u16 for two elements, and nothing widened
+//                  that the compiler would then keep in registers up to the cast.
+template <typename XT>
+struct Group;
+
+// the dword of lane ^ 1 (quad_perm [1, 0, 3, 2])
+__device__ inline uint32_t dpp_xor1(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false); }
+// the dword of lane ^ 2 (quad_perm [2, 3, 0, 1])
+__device__ inline uint32_t dpp_xor2(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false); }
+
+template <>
+struct Group<float> {
+    uint4 v[4];
+    template <bool NT>
+    __device__ void load(const float *xrow, int col0, int K, int sub) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int col = col0 + 32 * j + 4 * sub;
+            v[j] = load16<NT>(xrow + (col < K - 4 ? col : K - 4));
+        }
+    }
+    __device__ float get(int i) const {
+        const uint4 &f = v[i >> 2];
+        switch (i & 3) {
+            case 0: return __uint_as_float(f.x);
+            case 1: return __uint_as_float(f.y);
+            case 2: return __uint_as_float(f.z);
+            default: return __uint_as_float(f.w);
+        }
+    }
+    static __device__ int unit_of(int sub) { return 2 * (sub & 3) + (sub >> 2); }
+    // dword j of the four lanes of a quad belongs to one unit: a 4 x 4 transpose inside the quad
+    static __device__ uint4 gather_codes(const uint32_t (&w)[4], int sub) {
+        const bool odd = sub & 1, high = sub & 2;
+        // swap across lane ^ 1: afterwards a[2 p + o] holds dwords of columns j with j % 2 == own parity
+        const uint32_t s0 = dpp_xor1(odd ? w[0] : w[1]), s1 = dpp_xor1(odd ? w[2] : w[3]);
+        const uint32_t a0 = odd ? s0 : w[0], a1 = odd ? w[1] : s0;   // lanes (even, odd) of the pair, dword own parity
+        const uint32_t b0 = odd ? s1 : w[2], b1 = odd ? w[3] : s1;   // the same for dword 2 + own parity
+        const uint32_t t0 = dpp_xor2(high ? a0 : b0), t1 = dpp_xor2(high ? a1 : b1);
+        return high ? make_uint4(t0, t1, b0, b1) : make_uint4(a0, a1, t0, t1);
+    }
+    typedef float Max;
+    __device__ void absmax_into(Max &m) const {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(get(i)));
+    }
+    static __device__ Max no_max() { return 0.0f; }
+    static __device__ float absmax_value(Max m) { return m; }
+};
+
+template <>
+struct Group<uint16_t> {  // bf16 bit patterns
+    uint4 v[2];
+    template <bool NT>
+    __device__ void load(const uint16_t *xrow, int col0, int K, int sub) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int col = col0 + 64 * j + 8 * sub;
+            v[j] = load16<NT>(xrow + (col < K - 8 ? col : K - 8));
+        }
+    }
+    __device__ float get(int i) const {
+        const uint4 &u = v[i >> 3];
+        uint32_t w;
+        switch ((i >> 1) & 3) { case 0: w = u.x; break; case 1: w = u.y; break; case 2: w = u.z; break; default: w = u.w; }
+        return (i & 1) ? bf16_hi(w) : bf16_lo(w);
+    }
+    static __device__ int unit_of(int sub) { return (sub >> 1) + 4 * (sub & 1); }
+    static __device__ uint4 gather_codes(const uint32_t (&w)[4], int sub) {
+        const bool odd = sub & 1;
+        const uint32_t s0 = dpp_xor1(odd ? w[0] : w[2]), s1 = dpp_xor1(odd ? w[1] : w[3]);
+        return odd ? make_uint4(s0, s1, w[2], w[3]) : make_uint4(w[0], w[1], s0, s1);
+    }
+    typedef u16x2 Max;
+    __device__ void absmax_into(Max &m) const {
+        const uint32_t w[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[i] & 0x7fff7fffu));
+    }
+    static __device__ Max no_max() { return u16x2{0, 0}; }
+    static __device__ float absmax_value(Max m) {
+        return __uint_as_float((uint32_t)(m.x > m.y ? m.x : m.y) << 16);
+    }
+};
+
+// 16 consecutive elements of one row, widened to float by get().
+template <typename XT>
+struct Unit;
+
+template <>
+struct Unit<float> {
+    float4 v[4];
+    template <bool NT>
+    __device__ void load(const float *p) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 w = load16<NT>(p + 4 * i);
+            v[i] = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
+        }
+    }
+    __device__ void zero() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __device__ float get(int i) const {
+        const float4 &f = v[i >> 2];
+        switch (i & 3) { case 0: return f.x; case 1: return f.y; case 2: return f.z; default: return f.w; }
+    }
+};
+
+template <>
+struct Unit<uint16_t> {  // bf16 bit patterns
+    uint4 v[2];
+    template <bool NT>
+    __device__ void load(const uint16_t *p) {
+        v[0] = load16<NT>(p);
+        v[1] = load16<NT>(p + 8);
+    }
+    __device__ void zero() { v[0] = v[1] = make_uint4(0, 0, 0, 0); }
+    __device__ float get(int i) const {
+        const uint4 &u = v[i >> 3];
+        uint32_t w;
+        switch ((i >> 1) & 3) { case 0: w = u.x; break; case 1: w = u.y; break; case 2: w = u.z; break; default: w = u.w; }
+        return (i & 1) ? bf16_hi(w) : bf16_lo(w);
+    }
+};
+
+// RN(x / s) from r = RN(1 / s): product, exact residual, one correction.
+__device__ inline float quotient(float x, float s, float r) {
+    const float q = x * r;
+    return fmaf(fmaf(-s, q, x), r, q);
+}
+
+// Four quotients of the symmetric quantizer -> four int8 codes in one dword.  No clamp: with s =
+// RN(a / qmax) and |x| <= a the quotient is at most qmax (1 + 2^-22), which rounds to qmax.  Adding
+// 1.5 * 2^23 rounds to an integer (ties to even) and leaves its two's complement low byte in the
+// low byte of the float.
+__device__ inline uint32_t codes4(float q0, float q1, float q2, float q3) {
+    const float magic = 12582912.0f;
+    const uint32_t y0 = __float_as_uint(q0 + magic), y1 = __float_as_uint(q1 + magic);
+    const uint32_t y2 = __float_as_uint(q2 + magic), y3 = __float_as_uint(q3 + magic);
+    const uint32_t lo = __builtin_amdgcn_perm(y1, y0, 0x0c0c0400u);  // [y0.b0, y1.b0, 0, 0]
+    const uint32_t hi = __builtin_amdgcn_perm(y3, y2, 0x04000c0cu);  // [0, 0, y2.b0, y3.b0]
+    return lo | hi;
+}
+
+__device__ inline float scale_of(float absmax, float qmax) { return fmaxf(absmax, kAbsmaxFloor) / qmax; }
+
+__device__ inline float gelu_tanh_f(float y) {
+    // 0.5 y (1 + tanh(u)) = y / (1 + exp(-2u)),  u = sqrt(2/pi) (y + 0.044715 y^3)
+    const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;  // -2 sqrt(2/pi) log2(e)
+    const float c2 = c1 * 0.044715f;
+    const float t = y * fmaf(c2, y * y, c1);
+    return y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
+}
+
+// 0.5 y (1 + erf(y / sqrt 2)) with erfc(x) = t (a1 + t (a2 + .. a5 t)) exp(-x^2), t = 1 / (1 + p x)
+// for x >= 0 (Abramowitz and Stegun 7.1.26, absolute error below 1.5e-7) and erf odd.  For
+// negative y the product form keeps the small result's relative accuracy.  Far fewer registers
+// than the math library's erff, which matters next to 128 live accumulators.
+__device__ inline float gelu_erf_f(float y) {
+    const float x = fabsf(y) * 0.70710678118654752f;
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
+    float p = fmaf(1.061405429f, t, -1.453152027f);
+    p = fmaf(p, t, 1.421413741f);
+    p = fmaf(p, t, -0.284496736f);
+    p = fmaf(p, t, 0.254829592f);
+    const float q = p * t * __builtin_amdgcn_exp2f(x * x * -1.4426950408889634f);  // erfc(x)
+    const float gate = y >= 0.0f ? 2.0f - q : q;
+    return 0.5f * y * gate;
+}
+
+// two floats -> two bf16 (round to nearest even), one v_cvt_pk_bf16_f32
+__device__ inline uint32_t pack_bf16x2(float lo, float hi) {
+    typedef float f2v __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
+    const f2v v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2v));
+}
+
+}  // namespace
+}  // namespace qc

@@ -26,17 +26,15 @@
 // panels out of the L2.
 #include <type_traits>
 
-#include "qc_internal.h"
+#include "qc_device.h"
 
 namespace qc {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 constexpr int kStages = 3;   // LDS ring of weight stages (4 and 6 were measured: 1.5 % and 3 % slower)
@@ -73,36 +71,6 @@ __device__ inline void lds_dma_16(const uint8_t *gsrc, uint8_t *lds_dst) {
     __builtin_amdgcn_global_load_lds(
         (const __attribute__((address_space(1))) void *)gsrc,
         (__attribute__((address_space(3))) void *)lds_dst, 16, 0, 0);
-}
-
-__device__ inline float gelu_tanh_f(float y) {
-    // 0.5 y (1 + tanh(u)) = y / (1 + exp(-2u)),  u = sqrt(2/pi) (y + 0.044715 y^3)
-    const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;  // -2 sqrt(2/pi) log2(e)
-    const float c2 = c1 * 0.044715f;
-    const float t = y * fmaf(c2, y * y, c1);
-    return y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-
-// 0.5 y (1 + erf(y / sqrt 2)) with erfc(x) = t (a1 + t (a2 + .. a5 t)) exp(-x^2), t = 1 / (1 + p x)
-// for x >= 0 (Abramowitz and Stegun 7.1.26, absolute error below 1.5e-7) and erf odd.  For
-// negative y the product form keeps the small result's relative accuracy.  Far fewer registers
-// than the math library's erff, which matters next to 128 live accumulators.
-__device__ inline float gelu_erf_f(float y) {
-    const float x = fabsf(y) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-    float p = fmaf(1.061405429f, t, -1.453152027f);
-    p = fmaf(p, t, 1.421413741f);
-    p = fmaf(p, t, -0.284496736f);
-    p = fmaf(p, t, 0.254829592f);
-    const float q = p * t * __builtin_amdgcn_exp2f(x * x * -1.4426950408889634f);  // erfc(x)
-    const float gate = y >= 0.0f ? 2.0f - q : q;
-    return 0.5f * y * gate;
-}
-
-// two floats -> two bf16 (round to nearest even), one v_cvt_pk_bf16_f32
-__device__ inline uint32_t pack_bf16x2(float lo, float hi) {
-    const f2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2));
 }
 
 // Map the launch's block index to a tile so that the blocks resident on one XCD at a time

@@ -2,9 +2,10 @@
 // parameters computed online; Section 3.1 Eq. (3)-(4) in symmetric signed form).
 //
 // HBM-bound: every element of X is read once and one int8 code is written.  A row is held in
-// registers between the absmax pass and the cast, so there is no second read.  Blocks are
-// small (one wavefront per 1152 columns of 8 rows) and many per CU, so that the load,
-// arithmetic and store phases of different blocks overlap.
+// registers between the absmax pass and the cast, so there is no second read.  Wavefronts are short
+// (at most 384 columns of 8 rows up to K = 6144) and many per CU, so that the load, arithmetic and
+// store phases of different rows overlap; on few rows, where nothing fills the chip, a wavefront's
+// own chain of instructions is what the call waits for, and it is made shorter still.
 //
 // The quotient x / s is the correctly rounded IEEE one, computed without a division per
 // element: with r = RN(1 / s) (one true division per row) and q0 = RN(x * r), the residual
@@ -14,85 +15,21 @@
 // binary32 ones, constructed near-ties and the scales whose significand is all ones).
 #include <type_traits>
 
-#include "qc_internal.h"
+#include "qc_device.h"
 
 namespace qc {
 namespace {
 
 constexpr int kGenericThreads = 256;
-constexpr int kUnit = 16;          // elements handled as one unit: 16 codes = one 16 B store
-constexpr int kUnitsPerThread = 9; // units held by one lane
 
 // How a kernel treats the caches on its one pass (picked per call by cache_policy()): the chip's
 // last-level cache in front of HBM holds 256 MiB, and what the pass leaves in it decides whether
 // the GEMM that follows finds the codes there.
 enum CachePolicy {
     kCachePlain = 0,    // input and codes both fit: ordinary loads and stores
-    kStreamLoads = 1,   // the codes fit, not the input beside them: non-temporal loads of X
-    kStreamStores = 2,  // the codes do not fit either: non-temporal stores of the codes
-};
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <bool NT>
-__device__ inline uint4 load16(const void *p) {
-    if constexpr (NT) {
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-        return make_uint4(v.x, v.y, v.z, v.w);
-    } else {
-        return *reinterpret_cast<const uint4 *>(p);
-    }
-}
-
-template <bool NT>
-__device__ inline void store16(void *p, const uint4 &v) {
-    if constexpr (NT) __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
-    else *reinterpret_cast<uint4 *>(p) = v;
-}
-
-__device__ inline float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-
-// 16 elements of one row, widened to float.
-template <typename XT>
-struct Unit;
-
-template <>
-struct Unit<float> {
-    float4 v[4];
-    template <bool NT>
-    __device__ void load(const float *p) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint4 w = load16<NT>(p + 4 * i);
-            v[i] = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
-        }
-    }
-    __device__ void zero() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __device__ float get(int i) const {
-        const float4 &f = v[i >> 2];
-        switch (i & 3) { case 0: return f.x; case 1: return f.y; case 2: return f.z; default: return f.w; }
-    }
-};
-
-template <>
-struct Unit<uint16_t> {  // bf16 bit patterns
-    uint4 v[2];
-    template <bool NT>
-    __device__ void load(const uint16_t *p) {
-        v[0] = load16<NT>(p);
-        v[1] = load16<NT>(p + 8);
-    }
-    __device__ void zero() { v[0] = v[1] = make_uint4(0, 0, 0, 0); }
-    __device__ float get(int i) const {
-        const uint4 &u = v[i >> 3];
-        uint32_t w;
-        switch ((i >> 1) & 3) { case 0: w = u.x; break; case 1: w = u.y; break; case 2: w = u.z; break; default: w = u.w; }
-        return (i & 1) ? bf16_hi(w) : bf16_lo(w);
-    }
+    kStreamLoads = 1,   // non-temporal loads of X
+    kStreamStores = 2,  // non-temporal stores of the codes
+    kStreamBoth = 3,
 };
 
 // code = clamp(rne(x / s), -qmax, qmax): true IEEE division, then round half to even.
@@ -101,28 +38,6 @@ __device__ inline int quant_code(float x, float s, float qmax) {
     r = fminf(fmaxf(r, -qmax), qmax);
     return (int)r;
 }
-
-// RN(x / s) from r = RN(1 / s): product, exact residual, one correction.
-__device__ inline float quotient(float x, float s, float r) {
-    const float q = x * r;
-    return fmaf(fmaf(-s, q, x), r, q);
-}
-
-// Four quotients -> four int8 codes in one dword.  Clamping to [-qmax, qmax] before rounding
-// equals rounding then clamping; adding 1.5 * 2^23 rounds to an integer (ties to even) and
-// leaves its two's complement low byte in the low byte of the float.
-__device__ inline uint32_t codes4(float q0, float q1, float q2, float q3, float qmax) {
-    const float magic = 12582912.0f;
-    const uint32_t y0 = __float_as_uint(__builtin_amdgcn_fmed3f(q0, -qmax, qmax) + magic);
-    const uint32_t y1 = __float_as_uint(__builtin_amdgcn_fmed3f(q1, -qmax, qmax) + magic);
-    const uint32_t y2 = __float_as_uint(__builtin_amdgcn_fmed3f(q2, -qmax, qmax) + magic);
-    const uint32_t y3 = __float_as_uint(__builtin_amdgcn_fmed3f(q3, -qmax, qmax) + magic);
-    const uint32_t lo = __builtin_amdgcn_perm(y1, y0, 0x0c0c0400u);  // [y0.b0, y1.b0, 0, 0]
-    const uint32_t hi = __builtin_amdgcn_perm(y3, y2, 0x04000c0cu);  // [0, 0, y2.b0, y3.b0]
-    return lo | hi;
-}
-
-__device__ inline float scale_of(float absmax, float qmax) { return fmaxf(absmax, kAbsmaxFloor) / qmax; }
 
 // One scale for a whole activation tensor (Section 4.1 "Quantization Scheme": activation
 // quantization per layer, parameters computed online): a first launch leaves the absmax of up to
@@ -182,25 +97,30 @@ __global__ __launch_bounds__(kSlabThreads) void tensor_absmax_kernel(const XT *_
     }
 }
 
-// 8 lanes share a row and a wavefront holds 8 rows x 1152 columns (72 units of 16, 9 per lane)
-// in registers, so that every 16 B store of the fragment layout completes a 128 B line (8 rows
-// x 16 B) within one instruction.  Longer rows are cut into column slices of 1152, one
-// wavefront of the block per slice; the slices agree on the row absmax through LDS.  Needs
-// K % 16 == 0 and K <= 8 slices.
+// 8 lanes share a row and a wavefront holds 8 rows x 8 UPT units of 16 columns in registers (UPT
+// units per lane, picked by units_per_lane()), so that every 16 B store of the fragment
+// layout completes a 128 B line (8 rows x 16 B) within one instruction.  A row is cut into column
+// slices of that width, one wavefront of the block per slice; the slices agree on the row absmax
+// through LDS.  Needs K % 16 == 0 and K <= 9216.
 constexpr int kLanesPerRow = 8;
 constexpr int kRowsPerBlock = 64 / kLanesPerRow;
-constexpr int kUnitsPerSlice = kLanesPerRow * kUnitsPerThread;  // 72 units = 1152 columns
-constexpr int kMaxSlices = 8;
+constexpr int kGroup = kLanesPerRow * kUnit;      // 128 columns: what the lanes of a row hold per step
+constexpr int kUnitsMost = 9 * kLanesPerRow * 8;  // units of the longest row: 8 slices at UPT = 9
+
+// Most wavefronts of a block: with 9 units per lane a wavefront holds 1152 columns and uses most of
+// its registers; with fewer units the block takes up to 16 wavefronts.
+template <int UPT>
+constexpr int kMaxSlices = UPT == 9 ? 8 : 16;
 
 // TENSOR: the absmax comes from `tmax` (one scale for the whole tensor).  A template parameter
 // rather than a test of tmax.partials, so that the per-token kernel is compiled exactly as if
 // the other did not exist.
-template <typename XT, bool TENSOR, int POLICY>
-__global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_kernel(
+template <typename XT, bool TENSOR, int POLICY, int UPT>
+__global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, int8_t *__restrict__ qx,
     uint8_t *__restrict__ qx_tiled, int64_t KF, float *__restrict__ x_scale, float qmax,
     TensorMax tmax) {
-    __shared__ float slice_max[kMaxSlices][kRowsPerBlock];
+    __shared__ float slice_max[kMaxSlices<UPT>][kRowsPerBlock];
     const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, slices = blockDim.x >> 6;
     const int sub = lane % kLanesPerRow, row_in_block = lane / kLanesPerRow;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + row_in_block;
@@ -208,22 +128,20 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_kernel(
     const bool live = row < M;
     const XT *xrow = X + (live ? row : 0) * K;
 
-    Unit<XT> u[kUnitsPerThread];
+    Group<XT> u[UPT];
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
-        if (live && ui < units) u[i].template load<POLICY == kStreamLoads>(xrow + (int64_t)ui * kUnit);
-        else u[i].zero();
+    for (int i = 0; i < UPT; ++i) {
+        u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
     }
 
     float a = 0.0f;
     if (TENSOR) {  // one scale for the whole tensor: its absmax was reduced beforehand
         a = tensor_absmax(tmax, lane);
     } else {
+        auto running = Group<XT>::no_max();
 #pragma unroll
-        for (int i = 0; i < kUnitsPerThread; ++i)
-#pragma unroll
-            for (int e = 0; e < kUnit; ++e) a = fmaxf(a, fabsf(u[i].get(e)));
+        for (int i = 0; i < UPT; ++i) u[i].absmax_into(running);
+        a = Group<XT>::absmax_value(running);
 #pragma unroll
         for (int d = 1; d < kLanesPerRow; d <<= 1) a = fmaxf(a, __shfl_xor(a, d));
         if (slices > 1) {  // uniform over the block
@@ -245,19 +163,21 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_kernel(
     int8_t *out_rows = qx ? qx + row * K : nullptr;
     uint8_t *out_tiled = qx_tiled ? qx_tiled + act_frag_offset(row, 0, KF) : nullptr;
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
-        if (ui >= units) continue;
+    for (int i = 0; i < UPT; ++i) {
+        const int ui0 = (slice * UPT + i) * kLanesPerRow;   // first unit of the group
+        if (ui0 >= units) break;                            // the same for all lanes
         uint32_t w[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
             w[d] = codes4(quotient(u[i].get(4 * d + 0), s, r), quotient(u[i].get(4 * d + 1), s, r),
-                          quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r), qmax);
-        const uint4 out = make_uint4(w[0], w[1], w[2], w[3]);
-        if (out_rows) store16<POLICY == kStreamStores>(out_rows + (int64_t)ui * kUnit, out);
+                          quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r));
+        const uint4 out = Group<XT>::gather_codes(w, sub);
+        const int ui = ui0 + Group<XT>::unit_of(sub);
+        if (ui >= units) continue;
+        if (out_rows) store16<(POLICY & kStreamStores) != 0>(out_rows + (int64_t)ui * kUnit, out);
         // unit ui covers k = 16 ui ..: 64-k stage ui / 4, k quarter ui % 4 (see act_frag_offset)
         if (out_tiled)
-            store16<POLICY == kStreamStores>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
+            store16<(POLICY & kStreamStores) != 0>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
     }
 }
 
@@ -284,11 +204,11 @@ __device__ inline float dpp_xor4(float v) {
     return __int_as_float(t);
 }
 
-template <typename XT, int POLICY>
-__global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_rot_kernel(
+template <typename XT, int POLICY, int UPT>
+__global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, int8_t *__restrict__ qx,
     uint8_t *__restrict__ qx_tiled, int64_t KF, float *__restrict__ x_scale, float qmax, int rot) {
-    __shared__ float slice_max[kMaxSlices][kRowsPerBlock];
+    __shared__ float slice_max[kMaxSlices<UPT>][kRowsPerBlock];
     const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, slices = blockDim.x >> 6;
     const int sub = lane % kLanesPerRow, row_in_block = lane / kLanesPerRow;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + row_in_block;
@@ -296,11 +216,11 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_rot_kernel(
     const bool live = row < M;
     const XT *xrow = X + (live ? row : 0) * K;
 
-    Unit<XT> u[kUnitsPerThread];
+    Unit<XT> u[UPT];
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
-        if (live && ui < units) u[i].template load<POLICY == kStreamLoads>(xrow + (int64_t)ui * kUnit);
+    for (int i = 0; i < UPT; ++i) {
+        const int ui = slice * (UPT * kLanesPerRow) + i * kLanesPerRow + sub;
+        if (live && ui < units) u[i].template load<(POLICY & kStreamLoads) != 0>(xrow + (int64_t)ui * kUnit);
         else u[i].zero();
     }
 
@@ -308,10 +228,10 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_rot_kernel(
     // fma(sign, own, other) is own + other below and other - own above, one rounding either way
     const float sg1 = (sub & 1) ? -1.0f : 1.0f, sg2 = (sub & 2) ? -1.0f : 1.0f,
                 sg4 = (sub & 4) ? -1.0f : 1.0f;
-    float f[kUnitsPerThread][kUnit];
+    float f[UPT][kUnit];
     float a = 0.0f;
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
+    for (int i = 0; i < UPT; ++i) {
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) f[i][e] = u[i].get(e);
 #pragma unroll
@@ -354,18 +274,18 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_rot_kernel(
     int8_t *out_rows = qx ? qx + row * K : nullptr;
     uint8_t *out_tiled = qx_tiled ? qx_tiled + act_frag_offset(row, 0, KF) : nullptr;
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
+    for (int i = 0; i < UPT; ++i) {
+        const int ui = slice * (UPT * kLanesPerRow) + i * kLanesPerRow + sub;
         if (ui >= units) continue;
         uint32_t w[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
             w[d] = codes4(quotient(f[i][4 * d + 0], s, r), quotient(f[i][4 * d + 1], s, r),
-                          quotient(f[i][4 * d + 2], s, r), quotient(f[i][4 * d + 3], s, r), qmax);
+                          quotient(f[i][4 * d + 2], s, r), quotient(f[i][4 * d + 3], s, r));
         const uint4 out = make_uint4(w[0], w[1], w[2], w[3]);
-        if (out_rows) store16<POLICY == kStreamStores>(out_rows + (int64_t)ui * kUnit, out);
+        if (out_rows) store16<(POLICY & kStreamStores) != 0>(out_rows + (int64_t)ui * kUnit, out);
         if (out_tiled)
-            store16<POLICY == kStreamStores>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
+            store16<(POLICY & kStreamStores) != 0>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
     }
 }
 
@@ -375,12 +295,12 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_rot_kernel(
 // exact for these larger quotients as well, checked on the host).  `shifted` selects what is
 // stored: the canonical unsigned code and z, or, for the GEMM, code - shift as a signed byte
 // and the correction shift - z (shift = asym_code_shift(act_bits)).
-template <typename XT, int POLICY>
-__global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_asym_kernel(
+template <typename XT, int POLICY, int UPT>
+__global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_asym_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, uint8_t *__restrict__ qx,
     uint8_t *__restrict__ qx_tiled, int64_t KF, float *__restrict__ x_scale,
     float *__restrict__ x_aux, float levels, float shift, bool shifted) {
-    __shared__ float slice_lo[kMaxSlices][kRowsPerBlock], slice_hi[kMaxSlices][kRowsPerBlock];
+    __shared__ float slice_lo[kMaxSlices<UPT>][kRowsPerBlock], slice_hi[kMaxSlices<UPT>][kRowsPerBlock];
     const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, slices = blockDim.x >> 6;
     const int sub = lane % kLanesPerRow, row_in_block = lane / kLanesPerRow;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + row_in_block;
@@ -388,25 +308,19 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_asym_kernel(
     const bool live = row < M;
     const XT *xrow = X + (live ? row : 0) * K;
 
-    Unit<XT> u[kUnitsPerThread];
+    Group<XT> u[UPT];
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
-        if (live && ui < units) u[i].template load<POLICY == kStreamLoads>(xrow + (int64_t)ui * kUnit);
-        else u[i].zero();
+    for (int i = 0; i < UPT; ++i) {
+        u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
     }
 
-    // units past the end of the row hold zeros, which must not enter the minimum or maximum
     float lo = __builtin_inff(), hi = -__builtin_inff();
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
-        if (ui < units) {
+    for (int i = 0; i < UPT; ++i) {
 #pragma unroll
-            for (int e = 0; e < kUnit; ++e) {
-                lo = fminf(lo, u[i].get(e));
-                hi = fmaxf(hi, u[i].get(e));
-            }
+        for (int e = 0; e < kUnit; ++e) {
+            lo = fminf(lo, u[i].get(e));
+            hi = fmaxf(hi, u[i].get(e));
         }
     }
 #pragma unroll
@@ -439,9 +353,9 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_asym_kernel(
     uint8_t *out_rows = qx ? qx + row * K : nullptr;
     uint8_t *out_tiled = qx_tiled ? qx_tiled + act_frag_offset(row, 0, KF) : nullptr;
 #pragma unroll
-    for (int i = 0; i < kUnitsPerThread; ++i) {
-        const int ui = slice * kUnitsPerSlice + i * kLanesPerRow + sub;
-        if (ui >= units) continue;
+    for (int i = 0; i < UPT; ++i) {
+        const int ui0 = (slice * UPT + i) * kLanesPerRow;   // first unit of the group
+        if (ui0 >= units) break;                            // the same for all lanes
         uint32_t w[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
@@ -453,10 +367,12 @@ __global__ __launch_bounds__(64 * kMaxSlices) void quant_rows_asym_kernel(
             }
             w[d] = __builtin_amdgcn_perm(y[1], y[0], 0x0c0c0400u) | __builtin_amdgcn_perm(y[3], y[2], 0x04000c0cu);
         }
-        const uint4 out = make_uint4(w[0], w[1], w[2], w[3]);
-        if (out_rows) store16<POLICY == kStreamStores>(out_rows + (int64_t)ui * kUnit, out);
+        const uint4 out = Group<XT>::gather_codes(w, sub);
+        const int ui = ui0 + Group<XT>::unit_of(sub);
+        if (ui >= units) continue;
+        if (out_rows) store16<(POLICY & kStreamStores) != 0>(out_rows + (int64_t)ui * kUnit, out);
         if (out_tiled)
-            store16<POLICY == kStreamStores>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
+            store16<(POLICY & kStreamStores) != 0>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
     }
 }
 
@@ -496,47 +412,65 @@ __global__ __launch_bounds__(kGenericThreads) void quant_rows_generic_kernel(
     }
 }
 
-// Measured with bf16 input at K = 1152 and 4608 (whole qc_qlinear, GEMM included): up to 226 MB
-// of input plus codes ordinary accesses are the fastest (non-temporal ones 8 % slower on the
-// quantization); from 339 MB on, while the codes alone stay below the cache size, non-temporal
-// loads leave the codes in the cache for the GEMM (M = 131072, K = 1152: quantization 83 -> 75 us,
-// whole call 545 -> 512 us); with more than 256 MiB of codes non-temporal stores win instead
-// (M = 131072, K = 4608: 324 -> 304 us, whole call 848 -> 836 us).
+// Measured with bf16 input, the GEMM that follows included.  While input and codes fit the cache
+// together, ordinary accesses are the fastest (M = 16384, QKV: 68 us against 72 with non-temporal
+// loads; M = 65536, fc1: the same).  Beyond that non-temporal loads leave the codes in the cache for
+// the GEMM (M = 131072, K = 1152: quantization 80 -> 69 us, QKV whole 562 -> 502 us), also while the
+// codes alone are somewhat larger than the cache (302 MB of codes, fc2 with 4-bit weights: 418 us
+// plain, 403 with non-temporal loads, 409 with non-temporal stores as well).  With twice the cache in
+// codes nothing is left of them to find, and non-temporal stores win too (604 MB, fc2: 852 -> 836 us).
 int cache_policy(int64_t M, int64_t K, size_t x_elem_bytes) {
     constexpr int64_t kLastLevelCache = (int64_t)256 << 20;
     const int64_t codes = M * K, input = codes * (int64_t)x_elem_bytes;
-    if (codes > kLastLevelCache) return kStreamStores;
-    if (input + codes > kLastLevelCache) return kStreamLoads;
-    return kCachePlain;
+    if (codes > kLastLevelCache * 3 / 2) return kStreamBoth;
+    return input + codes > kLastLevelCache ? kStreamLoads : kCachePlain;
 }
 
-// calls f(std::integral_constant<int, policy>) for the policy picked at run time
+// Units per lane of the row kernels.  One unit, a wavefront per 128 columns, where a block of 16
+// wavefronts holds the row and the call is bound by latency: a wavefront alone on its SIMD issues an
+// instruction every 8 clocks or so, and nine units are some 1600 of them (K = 1152, M = 1024: 9 units
+// 5.5 us, 3 units 3.6, 1 unit 3.3; equal from M = 8192 on).  Three units otherwise: against nine the
+// registers allow more wavefronts per SIMD and more of them are at different phases (M = 131072,
+// K = 1152: 71.6 -> 68.6 us, K = 4608: 300 -> 292 us).  Nine for the rows 16 x 384 columns do not cover.
+constexpr int kBlockWaves = 16;
+int units_per_lane(int64_t M, int64_t K) {
+    if (K <= kBlockWaves * kGroup && M * K <= (int64_t)8192 * 1152) return 1;
+    return K <= 3 * kBlockWaves * kGroup ? 3 : 9;
+}
+
+dim3 row_grid(int64_t M) { return dim3((unsigned)((M + kRowsPerBlock - 1) / kRowsPerBlock)); }
+dim3 row_block(int64_t K, int upt) {
+    return dim3((unsigned)(64 * ((K + (int64_t)upt * kGroup - 1) / ((int64_t)upt * kGroup))));
+}
+
+// calls f(policy, units per lane), both std::integral_constant, for the pair picked at run time
 template <typename F>
-hipError_t with_policy(int policy, F &&f) {
-    switch (policy) {
-        case kStreamLoads: return f(std::integral_constant<int, kStreamLoads>{});
-        case kStreamStores: return f(std::integral_constant<int, kStreamStores>{});
-        default: return f(std::integral_constant<int, kCachePlain>{});
-    }
+void with_row_variant(int64_t M, int64_t K, size_t x_elem_bytes, F &&f) {
+    const int upt = units_per_lane(M, K), policy = cache_policy(M, K, x_elem_bytes);
+    auto with_policy = [&](auto u) {
+        if (policy == kStreamBoth) f(std::integral_constant<int, kStreamBoth>{}, u);
+        else if (policy == kStreamLoads) f(std::integral_constant<int, kStreamLoads>{}, u);
+        else f(std::integral_constant<int, kCachePlain>{}, u);
+    };
+    if (upt == 1) f(std::integral_constant<int, kCachePlain>{}, std::integral_constant<int, 1>{});  // small: plain
+    else if (upt == 3) with_policy(std::integral_constant<int, 3>{});
+    else with_policy(std::integral_constant<int, 9>{});
 }
 
 template <typename XT>
 hipError_t launch_typed(const XT *X, int64_t M, int64_t K, int8_t *qx, uint8_t *qx_tiled,
                         int64_t KF, float *x_scale, float qmax, int rot, TensorMax tmax,
                         hipStream_t stream) {
-    const int64_t units = K / kUnit;
-    const int64_t slices = (units + kUnitsPerSlice - 1) / kUnitsPerSlice;
-    const bool vec = (K % kUnit == 0) && slices <= kMaxSlices;
-    const int policy = cache_policy(M, K, sizeof(XT));
+    const bool vec = quant_vector_path(K);
     if (rot) {
         if (!vec || K % rot) return hipErrorInvalidValue;  // the entry points reject these first
-        const int64_t blocks = (M + kRowsPerBlock - 1) / kRowsPerBlock;
-        return with_policy(policy, [&](auto pol) {
-            quant_rows_rot_kernel<XT, decltype(pol)::value>
-                <<<dim3((unsigned)blocks), dim3((unsigned)(64 * slices)), 0, stream>>>(
+        with_row_variant(M, K, sizeof(XT), [&](auto pol, auto upt) {
+            // plain loads: a lane's 16 consecutive elements make every load touch lines in part
+            quant_rows_rot_kernel<XT, decltype(pol)::value & kStreamStores, decltype(upt)::value>
+                <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
                     X, M, K, qx, qx_tiled, KF, x_scale, qmax, rot);
-            return hipGetLastError();
         });
+        return hipGetLastError();
     }
     if (!vec) {
         const int64_t blocks = (M + 3) / 4;
@@ -544,25 +478,24 @@ hipError_t launch_typed(const XT *X, int64_t M, int64_t K, int8_t *qx, uint8_t *
             X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
         return hipGetLastError();
     }
-    const int64_t blocks = (M + kRowsPerBlock - 1) / kRowsPerBlock;
-    if (tmax.partials) {
+    with_row_variant(M, K, sizeof(XT), [&](auto pol, auto upt) {
         // the tensor was read once already for its absmax: what the caches still hold of it helps
-        quant_rows_kernel<XT, true, kCachePlain><<<dim3((unsigned)blocks), dim3((unsigned)(64 * slices)), 0, stream>>>(
-            X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
-        return hipGetLastError();
-    }
-    return with_policy(policy, [&](auto pol) {
-        quant_rows_kernel<XT, false, decltype(pol)::value>
-            <<<dim3((unsigned)blocks), dim3((unsigned)(64 * slices)), 0, stream>>>(
-                X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
-        return hipGetLastError();
+        if (tmax.partials)
+            quant_rows_kernel<XT, true, kCachePlain, decltype(upt)::value>
+                <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
+                    X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
+        else
+            quant_rows_kernel<XT, false, decltype(pol)::value, decltype(upt)::value>
+                <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
+                    X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
     });
+    return hipGetLastError();
 }
 
 }  // namespace
 
 bool quant_vector_path(int64_t K) {
-    return K % kUnit == 0 && K / kUnit <= (int64_t)kUnitsPerSlice * kMaxSlices;
+    return K % kUnit == 0 && K / kUnit <= kUnitsMost;
 }
 
 hipError_t launch_quant_act_asym(const void *X, qc_dtype xdt, int64_t M, int64_t K, uint8_t *qx_rowmajor,
@@ -570,24 +503,21 @@ hipError_t launch_quant_act_asym(const void *X, qc_dtype xdt, int64_t M, int64_t
                                  int act_bits, bool shifted, hipStream_t stream) {
     if (!quant_vector_path(K)) return hipErrorInvalidValue;  // the entry points reject these first
     const float levels = (float)((1 << act_bits) - 1), shift = (float)asym_code_shift(act_bits);
-    const int64_t slices = (K / kUnit + kUnitsPerSlice - 1) / kUnitsPerSlice;
-    const dim3 grid((unsigned)((M + kRowsPerBlock - 1) / kRowsPerBlock)), block((unsigned)(64 * slices));
-    if (xdt == QC_BF16)
-        return with_policy(cache_policy(M, K, 2), [&](auto pol) {
-            quant_rows_asym_kernel<uint16_t, decltype(pol)::value><<<grid, block, 0, stream>>>(
-                (const uint16_t *)X, M, K, qx_rowmajor, qx_tiled, KF, x_scale, x_aux, levels, shift, shifted);
-            return hipGetLastError();
+    auto launch = [&](const auto *typed) {
+        typedef std::remove_cv_t<std::remove_pointer_t<decltype(typed)>> XT;
+        with_row_variant(M, K, sizeof(XT), [&](auto pol, auto upt) {
+            quant_rows_asym_kernel<XT, decltype(pol)::value, decltype(upt)::value>
+                <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
+                    typed, M, K, qx_rowmajor, qx_tiled, KF, x_scale, x_aux, levels, shift, shifted);
         });
-    return with_policy(cache_policy(M, K, 4), [&](auto pol) {
-        quant_rows_asym_kernel<float, decltype(pol)::value><<<grid, block, 0, stream>>>(
-            (const float *)X, M, K, qx_rowmajor, qx_tiled, KF, x_scale, x_aux, levels, shift, shifted);
         return hipGetLastError();
-    });
+    };
+    return xdt == QC_BF16 ? launch((const uint16_t *)X) : launch((const float *)X);
 }
 
 bool quant_rotation_supported(int64_t K, int rot_block) {
     if (rot_block != 16 && rot_block != 32 && rot_block != 64 && rot_block != 128) return false;
-    return K % rot_block == 0 && K / kUnit <= (int64_t)kUnitsPerSlice * kMaxSlices;
+    return K % rot_block == 0 && quant_vector_path(K);
 }
 
 hipError_t launch_quant_act(const void *X, qc_dtype xdt, int64_t M, int64_t K, int8_t *qx_rowmajor,
