@@ -267,12 +267,14 @@ qc_status qc_debug_workspace_act(const void *workspace, int64_t M, int64_t K, in
                                  float *x_scale, void *stream);
 
 /* Test hooks for the GEMM stage, host only (no device is touched).  The GEMM (Section 4.1
- * "Hardware Implementation") exists as two kernels: one streams the weight tile of a block through
+ * "Hardware Implementation") exists as three kernels: one for outputs too small to fill the chip,
+ * which splits the reduction inside a block, one that streams the weight tile of a block through
  * a ring in LDS, the other keeps a whole 128-channel weight tile resident in LDS and is taken for
  * short reductions (K <= 1152 with 8-bit weights, <= 2304 with 4-bit ones) on problems large
  * enough for its static schedule.
  *   qc_debug_gemm_kernel    which one qc_qlinear_gemm takes for (M, K, N, bits): 1 the ring,
- *                           2 the resident one, 0 if the shape is unsupported
+ *                           2 the resident one, 3 the one for few tokens, 0 if the shape is
+ *                           unsupported
  *   qc_debug_gemm_schedule  the rounds of block `block` (0 .. 255) of the resident kernel for an
  *                           [M, N] output, in the order the block runs them: pairs[2 i] is the
  *                           128-channel tile, pairs[2 i + 1] the 512-token chunk of round i.

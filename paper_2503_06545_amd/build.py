@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqc.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["qc_api.hip", "qc_quant.hip", "qc_pack.hip", "qc_gemm.hip", "qc_delta.hip"]
+SOURCES = ["qc_api.hip", "qc_quant.hip", "qc_pack.hip", "qc_gemm.hip", "qc_small.hip", "qc_delta.hip"]
 ROOFS_SRC = os.path.join(ROOT, "bench", "qc_roofs.hip")
 ROOFS = os.path.join(ROOT, "bench", "qc_roofs")  # stand-alone roofline micro-benchmark
 RESOURCE_REPORT = os.path.join(OBJ_DIR, "kernel_resources.txt")

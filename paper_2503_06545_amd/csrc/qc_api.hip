@@ -155,7 +155,14 @@ qc_status qlinear_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, ActQuan
     QC_TRY(check_workspace_pointer(workspace));
     QC_TRY(check_quant_supported(M, K, how.act_bits, false, how.rot_block));
     QC_TRY(check_gemm_supported(M, K, N, bits));
-    if (workspace_bytes < act_workspace(M, K).total_bytes) return QC_ERR_WORKSPACE;
+    const ActWorkspace ws = act_workspace(M, K);
+    if (workspace_bytes < ws.total_bytes) return QC_ERR_WORKSPACE;
+    if (how.rot_block == 0 && qlinear_small_chosen(M, N, K)) {
+        uint8_t *base = (uint8_t *)workspace;
+        return device_status(launch_qlinear_small(X, xdt, base + ws.scale_bytes, (float *)base,
+                                                  (const uint8_t *)packed, w_scale, bias, Y, M, N, K,
+                                                  how.act_bits, bits, epi, ydt, (hipStream_t)stream));
+    }
     QC_TRY(qlinear_quant_any(X, xdt, M, K, how, workspace, workspace_bytes, stream));
     return qc_qlinear_gemm(workspace, workspace_bytes, M, K, packed, w_scale, bits, N, bias, epi, Y,
                            ydt, stream);
@@ -367,7 +374,8 @@ extern "C" qc_status qc_qlinear_tensor(const void *X, qc_dtype xdt, int64_t M, i
 
 extern "C" int qc_debug_gemm_kernel(int64_t M, int64_t K, int64_t N, int bits) {
     if (M < 1 || K < 1 || N < 1 || check_gemm_supported(M, K, N, bits) != QC_OK) return 0;
-    return gemm_resident_chosen(M, N, K, bits) ? 2 : 1;
+    if (gemm_small_chosen(M, N)) return kGemmSmall;
+    return gemm_resident_chosen(M, N, K, bits) ? kGemmResident : kGemmRing;
 }
 
 extern "C" int qc_debug_gemm_schedule(int64_t M, int64_t N, int block, int32_t *pairs, int cap) {

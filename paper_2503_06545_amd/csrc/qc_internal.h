@@ -231,12 +231,25 @@ __host__ __device__ inline int resident_block_rounds(int b, int nb, int n_tiles,
     return n;
 }
 
-enum GemmKernel { kGemmAuto = 0, kGemmRing = 1, kGemmResident = 2 };
+enum GemmKernel { kGemmAuto = 0, kGemmRing = 1, kGemmResident = 2, kGemmSmall = 3 };
 // whether a 128-channel weight tile of this reduction length fits the resident kernel's LDS
 bool gemm_resident_fits(int64_t K, int bits);
 // whether launch_gemm picks the resident kernel for this problem by itself
 bool gemm_resident_chosen(int64_t M, int64_t N, int64_t K, int bits);
 int gemm_resident_blocks();
+
+// The kernels for few tokens (qc_small.hip).  gemm_small_chosen: launch_gemm picks them for this
+// problem by itself; qlinear_small_chosen: quantization and GEMM in one launch.
+bool gemm_small_chosen(int64_t M, int64_t N);
+hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
+                             const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
+                             int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
+                             const int32_t *w_rowsum, hipStream_t stream);
+bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K);
+hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale,
+                                const uint8_t *w_packed, const float *w_scale, const float *bias, void *Y,
+                                int64_t M, int64_t N, int64_t K, int act_bits, int bits, qc_epilogue epi,
+                                qc_out ydt, hipStream_t stream);
 
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2503_06545_amd import binding as qc
-from test_gpu_parity import bits_equal, dev, random_x
+from test_gpu_parity import bits_equal, dev, random_x, run_asym_case, run_linear_case
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +32,38 @@ def test_row_quantizers_at_the_edges_of_their_column_slices(M, K, dtype):
         r_ref = oracle.quant_act_rot(x, 16, 8)
         qr, sr = qc.quant_act_t(dev(x), 8, 16)
         assert bits_equal(sr.cpu().numpy(), r_ref[1]) and np.array_equal(qr.cpu().numpy(), r_ref[0])
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N", [
+    (1, 16, 1), (2, 9216, 40), (3, 6144, 33), (16, 1536, 4100), (16, 1552, 70), (17, 1152, 128), (31, 1280, 2050),
+    (32, 1296, 100), (33, 192, 4100), (100, 1152, 4100), (255, 320, 2048), (256, 64, 2050), (512, 208, 2047),
+    (1024, 64, 1024), (1025, 64, 1024), (300, 1000, 131)])
+def test_qlinear_on_few_tokens_at_the_edges_of_its_tiles(M, K, N, bits):
+    """Both sides of every change of tile (16 x 32, 32 x 32, 32 x 64, 64 x 64, then the ring kernel),
+    of the longest rows the one-launch form takes (16 tokens: K = 1536, 32: 1280) and of row counts
+    below a power of two; every quantizer, every output type, channel counts of every store width."""
+    rng = np.random.default_rng(M * 31 + K * 7 + N + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == (3 if M < 1025 else 1)
+    x = random_x(rng, M, K, "bf16")
+    run_linear_case(x, W, b, bits, "gelu_tanh", "bf16")
+    run_linear_case(random_x(rng, M, K, "f32"), W, None, bits, "gelu_erf", "f32", act_bits=6, check_acc=False)
+    if K % 16 == 0:
+        run_linear_case(x, W, b, bits, "none", "f32", rot_block=16, check_acc=False)
+        run_asym_case(x, W, b, bits, "none", "bf16")
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("N", [129, 130, 132, 136])
+def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
+    """The kernel that streams its weights, whose smallest problems are larger than the few-token
+    kernel's: partial tiles in both directions, channel counts of every store width."""
+    M, K = 16421, 64
+    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    rng = np.random.default_rng(100 * bits + N)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    run_linear_case(random_x(rng, M, K, "f32"), W, b, bits, "none", "f32")
+    run_linear_case(random_x(rng, M, K, "bf16"), W, b, bits, "gelu_tanh", "bf16", check_acc=False)
