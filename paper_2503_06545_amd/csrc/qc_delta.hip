@@ -1,27 +1,32 @@
-// Latent change reduction (Section 3.2 HLC, Eq. (5)): sum|cur - prev| and sum|prev| in one
-// pass over both tensors, deterministic result.
+// The decision reductions: latent change (Section 3.2 HLC, Eq. (5)), cosine similarity of two feature
+// tensors (Section 3.3 SRAP, Eq. (9)), inter-frame gradient norm (second factor of Eq. (5)) and
+// cumulative variation over the previous steps (Eq. (11)).  Each is one pass over its tensors with a
+// deterministic result: groups of four terms are summed in binary32, everything after that in
+// binary64 and in an order that does not depend on scheduling.
 //
-// HBM-bound (8 bytes read per element, 12 bytes written in total).  The grid is at most one
-// block of 1024 threads per CU; a lane has four 16 B loads per tensor in flight (128 KiB per
-// CU), sums four terms in binary32 and carries the running sums in binary64.  Wavefronts
-// combine with DPP moves (no LDS round trips) and every block leaves one partial pair.  A
-// second, single-block launch adds the partial pairs in index order, so the bits do not depend
-// on scheduling.  Single-launch forms were measured and are not faster: the block that arrives
-// last has to see the others' partial sums, and on this chip (one L2 per XCD) that costs either
-// a release fence per block, which writes the L2 back (35 us for 1024 blocks), or stores and
-// arrival counters that go to memory and are waited for one after the other (2.3 us, what the
-// second launch costs).
+// HBM-bound where they are large, bound by launches and dependent round trips where they are small,
+// hence two forms of one kernel:
+//   * Two launches, for large tensors: at most one block per CU (256), every lane with its next
+//     chunk's loads in flight while it sums the present one; a second, single-block launch adds the
+//     blocks' partial sums.
+//   * One launch, for up to 12 MB of input: at most 128 blocks, and the block that sees all partial
+//     sums finishes the job (finish_here() says how, without a counter that somebody would have to
+//     clear).  Latent delta, GPU time: 65536 elements 5.0 -> 4.3 us, 262144 6.0 -> 5.3, 1048576
+//     6.8 -> 6.7, and a launch (3 us of host time) less; at 4194304 the 128 blocks cannot pull enough
+//     (11.7 us against 9.2).
 #include <atomic>
 
-#include "qc_internal.h"
+#include "qc_device.h"
 
 namespace qc {
 namespace {
 
-constexpr int kThreads = 256;       // combine kernels, variation pass
-constexpr int kWideThreads = 1024;  // streaming passes: 16 wavefronts per CU
-constexpr int kMaxBlocks = 256;     // one block per CU
-constexpr int kUnroll = 4;          // float4 loads in flight per tensor per lane
+constexpr int kFinalThreads = 256;  // the second launch: one partial sum tuple per thread
+constexpr int kMaxBlocks = 256;     // two launches: one block per CU
+constexpr int kOneThreads = 512;    // one launch
+constexpr int kOneMaxBlocks = 128;  // their records (a value and its check) fill the same workspace
+constexpr int64_t kOneLaunchBytes = 12 << 20;
+static_assert(kFinalThreads >= kMaxBlocks && kOneThreads >= kOneMaxBlocks, "a thread per block in the combine");
 
 // one DPP move of a binary64 value (two 32-bit halves); CTRL as in the ISA's dpp_ctrl field
 template <int CTRL>
@@ -47,33 +52,8 @@ __device__ inline double wave_sum(double v) {
     return (r[0] + r[1]) + (r[2] + r[3]);
 }
 
-// A reduction reads its tensors once, so it loads them non-temporally: measured against ordinary
-// loads this is 6 % faster on the 33.5 MB latent pair (cold 9.7 -> 9.1 us) and 10-13 % faster from
-// 0.5 GB on (2.1 GB: 5.8 -> 6.6 TB/s), provided every load instruction of a wavefront covers whole
-// lines (a lane stride of 16 B); the exception is the frame gradient, whose second read of every
-// element is meant to hit in the caches.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline float4 stream4f(const float4 *p) {
-    const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-
-__device__ inline uint4 stream4u(const void *p) {
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-__device__ inline float abs4(const float4 &a, const float4 &b) {
-    return (fabsf(a.x - b.x) + fabsf(a.y - b.y)) + (fabsf(a.z - b.z) + fabsf(a.w - b.w));
-}
-__device__ inline float abs4(const float4 &b) {
-    return (fabsf(b.x) + fabsf(b.y)) + (fabsf(b.z) + fabsf(b.w));
-}
-
-// block-wide sums of COUNT values in wavefront order; result valid in thread 0.
-// sh holds COUNT * (THREADS / 64) doubles and may be reused after the call.
+// Block-wide sums of COUNT values, in a fixed order; the result is valid in wavefront 0.  sh holds
+// COUNT * (THREADS / 64) doubles and may be reused after the next barrier.
 template <int THREADS, int COUNT>
 __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -83,87 +63,110 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
         if (lane == 0) sh[COUNT * wave + c] = v[c];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0) {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) v[c] = wave_sum(lane < THREADS / 64 ? sh[COUNT * lane + c] : 0.0);
+    }
+}
+
+// The one-launch form's end.  v: this block's sums, valid in wavefront 0.  Every block publishes its
+// sums as pairs (value, value ^ nonce) with device-scope stores, waits until they are out, and then
+// reads everybody's pairs.  A pair counts once its halves agree with the launch's nonce, whatever the
+// workspace held before, and whichever halves a reader catches.  The block whose stores come last
+// sees all pairs: at least one block finds everything present, forms the totals (every block that
+// does forms the same ones) and clears the checks, so that a replay of this launch from a graph, with
+// the same nonce, finds nothing stale.  Nobody waits for anybody.  Returns whether this block has
+// the totals in v (all threads).
+template <int THREADS, int COUNT>
+__device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *records, uint64_t nonce) {
+    const int tid = threadIdx.x, blocks = gridDim.x;
+    if (tid < 64) {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c)
+            if (tid == c) {
+                uint64_t *r = records + 2 * (COUNT * blockIdx.x + c);
+                const uint64_t bits = (uint64_t)__double_as_longlong(v[c]);
+                __hip_atomic_store(r, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(r + 1, bits ^ nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores have reached memory
+    }
+    __syncthreads();
+    bool present = true;
+    if (tid < kOneMaxBlocks) {
+        const int b = tid < blocks ? tid : 0;
+        uint64_t value[COUNT], check[COUNT];
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
-            double t = sh[c];
-            for (int w = 1; w < THREADS / 64; ++w) t += sh[COUNT * w + c];
-            v[c] = t;
+            uint64_t *r = records + 2 * (COUNT * b + c);
+            value[c] = __hip_atomic_load(r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            check[c] = __hip_atomic_load(r + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+            present = present && (value[c] ^ check[c]) == nonce;
+            v[c] = tid < blocks ? __longlong_as_double((long long)value[c]) : 0.0;
+        }
+    }
+    if (!__syncthreads_and(present)) return false;
+    if (tid < blocks) {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c)
+            __hip_atomic_store(records + 2 * (COUNT * tid + c) + 1, ~nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (tid < kOneMaxBlocks) {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+            v[c] = wave_sum(v[c]);
+            if ((tid & 63) == 0) sh[COUNT * (tid >> 6) + c] = v[c];
         }
     }
     __syncthreads();
-}
-
-// A block takes contiguous chunks of kWideThreads * kUnroll float4 (64 KiB per tensor) and
-// strides over the tensor by the grid; all of a chunk's loads are issued before the first use.
-__global__ __launch_bounds__(kWideThreads) void latent_delta_partial_kernel(
-    const float *__restrict__ cur, const float *__restrict__ prev, int64_t n,
-    double *__restrict__ partials) {
-    __shared__ double sh[2 * (kWideThreads / 64)];
-    const int64_t n4 = n / 4;
-    const float4 *c4 = reinterpret_cast<const float4 *>(cur);
-    const float4 *p4 = reinterpret_cast<const float4 *>(prev);
-    constexpr int64_t kChunk = (int64_t)kWideThreads * kUnroll;
-    double s[2] = {0.0, 0.0};
-    for (int64_t base = (int64_t)blockIdx.x * kChunk; base < n4; base += (int64_t)gridDim.x * kChunk) {
-        float4 a[kUnroll], b[kUnroll];
-        bool ok[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int64_t i = base + u * kWideThreads + threadIdx.x;
-            ok[u] = i < n4;
-            const int64_t j = ok[u] ? i : 0;   // a valid index either way
-            a[u] = stream4f(c4 + j);
-            b[u] = stream4f(p4 + j);
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            if (ok[u]) { s[0] += (double)abs4(a[u], b[u]); s[1] += (double)abs4(b[u]); }
-    }
-    if (blockIdx.x == 0 && threadIdx.x < (int)(n - n4 * 4)) {  // up to 3 trailing elements
-        const int64_t j = n4 * 4 + threadIdx.x;
-        s[0] += (double)fabsf(cur[j] - prev[j]);
-        s[1] += (double)fabsf(prev[j]);
-    }
-    block_sum<kWideThreads, 2>(s, sh);
-    if (threadIdx.x == 0) {
-        partials[2 * blockIdx.x] = s[0];
-        partials[2 * blockIdx.x + 1] = s[1];
-    }
+    for (int c = 0; c < COUNT; ++c) v[c] = sh[c] + sh[COUNT + c];
+    static_assert(kOneMaxBlocks == 128, "two wavefronts hold the records");
+    return true;
 }
 
-// one block: fixed-order combine of the partial pairs, then the ratio
-__global__ __launch_bounds__(kThreads) void latent_delta_final_kernel(
-    const double *__restrict__ partials, int count, float *__restrict__ out3) {
-    __shared__ double sh[2 * (kThreads / 64)];
-    double s[2] = {0.0, 0.0};
-    for (int b = threadIdx.x; b < count; b += kThreads) {
-        s[0] += partials[2 * b];
-        s[1] += partials[2 * b + 1];
-    }
-    block_sum<kThreads, 2>(s, sh);
-    if (threadIdx.x == 0) {
-        const double num = s[0], den = s[1];
-        float rel;
-        if (den > 0.0) rel = (float)(num / den);
-        else rel = num > 0.0 ? __builtin_inff() : 0.0f;
-        out3[0] = (float)num;
-        out3[1] = (float)den;
-        out3[2] = rel;
-    }
+// ---- the passes ------------------------------------------------------------------------------
+// An Op describes one reduction over packs of consecutive elements (16 B per tensor and pack):
+//   kCount, kElems       sums it keeps; elements per pack
+//   kThreads, kUnroll    launch shape of the two-launch form: threads, packs in flight per lane
+//   Regs, load, add      what a pack occupies, how it is read and summed
+//   tail                 one element past the last whole pack
+//   finish               totals -> outputs
+// A reduction reads its tensors once, so it loads them non-temporally: measured against ordinary
+// loads this is 6 % faster on the 33.5 MB latent pair and 10-13 % faster from 0.5 GB on, provided
+// every load instruction of a wavefront covers whole lines (a lane stride of 16 B); the exception is
+// the frame gradient, whose second read of every element is meant to hit in the caches.
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ inline float4 stream4f(const float *p) {
+    const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// ---- cosine similarity of two feature tensors (Section 3.3 SRAP, Eq. (9)) -------------------
-// Same scheme with three running sums: <a, b>, <a, a>, <b, b>.
+__device__ inline float abs4(const float4 &a, const float4 &b) {
+    return (fabsf(a.x - b.x) + fabsf(a.y - b.y)) + (fabsf(a.z - b.z) + fabsf(a.w - b.w));
+}
+__device__ inline float abs4(const float4 &b) {
+    return (fabsf(b.x) + fabsf(b.y)) + (fabsf(b.z) + fabsf(b.w));
+}
 
-// One 16 B load of a float or bf16 tensor (4 or 8 consecutive elements), widened to float.
+// One 16 B piece of a float or bf16 tensor (4 or 8 consecutive elements), widened by get().
 template <typename T>
 struct Pack;
 template <>
 struct Pack<float> {
     static constexpr int kElems = 4;
     float4 v;
-    __device__ void stream(const float *p) { v = stream4f(reinterpret_cast<const float4 *>(p)); }
+    __device__ void stream(const float *p) { v = stream4f(p); }
+    __device__ void load(const float *p) {   // any alignment of p
+        f32x4 t;
+        __builtin_memcpy(&t, p, 16);
+        v = make_float4(t.x, t.y, t.z, t.w);
+    }
     __device__ float get(int i) const {
         switch (i) { case 0: return v.x; case 1: return v.y; case 2: return v.z; default: return v.w; }
     }
@@ -172,250 +175,251 @@ template <>
 struct Pack<uint16_t> {  // bf16 bit patterns
     static constexpr int kElems = 8;
     uint4 v;
-    __device__ void stream(const uint16_t *p) { v = stream4u(p); }
+    __device__ void stream(const uint16_t *p) { v = load16<true>(p); }
+    __device__ void load(const uint16_t *p) {
+        u32x4 t;
+        __builtin_memcpy(&t, p, 16);
+        v = make_uint4(t.x, t.y, t.z, t.w);
+    }
     __device__ float get(int i) const {
         uint32_t w;
         switch (i >> 1) { case 0: w = v.x; break; case 1: w = v.y; break; case 2: w = v.z; break; default: w = v.w; }
-        return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
-    }
-};
-
-// A block takes contiguous chunks of kWideThreads * kUnroll packs per tensor; consecutive lanes
-// take consecutive packs.  Every four consecutive elements are summed in binary32, the sums
-// carried in binary64.
-template <typename T>
-__global__ __launch_bounds__(kWideThreads) void similarity_partial_kernel(
-    const T *__restrict__ a, const T *__restrict__ b, int64_t n, double *__restrict__ partials) {
-    __shared__ double sh[3 * (kWideThreads / 64)];
-    constexpr int E = Pack<T>::kElems;
-    const int64_t packs = n / E;
-    constexpr int64_t kChunk = (int64_t)kWideThreads * kUnroll;
-    double s[3] = {0.0, 0.0, 0.0};  // <a,b>, <a,a>, <b,b>
-    for (int64_t base = (int64_t)blockIdx.x * kChunk; base < packs; base += (int64_t)gridDim.x * kChunk) {
-        Pack<T> x[kUnroll], y[kUnroll];
-        bool ok[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int64_t i = base + u * kWideThreads + threadIdx.x;
-            ok[u] = i < packs;
-            const int64_t j = ok[u] ? i : 0;   // a valid index either way
-            x[u].stream(a + E * j);
-            y[u].stream(b + E * j);
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            if (!ok[u]) continue;
-#pragma unroll
-            for (int g = 0; g < E / 4; ++g) {
-                float pab = 0.f, paa = 0.f, pbb = 0.f;
-#pragma unroll
-                for (int e = 4 * g; e < 4 * g + 4; ++e) {
-                    const float xv = x[u].get(e), yv = y[u].get(e);
-                    pab += xv * yv;
-                    paa += xv * xv;
-                    pbb += yv * yv;
-                }
-                s[0] += (double)pab;
-                s[1] += (double)paa;
-                s[2] += (double)pbb;
-            }
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x < (int)(n - packs * E)) {  // up to E - 1 trailing elements
-        const int64_t j = packs * E + threadIdx.x;
-        float xv, yv;
-        if constexpr (sizeof(T) == 2) {
-            xv = __uint_as_float((uint32_t)a[j] << 16);
-            yv = __uint_as_float((uint32_t)b[j] << 16);
-        } else {
-            xv = a[j];
-            yv = b[j];
-        }
-        s[0] += (double)(xv * yv);
-        s[1] += (double)(xv * xv);
-        s[2] += (double)(yv * yv);
-    }
-    block_sum<kWideThreads, 3>(s, sh);
-    if (threadIdx.x == 0) {
-        partials[3 * blockIdx.x] = s[0];
-        partials[3 * blockIdx.x + 1] = s[1];
-        partials[3 * blockIdx.x + 2] = s[2];
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void similarity_final_kernel(
-    const double *__restrict__ partials, int count, float *__restrict__ out4) {
-    __shared__ double sh[3 * (kThreads / 64)];
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < count; b += kThreads) {
-        s[0] += partials[3 * b]; s[1] += partials[3 * b + 1]; s[2] += partials[3 * b + 2];
-    }
-    block_sum<kThreads, 3>(s, sh);
-    if (threadIdx.x == 0) {
-        const double denom = sqrt(s[1]) * sqrt(s[2]);
-        out4[0] = (float)s[0];
-        out4[1] = (float)s[1];
-        out4[2] = (float)s[2];
-        out4[3] = denom > 0.0 ? (float)(s[0] / denom) : 0.0f;
-    }
-}
-
-// ---- inter-frame gradient norm (Section 3.2 HLC, second factor of Eq. (5)) -----------------
-// The feature map is [frames, inner]; the gradient is the forward difference along the frame
-// axis and the norm is Euclidean.  As a reduction it is a pass over the pair (m, m + inner):
-// every element is read twice, the second time one frame (inner elements) later, which the
-// caches absorb for the frame sizes of a latent.
-
-// 8 consecutive elements of a float or bf16 tensor, widened to float
-template <typename T>
-struct Oct;
-template <>
-struct Oct<float> {
-    float4 lo, hi;
-    __device__ void load(const float *p) {
-        lo = reinterpret_cast<const float4 *>(p)[0];
-        hi = reinterpret_cast<const float4 *>(p)[1];
-    }
-    __device__ float get(int i) const {
-        const float4 &f = i < 4 ? lo : hi;
-        switch (i & 3) { case 0: return f.x; case 1: return f.y; case 2: return f.z; default: return f.w; }
-    }
-};
-template <>
-struct Oct<uint16_t> {  // bf16 bit patterns
-    uint4 v;
-    __device__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
-    __device__ float get(int i) const {
-        uint32_t w;
-        switch (i >> 1) { case 0: w = v.x; break; case 1: w = v.y; break; case 2: w = v.z; break; default: w = v.w; }
-        return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
+        return (i & 1) ? bf16_hi(w) : bf16_lo(w);
     }
 };
 
 __device__ inline float widen(float v) { return v; }
 __device__ inline float widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
-// VEC: inner is a multiple of 8, so both streams can be read 8 elements at a time.
-template <typename T, bool VEC>
-__global__ __launch_bounds__(kWideThreads) void gradient_partial_kernel(
-    const T *__restrict__ m, int64_t inner, int64_t n, double *__restrict__ partials) {
-    __shared__ double sh[kWideThreads / 64];
-    const T *lo = m, *hi = m + inner;
-    double s[1] = {0.0};
-    int64_t done = 0;
-    if constexpr (VEC) {
-        const int64_t n8 = n / 8;
-        constexpr int64_t kChunk = (int64_t)kWideThreads * 2;
-        for (int64_t base = (int64_t)blockIdx.x * kChunk; base < n8; base += (int64_t)gridDim.x * kChunk) {
-            Oct<T> x[2], y[2];
-            const int64_t i0 = base + threadIdx.x, i1 = i0 + kWideThreads;
-            const bool ok[2] = {i0 < n8, i1 < n8};
-            x[0].load(lo + 8 * (ok[0] ? i0 : 0));
-            y[0].load(hi + 8 * (ok[0] ? i0 : 0));
-            x[1].load(lo + 8 * (ok[1] ? i1 : 0));
-            y[1].load(hi + 8 * (ok[1] ? i1 : 0));
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                if (!ok[u]) continue;
-                float p[2] = {0.f, 0.f};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {  // two 4-term binary32 sums
-                    const float d = y[u].get(e) - x[u].get(e);
-                    p[e >> 2] += d * d;
-                }
-                s[0] += (double)p[0] + (double)p[1];
-            }
-        }
-        done = n8 * 8;
+// sum|cur - prev|, sum|prev| -> both and their ratio
+struct DeltaOp {
+    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4;
+    const float *cur, *prev;
+    struct Regs { float4 a, b; };
+    __device__ void load(Regs &r, int64_t i) const { r.a = stream4f(cur + 4 * i); r.b = stream4f(prev + 4 * i); }
+    __device__ void add(const Regs &r, double (&s)[kCount]) const {
+        s[0] += (double)abs4(r.a, r.b);
+        s[1] += (double)abs4(r.b);
     }
-    const int64_t stride = (int64_t)gridDim.x * kWideThreads;
-    for (int64_t j = done + (int64_t)blockIdx.x * kWideThreads + threadIdx.x; j < n; j += stride) {
-        const float d = widen(hi[j]) - widen(lo[j]);
+    __device__ void tail(int64_t j, double (&s)[kCount]) const {
+        s[0] += (double)fabsf(cur[j] - prev[j]);
+        s[1] += (double)fabsf(prev[j]);
+    }
+    __device__ static void finish(const double (&s)[kCount], float *out) {
+        out[0] = (float)s[0];
+        out[1] = (float)s[1];
+        out[2] = s[1] > 0.0 ? (float)(s[0] / s[1]) : s[0] > 0.0 ? __builtin_inff() : 0.0f;
+    }
+};
+
+// <a, b>, <a, a>, <b, b> -> all three and the cosine
+template <typename T>
+struct SimilarityOp {
+    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4;
+    const T *a, *b;
+    struct Regs { Pack<T> x, y; };
+    __device__ void load(Regs &r, int64_t i) const { r.x.stream(a + kElems * i); r.y.stream(b + kElems * i); }
+    __device__ void add(const Regs &r, double (&s)[kCount]) const {
+#pragma unroll
+        for (int g = 0; g < kElems / 4; ++g) {
+            float pab = 0.f, paa = 0.f, pbb = 0.f;
+#pragma unroll
+            for (int e = 4 * g; e < 4 * g + 4; ++e) {
+                const float xv = r.x.get(e), yv = r.y.get(e);
+                pab = fmaf(xv, yv, pab);
+                paa = fmaf(xv, xv, paa);
+                pbb = fmaf(yv, yv, pbb);
+            }
+            s[0] += (double)pab;
+            s[1] += (double)paa;
+            s[2] += (double)pbb;
+        }
+    }
+    __device__ void tail(int64_t j, double (&s)[kCount]) const {
+        const float xv = widen(a[j]), yv = widen(b[j]);
+        s[0] += (double)(xv * yv);
+        s[1] += (double)(xv * xv);
+        s[2] += (double)(yv * yv);
+    }
+    __device__ static void finish(const double (&s)[kCount], float *out) {
+        const double denom = sqrt(s[1]) * sqrt(s[2]);
+        out[0] = (float)s[0];
+        out[1] = (float)s[1];
+        out[2] = (float)s[2];
+        out[3] = denom > 0.0 ? (float)(s[0] / denom) : 0.0f;
+    }
+};
+
+// The feature map is [frames, inner]; the gradient is the forward difference along the frame axis
+// and the norm is Euclidean: a pass over the pair (m, m + inner), of which the second is aligned to
+// its elements only (the hardware takes 16 B loads at any address).
+template <typename T>
+struct GradientOp {
+    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4;
+    const T *m;
+    int64_t inner;
+    struct Regs { Pack<T> x, y; };
+    __device__ void load(Regs &r, int64_t i) const { r.x.load(m + kElems * i); r.y.load(m + inner + kElems * i); }
+    __device__ void add(const Regs &r, double (&s)[kCount]) const {
+#pragma unroll
+        for (int g = 0; g < kElems / 4; ++g) {
+            float p = 0.f;
+#pragma unroll
+            for (int e = 4 * g; e < 4 * g + 4; ++e) {
+                const float d = r.y.get(e) - r.x.get(e);
+                p = fmaf(d, d, p);
+            }
+            s[0] += (double)p;
+        }
+    }
+    __device__ void tail(int64_t j, double (&s)[kCount]) const {
+        const float d = widen(m[inner + j]) - widen(m[j]);
         s[0] += (double)(d * d);
     }
-    block_sum<kWideThreads, 1>(s, sh);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s[0];
-}
-
-__global__ __launch_bounds__(kThreads) void gradient_final_kernel(
-    const double *__restrict__ partials, int count, float *__restrict__ out2) {
-    __shared__ double sh[kThreads / 64];
-    double s[1] = {0.0};
-    for (int b = threadIdx.x; b < count; b += kThreads) s[0] += partials[b];
-    block_sum<kThreads, 1>(s, sh);
-    if (threadIdx.x == 0) {
-        out2[0] = (float)s[0];
-        out2[1] = (float)sqrt(s[0]);
+    __device__ static void finish(const double (&s)[kCount], float *out) {
+        out[0] = (float)s[0];
+        out[1] = (float)sqrt(s[0]);
     }
-}
+};
 
-// ---- cumulative variation over the previous steps (Section 3.3 SRAP, Eq. (11)) --------------
-// L1 distance of the current tensor to each of COUNT earlier ones in one pass: the current
-// tensor is read once, not once per distance.
-
+// L1 distance of the current tensor to each of COUNT earlier ones: the current tensor is read once,
+// not once per distance.
 struct PrevList { const float *p[QC_MAX_PREV]; };
-constexpr int kVarThreads = 512;   // two wavefronts per SIMD: room for 2 (COUNT + 1) float4 per lane
 
 template <int COUNT>
-__global__ __launch_bounds__(kVarThreads) void variation_partial_kernel(
-    const float *__restrict__ cur, PrevList prevs, int64_t n, double *__restrict__ partials) {
-    __shared__ double sh[COUNT * (kVarThreads / 64)];
-    const int64_t n4 = n / 4;
-    const float4 *c4 = reinterpret_cast<const float4 *>(cur);
-    constexpr int64_t kChunk = (int64_t)kVarThreads * 2;
-    double d[COUNT];
+struct VariationOp {
+    // two wavefronts per SIMD: room for 2 x 2 (COUNT + 1) float4 per lane
+    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2;
+    const float *cur;
+    PrevList prevs;
+    struct Regs { float4 a, b[COUNT]; };
+    __device__ void load(Regs &r, int64_t i) const {
+        r.a = stream4f(cur + 4 * i);
 #pragma unroll
-    for (int c = 0; c < COUNT; ++c) d[c] = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * kChunk; base < n4; base += (int64_t)gridDim.x * kChunk) {
-        const int64_t i = base + threadIdx.x;
-        const bool first = i < n4, second = i + kVarThreads < n4;
-        const int64_t i0 = first ? i : 0, i1 = second ? i + kVarThreads : 0;  // valid either way
-        const float4 a0 = stream4f(c4 + i0), a1 = stream4f(c4 + i1);
-        float4 b0[COUNT], b1[COUNT];
+        for (int c = 0; c < COUNT; ++c) r.b[c] = stream4f(prevs.p[c] + 4 * i);
+    }
+    __device__ void add(const Regs &r, double (&s)[kCount]) const {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) s[c] += (double)abs4(r.a, r.b[c]);
+    }
+    __device__ void tail(int64_t j, double (&s)[kCount]) const {
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) s[c] += (double)fabsf(cur[j] - prevs.p[c][j]);
+    }
+    __device__ static void finish(const double (&s)[kCount], float *out) {
+        double total = 0.0;
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
-            const float4 *p4 = reinterpret_cast<const float4 *>(prevs.p[c]);
-            b0[c] = stream4f(p4 + i0);
-            b1[c] = stream4f(p4 + i1);
+            out[c] = (float)s[c];
+            total += s[c];
         }
+        out[COUNT] = (float)total;
+    }
+};
+
+// A block takes contiguous chunks of THREADS * U packs, consecutive lanes consecutive packs, and
+// strides over the tensors by the grid; a chunk's loads are in flight while the one before is summed.
+template <typename Op, int THREADS, int U, bool ONE_LAUNCH>
+__global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, double *__restrict__ partials,
+                                                         float *__restrict__ out, uint64_t nonce) {
+    constexpr int C = Op::kCount;
+    __shared__ double sh[C * (THREADS / 64)];
+    const int64_t packs = n / Op::kElems;
+    constexpr int64_t kChunk = (int64_t)THREADS * U;
+    const int64_t base0 = (int64_t)blockIdx.x * kChunk + threadIdx.x, stride = (int64_t)gridDim.x * kChunk;
+    double s[C];
 #pragma unroll
-        for (int c = 0; c < COUNT; ++c) {
-            if (first) d[c] += (double)abs4(a0, b0[c]);
-            if (second) d[c] += (double)abs4(a1, b1[c]);
+    for (int c = 0; c < C; ++c) s[c] = 0.0;
+    auto load = [&](typename Op::Regs (&r)[U], int64_t base) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = base + u * THREADS;
+            op.load(r[u], i < packs ? i : packs - 1);   // a valid pack either way
+        }
+    };
+    auto add = [&](const typename Op::Regs (&r)[U], int64_t base) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (base + u * THREADS < packs) op.add(r[u], s);
+    };
+    const int64_t first = (int64_t)blockIdx.x * kChunk;   // uniform over the block
+    if (first < packs) {
+        const int64_t chunks = (packs - first + stride - 1) / stride;
+        typename Op::Regs a[U], b[U];
+        load(a, base0);
+        int64_t k = 0;
+        for (; k + 2 < chunks; k += 2) {
+            load(b, base0 + (k + 1) * stride);
+            add(a, base0 + k * stride);
+            load(a, base0 + (k + 2) * stride);
+            add(b, base0 + (k + 1) * stride);
+        }
+        if (k + 1 < chunks) {
+            load(b, base0 + (k + 1) * stride);
+            add(a, base0 + k * stride);
+            add(b, base0 + (k + 1) * stride);
+        } else {
+            add(a, base0 + k * stride);
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x < (int)(n - n4 * 4)) {  // up to 3 trailing elements
-        const int64_t j = n4 * 4 + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x < (int)(n - packs * Op::kElems)) op.tail(packs * Op::kElems + threadIdx.x, s);
+    block_sum<THREADS, C>(s, sh);
+    if constexpr (ONE_LAUNCH) {
+        if (finish_here<THREADS, C>(s, sh, reinterpret_cast<uint64_t *>(partials), nonce) && threadIdx.x == 0)
+            Op::finish(s, out);
+    } else if (threadIdx.x == 0) {
 #pragma unroll
-        for (int c = 0; c < COUNT; ++c) d[c] += (double)fabsf(cur[j] - prevs.p[c][j]);
-    }
-    block_sum<kVarThreads, COUNT>(d, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int c = 0; c < COUNT; ++c) partials[(int64_t)blockIdx.x * QC_MAX_PREV + c] = d[c];
+        for (int c = 0; c < C; ++c) partials[C * blockIdx.x + c] = s[c];
     }
 }
 
-__global__ __launch_bounds__(kThreads) void variation_final_kernel(
-    const double *__restrict__ partials, int blocks, int count, float *__restrict__ out) {
-    __shared__ double sh[kThreads / 64];
-    double total = 0.0;
-    for (int c = 0; c < count; ++c) {
-        double v[1] = {0.0};
-        for (int b = threadIdx.x; b < blocks; b += kThreads) v[0] += partials[(int64_t)b * QC_MAX_PREV + c];
-        block_sum<kThreads, 1>(v, sh);
-        if (threadIdx.x == 0) {
-            out[c] = (float)v[0];
-            total += v[0];
-        }
+// one block: fixed-order combine of the partial sums
+template <typename Op>
+__global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__restrict__ partials, int count,
+                                                              float *__restrict__ out) {
+    constexpr int C = Op::kCount;
+    __shared__ double sh[C * (kFinalThreads / 64)];
+    double s[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) s[c] = (int)threadIdx.x < count ? partials[C * threadIdx.x + c] : 0.0;
+    block_sum<kFinalThreads, C>(s, sh);
+    if (threadIdx.x == 0) Op::finish(s, out);
+}
+
+// a number no earlier launch of this process has used (splitmix64 of a counter)
+uint64_t next_nonce() {
+    static std::atomic<uint64_t> counter{0};
+    uint64_t z = (counter.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+
+// bytes: what one pass reads, for the choice of form
+template <typename Op>
+qc_status launch_reduction(const Op &op, int64_t n, int64_t bytes, float *out, void *workspace, void *stream) {
+    double *partials = (double *)workspace;
+    hipStream_t st = (hipStream_t)stream;
+    auto blocks_for = [&](int64_t chunk, int most) {
+        const int64_t b = (n / Op::kElems + chunk - 1) / chunk;
+        return (unsigned)(b < 1 ? 1 : b > most ? most : b);
+    };
+    if (bytes <= kOneLaunchBytes) {
+        constexpr int U = Op::kCount > 4 ? 1 : 2;
+        reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks_for((int64_t)kOneThreads * U, kOneMaxBlocks)), dim3(kOneThreads), 0, st>>>(
+            op, n, partials, out, next_nonce());
+        return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
     }
-    if (threadIdx.x == 0) out[count] = (float)total;
+    const unsigned blocks = blocks_for((int64_t)Op::kThreads * Op::kUnroll, kMaxBlocks);
+    reduce_kernel<Op, Op::kThreads, Op::kUnroll, false><<<dim3(blocks), dim3(Op::kThreads), 0, st>>>(op, n, partials, nullptr, 0);
+    if (hipGetLastError() != hipSuccess) return QC_ERR_DEVICE;
+    final_kernel<Op><<<dim3(1), dim3(kFinalThreads), 0, st>>>(partials, (int)blocks, out);
+    return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
 }
 
 template <int COUNT>
-void launch_variation(const float *cur, const PrevList &prevs, int64_t n, double *partials,
-                      unsigned blocks, hipStream_t stream) {
-    variation_partial_kernel<COUNT><<<dim3(blocks), dim3(kVarThreads), 0, stream>>>(cur, prevs, n, partials);
+qc_status launch_variation(const float *cur, const PrevList &prevs, int64_t n, float *out, void *workspace, void *stream) {
+    return launch_reduction(VariationOp<COUNT>{cur, prevs}, n, 4 * n * (COUNT + 1), out, workspace, stream);
 }
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -436,17 +440,7 @@ extern "C" qc_status qc_latent_delta(const float *cur, const float *prev, int64_
     if (!aligned(cur, 16) || !aligned(prev, 16) || !aligned(out3, 4) || !aligned(workspace, 256))
         return QC_ERR_INVALID_ARG;
     if (workspace_bytes < qc_latent_delta_workspace_bytes(n)) return QC_ERR_WORKSPACE;
-    // one chunk of kWideThreads * kUnroll float4 per block and pass; at most one block per CU
-    int64_t blocks = (n / 4 + (int64_t)kWideThreads * kUnroll - 1) / ((int64_t)kWideThreads * kUnroll);
-    if (blocks < 1) blocks = 1;
-    if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-    double *partials = (double *)workspace;
-    latent_delta_partial_kernel<<<dim3((unsigned)blocks), dim3(kWideThreads), 0, (hipStream_t)stream>>>(
-        cur, prev, n, partials);
-    if (hipGetLastError() != hipSuccess) return QC_ERR_DEVICE;
-    latent_delta_final_kernel<<<dim3(1), dim3(kThreads), 0, (hipStream_t)stream>>>(
-        partials, (int)blocks, out3);
-    return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
+    return launch_reduction(DeltaOp{cur, prev}, n, 8 * n, out3, workspace, stream);
 }
 
 // ---- qc_latent_delta for callers that cannot allocate ---------------------------------------
@@ -497,20 +491,10 @@ extern "C" qc_status qc_layer_similarity(const void *a, const void *b, qc_dtype 
     if (!aligned(a, 16) || !aligned(b, 16) || !aligned(out4, 4) || !aligned(workspace, 256))
         return QC_ERR_INVALID_ARG;
     if (workspace_bytes < qc_layer_similarity_workspace_bytes(n)) return QC_ERR_WORKSPACE;
-    const int64_t packs = n / (dt == QC_BF16 ? 8 : 4);
-    int64_t blocks = (packs + (int64_t)kWideThreads * kUnroll - 1) / ((int64_t)kWideThreads * kUnroll);
-    if (blocks < 1) blocks = 1;
-    if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-    double *partials = (double *)workspace;
-    const dim3 grid((unsigned)blocks), block(kWideThreads);
-    hipStream_t st = (hipStream_t)stream;
     if (dt == QC_BF16)
-        similarity_partial_kernel<uint16_t><<<grid, block, 0, st>>>((const uint16_t *)a, (const uint16_t *)b, n, partials);
-    else
-        similarity_partial_kernel<float><<<grid, block, 0, st>>>((const float *)a, (const float *)b, n, partials);
-    if (hipGetLastError() != hipSuccess) return QC_ERR_DEVICE;
-    similarity_final_kernel<<<dim3(1), dim3(kThreads), 0, (hipStream_t)stream>>>(partials, (int)blocks, out4);
-    return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
+        return launch_reduction(SimilarityOp<uint16_t>{(const uint16_t *)a, (const uint16_t *)b}, n, 4 * n, out4,
+                                workspace, stream);
+    return launch_reduction(SimilarityOp<float>{(const float *)a, (const float *)b}, n, 8 * n, out4, workspace, stream);
 }
 
 extern "C" size_t qc_frame_gradient_norm_workspace_bytes(int64_t frames, int64_t inner) {
@@ -527,24 +511,9 @@ extern "C" qc_status qc_frame_gradient_norm(const void *m, qc_dtype dt, int64_t 
     if (frames > INT64_MAX / inner) return QC_ERR_INVALID_ARG;
     if (workspace_bytes < qc_frame_gradient_norm_workspace_bytes(frames, inner)) return QC_ERR_WORKSPACE;
     const int64_t n = (frames - 1) * inner;  // number of differences
-    const bool vec = inner % 8 == 0;
-    const int64_t per_block = (int64_t)kWideThreads * (vec ? 16 : 4);
-    int64_t blocks = (n + per_block - 1) / per_block;
-    if (blocks < 1) blocks = 1;
-    if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-    double *partials = (double *)workspace;
-    const dim3 grid((unsigned)blocks), block(kWideThreads);
-    hipStream_t st = (hipStream_t)stream;
-    if (dt == QC_BF16) {
-        if (vec) gradient_partial_kernel<uint16_t, true><<<grid, block, 0, st>>>((const uint16_t *)m, inner, n, partials);
-        else gradient_partial_kernel<uint16_t, false><<<grid, block, 0, st>>>((const uint16_t *)m, inner, n, partials);
-    } else {
-        if (vec) gradient_partial_kernel<float, true><<<grid, block, 0, st>>>((const float *)m, inner, n, partials);
-        else gradient_partial_kernel<float, false><<<grid, block, 0, st>>>((const float *)m, inner, n, partials);
-    }
-    if (hipGetLastError() != hipSuccess) return QC_ERR_DEVICE;
-    gradient_final_kernel<<<dim3(1), dim3(kThreads), 0, st>>>(partials, (int)blocks, out2);
-    return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
+    if (dt == QC_BF16)
+        return launch_reduction(GradientOp<uint16_t>{(const uint16_t *)m, inner}, n, 2 * n, out2, workspace, stream);
+    return launch_reduction(GradientOp<float>{(const float *)m, inner}, n, 4 * n, out2, workspace, stream);
 }
 
 extern "C" size_t qc_cumulative_variation_workspace_bytes(int64_t n, int count) {
@@ -564,23 +533,14 @@ extern "C" qc_status qc_cumulative_variation(const float *cur, const float *cons
         if (c < count && (!prevs[c] || !aligned(prevs[c], 16))) return QC_ERR_INVALID_ARG;
     }
     if (workspace_bytes < qc_cumulative_variation_workspace_bytes(n, count)) return QC_ERR_WORKSPACE;
-    int64_t blocks = (n / 4 + (int64_t)kVarThreads * 2 - 1) / ((int64_t)kVarThreads * 2);
-    if (blocks < 1) blocks = 1;
-    if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-    double *partials = (double *)workspace;
-    hipStream_t st = (hipStream_t)stream;
-    const unsigned g = (unsigned)blocks;
     switch (count) {
-        case 1: launch_variation<1>(cur, list, n, partials, g, st); break;
-        case 2: launch_variation<2>(cur, list, n, partials, g, st); break;
-        case 3: launch_variation<3>(cur, list, n, partials, g, st); break;
-        case 4: launch_variation<4>(cur, list, n, partials, g, st); break;
-        case 5: launch_variation<5>(cur, list, n, partials, g, st); break;
-        case 6: launch_variation<6>(cur, list, n, partials, g, st); break;
-        case 7: launch_variation<7>(cur, list, n, partials, g, st); break;
-        default: launch_variation<8>(cur, list, n, partials, g, st); break;
+        case 1: return launch_variation<1>(cur, list, n, out, workspace, stream);
+        case 2: return launch_variation<2>(cur, list, n, out, workspace, stream);
+        case 3: return launch_variation<3>(cur, list, n, out, workspace, stream);
+        case 4: return launch_variation<4>(cur, list, n, out, workspace, stream);
+        case 5: return launch_variation<5>(cur, list, n, out, workspace, stream);
+        case 6: return launch_variation<6>(cur, list, n, out, workspace, stream);
+        case 7: return launch_variation<7>(cur, list, n, out, workspace, stream);
+        default: return launch_variation<8>(cur, list, n, out, workspace, stream);
     }
-    if (hipGetLastError() != hipSuccess) return QC_ERR_DEVICE;
-    variation_final_kernel<<<dim3(1), dim3(kThreads), 0, st>>>(partials, (int)blocks, count, out);
-    return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
 }

@@ -67,3 +67,57 @@ def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
     run_linear_case(random_x(rng, M, K, "f32"), W, b, bits, "none", "f32")
     run_linear_case(random_x(rng, M, K, "bf16"), W, b, bits, "gelu_tanh", "bf16", check_acc=False)
+
+
+@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 128 * 4096, 128 * 4096 + 5, (12 << 20) // 8, (12 << 20) // 8 + 1])
+def test_reductions_on_both_sides_of_the_one_launch_form(n):
+    """Up to 12 MB of input the block that sees all partial sums finishes (128 blocks at most, one pass
+    of 4096 elements each, more above); beyond that a second launch does.  The workspace holds
+    arbitrary bytes, then what the call before left in it."""
+    rng = np.random.default_rng(n)
+    cur, prev = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
+    ref = np.asarray(oracle.latent_delta(cur, prev), np.float64)
+    ws = torch.randint(0, 256, (qc.qc_latent_delta_workspace_bytes(n),), dtype=torch.uint8, device="cuda")
+    c, p = dev(cur), dev(prev)
+    first = qc.latent_delta_t(c, p, workspace=ws).cpu().numpy()
+    assert np.all(np.abs(first - ref) <= 1e-5 * np.abs(ref))
+    for _ in range(3):
+        assert bits_equal(qc.latent_delta_t(c, p, workspace=ws).cpu().numpy(), first)
+    other = qc.latent_delta_t(p, c, workspace=ws).cpu().numpy()
+    ref = np.asarray(oracle.latent_delta(prev, cur), np.float64)
+    assert np.all(np.abs(other - ref) <= 1e-5 * np.abs(ref))
+
+
+def test_one_launch_reductions_replay_from_a_graph():
+    """A replayed launch carries the same arguments as the time before, the number that marks its
+    partial sums included: every replay has to form its result from its own inputs."""
+    rng = np.random.default_rng(3)
+    n, inner = 65536, 4099
+    a, b = (torch.from_numpy(rng.standard_normal(n).astype(np.float32)).cuda() for _ in range(2))
+    m = torch.from_numpy(rng.standard_normal((16, inner)).astype(np.float32)).cuda()
+    ws = [torch.empty(16384, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    outs = [torch.zeros(k, device="cuda") for k in (3, 4, 2, 4)]
+
+    def step():
+        qc.latent_delta_t(a, b, workspace=ws[0], out3=outs[0])
+        qc.layer_similarity_t(a, b, workspace=ws[1], out4=outs[1])
+        qc.frame_gradient_norm_t(m, workspace=ws[2], out2=outs[2])
+        qc.cumulative_variation_t(a, [b, a, b], workspace=ws[3], out=outs[3])
+
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        step()
+    for k in range(4):
+        a.copy_(torch.from_numpy(rng.standard_normal(n).astype(np.float32)))
+        m.mul_(1.0 + k)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [o.clone() for o in outs]
+        for o in outs:
+            o.zero_()
+        step()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(got, outs)), k
+        ref = np.asarray(oracle.latent_delta(a.cpu().numpy(), b.cpu().numpy()), np.float64)
+        assert np.all(np.abs(got[0].cpu().numpy() - ref) <= 1e-5 * np.abs(ref))
