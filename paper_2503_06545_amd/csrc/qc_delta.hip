@@ -9,11 +9,12 @@
 //   * Two launches, for large tensors: at most one block per CU (256), every lane with its next
 //     chunk's loads in flight while it sums the present one; a second, single-block launch adds the
 //     blocks' partial sums.
-//   * One launch, for up to 12 MB of input: at most 128 blocks, and the block that sees all partial
-//     sums finishes the job (finish_here() says how, without a counter that somebody would have to
-//     clear).  Latent delta, GPU time: 65536 elements 5.0 -> 4.3 us, 262144 6.0 -> 5.3, 1048576
-//     6.8 -> 6.7, and a launch (3 us of host time) less; at 4194304 the 128 blocks cannot pull enough
-//     (11.7 us against 9.2).
+//   * One launch, for up to 12 MB of input: the block that sees all partial sums finishes the job
+//     (finish_here() says how, without a counter that somebody would have to clear).  A launch (3 us
+//     of host time) less, and less time on the GPU while the launch boundary weighs more than the
+//     few blocks whose records fit the workspace.  Calls back to back, two launches against one:
+//     latent delta of 65536 elements 6.3 and 4.7 us, 262144 6.8 and 5.4, 1048576 6.9 and 6.9,
+//     4194304 9.3 and 10.2; variation over 3 tensors of 262144 6.6 and 5.8, of 1048576 6.9 and 7.1.
 #include <atomic>
 
 #include "qc_device.h"
@@ -24,9 +25,17 @@ namespace {
 constexpr int kFinalThreads = 256;  // the second launch: one partial sum tuple per thread
 constexpr int kMaxBlocks = 256;     // two launches: one block per CU
 constexpr int kOneThreads = 512;    // one launch
-constexpr int kOneMaxBlocks = 128;  // their records (a value and its check) fill the same workspace
 constexpr int64_t kOneLaunchBytes = 12 << 20;
-static_assert(kFinalThreads >= kMaxBlocks && kOneThreads >= kOneMaxBlocks, "a thread per block in the combine");
+static_assert(kFinalThreads >= kMaxBlocks && kOneThreads >= kMaxBlocks, "a thread per block in the combine");
+
+// the workspaces: a double per sum and block of the two-launch form
+constexpr size_t kDeltaBytes = kMaxBlocks * 2 * sizeof(double), kSimilarityBytes = kMaxBlocks * 3 * sizeof(double);
+constexpr size_t kGradientBytes = kMaxBlocks * sizeof(double), kVariationBytes = kMaxBlocks * QC_MAX_PREV * sizeof(double);
+// blocks of the one-launch form whose records, the sums and a check word, fit there
+constexpr int one_launch_blocks(size_t bytes, int sums) {
+    const size_t b = bytes / (sizeof(double) * (sums + 1));
+    return b < kMaxBlocks ? (int)b : kMaxBlocks;
+}
 
 // one DPP move of a binary64 value (two 32-bit halves); CTRL as in the ISA's dpp_ctrl field
 template <int CTRL>
@@ -70,51 +79,47 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
 }
 
 // The one-launch form's end.  v: this block's sums, valid in wavefront 0.  Every block publishes its
-// sums as pairs (value, value ^ nonce) with device-scope stores, waits until they are out, and then
-// reads everybody's pairs.  A pair counts once its halves agree with the launch's nonce, whatever the
-// workspace held before, and whichever halves a reader catches.  The block whose stores come last
-// sees all pairs: at least one block finds everything present, forms the totals (every block that
-// does forms the same ones) and clears the checks, so that a replay of this launch from a graph, with
-// the same nonce, finds nothing stale.  Nobody waits for anybody.  Returns whether this block has
-// the totals in v (all threads).
+// sums and a check word, the exclusive or of the (rotated) sums and the launch's nonce, with
+// device-scope stores, waits until they are out, and then reads everybody's.  A block's sums count
+// once they fit their check, whatever the workspace held before, and whichever words a reader
+// catches.  The block whose stores come last sees all of them: at least one block finds everything
+// present, forms the totals (every block that does forms the same ones) and spoils the checks, so
+// that a replay of this launch from a graph, with the same nonce, finds nothing stale.  Nobody waits
+// for anybody.  Returns whether this block has the totals in v (all threads).
+__device__ inline uint64_t rotate(uint64_t x, int n) { return n ? (x << n) | (x >> (64 - n)) : x; }
+
 template <int THREADS, int COUNT>
 __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *records, uint64_t nonce) {
+    constexpr int kWords = COUNT + 1, kWaves = kMaxBlocks / 64;
     const int tid = threadIdx.x, blocks = gridDim.x;
-    if (tid < 64) {
+    if (tid == 0) {
+        uint64_t *r = records + kWords * blockIdx.x, check = nonce;
 #pragma unroll
-        for (int c = 0; c < COUNT; ++c)
-            if (tid == c) {
-                uint64_t *r = records + 2 * (COUNT * blockIdx.x + c);
-                const uint64_t bits = (uint64_t)__double_as_longlong(v[c]);
-                __hip_atomic_store(r, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(r + 1, bits ^ nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int c = 0; c < COUNT; ++c) {
+            const uint64_t bits = (uint64_t)__double_as_longlong(v[c]);
+            __hip_atomic_store(r + c, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            check ^= rotate(bits, c);
+        }
+        __hip_atomic_store(r + COUNT, check, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores have reached memory
     }
     __syncthreads();
     bool present = true;
-    if (tid < kOneMaxBlocks) {
-        const int b = tid < blocks ? tid : 0;
-        uint64_t value[COUNT], check[COUNT];
+    if (tid < kMaxBlocks) {
+        uint64_t *r = records + kWords * (tid < blocks ? tid : 0), word[kWords];
+#pragma unroll
+        for (int c = 0; c < kWords; ++c) word[c] = __hip_atomic_load(r + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t check = word[COUNT];
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
-            uint64_t *r = records + 2 * (COUNT * b + c);
-            value[c] = __hip_atomic_load(r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            check[c] = __hip_atomic_load(r + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            check ^= rotate(word[c], c);
+            v[c] = tid < blocks ? __longlong_as_double((long long)word[c]) : 0.0;
         }
-#pragma unroll
-        for (int c = 0; c < COUNT; ++c) {
-            present = present && (value[c] ^ check[c]) == nonce;
-            v[c] = tid < blocks ? __longlong_as_double((long long)value[c]) : 0.0;
-        }
+        present = check == nonce;
     }
     if (!__syncthreads_and(present)) return false;
-    if (tid < blocks) {
-#pragma unroll
-        for (int c = 0; c < COUNT; ++c)
-            __hip_atomic_store(records + 2 * (COUNT * tid + c) + 1, ~nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (tid < kOneMaxBlocks) {
+    if (tid < blocks) __hip_atomic_store(records + kWords * tid + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < kMaxBlocks) {
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
             v[c] = wave_sum(v[c]);
@@ -123,8 +128,11 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
     }
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < COUNT; ++c) v[c] = sh[c] + sh[COUNT + c];
-    static_assert(kOneMaxBlocks == 128, "two wavefronts hold the records");
+    for (int c = 0; c < COUNT; ++c) {
+        v[c] = sh[c];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) v[c] += sh[COUNT * w + c];
+    }
     return true;
 }
 
@@ -132,6 +140,7 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
 // An Op describes one reduction over packs of consecutive elements (16 B per tensor and pack):
 //   kCount, kElems       sums it keeps; elements per pack
 //   kThreads, kUnroll    launch shape of the two-launch form: threads, packs in flight per lane
+//   kOneUnroll, kBytes   packs in flight in the one-launch form (512 threads); the workspace
 //   Regs, load, add      what a pack occupies, how it is read and summed
 //   tail                 one element past the last whole pack
 //   finish               totals -> outputs
@@ -193,7 +202,8 @@ __device__ inline float widen(uint16_t v) { return __uint_as_float((uint32_t)v <
 
 // sum|cur - prev|, sum|prev| -> both and their ratio
 struct DeltaOp {
-    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4;
+    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2;
+    static constexpr size_t kBytes = kDeltaBytes;
     const float *cur, *prev;
     struct Regs { float4 a, b; };
     __device__ void load(Regs &r, int64_t i) const { r.a = stream4f(cur + 4 * i); r.b = stream4f(prev + 4 * i); }
@@ -215,7 +225,9 @@ struct DeltaOp {
 // <a, b>, <a, a>, <b, b> -> all three and the cosine
 template <typename T>
 struct SimilarityOp {
-    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4;
+    // (1024 threads, 4 packs: 48.3 us on two bf16 tensors of 65536 x 1152; 512 and 2: 47.1)
+    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 2, kOneUnroll = 2;
+    static constexpr size_t kBytes = kSimilarityBytes;
     const T *a, *b;
     struct Regs { Pack<T> x, y; };
     __device__ void load(Regs &r, int64_t i) const { r.x.stream(a + kElems * i); r.y.stream(b + kElems * i); }
@@ -255,7 +267,8 @@ struct SimilarityOp {
 // its elements only (the hardware takes 16 B loads at any address).
 template <typename T>
 struct GradientOp {
-    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4;
+    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4, kOneUnroll = 2;
+    static constexpr size_t kBytes = kGradientBytes;
     const T *m;
     int64_t inner;
     struct Regs { Pack<T> x, y; };
@@ -289,7 +302,8 @@ struct PrevList { const float *p[QC_MAX_PREV]; };
 template <int COUNT>
 struct VariationOp {
     // two wavefronts per SIMD: room for 2 x 2 (COUNT + 1) float4 per lane
-    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2;
+    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1;
+    static constexpr size_t kBytes = kVariationBytes;
     const float *cur;
     PrevList prevs;
     struct Regs { float4 a, b[COUNT]; };
@@ -405,9 +419,9 @@ qc_status launch_reduction(const Op &op, int64_t n, int64_t bytes, float *out, v
         return (unsigned)(b < 1 ? 1 : b > most ? most : b);
     };
     if (bytes <= kOneLaunchBytes) {
-        constexpr int U = Op::kCount > 4 ? 1 : 2;
-        reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks_for((int64_t)kOneThreads * U, kOneMaxBlocks)), dim3(kOneThreads), 0, st>>>(
-            op, n, partials, out, next_nonce());
+        constexpr int U = Op::kOneUnroll;
+        const unsigned blocks = blocks_for((int64_t)kOneThreads * U, one_launch_blocks(Op::kBytes, Op::kCount));
+        reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks), dim3(kOneThreads), 0, st>>>(op, n, partials, out, next_nonce());
         return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
     }
     const unsigned blocks = blocks_for((int64_t)Op::kThreads * Op::kUnroll, kMaxBlocks);
@@ -431,7 +445,7 @@ using namespace qc;
 
 extern "C" size_t qc_latent_delta_workspace_bytes(int64_t n) {
     if (n < 1) return 0;
-    return (size_t)kMaxBlocks * 2 * sizeof(double);
+    return kDeltaBytes;
 }
 
 extern "C" qc_status qc_latent_delta(const float *cur, const float *prev, int64_t n, float *out3,
@@ -448,7 +462,7 @@ extern "C" qc_status qc_latent_delta(const float *cur, const float *prev, int64_
 // `scratch` below is the host-side handle of that array, not a device address: host code asks
 // the runtime once per device for the address of that device's copy and uses only that.
 namespace {
-constexpr size_t kStaticScratchBytes = (size_t)kMaxBlocks * 2 * sizeof(double);
+constexpr size_t kStaticScratchBytes = kDeltaBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 std::atomic<void *> g_scratch_ptr[kMaxDevices];
@@ -480,7 +494,7 @@ extern "C" qc_status qc_latent_delta_static(const float *cur, const float *prev,
 
 extern "C" size_t qc_layer_similarity_workspace_bytes(int64_t n) {
     if (n < 1) return 0;
-    return (size_t)kMaxBlocks * 3 * sizeof(double);
+    return kSimilarityBytes;
 }
 
 extern "C" qc_status qc_layer_similarity(const void *a, const void *b, qc_dtype dt, int64_t n,
@@ -499,7 +513,7 @@ extern "C" qc_status qc_layer_similarity(const void *a, const void *b, qc_dtype 
 
 extern "C" size_t qc_frame_gradient_norm_workspace_bytes(int64_t frames, int64_t inner) {
     if (frames < 1 || inner < 1) return 0;
-    return (size_t)kMaxBlocks * sizeof(double);
+    return kGradientBytes;
 }
 
 extern "C" qc_status qc_frame_gradient_norm(const void *m, qc_dtype dt, int64_t frames,
@@ -518,7 +532,7 @@ extern "C" qc_status qc_frame_gradient_norm(const void *m, qc_dtype dt, int64_t 
 
 extern "C" size_t qc_cumulative_variation_workspace_bytes(int64_t n, int count) {
     if (n < 1 || count < 1 || count > QC_MAX_PREV) return 0;
-    return (size_t)kMaxBlocks * QC_MAX_PREV * sizeof(double);
+    return kVariationBytes;
 }
 
 extern "C" qc_status qc_cumulative_variation(const float *cur, const float *const *prevs, int count,

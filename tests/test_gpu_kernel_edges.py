@@ -69,9 +69,9 @@ def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
     run_linear_case(random_x(rng, M, K, "bf16"), W, b, bits, "gelu_tanh", "bf16", check_acc=False)
 
 
-@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 128 * 4096, 128 * 4096 + 5, (12 << 20) // 8, (12 << 20) // 8 + 1])
+@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 170 * 4096, 170 * 4096 + 5, (12 << 20) // 8, (12 << 20) // 8 + 1])
 def test_reductions_on_both_sides_of_the_one_launch_form(n):
-    """Up to 12 MB of input the block that sees all partial sums finishes (128 blocks at most, one pass
+    """Up to 12 MB of input the block that sees all partial sums finishes (170 blocks at most, one pass
     of 4096 elements each, more above); beyond that a second launch does.  The workspace holds
     arbitrary bytes, then what the call before left in it."""
     rng = np.random.default_rng(n)
@@ -86,6 +86,22 @@ def test_reductions_on_both_sides_of_the_one_launch_form(n):
     other = qc.latent_delta_t(p, c, workspace=ws).cpu().numpy()
     ref = np.asarray(oracle.latent_delta(prev, cur), np.float64)
     assert np.all(np.abs(other - ref) <= 1e-5 * np.abs(ref))
+
+
+@pytest.mark.parametrize("count", [1, 4, 5, 7, 8])
+def test_one_launch_variation_fills_its_workspace(count):
+    """256 blocks, or 227 with eight distances, on a workspace of exactly the stated size with guard
+    bytes behind it."""
+    n = (12 << 20) // (4 * (count + 1))
+    rng = np.random.default_rng(count)
+    cur = rng.standard_normal(n).astype(np.float32)
+    prevs = rng.standard_normal((count, n)).astype(np.float32)
+    ref = np.asarray(oracle.cumulative_variation(cur, prevs), np.float64)
+    size = qc.qc_cumulative_variation_workspace_bytes(n, count)
+    buf = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    got = qc.cumulative_variation_t(dev(cur), [dev(p) for p in prevs], workspace=buf[:size]).cpu().numpy()
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+    assert bool((buf[size:] == 0x5a).all())
 
 
 def test_one_launch_reductions_replay_from_a_graph():
