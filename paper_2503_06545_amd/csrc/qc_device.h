@@ -46,8 +46,13 @@ __device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0
 //                  For bf16 it stays two packed 16-bit patterns (magnitudes order like their bit
 //                  patterns): one v_and and one v_pk_max_u16 for two elements, and nothing widened
 //                  that the compiler would then keep in registers up to the cast.
+//   load_ragged()  the same for a K that is no multiple of 16: rows at any alignment (the hardware takes
+//                  16 B loads at any address), the row's last, partial piece element by element, zeros
+//                  past it
 template <typename XT>
 struct Group;
+
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // 16 B at any element
 
 // the dword of lane ^ 1 (quad_perm [1, 0, 3, 2])
 __device__ inline uint32_t dpp_xor1(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false); }
@@ -63,6 +68,22 @@ struct Group<float> {
         for (int j = 0; j < 4; ++j) {
             const int col = col0 + 32 * j + 4 * sub;
             v[j] = load16<NT>(xrow + (col < K - 4 ? col : K - 4));
+        }
+    }
+    __device__ void load_ragged(const float *xrow, int col0, int K, int sub) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int col = col0 + 32 * j + 4 * sub;
+            v[j] = make_uint4(0, 0, 0, 0);
+            if (col + 4 <= K) {
+                const u32x4_any t = *reinterpret_cast<const u32x4_any *>(xrow + col);
+                v[j] = make_uint4(t.x, t.y, t.z, t.w);
+            } else if (col < K) {
+                const uint32_t *p = reinterpret_cast<const uint32_t *>(xrow + col);
+                v[j].x = p[0];
+                if (col + 1 < K) v[j].y = p[1];
+                if (col + 2 < K) v[j].z = p[2];
+            }
         }
     }
     __device__ float get(int i) const {
@@ -103,6 +124,23 @@ struct Group<uint16_t> {  // bf16 bit patterns
         for (int j = 0; j < 2; ++j) {
             const int col = col0 + 64 * j + 8 * sub;
             v[j] = load16<NT>(xrow + (col < K - 8 ? col : K - 8));
+        }
+    }
+    __device__ void load_ragged(const uint16_t *xrow, int col0, int K, int sub) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int col = col0 + 64 * j + 8 * sub;
+            v[j] = make_uint4(0, 0, 0, 0);
+            if (col + 8 <= K) {
+                const u32x4_any t = *reinterpret_cast<const u32x4_any *>(xrow + col);
+                v[j] = make_uint4(t.x, t.y, t.z, t.w);
+            } else if (col < K) {
+                uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (col + e < K) w[e / 2] |= (uint32_t)xrow[col + e] << (16 * (e % 2));
+                v[j] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
         }
     }
     __device__ float get(int i) const {

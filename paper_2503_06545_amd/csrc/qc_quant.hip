@@ -49,16 +49,44 @@ struct TensorMax {
     bool single_scale;      // write x_scale[0] only, not one (equal) value per row
 };
 
-__device__ inline float tensor_absmax(const TensorMax &t, int lane) {
-    float a = 0.0f;
-    for (int j = lane; j < t.count; j += 64) a = fmaxf(a, t.partials[j]);
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) a = fmaxf(a, __shfl_xor(a, d));
-    return a;
+constexpr int kMaxSlabs = 256;
+
+template <int CTRL>
+__device__ inline float dpp_max(float v) {
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false)));
 }
 
-constexpr int kSlabThreads = 256;
-constexpr int kMaxSlabs = 256;
+// A wavefront asks for the partial maxima in one load, before its rows, and combines them with DPP
+// moves and four readlanes afterwards (a chain of shuffles through LDS cost 4 us of 24 at
+// 32768 x 1152, every wavefront doing it).
+struct TensorMaxLoad {
+    float4 v;
+    __device__ void load(const TensorMax &t, int lane) {   // the array holds kMaxSlabs values, count of them written
+        v = reinterpret_cast<const float4 *>(t.partials)[lane];
+        const int i = 4 * lane;
+        v.x = i < t.count ? v.x : 0.0f;
+        v.y = i + 1 < t.count ? v.y : 0.0f;
+        v.z = i + 2 < t.count ? v.z : 0.0f;
+        v.w = i + 3 < t.count ? v.w : 0.0f;
+    }
+    __device__ float combine() const {
+        float a = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+        a = dpp_max<0xB1>(a);    // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror: 16 lanes
+        a = dpp_max<0x4E>(a);
+        a = dpp_max<0x141>(a);
+        a = dpp_max<0x140>(a);
+        float r = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r = fmaxf(r, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 16 * i)));
+        return r;
+    }
+};
+
+// The slabs' maxima: at most one block of 1024 threads per CU, four 16 B loads in flight per lane
+// (64 KiB per CU; with 256 threads and one load the pass ran at 2.3 TB/s: 32768 x 1152 bf16 33 us).
+// bf16 magnitudes are compared as packed bit patterns, see Group.
+constexpr int kSlabThreads = 1024;
+constexpr int kSlabUnroll = 4;
 
 template <typename XT>
 __global__ __launch_bounds__(kSlabThreads) void tensor_absmax_kernel(const XT *__restrict__ X, int64_t n,
@@ -66,26 +94,35 @@ __global__ __launch_bounds__(kSlabThreads) void tensor_absmax_kernel(const XT *_
     __shared__ float wave_max[kSlabThreads / 64];
     constexpr int kPer = 16 / (int)sizeof(XT);  // elements per 16 B load
     const int64_t nv = n / kPer;
-    const int64_t stride = (int64_t)gridDim.x * kSlabThreads;
+    const int64_t stride = (int64_t)gridDim.x * kSlabThreads * kSlabUnroll;
+    u16x2 packed = {0, 0};
     float a = 0.0f;
-    for (int64_t i = (int64_t)blockIdx.x * kSlabThreads + threadIdx.x; i < nv; i += stride) {
-        const uint4 v = reinterpret_cast<const uint4 *>(X)[i];
+    auto fold = [&](const uint4 &v) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if constexpr (sizeof(XT) == 2) {
-                a = fmaxf(a, fabsf(bf16_lo(w[j])));
-                a = fmaxf(a, fabsf(bf16_hi(w[j])));
-            } else {
+            if constexpr (sizeof(XT) == 2)
+                packed = __builtin_elementwise_max(packed, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
+            else
                 a = fmaxf(a, fabsf(__uint_as_float(w[j])));
-            }
         }
+    };
+    for (int64_t base = (int64_t)blockIdx.x * kSlabThreads * kSlabUnroll + threadIdx.x; base < nv; base += stride) {
+        uint4 v[kSlabUnroll];
+#pragma unroll
+        for (int u = 0; u < kSlabUnroll; ++u) {   // past the end the last piece again: the same maximum
+            const int64_t i = base + u * kSlabThreads;
+            v[u] = reinterpret_cast<const uint4 *>(X)[i < nv ? i : nv - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kSlabUnroll; ++u) fold(v[u]);
     }
     if (blockIdx.x == 0 && threadIdx.x < (int)(n - nv * kPer)) {  // trailing elements
         const XT t = X[nv * kPer + threadIdx.x];
         if constexpr (sizeof(XT) == 2) a = fmaxf(a, fabsf(__uint_as_float((uint32_t)t << 16)));
         else a = fmaxf(a, fabsf(t));
     }
+    if constexpr (sizeof(XT) == 2) a = fmaxf(a, Group<XT>::absmax_value(packed));
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) a = fmaxf(a, __shfl_xor(a, d));
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = a;
@@ -114,8 +151,9 @@ constexpr int kMaxSlices = UPT == 9 ? 8 : 16;
 
 // TENSOR: the absmax comes from `tmax` (one scale for the whole tensor).  A template parameter
 // rather than a test of tmax.partials, so that the per-token kernel is compiled exactly as if
-// the other did not exist.
-template <typename XT, bool TENSOR, int POLICY, int UPT>
+// the other did not exist.  RAGGED: a K that is no multiple of 16, for the fragment layout only; the
+// codes of columns K .. up to the next multiple of 16 are written too, where the weights are zero.
+template <typename XT, bool TENSOR, int POLICY, int UPT, bool RAGGED>
 __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, int8_t *__restrict__ qx,
     uint8_t *__restrict__ qx_tiled, int64_t KF, float *__restrict__ x_scale, float qmax,
@@ -123,20 +161,25 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
     __shared__ float slice_max[kMaxSlices<UPT>][kRowsPerBlock];
     const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, slices = blockDim.x >> 6;
     const int sub = lane % kLanesPerRow, row_in_block = lane / kLanesPerRow;
-    const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + row_in_block;
-    const int units = (int)(K / kUnit);
+    // TENSOR: the last rows first, which the pass for the maximum left in the last-level cache
+    const int64_t row_block = TENSOR ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const int64_t row = row_block * kRowsPerBlock + row_in_block;
+    const int units = (int)((K + kUnit - 1) / kUnit);
     const bool live = row < M;
     const XT *xrow = X + (live ? row : 0) * K;
 
+    TensorMaxLoad slabs;
+    if (TENSOR) slabs.load(tmax, lane);   // uniform over the launch
     Group<XT> u[UPT];
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
-        u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
+        if constexpr (RAGGED) u[i].load_ragged(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
+        else u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
     }
 
     float a = 0.0f;
     if (TENSOR) {  // one scale for the whole tensor: its absmax was reduced beforehand
-        a = tensor_absmax(tmax, lane);
+        a = slabs.combine();
     } else {
         auto running = Group<XT>::no_max();
 #pragma unroll
@@ -377,7 +420,8 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_asym_kernel(
 }
 
 // Any K, any alignment: one wavefront per row, two passes over the row (the second one is
-// served by the caches).  Slow path for shapes the vector kernel does not take.
+// served by the caches).  For what the row kernels do not take: row-major codes of rows that are no
+// multiple of 16 long, and rows longer than 9216.
 template <typename XT>
 __global__ __launch_bounds__(kGenericThreads) void quant_rows_generic_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, int8_t *__restrict__ qx,
@@ -393,7 +437,9 @@ __global__ __launch_bounds__(kGenericThreads) void quant_rows_generic_kernel(
     };
     float a = 0.0f;
     if (tmax.partials) {
-        a = tensor_absmax(tmax, lane);
+        TensorMaxLoad slabs;
+        slabs.load(tmax, lane);
+        a = slabs.combine();
     } else {
         for (int64_t k = lane; k < K; k += 64) a = fmaxf(a, fabsf(widen(xrow[k])));
 #pragma unroll
@@ -472,22 +518,28 @@ hipError_t launch_typed(const XT *X, int64_t M, int64_t K, int8_t *qx, uint8_t *
         });
         return hipGetLastError();
     }
-    if (!vec) {
+    // Rows of any other length: the same kernels when only the fragment layout is wanted (4099 x 1000
+    // bf16: 12.2 us with a wavefront per row and byte stores); row-major codes of ragged rows, and rows
+    // longer than 9216, take the generic one.
+    const bool ragged = !vec && !qx && K <= (int64_t)kUnitsMost * kUnit;
+    if (!vec && !ragged) {
         const int64_t blocks = (M + 3) / 4;
         quant_rows_generic_kernel<XT><<<dim3((unsigned)blocks), dim3(kGenericThreads), 0, stream>>>(
             X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
         return hipGetLastError();
     }
     with_row_variant(M, K, sizeof(XT), [&](auto pol, auto upt) {
+        constexpr int P = decltype(pol)::value, U = decltype(upt)::value;
+        const dim3 grid = row_grid(M), block = row_block(K, U);
         // the tensor was read once already for its absmax: what the caches still hold of it helps
-        if (tmax.partials)
-            quant_rows_kernel<XT, true, kCachePlain, decltype(upt)::value>
-                <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
-                    X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
+        if (tmax.partials && ragged)
+            quant_rows_kernel<XT, true, kCachePlain, U, true><<<grid, block, 0, stream>>>(X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
+        else if (tmax.partials)
+            quant_rows_kernel<XT, true, kCachePlain, U, false><<<grid, block, 0, stream>>>(X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
+        else if (ragged)
+            quant_rows_kernel<XT, false, kCachePlain, U, true><<<grid, block, 0, stream>>>(X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
         else
-            quant_rows_kernel<XT, false, decltype(pol)::value, decltype(upt)::value>
-                <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
-                    X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
+            quant_rows_kernel<XT, false, P, U, false><<<grid, block, 0, stream>>>(X, M, K, qx, qx_tiled, KF, x_scale, qmax, tmax);
     });
     return hipGetLastError();
 }
@@ -541,7 +593,7 @@ hipError_t launch_quant_act_tensor(const void *X, qc_dtype xdt, int64_t M, int64
     const float qmax = (float)((1 << (act_bits - 1)) - 1);
     const int64_t n = M * K;
     const int per = xdt == QC_BF16 ? 8 : 4;
-    int64_t slabs = (n / per + (int64_t)kSlabThreads * 8 - 1) / ((int64_t)kSlabThreads * 8);
+    int64_t slabs = (n / per + (int64_t)kSlabThreads * kSlabUnroll - 1) / ((int64_t)kSlabThreads * kSlabUnroll);
     if (slabs < 1) slabs = 1;
     if (slabs > kMaxSlabs) slabs = kMaxSlabs;
     if (xdt == QC_BF16)

@@ -104,9 +104,14 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
     const bool live = m0 + row < a.M;
     if constexpr (FUSED) {
         const XT *xrow = reinterpret_cast<const XT *>(a.X) + (live ? m0 + row : m0) * a.K;
+        if (a.K % kUnit == 0) {
 #pragma unroll
-        for (int i = 0; i < UPT; ++i)
-            u[i].template load<false>(xrow, (group0 + i * groups_per_step) * kGroup, (int)a.K, sub);
+            for (int i = 0; i < UPT; ++i)
+                u[i].template load<false>(xrow, (group0 + i * groups_per_step) * kGroup, (int)a.K, sub);
+        } else {
+#pragma unroll
+            for (int i = 0; i < UPT; ++i) u[i].load_ragged(xrow, (group0 + i * groups_per_step) * kGroup, (int)a.K, sub);
+        }
     }
 
     // what the epilogue needs, requested first: a thread keeps one column of channels, n0 .. n0 + NF - 1,
@@ -449,10 +454,10 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
     return bits == 8 ? launch_bits<8>(tile, kCodes, a, stream) : launch_bits<4>(tile, kCodes, a, stream);
 }
 
-// What limits the fused form, beyond the tile: the columns a thread holds, K in whole units, and LDS.
+// What limits the fused form, beyond the tile: the columns a thread holds and LDS.
 bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K) {
     const int tile = pick_tile(M, N);
-    if (tile < 0 || kTiles[tile].upt == 0 || K % kUnit) return false;
+    if (tile < 0 || kTiles[tile].upt == 0) return false;
     const int rp_log2 = live_rows_log2(M, kTiles[tile].tokens);
     const int64_t columns = (int64_t)kTiles[tile].upt * kUnit * (kThreads >> rp_log2);
     const int64_t lds = round_up(K, kKAlign) / kFragK * 4 * quarter_stride(rp_log2);

@@ -6,6 +6,7 @@ import torch
 
 import oracle
 from paper_2503_06545_amd import binding as qc
+from paper_2503_06545_amd import synth
 from test_gpu_parity import bits_equal, dev, random_x, run_asym_case, run_linear_case
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +138,47 @@ def test_one_launch_reductions_replay_from_a_graph():
         assert all(torch.equal(x, y) for x, y in zip(got, outs)), k
         ref = np.asarray(oracle.latent_delta(a.cpu().numpy(), b.cpu().numpy()), np.float64)
         assert np.all(np.abs(got[0].cpu().numpy() - ref) <= 1e-5 * np.abs(ref))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K", [(1, 7), (32, 1024), (33, 1000), (8192, 1024), (8193, 1024)])
+def test_tensor_scale_at_the_edges_of_its_slabs(M, K, dtype):
+    """One slab exactly, one and a little, 256 slabs (bf16) exactly and more; the largest magnitude last."""
+    rng = np.random.default_rng(M + K)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x[-1, -1] = -9.0
+    x = synth.to_bf16_bits(x) if dtype == "bf16" else x
+    q_ref, s_ref = oracle.quant_act_tensor(x)
+    qx, sx = qc.quant_act_tensor_t(dev(x))
+    torch.cuda.synchronize()
+    assert bits_equal(sx.cpu().numpy(), np.asarray(s_ref, np.float32).reshape(1)) and np.array_equal(qx.cpu().numpy(), q_ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K", [(3, 1), (37, 7), (9, 127), (9, 129), (4099, 1000), (9, 2049), (5, 6145), (3, 9215), (2, 9217)])
+def test_ragged_rows_in_the_fragment_layout(M, K, dtype):
+    """Row lengths that are no multiple of 16: rows at every alignment, partial last pieces, both sides
+    of each change of the number of steps; per token and with one scale for the tensor."""
+    rng = np.random.default_rng(M * 7 + K)
+    x = random_x(rng, M, K, dtype)
+    xd = dev(x)
+    for tensor in (False, True):
+        q_ref, s_ref = oracle.quant_act_tensor(x) if tensor else oracle.quant_act(x)
+        W = np.ones((8, K), np.float32)
+        pw = qc.pack_weight_t(dev(W), 8)
+        if tensor:
+            ws = qc.qlinear_tensor_workspace_t(M, K, 8)
+            ws.fill_(0x7f)
+            acc = qc.qlinear_tensor_t(xd, pw, out="i32", workspace=ws)
+        else:
+            ws = qc.qlinear_workspace_t(M, K, 8)
+            ws.fill_(0x7f)
+            assert qc.qc_qlinear_quant(xd.data_ptr(), qc.QC_BF16 if dtype == "bf16" else qc.QC_F32, M, K, ws.data_ptr(),
+                                       ws.numel(), torch.cuda.current_stream().cuda_stream) == qc.QC_OK
+            acc = None
+        qx, sx = qc.debug_workspace_act_t(ws, M, K)
+        torch.cuda.synchronize()
+        assert np.array_equal(qx.cpu().numpy(), q_ref)
+        assert bits_equal(sx.cpu().numpy(), np.broadcast_to(np.asarray(s_ref, np.float32), (M,)))
+        if acc is not None:
+            assert np.array_equal(acc.cpu().numpy(), np.repeat(127 * q_ref.astype(np.int64).sum(axis=1)[:, None], 8, axis=1))
