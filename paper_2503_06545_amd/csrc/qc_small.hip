@@ -24,10 +24,6 @@ namespace qc {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;
 constexpr int kGroup = 128;   // columns that eight lanes quantize per step
@@ -272,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
             for (int q = 0; q < 4; ++q) mine[(16 * i + q) * L::kLd + t * 16] = acc[i][t][q];
     __syncthreads();
 
-    const bool vec = n0 + NF <= a.N && a.N % NF == 0;
+    const bool vec = n0 + NF <= a.N;   // stored in one piece, at any alignment of Y's elements
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {
         const int m = em + 32 * j;
@@ -309,12 +305,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
         if (a.out == QC_OUT_F32) {
             float *o = reinterpret_cast<float *>(a.Y) + at;
             if (vec) {
-                if constexpr (NF == 2) {
-                    *reinterpret_cast<f2 *>(o) = f2{y[0], y[1]};
-                } else {
-#pragma unroll
-                    for (int t = 0; t < NF; t += 4) *reinterpret_cast<f4 *>(o + t) = f4{y[t], y[t + 1], y[t + 2], y[t + 3]};
-                }
+                __builtin_memcpy(o, y, sizeof(y));
             } else {
 #pragma unroll
                 for (int t = 0; t < NF; ++t)
@@ -326,9 +317,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
 #pragma unroll
             for (int t = 0; t < NF / 2; ++t) pk[t] = pack_bf16x2(y[2 * t], y[2 * t + 1]);
             if (vec) {
-                if constexpr (NF == 2) *reinterpret_cast<uint32_t *>(o) = pk[0];
-                else if constexpr (NF == 4) *reinterpret_cast<u2 *>(o) = u2{pk[0], pk[1]};
-                else *reinterpret_cast<u4 *>(o) = u4{pk[0], pk[1], pk[2], pk[3]};
+                __builtin_memcpy(o, pk, sizeof(pk));
             } else {
 #pragma unroll
                 for (int t = 0; t < NF; ++t)
