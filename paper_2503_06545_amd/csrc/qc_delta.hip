@@ -79,14 +79,17 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
 }
 
 // The one-launch form's end.  v: this block's sums, valid in wavefront 0.  Every block publishes its
-// sums and a check word, the exclusive or of the (rotated) sums and the launch's nonce, with
-// device-scope stores, waits until they are out, and then reads everybody's.  A block's sums count
+// sums and a check word, a hash of the launch's nonce and the sums, with device-scope stores, passes a
+// sequentially consistent fence, and then reads everybody's.  A block's sums count
 // once they fit their check, whatever the workspace held before, and whichever words a reader
 // catches.  The block whose stores come last sees all of them: at least one block finds everything
 // present, forms the totals (every block that does forms the same ones) and spoils the checks, so
 // that a replay of this launch from a graph, with the same nonce, finds nothing stale.  Nobody waits
 // for anybody.  Returns whether this block has the totals in v (all threads).
-__device__ inline uint64_t rotate(uint64_t x, int n) { return n ? (x << n) | (x >> (64 - n)) : x; }
+__device__ inline uint64_t mix(uint64_t hash, uint64_t bits) {
+    hash = (hash ^ bits) * 0x9E3779B97F4A7C15ull;   // odd: a bijection of hash ^ bits
+    return hash ^ (hash >> 32);
+}
 
 template <int THREADS, int COUNT>
 __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *records, uint64_t nonce) {
@@ -98,10 +101,10 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
         for (int c = 0; c < COUNT; ++c) {
             const uint64_t bits = (uint64_t)__double_as_longlong(v[c]);
             __hip_atomic_store(r + c, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            check ^= rotate(bits, c);
+            check = mix(check, bits);
         }
         __hip_atomic_store(r + COUNT, check, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores have reached memory
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");   // the stores before anybody's loads below
     }
     __syncthreads();
     bool present = true;
@@ -109,13 +112,13 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
         uint64_t *r = records + kWords * (tid < blocks ? tid : 0), word[kWords];
 #pragma unroll
         for (int c = 0; c < kWords; ++c) word[c] = __hip_atomic_load(r + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint64_t check = word[COUNT];
+        uint64_t check = nonce;
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
-            check ^= rotate(word[c], c);
+            check = mix(check, word[c]);
             v[c] = tid < blocks ? __longlong_as_double((long long)word[c]) : 0.0;
         }
-        present = check == nonce;
+        present = check == word[COUNT];
     }
     if (!__syncthreads_and(present)) return false;
     if (tid < blocks) __hip_atomic_store(records + kWords * tid + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
