@@ -37,8 +37,9 @@ typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-constexpr int kStages = 3;   // LDS ring of weight stages (4 and 6 were measured: 1.5 % and 3 % slower)
-constexpr int kXSlots = 3;   // register ring of activation stages
+constexpr int kStages = 3;   // both rings: weight stages in LDS (4 and 6 were measured: 1.5 % and 3 % slower) and
+                             // activation stages in registers.  The half-height tile gains nothing from 6
+                             // either: alone on its CU a block waits for bandwidth, not for latency.
 
 template <int BITS>
 struct StageLayout {
@@ -62,9 +63,11 @@ struct GemmArgs {
     void *Y;
     int64_t M, N;
     int KF;         // 64-k stages (Kp / 64)
-    int m_tiles, n_tiles;
+    int m_tiles, n_tiles;   // m_tiles: of 256 tokens, of 128 for the half-height ring kernel
     int group_m;    // token tiles per patch of the block -> tile map (ring kernel)
     bool resident;  // run the kernel that keeps the weight tile in LDS
+    bool half;      // ring kernel: tiles of 128 tokens
+    bool keep_output;  // ring kernel, f32 output: stores through the caches
 };
 
 __device__ inline void lds_dma_16(const uint8_t *gsrc, uint8_t *lds_dst) {
@@ -93,20 +96,20 @@ __device__ inline void tile_of_block(int b, int nblocks, int m_tiles, int n_tile
 // vmcnt(n) with the other counters left unconstrained (gfx9 encoding: bits 3:0 and 15:14, n < 64)
 #define QC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// One piece of a row of Y.  ANY: at any alignment of its elements, and not past the caches, where the
+// One piece of a row of Y.  CACHED: at any alignment of its elements, and not past the caches, where the
 // pieces of a line that two tiles or two rows share meet.
-template <bool ANY, typename T, typename V>
+template <bool CACHED, typename T, typename V>
 __device__ inline void store_piece(T *p, V v) {
-    if constexpr (ANY) __builtin_memcpy(p, &v, sizeof(v));
+    if constexpr (CACHED) __builtin_memcpy(p, &v, sizeof(v));
     else __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
 }
 
-// Epilogue of one wavefront's 64 x 128 tile: registers -> Y.  Lane (c = lane % 16, h = lane / 16)
+// Epilogue of one wavefront's tile of 16 MI tokens x 128 channels: registers -> Y.  Lane (c = lane % 16, h = lane / 16)
 // of MFMA tile (i, t) holds, in register r, token m_wave + 16 i + 4 h + r and channel
-// 128 nt + 8 c + t.  sx64 / cx64: the tile's 64 token scales / corrections, lds_sw / lds_bs /
+// 128 nt + 8 c + t.  sx64 / cx64: the tile's token scales / corrections, lds_sw / lds_bs /
 // lds_rs: the channel tile's 128 scales, biases and code sums, all in LDS.
-template <int BITS, int OUT, int EPI, bool ASYM>
-__device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs &a, int64_t m_wave, int nt,
+template <int BITS, int OUT, int EPI, bool ASYM, bool MAY_KEEP, int MI>
+__device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArgs &a, int64_t m_wave, int nt,
                                                 int lane, const float *sx64, const float *cx64,
                                                 const float *lds_sw, const float *lds_bs, const float *lds_rs) {
     const int c = lane & 15, h = lane >> 4;
@@ -114,13 +117,13 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs
     const int64_t m0 = m_wave + 4 * h;
     constexpr int kOutBytes = OUT == QC_OUT_BF16 ? 2 : 4;
     constexpr int kVecChannels = 16 / kOutBytes;  // channels in one 16 B store
-    const bool interior = m_wave + kWaveM <= a.M && (int64_t)(nt + 1) * kTileN <= a.N &&
+    const bool interior = m_wave + 16 * MI <= a.M && (int64_t)(nt + 1) * kTileN <= a.N &&
                           (a.N % kVecChannels) == 0;  // uniform over the wavefront
     char *const y_wave = reinterpret_cast<char *>(a.Y) + (m_wave * a.N + (int64_t)nt * kTileN) * kOutBytes;
     const uint32_t lane_off = (uint32_t)((4 * h * a.N + 8 * c) * kOutBytes);  // N <= 2^26
 
-    auto write_tile = [&](auto checked_tag) {
-        constexpr bool CHECKED = decltype(checked_tag)::value;
+    auto write_tile = [&](auto checked_tag, auto cached_tag) {
+        constexpr bool CHECKED = decltype(checked_tag)::value, CACHED = decltype(cached_tag)::value;
         if (CHECKED && n0 >= a.N) return;
         // Whole 16 B (8 B) pieces are stored as such at any alignment, which the hardware takes; rows
         // of Y that are no multiple of 16 B long thus differ from the others in the last channels
@@ -149,7 +152,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs
         }
 
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MI; ++i) {
             const int64_t m4 = m0 + 16 * i;
             if (CHECKED && m4 >= a.M) continue;
             float sx[4] = {0.f, 0.f, 0.f, 0.f}, cx[4] = {0.f, 0.f, 0.f, 0.f};
@@ -177,7 +180,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         if (vec[j]) {
-                            store_piece<CHECKED>(y + 4 * j, v4i{raw[4 * j], raw[4 * j + 1], raw[4 * j + 2], raw[4 * j + 3]});
+                            store_piece<CACHED>(y + 4 * j, v4i{raw[4 * j], raw[4 * j + 1], raw[4 * j + 2], raw[4 * j + 3]});
                         } else {
 #pragma unroll
                             for (int t = 4 * j; t < 4 * j + 4; ++t) if (n0 + t < a.N) y[t] = raw[t];
@@ -199,7 +202,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
                             if (vec[j]) {
-                                store_piece<CHECKED>(y + 4 * j, f4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]});
+                                store_piece<CACHED>(y + 4 * j, f4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]});
                             } else {
 #pragma unroll
                                 for (int t = 4 * j; t < 4 * j + 4; ++t) if (n0 + t < a.N) y[t] = v[t];
@@ -211,12 +214,12 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs
 #pragma unroll
                         for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(v[2 * j], v[2 * j + 1]);
                         if (vec8) {
-                            store_piece<CHECKED>(y, u4{pk[0], pk[1], pk[2], pk[3]});
+                            store_piece<CACHED>(y, u4{pk[0], pk[1], pk[2], pk[3]});
                         } else {
 #pragma unroll
                             for (int j = 0; j < 2; ++j) {
                                 if (vec[j]) {
-                                    store_piece<CHECKED>(y + 4 * j, u2{pk[2 * j], pk[2 * j + 1]});
+                                    store_piece<CACHED>(y + 4 * j, u2{pk[2 * j], pk[2 * j + 1]});
                                 } else {
 #pragma unroll
                                     for (int t = 4 * j; t < 4 * j + 4; ++t)
@@ -230,16 +233,18 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[4][8], const GemmArgs
             }
         }
     };
-    if (interior) write_tile(std::false_type{});
-    else write_tile(std::true_type{});
+    if (!interior) write_tile(std::true_type{}, std::true_type{});
+    else if (MAY_KEEP && a.keep_output) write_tile(std::false_type{}, std::bool_constant<MAY_KEEP>{});
+    else write_tile(std::false_type{}, std::false_type{});
 }
 
 // ASYM: the activation codes are the unsigned codes of the asymmetric quantizer minus a shift h
 // (128 for 8-bit codes, else 0; Section 3.1 Eq. (3)-(4) as printed).  With c[m] = h - z[m] the dequantized activation
 // is sx (code + c), so the epilogue adds c[m] * sum_k qw[n, k] to the accumulator.
-template <int BITS, int OUT, int EPI, bool ASYM>
-__global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
+template <int BITS, int OUT, int EPI, bool ASYM, int MI>
+__global__ __launch_bounds__(kThreads, MI == 4 ? 2 : 3) void gemm_kernel(GemmArgs a) {
     using L = StageLayout<BITS>;
+    constexpr int TM = 4 * 16 * MI;   // tokens of the block, 16 MI of them a wavefront's
     constexpr int FPW = L::kFragsPerWave;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
@@ -252,15 +257,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
     // The epilogue's scales and bias are fetched now (one value per thread) and handed round
     // through LDS after the main loop, so that the epilogue does not start with a chain of L2
     // round trips.
-    float *lds_sx = reinterpret_cast<float *>(lds + kStages * L::kBytes);  // 256 token scales
+    float *lds_sx = reinterpret_cast<float *>(lds + kStages * L::kBytes);  // TM token scales (room for 256)
     float *lds_sw = lds_sx + kTileM;                                       // 128 channel scales
     float *lds_bs = lds_sw + kTileN;                                       // 128 biases
     float *lds_cx = lds_bs + kTileN;                                       // ASYM: 256 corrections
     float *lds_rs = lds_cx + kTileM;                                       // ASYM: 128 code sums
     float my_sx = 0.0f, my_sw = 0.0f, my_bs = 0.0f, my_cx = 0.0f, my_rs = 0.0f;
     if (OUT != QC_OUT_I32_ACC) {
-        my_sx = a.x_scale[(int64_t)mt * kTileM + threadIdx.x];  // x_scale is padded to Mp
-        if (ASYM) my_cx = a.x_corr[(int64_t)mt * kTileM + threadIdx.x];
+        my_sx = a.x_scale[(int64_t)mt * TM + threadIdx.x % TM];  // x_scale is padded to Mp
+        if (ASYM) my_cx = a.x_corr[(int64_t)mt * TM + threadIdx.x % TM];
         const int64_t n = (int64_t)nt * kTileN + threadIdx.x;
         if (threadIdx.x < kTileN && n < a.N) {
             my_sw = a.w_scale[n];
@@ -275,21 +280,22 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
     // The pieces of the weight stage tile this wavefront copies HBM -> LDS, at stage 0 (a
     // stage tile is contiguous in memory).
     const uint8_t *const wsrc = a.w_codes + (int64_t)nt * a.KF * L::kBytes + wave * FPW * kFragBytes + lane * 16;
-    // copy the weight pieces of K stage `stage` into ring buffer `ring % 3`
-    auto issue_w = [&](int stage, int ring) {
-        uint8_t *buf = lds + (ring % kStages) * L::kBytes;
+    // copy the weight pieces of K stage `stage` into ring buffer `slot`
+    auto issue_w = [&](int stage, int slot) {
+        uint8_t *buf = lds + slot * L::kBytes;
 #pragma unroll
         for (int j = 0; j < FPW; ++j)
             lds_dma_16(wsrc + (int64_t)stage * L::kBytes + j * kFragBytes, buf + (wave * FPW + j) * kFragBytes);
     };
 
-    // Activation fragments are private to a wavefront (its 64 tokens), so they skip LDS:
+    // Activation fragments are private to a wavefront (its 16 MI tokens), so they skip LDS:
     // HBM -> registers, 16 B per lane, two stages ahead.  xq[slot][i]: tokens 16 i .. of the
     // stage held in `slot`.  Loads and LDS reads are asm so that they stay
     // in flight across loop iterations under explicit s_waitcnt counts; each wait names the
     // registers it makes valid, which orders the MFMAs that consume them behind it.
-    v4i xq[kXSlots][4];
-    const uint8_t *const xsrc = a.x_tiled + ((int64_t)(mt * (kTileM / kWaveM) + wave) * a.KF) * (4 * kFragBytes) + lane * 16;
+    v4i xq[kStages][MI];
+    const int frag0 = (mt * 4 + wave) * MI;   // first of its blocks of 16 tokens, four to a panel of 64
+    const uint8_t *const xsrc = a.x_tiled + ((int64_t)(frag0 / 4) * a.KF) * (4 * kFragBytes) + frag0 % 4 * kFragBytes + lane * 16;
 
 #define QC_GLOBAL_LOAD(dst, ptr, imm) \
     asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(dst) : "v"(ptr), "n"(imm) : "memory")
@@ -298,12 +304,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
         const uint8_t *p_ = xsrc + (int64_t)(stage) * (4 * kFragBytes);      \
         QC_GLOBAL_LOAD(xq[SLOT][0], p_, 0);                                  \
         QC_GLOBAL_LOAD(xq[SLOT][1], p_, kFragBytes);                         \
-        QC_GLOBAL_LOAD(xq[SLOT][2], p_, 2 * kFragBytes);                     \
-        QC_GLOBAL_LOAD(xq[SLOT][3], p_, 3 * kFragBytes);                     \
+        if constexpr (MI == 4) {                                             \
+            QC_GLOBAL_LOAD(xq[SLOT][2], p_, 2 * kFragBytes);                 \
+            QC_GLOBAL_LOAD(xq[SLOT][3], p_, 3 * kFragBytes);                 \
+        }                                                                    \
     } while (0)
 #define QC_WAIT_X(n, SLOT)                                                                    \
-    asm volatile("s_waitcnt vmcnt(" #n ")" : "+v"(xq[SLOT][0]), "+v"(xq[SLOT][1]),            \
-                 "+v"(xq[SLOT][2]), "+v"(xq[SLOT][3]))
+    do {                                                                                      \
+        if constexpr (MI == 4)                                                                \
+            asm volatile("s_waitcnt vmcnt(%4)" : "+v"(xq[SLOT][0]), "+v"(xq[SLOT][1]),        \
+                         "+v"(xq[SLOT][2]), "+v"(xq[SLOT][3]) : "n"(n));                      \
+        else                                                                                  \
+            asm volatile("s_waitcnt vmcnt(%2)" : "+v"(xq[SLOT][0]), "+v"(xq[SLOT][1]) : "n"(n)); \
+    } while (0)
 
     // LDS -> registers for the weight fragments.
     //   wr[h][t]: 16-channel block 4 h + t (8 bit);  wr[0][u]: nibble unit of blocks 2 u, 2 u + 1 (4 bit)
@@ -311,9 +324,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
     const uint32_t lds_lane = (uint32_t)(uintptr_t)lds + lane * 16;  // LDS byte address of this lane
 #define QC_DS_READ(dst, addr, imm) \
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
-#define QC_READ_W(stage, H)                                                          \
+#define QC_READ_W(SLOT, H)                                                           \
     do {                                                                             \
-        const uint32_t base_ = lds_lane + ((stage) % kStages) * L::kBytes;           \
+        const uint32_t base_ = lds_lane + (SLOT) * L::kBytes;                        \
         if (BITS == 8) {                                                             \
             QC_DS_READ(wr[H][0], base_, (4 * H + 0) * kFragBytes);                   \
             QC_DS_READ(wr[H][1], base_, (4 * H + 1) * kFragBytes);                   \
@@ -329,9 +342,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 #define QC_WAIT_W(n, H) \
     asm volatile("s_waitcnt lgkmcnt(" #n ")" : "+v"(wr[H][0]), "+v"(wr[H][1]), "+v"(wr[H][2]), "+v"(wr[H][3]))
 
-    v4i acc[4][8];   // [16-token block][16-channel block]
+    v4i acc[MI][8];   // [16-token block][16-channel block]
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc[i][t] = v4i{0, 0, 0, 0};
 
@@ -348,38 +361,35 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
         }
     };
 
-    // One 64-k stage.  SLOT = stage % 3 and NEXT2 = (stage + 2) % 3 are literal constants (the
-    // loop is unrolled by three) so the activation ring stays in fixed registers.
-    // VMEM operations complete in issue order; with D = kStages the issue order per wavefront is
-    //   W(0) .. W(D-3) X(0) W(D-2) X(1) W(D-1), then in stage s: X(s+2), W(s+D)
-    // i.e. from X(0) on an X and a W alternate.  X(s+2) goes out after the wait for X(s), among
-    // the first MFMAs of the stage, so at that wait W X(s+1) W are behind X(s) (2 FPW + 4
-    // operations).  At the wait for W(s+1) in the middle of the stage, D - 1 activation stages
-    // and D - 2 weight stages are behind it, once the stage is past the first D - 3, whose
-    // weights are waited for before the loop.  (A deeper weight ring buys nothing: the loop is
-    // not waiting for the weights.)  Past the end
-    // of K the stage index is clamped to the last stage: those copies repeat data that is not
-    // used again (they hit in cache), which keeps the instruction stream and the wait counts
-    // uniform.
-    constexpr int kWBehind = 4 * (kStages - 1) + FPW * (kStages - 2);
-    static_assert(kStages >= 3 && kWBehind < 64, "vmcnt is a 6-bit counter");
+    // One 64-k stage.  SLOT = stage % 3 is a literal constant (the loop is unrolled by three) so that
+    // the activation ring stays in fixed registers and the LDS ring needs no address arithmetic (with
+    // the remainder taken at run time 16384 x 1152 x 3456 took 0 to 3 % longer).  VMEM operations complete
+    // in issue order, which is W(0) X(0) W(1) X(1) W(2) before the loop, then X(s+2) and W(s+3) in stage s.
+    // X(s+2) goes out after the wait for X(s), among the first MFMAs of the stage, so at that wait two
+    // weight stages and one activation stage are behind X(s); at the wait for W(s+1) in the middle of
+    // the stage, two activation stages and one weight stage are behind it.  (A deeper weight ring buys
+    // nothing: the loop is not waiting for the weights.)  Past the end of K the stage index is clamped
+    // to the last stage: those copies repeat data that is not used again (they hit in cache), which
+    // keeps the instruction stream and the wait counts uniform.
+    constexpr int kXBehind = 2 * FPW + MI, kWBehind = 2 * MI + FPW;
+    static_assert(kStages == 3, "the loop is unrolled by the ring, and KF is a multiple of 3");
     const int last = stages - 1;
 #define QC_CLAMP(st) ((st) < last ? (st) : last)
-    // The sixteen MFMAs of a half stage (4 token blocks x 4 channel blocks) are independent, so
+    // The 4 MI MFMAs of a half stage (MI token blocks x 4 channel blocks) are independent, so
     // their order is free.  8 bit: token block outer.  4 bit: channel block outer, so that the
     // MFMAs that share an unpacked weight fragment follow each other.
 #define QC_MFMA_LOOPS                                                                           \
-    _Pragma("unroll") for (int o_ = 0; o_ < 16; ++o_)                                           \
-        for (int i = BITS == 8 ? o_ / 4 : o_ % 4, t = BITS == 8 ? o_ % 4 : o_ / 4, once_ = 1; once_; once_ = 0)
-#define QC_STAGE(s, SLOT, NEXT2)                                                               \
+    _Pragma("unroll") for (int o_ = 0; o_ < 4 * MI; ++o_)                                       \
+        for (int i = BITS == 8 ? o_ / 4 : o_ % MI, t = BITS == 8 ? o_ % 4 : o_ / MI, once_ = 1; once_; once_ = 0)
+#define QC_STAGE(s, SLOT)                                                                      \
     do {                                                                                       \
         QC_WAIT_W(0, 0);                                  /* channel half 0 of W(s) is here */ \
-        if (BITS == 8) QC_WAIT_X(8, SLOT); else QC_WAIT_X(6, SLOT);        /* X(s) is here */  \
+        QC_WAIT_X(kXBehind, SLOT);                                         /* X(s) is here */  \
         v4i w4a[4], w4b[4];                                                                    \
         if (BITS == 4) unpack(w4a, 0);                                                         \
         /* issued here, not before the waits, so that the loads go out under the MFMAs */      \
-        QC_ISSUE_X(QC_CLAMP((s) + 2), NEXT2);                                                  \
-        QC_READ_W((s), 1);        /* channel half 1: lands under the MFMAs of channel half 0 */ \
+        QC_ISSUE_X(QC_CLAMP((s) + 2), (SLOT + 2) % 3);                                                 \
+        QC_READ_W(SLOT, 1);       /* channel half 1: lands under the MFMAs of channel half 0 */ \
         QC_MFMA_LOOPS                                                                          \
                 acc[i][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(                             \
                     xq[SLOT][i], BITS == 8 ? wr[0][t] : w4a[t], acc[i][t], 0, 0, 0);           \
@@ -387,12 +397,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
         QC_WAIT_VMCNT(kWBehind);                                        /* W(s+1) has landed */\
         /* this wavefront's reads of W(s) are done ... */                                      \
         if (BITS == 8) QC_WAIT_W(0, 1);                                                        \
-        __builtin_amdgcn_s_barrier(); /* ... and everybody else's: ring buffer s % 3 is free */\
+        __builtin_amdgcn_s_barrier(); /* ... and everybody else's: ring buffer SLOT is free */\
         asm volatile("" ::: "memory");                                                         \
         if (BITS == 4) unpack(w4b, 1);   /* before the reads below overwrite the nibbles */     \
-        issue_w(QC_CLAMP((s) + kStages), (s) + kStages);                                       \
+        issue_w(QC_CLAMP((s) + 3), SLOT);                                                      \
         /* after the last stage this reads data that is not used */                            \
-        QC_READ_W((s) + 1, 0);                                                                 \
+        QC_READ_W((SLOT + 1) % 3, 0);                                                          \
         QC_MFMA_LOOPS                                                                          \
                 acc[i][4 + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(                         \
                     xq[SLOT][i], BITS == 8 ? wr[1][t] : w4b[t], acc[i][4 + t], 0, 0, 0);       \
@@ -400,22 +410,20 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
     } while (0)
 
     // ---- main loop -------------------------------------------------------------------
-#pragma unroll
-    for (int j = 0; j < kStages - 2; ++j) issue_w(QC_CLAMP(j), j);
+    issue_w(0, 0);
     QC_ISSUE_X(0, 0);
-    issue_w(QC_CLAMP(kStages - 2), kStages - 2);
+    issue_w(QC_CLAMP(1), 1);
     QC_ISSUE_X(QC_CLAMP(1), 1);
-    issue_w(QC_CLAMP(kStages - 1), kStages - 1);
-    // W(0) .. W(kStages - 3) have landed: behind them are X(0) W X(1) W
-    QC_WAIT_VMCNT(8 + 2 * FPW);
+    issue_w(QC_CLAMP(2), 2);
+    QC_WAIT_VMCNT(2 * MI + 2 * FPW);   // W(0) has landed
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     QC_READ_W(0, 0);
 
     for (int s = 0; s < stages; s += 3) {
-        QC_STAGE(s, 0, 2);
-        QC_STAGE(s + 1, 1, 0);
-        QC_STAGE(s + 2, 2, 1);
+        QC_STAGE(s, 0);
+        QC_STAGE(s + 1, 1);
+        QC_STAGE(s + 2, 2);
     }
     // drain everything still in flight before the registers are reused
     QC_WAIT_W(0, 0);
@@ -435,18 +443,18 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
     // park the scales (fetched at kernel start, long since arrived) where every lane can pick
     // the ones of its tokens and channels
     if (OUT != QC_OUT_I32_ACC) {
-        lds_sx[threadIdx.x] = my_sx;
+        if (threadIdx.x < TM) lds_sx[threadIdx.x] = my_sx;
         if (threadIdx.x < kTileN) { lds_sw[threadIdx.x] = my_sw; lds_bs[threadIdx.x] = my_bs; }
         if (ASYM) {
-            lds_cx[threadIdx.x] = my_cx;
+            if (threadIdx.x < TM) lds_cx[threadIdx.x] = my_cx;
             if (threadIdx.x < kTileN) lds_rs[threadIdx.x] = my_rs;
         }
         __syncthreads();
     }
 
     // ---- epilogue: registers -> Y --------------------------------------------------------
-    store_wave_tile<BITS, OUT, EPI, ASYM>(acc, a, (int64_t)mt * kTileM + wave * kWaveM, nt, lane,
-                                           lds_sx + wave * kWaveM, lds_cx + wave * kWaveM, lds_sw, lds_bs, lds_rs);
+    store_wave_tile<BITS, OUT, EPI, ASYM, OUT == QC_OUT_F32>(acc, a, (int64_t)mt * TM + wave * (16 * MI), nt, lane,
+                                           lds_sx + wave * (16 * MI), lds_cx + wave * (16 * MI), lds_sw, lds_bs, lds_rs);
 }
 
 // ---- the same GEMM with the weight tile resident in LDS (short reductions) ---------------------
@@ -488,7 +496,7 @@ __global__ __launch_bounds__(kResThreads, 1) void gemm_resident_kernel(GemmArgs 
     const int slot = xs.slot, nbx = xs.blocks, c_lo = xs.c_lo, c_hi = xs.c_hi;
     const int wave_tiles = a.m_tiles * (kTileM / kWaveM);          // 64-token tiles inside Mp
 
-    v4i xq[kXSlots][4];
+    v4i xq[kStages][4];
     v4i wr[2][4];
     const uint32_t lds_lane = (uint32_t)(uintptr_t)lds + lane * 16;
 
@@ -661,7 +669,7 @@ __global__ __launch_bounds__(kResThreads, 1) void gemm_resident_kernel(GemmArgs 
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        store_wave_tile<BITS, OUT, EPI, ASYM>(acc, a, (int64_t)wt_now * kWaveM, nt_now, lane, lds_sx, lds_cx,
+        store_wave_tile<BITS, OUT, EPI, ASYM, false>(acc, a, (int64_t)wt_now * kWaveM, nt_now, lane, lds_sx, lds_cx,
                                                lds_sw, lds_bs, lds_rs);
     } while (have);
 #undef QC_RES_STAGE
@@ -690,7 +698,8 @@ hipError_t launch_variant(const GemmArgs &args, hipStream_t stream) {
     // variant needs no set-up call and can be captured into a graph like any other
     static_assert(kLds <= 64 * 1024, "dynamic LDS beyond the default limit needs an attribute");
     const int blocks = args.m_tiles * args.n_tiles;
-    gemm_kernel<BITS, OUT, EPI, ASYM><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
+    if (args.half) gemm_kernel<BITS, OUT, EPI, ASYM, 2><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
+    else gemm_kernel<BITS, OUT, EPI, ASYM, 4><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
     return hipGetLastError();
 }
 
@@ -743,6 +752,28 @@ bool gemm_resident_chosen(int64_t M, int64_t N, int64_t K, int bits) {
 
 int gemm_resident_blocks() { return kResBlocks; }
 
+// Tiles of 128 tokens instead of 256 for the ring kernel where they spread the work better: while
+// even they leave at most one block per CU, and where the full ones are just more than one per
+// CU, so that the launch lasts for two of them on the CUs that have two.  Measured, full against half,
+// whole calls (full tiles: us): K = 1152: 36: 13.7 11.2, 108: 15.5 12.1, 288: 20.9 17.8, 324: 23.0 20.3,
+// 351: 25.6 24.0 but 24.5 24.1 on another box, 432: 24.2 25.2, 846: 51.0 54.9; K = 4608: 36: 33.6
+// 24.8, 108: 36.1 28.2, 144: 36.5 37.4, 216: 42.6 45.7, 288: 65.9 64.4, 423: 79.4 87.7.
+constexpr int kCus = 256;
+static bool ring_half_height(int m_tiles, int n_tiles) {
+    const int64_t tiles = (int64_t)m_tiles * n_tiles;
+    return 2 * tiles <= kCus || (tiles > kCus && tiles <= kCus * 13 / 10);
+}
+
+// 32-bit output: non-temporal stores write it to memory at once, ordinary ones into the last-level
+// cache, where the next layer finds it, if it fits there and is not so small that writing back the L2s
+// at the end of the launch weighs more.  Measured with N = 3456, K = 1152 (MB of output: us non-temporal,
+// ordinary): 14: 16.3 17.4, 21: 18.2 19.7, 28: 22.7 21.2, 113: 66.0 54.6, 226: 113 98, 331: 153 145,
+// 453 (the resident kernel): 173 203.  bf16 output is up to 9 % slower with ordinary stores.
+static bool keep_f32_output(int64_t M, int64_t N) {
+    const int64_t bytes = 4 * M * N;
+    return bytes >= (int64_t)24 << 20 && bytes <= (int64_t)256 << 20;
+}
+
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                        int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
@@ -774,6 +805,9 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     // Measured at M = 131072: 8 is the best of 4 .. 32 for the wide layers; for the narrow ones
     // 2 is the best of 1 .. 8 at K = 1152 and 3 the best of 2 .. 6 at K = 4608 (545 against
     // 557 us with 8-bit weights, no difference at M = 65536 or with 4-bit weights).
+    args.half = !args.resident && ring_half_height(args.m_tiles, args.n_tiles);
+    if (args.half) args.m_tiles = (int)((M + kTileM / 2 - 1) / (kTileM / 2));
+    args.keep_output = keep_f32_output(M, N);
     args.group_m = args.n_tiles > 16 ? 8 : (args.KF >= 36 ? 3 : 2);
     if (x_corr && w_rowsum)
         return bits == 8 ? launch_bits<8, true>(args, epi, ydt, stream)

@@ -70,6 +70,22 @@ def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
     run_linear_case(random_x(rng, M, K, "bf16"), W, b, bits, "gelu_tanh", "bf16", check_acc=False)
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N", [(5505, 192, 130), (16384, 64, 129), (16385, 64, 129), (21889, 64, 257), (21249, 320, 512),
+                                   (21250, 64, 511), (26001, 64, 512)])
+def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
+    """Tiles of 128 tokens up to 128 full tiles and from 257 to 332 of them, tiles of 256 otherwise; with
+    32-bit output also both kinds of store (through the caches from 24 MB on); an asymmetric one."""
+    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    rng = np.random.default_rng(M + N + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    x = random_x(rng, M, K, "bf16")
+    run_linear_case(x, W, b, bits, "gelu_tanh", "bf16")
+    run_linear_case(x, W, None, bits, "none", "f32", check_acc=False)
+    run_asym_case(x, W, b, bits, "gelu_erf", "bf16")
+
+
 @pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 170 * 4096, 170 * 4096 + 5, (12 << 20) // 8, (12 << 20) // 8 + 1])
 def test_reductions_on_both_sides_of_the_one_launch_form(n):
     """Up to 12 MB of input the block that sees all partial sums finishes (170 blocks at most, one pass
