@@ -242,7 +242,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
 // (128 for 8-bit codes, else 0; Section 3.1 Eq. (3)-(4) as printed).  With c[m] = h - z[m] the dequantized activation
 // is sx (code + c), so the epilogue adds c[m] * sum_k qw[n, k] to the accumulator.
 template <int BITS, int OUT, int EPI, bool ASYM, int MI>
-__global__ __launch_bounds__(kThreads, MI == 4 ? 2 : 3) void gemm_kernel(GemmArgs a) {
+__device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     using L = StageLayout<BITS>;
     constexpr int TM = 4 * 16 * MI;   // tokens of the block, 16 MI of them a wavefront's
     constexpr int FPW = L::kFragsPerWave;
@@ -455,6 +455,17 @@ __global__ __launch_bounds__(kThreads, MI == 4 ? 2 : 3) void gemm_kernel(GemmArg
     // ---- epilogue: registers -> Y --------------------------------------------------------
     store_wave_tile<BITS, OUT, EPI, ASYM, OUT == QC_OUT_F32>(acc, a, (int64_t)mt * TM + wave * (16 * MI), nt, lane,
                                            lds_sx + wave * (16 * MI), lds_cx + wave * (16 * MI), lds_sw, lds_bs, lds_rs);
+}
+
+template <int BITS, int OUT, int EPI, bool ASYM>
+__global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
+    ring_gemm<BITS, OUT, EPI, ASYM, 4>(a);
+}
+
+// tiles of 128 tokens x 128 channels: see ring_half_height()
+template <int BITS, int OUT, int EPI, bool ASYM>
+__global__ __launch_bounds__(kThreads, 3) void gemm_half_kernel(GemmArgs a) {
+    ring_gemm<BITS, OUT, EPI, ASYM, 2>(a);
 }
 
 // ---- the same GEMM with the weight tile resident in LDS (short reductions) ---------------------
@@ -698,8 +709,8 @@ hipError_t launch_variant(const GemmArgs &args, hipStream_t stream) {
     // variant needs no set-up call and can be captured into a graph like any other
     static_assert(kLds <= 64 * 1024, "dynamic LDS beyond the default limit needs an attribute");
     const int blocks = args.m_tiles * args.n_tiles;
-    if (args.half) gemm_kernel<BITS, OUT, EPI, ASYM, 2><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
-    else gemm_kernel<BITS, OUT, EPI, ASYM, 4><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
+    if (args.half) gemm_half_kernel<BITS, OUT, EPI, ASYM><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
+    else gemm_kernel<BITS, OUT, EPI, ASYM><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
     return hipGetLastError();
 }
 
