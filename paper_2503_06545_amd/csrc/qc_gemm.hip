@@ -68,6 +68,7 @@ struct GemmArgs {
     bool resident;  // run the kernel that keeps the weight tile in LDS
     bool half;      // ring kernel: tiles of 128 tokens
     bool keep_output;  // ring kernel, f32 output: stores through the caches
+    bool stream_edges; // bf16 output: non-temporal stores also for rows and tiles that are not whole
 };
 
 __device__ inline void lds_dma_16(const uint8_t *gsrc, uint8_t *lds_dst) {
@@ -96,12 +97,14 @@ __device__ inline void tile_of_block(int b, int nblocks, int m_tiles, int n_tile
 // vmcnt(n) with the other counters left unconstrained (gfx9 encoding: bits 3:0 and 15:14, n < 64)
 #define QC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// One piece of a row of Y.  CACHED: at any alignment of its elements, and not past the caches, where the
-// pieces of a line that two tiles or two rows share meet.
-template <bool CACHED, typename T, typename V>
+// One piece of a row of Y.  ANY: at any alignment of its elements.  CACHED: not past the caches, where
+// the pieces of a line that two tiles, two rows or two instructions share meet.
+template <bool ANY, bool CACHED, typename T, typename V>
 __device__ inline void store_piece(T *p, V v) {
-    if constexpr (CACHED) __builtin_memcpy(p, &v, sizeof(v));
-    else __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
+    typedef V VAny __attribute__((aligned(2)));
+    typedef std::conditional_t<ANY, VAny, V> P;
+    if constexpr (CACHED) *reinterpret_cast<P *>(p) = v;
+    else __builtin_nontemporal_store(v, reinterpret_cast<P *>(p));
 }
 
 // Epilogue of one wavefront's tile of 16 MI tokens x 128 channels: registers -> Y.  Lane (c = lane % 16, h = lane / 16)
@@ -180,7 +183,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         if (vec[j]) {
-                            store_piece<CACHED>(y + 4 * j, v4i{raw[4 * j], raw[4 * j + 1], raw[4 * j + 2], raw[4 * j + 3]});
+                            store_piece<CHECKED, CACHED>(y + 4 * j, v4i{raw[4 * j], raw[4 * j + 1], raw[4 * j + 2], raw[4 * j + 3]});
                         } else {
 #pragma unroll
                             for (int t = 4 * j; t < 4 * j + 4; ++t) if (n0 + t < a.N) y[t] = raw[t];
@@ -202,7 +205,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
                             if (vec[j]) {
-                                store_piece<CACHED>(y + 4 * j, f4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]});
+                                store_piece<CHECKED, CACHED>(y + 4 * j, f4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]});
                             } else {
 #pragma unroll
                                 for (int t = 4 * j; t < 4 * j + 4; ++t) if (n0 + t < a.N) y[t] = v[t];
@@ -214,12 +217,12 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
 #pragma unroll
                         for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(v[2 * j], v[2 * j + 1]);
                         if (vec8) {
-                            store_piece<CACHED>(y, u4{pk[0], pk[1], pk[2], pk[3]});
+                            store_piece<CHECKED, CACHED>(y, u4{pk[0], pk[1], pk[2], pk[3]});
                         } else {
 #pragma unroll
                             for (int j = 0; j < 2; ++j) {
                                 if (vec[j]) {
-                                    store_piece<CACHED>(y + 4 * j, u2{pk[2 * j], pk[2 * j + 1]});
+                                    store_piece<CHECKED, CACHED>(y + 4 * j, u2{pk[2 * j], pk[2 * j + 1]});
                                 } else {
 #pragma unroll
                                     for (int t = 4 * j; t < 4 * j + 4; ++t)
@@ -233,7 +236,8 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
             }
         }
     };
-    if (!interior) write_tile(std::true_type{}, std::true_type{});
+    if (!interior && OUT == QC_OUT_BF16 && a.stream_edges) write_tile(std::true_type{}, std::bool_constant<OUT != QC_OUT_BF16>{});
+    else if (!interior) write_tile(std::true_type{}, std::true_type{});
     else if (MAY_KEEP && a.keep_output) write_tile(std::false_type{}, std::bool_constant<MAY_KEEP>{});
     else write_tile(std::false_type{}, std::false_type{});
 }
@@ -785,6 +789,13 @@ static bool keep_f32_output(int64_t M, int64_t N) {
     return bytes >= (int64_t)24 << 20 && bytes <= (int64_t)256 << 20;
 }
 
+// Rows of bf16 that are no multiple of 16 B long, and partly filled tiles: through the caches while the
+// output fits the last-level cache, past them beyond (N = 3460, K = 1152, ordinary and non-temporal: 113 MB
+// 72.3 78.6 us, 454 MB 333 287; N = 1156: 303 MB 286 253).  With 32-bit output a piece covers half of the
+// bytes that its neighbours on the line need at once, and non-temporal stores always lose (N = 3457:
+// 227 MB 101 189, 906 MB 500 674).
+static bool stream_bf16_edges(int64_t M, int64_t N) { return 2 * M * N > (int64_t)256 << 20; }
+
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                        int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
@@ -819,6 +830,7 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     args.half = !args.resident && ring_half_height(args.m_tiles, args.n_tiles);
     if (args.half) args.m_tiles = (int)((M + kTileM / 2 - 1) / (kTileM / 2));
     args.keep_output = keep_f32_output(M, N);
+    args.stream_edges = stream_bf16_edges(M, N);
     args.group_m = args.n_tiles > 16 ? 8 : (args.KF >= 36 ? 3 : 2);
     if (x_corr && w_rowsum)
         return bits == 8 ? launch_bits<8, true>(args, epi, ydt, stream)

@@ -86,6 +86,14 @@ def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
     run_asym_case(x, W, b, bits, "gelu_erf", "bf16")
 
 
+def test_qlinear_ragged_rows_beyond_the_last_level_cache():
+    """bf16 output of more than 256 MB whose rows are no multiple of 16 B: non-temporal stores at any alignment."""
+    M, K, N = 262145, 64, 513
+    rng = np.random.default_rng(513)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    run_linear_case(random_x(rng, M, K, "bf16"), W, None, 8, "none", "bf16", check_acc=False)
+
+
 @pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 170 * 4096, 170 * 4096 + 5, (12 << 20) // 8, (12 << 20) // 8 + 1])
 def test_reductions_on_both_sides_of_the_one_launch_form(n):
     """Up to 12 MB of input the block that sees all partial sums finishes (170 blocks at most, one pass
