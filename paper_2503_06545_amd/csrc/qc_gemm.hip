@@ -5,7 +5,8 @@
 //   Y[m, n]   = act(acc * sx[m] * sw[n] + bias[n])
 //
 // Two kernels share the wavefront tile, the operand formats and the epilogue: gemm_kernel
-// streams its weight tile through a ring in LDS and takes any K; gemm_resident_kernel (further
+// streams its weight tile through a ring in LDS and takes any K (gemm_half_kernel the same with
+// tiles of 128 tokens); gemm_resident_kernel (further
 // down) keeps a whole weight tile in LDS and is taken for short reductions on large problems.
 //
 // gemm_kernel: block tile 256 tokens x 128 channels, 4 wavefronts stacked along the tokens, each
