@@ -120,7 +120,8 @@ qc_status qc_quant_act(const void *X, qc_dtype xdt, int64_t M, int64_t K, int8_t
  *   w_scale    device, float [N]
  *   bias       device, float [N], or NULL for no bias
  *   Y          device, [M, N] of float (QC_OUT_F32), bf16 (QC_OUT_BF16) or int32
- *              (QC_OUT_I32_ACC; bias and epi are then ignored)
+ *              (QC_OUT_I32_ACC; bias and epi are then ignored).  May lie over X, wholly or in
+ *              part: X is then quantized before anything of Y is written
  *   workspace  device, >= qc_qlinear_workspace_bytes(M, K, N) bytes, 256-byte aligned;
  *              contents on entry are irrelevant, on exit it holds the activation codes
  *              in tiled order (see qc_debug_workspace_act)

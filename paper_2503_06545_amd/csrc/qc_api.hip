@@ -145,6 +145,11 @@ qc_status qlinear_quant_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, A
                                           (hipStream_t)stream));
 }
 
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y ? y - x < a_bytes : x - y < b_bytes;
+}
+
 qc_status qlinear_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, ActQuant how,
                       const void *packed, const float *w_scale, int bits, int64_t N,
                       const float *bias, qc_epilogue epi, void *Y, qc_out ydt, void *workspace,
@@ -157,7 +162,11 @@ qc_status qlinear_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, ActQuan
     QC_TRY(check_gemm_supported(M, K, N, bits));
     const ActWorkspace ws = act_workspace(M, K);
     if (workspace_bytes < ws.total_bytes) return QC_ERR_WORKSPACE;
-    if (how.rot_block == 0 && qlinear_small_chosen(M, N, K)) {
+    // Y may lie over X: in two launches X has been read when the GEMM writes.  In one launch the blocks
+    // that write Y run beside others that still read X.
+    const size_t x_bytes = (size_t)M * (size_t)K * (xdt == QC_BF16 ? 2 : 4);
+    const size_t y_bytes = (size_t)M * (size_t)N * (ydt == QC_OUT_BF16 ? 2 : 4);
+    if (how.rot_block == 0 && qlinear_small_chosen(M, N, K) && !overlap(X, x_bytes, Y, y_bytes)) {
         uint8_t *base = (uint8_t *)workspace;
         return device_status(launch_qlinear_small(X, xdt, base + ws.scale_bytes, (float *)base,
                                                   (const uint8_t *)packed, w_scale, bias, Y, M, N, K,

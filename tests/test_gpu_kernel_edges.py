@@ -56,6 +56,30 @@ def test_qlinear_on_few_tokens_at_the_edges_of_its_tiles(M, K, N, bits):
         run_asym_case(x, W, b, bits, "none", "bf16")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("M,K,N,shift", [(2, 1152, 1152, 0), (64, 1152, 1152, 0), (256, 1152, 1152, 0), (100, 1152, 640, 0),
+                                         (64, 1152, 1152, 16), (64, 1152, 1152, -16), (33, 1000, 1000, 0), (64, 1152, 64, 1)])
+def test_qlinear_on_few_tokens_over_its_own_input(M, K, N, shift, dtype):
+    """Y over X, wholly or shifted by some rows, gives what a Y of its own gives: every block of the
+    one-launch form reads tokens that another block's output would have replaced."""
+    assert qc.qc_debug_gemm_kernel(M, K, N, 8) == 3
+    rng = np.random.default_rng(M + K + N + shift)
+    pw = qc.pack_weight_t(dev((rng.standard_normal((N, K)) * 0.02).astype(np.float32)), 8)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    off = 64 * 1152                                   # room for Y on either side
+    buf = torch.zeros(off + max(M * K, M * N) + off, dtype=t, device="cuda")
+    X = buf[off:off + M * K].view(M, K)
+    at = off + shift * N
+    Y = buf[at:at + M * N].view(M, N)
+    for _ in range(5):
+        x = dev(random_x(rng, M, K, dtype))
+        X.copy_(x)
+        want = qc.qlinear_t(x, pw, None, "none", dtype)
+        got = qc.qlinear_t(X, pw, None, "none", dtype, Y=Y)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("N", [129, 130, 132, 136])
 def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
