@@ -145,11 +145,6 @@ qc_status qlinear_quant_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, A
                                           (hipStream_t)stream));
 }
 
-bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
-    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-    return x < y ? y - x < a_bytes : x - y < b_bytes;
-}
-
 qc_status qlinear_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, ActQuant how,
                       const void *packed, const float *w_scale, int bits, int64_t N,
                       const float *bias, qc_epilogue epi, void *Y, qc_out ydt, void *workspace,

@@ -144,6 +144,7 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
 //   kCount, kElems       sums it keeps; elements per pack
 //   kThreads, kUnroll    launch shape of the two-launch form: threads, packs in flight per lane
 //   kOneUnroll, kBytes   packs in flight in the one-launch form (512 threads); the workspace
+//   kOuts                floats of output
 //   Regs, load, add      what a pack occupies, how it is read and summed
 //   tail                 one element past the last whole pack
 //   finish               totals -> outputs
@@ -205,7 +206,7 @@ __device__ inline float widen(uint16_t v) { return __uint_as_float((uint32_t)v <
 
 // sum|cur - prev|, sum|prev| -> both and their ratio
 struct DeltaOp {
-    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2;
+    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOuts = 3;
     static constexpr size_t kBytes = kDeltaBytes;
     const float *cur, *prev;
     struct Regs { float4 a, b; };
@@ -229,7 +230,7 @@ struct DeltaOp {
 template <typename T>
 struct SimilarityOp {
     // (1024 threads, 4 packs: 48.3 us on two bf16 tensors of 65536 x 1152; 512 and 2: 47.1)
-    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 2, kOneUnroll = 2;
+    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 2, kOneUnroll = 2, kOuts = 4;
     static constexpr size_t kBytes = kSimilarityBytes;
     const T *a, *b;
     struct Regs { Pack<T> x, y; };
@@ -270,7 +271,7 @@ struct SimilarityOp {
 // its elements only (the hardware takes 16 B loads at any address).
 template <typename T>
 struct GradientOp {
-    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4, kOneUnroll = 2;
+    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOuts = 2;
     static constexpr size_t kBytes = kGradientBytes;
     const T *m;
     int64_t inner;
@@ -305,7 +306,7 @@ struct PrevList { const float *p[QC_MAX_PREV]; };
 template <int COUNT>
 struct VariationOp {
     // two wavefronts per SIMD: room for 2 x 2 (COUNT + 1) float4 per lane
-    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1;
+    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1, kOuts = COUNT + 1;
     static constexpr size_t kBytes = kVariationBytes;
     const float *cur;
     PrevList prevs;
@@ -421,7 +422,9 @@ qc_status launch_reduction(const Op &op, int64_t n, int64_t bytes, float *out, v
         const int64_t b = (n / Op::kElems + chunk - 1) / chunk;
         return (unsigned)(b < 1 ? 1 : b > most ? most : b);
     };
-    if (bytes <= kOneLaunchBytes) {
+    // One launch needs the records to itself until every block that has the totals has spoiled the
+    // checks: outputs that lie in the workspace are written by the second launch.
+    if (bytes <= kOneLaunchBytes && !overlap(out, Op::kOuts * sizeof(float), workspace, Op::kBytes)) {
         constexpr int U = Op::kOneUnroll;
         const unsigned blocks = blocks_for((int64_t)kOneThreads * U, one_launch_blocks(Op::kBytes, Op::kCount));
         reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks), dim3(kOneThreads), 0, st>>>(op, n, partials, out, next_nonce());

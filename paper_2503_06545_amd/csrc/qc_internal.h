@@ -45,6 +45,12 @@ constexpr float kAbsmaxFloor = 0x1p-64f;
 
 __host__ __device__ inline int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
+// whether two ranges of memory have a byte in common
+inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y ? y - x < a_bytes : x - y < b_bytes;
+}
+
 __host__ __device__ inline int64_t byte_in_frag(int64_t row16, int64_t k) {
     return (((k % kFragK) / 16) * 16 + row16) * 16 + k % 16;
 }

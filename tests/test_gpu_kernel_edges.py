@@ -137,6 +137,26 @@ def test_reductions_on_both_sides_of_the_one_launch_form(n):
     assert np.all(np.abs(other - ref) <= 1e-5 * np.abs(ref))
 
 
+def test_reductions_into_their_own_workspace():
+    """Outputs inside the workspace, at its start or at the check word of a block's record, are what
+    outputs elsewhere are: no block may spoil a check that is an output by then.  (The two forms add the
+    same 64-bit sums in another order: a unit in the last place of the rounding to 32 bits, 1.2e-7.)"""
+    rng = np.random.default_rng(8)
+    a, b = (dev(rng.standard_normal(65536).astype(np.float32)) for _ in range(2))
+    m = dev(rng.standard_normal((16, 2048)).astype(np.float32))
+    for call, out, floats, bytes_ in (
+            (lambda **k: qc.latent_delta_t(a, b, **k), "out3", 3, qc.qc_latent_delta_workspace_bytes(65536)),
+            (lambda **k: qc.layer_similarity_t(a, b, **k), "out4", 4, qc.qc_layer_similarity_workspace_bytes(65536)),
+            (lambda **k: qc.frame_gradient_norm_t(m, **k), "out2", 2, qc.qc_frame_gradient_norm_workspace_bytes(16, 2048)),
+            (lambda **k: qc.cumulative_variation_t(a, [b, a], **k), "out", 3, qc.qc_cumulative_variation_workspace_bytes(65536, 2))):
+        ws = torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+        want = call(workspace=ws).cpu()
+        for at in (0, 8, 16, 24, bytes_ // 2, bytes_ - 4 * floats):
+            inside = ws[at:at + 4 * floats].view(torch.float32)
+            for _ in range(10):
+                assert torch.allclose(call(workspace=ws, **{out: inside}).cpu(), want, rtol=1e-6, atol=0), (out, at)
+
+
 @pytest.mark.parametrize("count", [1, 4, 5, 7, 8])
 def test_one_launch_variation_fills_its_workspace(count):
     """256 blocks, or 227 with eight distances, on a workspace of exactly the stated size with guard
