@@ -6,15 +6,21 @@
 //
 // HBM-bound where they are large, bound by launches and dependent round trips where they are small,
 // hence two forms of one kernel:
-//   * Two launches, for large tensors: at most one block per CU (256), every lane with its next
-//     chunk's loads in flight while it sums the present one; a second, single-block launch adds the
-//     blocks' partial sums.
-//   * One launch, for up to 12 MB of input: the block that sees all partial sums finishes the job
-//     (finish_here() says how, without a counter that somebody would have to clear).  A launch (3 us
-//     of host time) less, and less time on the GPU while the launch boundary weighs more than the
-//     few blocks whose records fit the workspace.  Calls back to back, two launches against one:
-//     latent delta of 65536 elements 6.3 and 4.7 us, 262144 6.8 and 5.4, 1048576 6.9 and 6.9,
-//     4194304 9.3 and 10.2; variation over 3 tensors of 262144 6.6 and 5.8, of 1048576 6.9 and 7.1.
+//   * Two launches: at most one block per CU (256), every lane with its next chunk's loads in flight
+//     while it sums the present one; a second, single-block launch adds the blocks' partial sums.
+//   * One launch, for small tensors: 16 or 32 blocks at most, of which the one that sees all partial
+//     sums finishes the job (finish_here() says how, without a counter that somebody would have to
+//     clear).  What it saves is a launch, 3 us of host time; what it costs on the GPU are the device
+//     fence of each block and the blocks' reading of each other's records, which grow with the number
+//     of blocks (frame gradient of 2 MB: 16 blocks 5.3 us, 32 4.6, 128 8.5; two launches 4.3).
+//     Each operation's limit (kOneMost) lies where one launch takes 1.5 us more on the GPU than two,
+//     half of what it saves the host.  us per call in a graph, two launches and one, warm and, behind
+//     the bar, cold inputs; from the host back to back it is 10.3 and 7.3 for all of them:
+//       latent delta     0.5 MB 4.7 4.1 | 6.0 4.6   1 MB 4.6 4.3 | 6.0 5.1   4 MB 4.8 5.4 | 6.3 6.6   8 MB 5.9 7.8 | 6.5 9.0
+//       similarity bf16  0.5 MB 4.7 4.6 | 5.2 5.1   1 MB 4.7 5.1 | 5.3 5.6   4 MB 4.8 6.3 | 5.6 7.2   8 MB 5.1 7.9 | 6.2 9.7
+//       frame gradient   0.5 MB 4.2 3.9 | 4.7 4.4   1 MB 4.3 4.5 | 4.8 4.8   2 MB 4.3 4.6 | 4.9 5.2   4 MB 4.3 5.6 | 6.3 8.6
+//       variation over 1, 3, 8 tensors of 65536 elements 3.6 4.6 7.7, 3.7 4.6 8.0 | 4.1 5.5 9.1, 4.3 5.5 9.0;
+//       of 262144 3.7 5.2 9.0, 4.4 6.4 11 | 4.4 5.7 9.4, 5.2 7.0 13
 #include <atomic>
 
 #include "qc_device.h"
@@ -25,17 +31,12 @@ namespace {
 constexpr int kFinalThreads = 256;  // the second launch: one partial sum tuple per thread
 constexpr int kMaxBlocks = 256;     // two launches: one block per CU
 constexpr int kOneThreads = 512;    // one launch
-constexpr int64_t kOneLaunchBytes = 12 << 20;
-static_assert(kFinalThreads >= kMaxBlocks && kOneThreads >= kMaxBlocks, "a thread per block in the combine");
+constexpr int kOneBlocks = 32;
+static_assert(kFinalThreads >= kMaxBlocks && kOneBlocks <= 64, "a thread, a lane per block in the combine");
 
 // the workspaces: a double per sum and block of the two-launch form
 constexpr size_t kDeltaBytes = kMaxBlocks * 2 * sizeof(double), kSimilarityBytes = kMaxBlocks * 3 * sizeof(double);
 constexpr size_t kGradientBytes = kMaxBlocks * sizeof(double), kVariationBytes = kMaxBlocks * QC_MAX_PREV * sizeof(double);
-// blocks of the one-launch form whose records, the sums and a check word, fit there
-constexpr int one_launch_blocks(size_t bytes, int sums) {
-    const size_t b = bytes / (sizeof(double) * (sums + 1));
-    return b < kMaxBlocks ? (int)b : kMaxBlocks;
-}
 
 // one DPP move of a binary64 value (two 32-bit halves); CTRL as in the ISA's dpp_ctrl field
 template <int CTRL>
@@ -79,21 +80,22 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
 }
 
 // The one-launch form's end.  v: this block's sums, valid in wavefront 0.  Every block publishes its
-// sums and a check word, a hash of the launch's nonce and the sums, with device-scope stores, passes a
-// sequentially consistent fence, and then reads everybody's.  A block's sums count
-// once they fit their check, whatever the workspace held before, and whichever words a reader
-// catches.  The block whose stores come last sees all of them: at least one block finds everything
-// present, forms the totals (every block that does forms the same ones) and spoils the checks, so
-// that a replay of this launch from a graph, with the same nonce, finds nothing stale.  Nobody waits
-// for anybody.  Returns whether this block has the totals in v (all threads).
+// sums and a check word, a 64-bit hash of the launch's nonce and the sums, with device-scope stores,
+// passes a sequentially consistent fence, and then reads everybody's.  A block's sums count once they
+// fit their check.  Words of a record half written or left by something else fit it with a probability
+// of 2^-64; a whole record of an earlier launch with the same nonce, a replay of this one from a
+// graph, is not there, because a launch clears its checks before it ends.  The block whose stores come
+// last sees all records: at least one block finds everything present, forms the totals (every block
+// that does forms the same ones) and clears the checks.  Nobody waits for anybody.  Returns whether
+// this block has the totals in v (wavefront 0).
 __device__ inline uint64_t mix(uint64_t hash, uint64_t bits) {
     hash = (hash ^ bits) * 0x9E3779B97F4A7C15ull;   // odd: a bijection of hash ^ bits
     return hash ^ (hash >> 32);
 }
 
-template <int THREADS, int COUNT>
-__device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *records, uint64_t nonce) {
-    constexpr int kWords = COUNT + 1, kWaves = kMaxBlocks / 64;
+template <int COUNT>
+__device__ inline bool finish_here(double (&v)[COUNT], uint64_t *records, uint64_t nonce) {
+    constexpr int kWords = COUNT + 1;
     const int tid = threadIdx.x, blocks = gridDim.x;
     if (tid == 0) {
         uint64_t *r = records + kWords * blockIdx.x, check = nonce;
@@ -108,7 +110,7 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
     }
     __syncthreads();
     bool present = true;
-    if (tid < kMaxBlocks) {
+    if (tid < 64) {
         uint64_t *r = records + kWords * (tid < blocks ? tid : 0), word[kWords];
 #pragma unroll
         for (int c = 0; c < kWords; ++c) word[c] = __hip_atomic_load(r + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -121,20 +123,10 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
         present = check == word[COUNT];
     }
     if (!__syncthreads_and(present)) return false;
-    if (tid < blocks) __hip_atomic_store(records + kWords * tid + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid < kMaxBlocks) {
+    if (tid < 64) {
+        if (tid < blocks) __hip_atomic_store(records + kWords * tid + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int c = 0; c < COUNT; ++c) {
-            v[c] = wave_sum(v[c]);
-            if ((tid & 63) == 0) sh[COUNT * (tid >> 6) + c] = v[c];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < COUNT; ++c) {
-        v[c] = sh[c];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) v[c] += sh[COUNT * w + c];
+        for (int c = 0; c < COUNT; ++c) v[c] = wave_sum(v[c]);
     }
     return true;
 }
@@ -144,7 +136,7 @@ __device__ inline bool finish_here(double (&v)[COUNT], double *sh, uint64_t *rec
 //   kCount, kElems       sums it keeps; elements per pack
 //   kThreads, kUnroll    launch shape of the two-launch form: threads, packs in flight per lane
 //   kOneUnroll, kBytes   packs in flight in the one-launch form (512 threads); the workspace
-//   kOuts                floats of output
+//   kOneMost, kOuts      elements up to which that form is taken (see the top); floats of output
 //   Regs, load, add      what a pack occupies, how it is read and summed
 //   tail                 one element past the last whole pack
 //   finish               totals -> outputs
@@ -208,6 +200,7 @@ __device__ inline float widen(uint16_t v) { return __uint_as_float((uint32_t)v <
 struct DeltaOp {
     static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOuts = 3;
     static constexpr size_t kBytes = kDeltaBytes;
+    static constexpr int64_t kOneMost = 1 << 19;
     const float *cur, *prev;
     struct Regs { float4 a, b; };
     __device__ void load(Regs &r, int64_t i) const { r.a = stream4f(cur + 4 * i); r.b = stream4f(prev + 4 * i); }
@@ -232,6 +225,7 @@ struct SimilarityOp {
     // (1024 threads, 4 packs: 48.3 us on two bf16 tensors of 65536 x 1152; 512 and 2: 47.1)
     static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 2, kOneUnroll = 2, kOuts = 4;
     static constexpr size_t kBytes = kSimilarityBytes;
+    static constexpr int64_t kOneMost = (5 << 19) / sizeof(T);
     const T *a, *b;
     struct Regs { Pack<T> x, y; };
     __device__ void load(Regs &r, int64_t i) const { r.x.stream(a + kElems * i); r.y.stream(b + kElems * i); }
@@ -273,6 +267,7 @@ template <typename T>
 struct GradientOp {
     static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOuts = 2;
     static constexpr size_t kBytes = kGradientBytes;
+    static constexpr int64_t kOneMost = (3 << 20) / sizeof(T);
     const T *m;
     int64_t inner;
     struct Regs { Pack<T> x, y; };
@@ -308,6 +303,7 @@ struct VariationOp {
     // two wavefronts per SIMD: room for 2 x 2 (COUNT + 1) float4 per lane
     static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1, kOuts = COUNT + 1;
     static constexpr size_t kBytes = kVariationBytes;
+    static constexpr int64_t kOneMost = 5 << 15;
     const float *cur;
     PrevList prevs;
     struct Regs { float4 a, b[COUNT]; };
@@ -383,7 +379,7 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, doubl
     if (blockIdx.x == 0 && threadIdx.x < (int)(n - packs * Op::kElems)) op.tail(packs * Op::kElems + threadIdx.x, s);
     block_sum<THREADS, C>(s, sh);
     if constexpr (ONE_LAUNCH) {
-        if (finish_here<THREADS, C>(s, sh, reinterpret_cast<uint64_t *>(partials), nonce) && threadIdx.x == 0)
+        if (finish_here(s, reinterpret_cast<uint64_t *>(partials), nonce) && threadIdx.x == 0)
             Op::finish(s, out);
     } else if (threadIdx.x == 0) {
 #pragma unroll
@@ -413,9 +409,8 @@ uint64_t next_nonce() {
     return z ^ (z >> 31);
 }
 
-// bytes: what one pass reads, for the choice of form
 template <typename Op>
-qc_status launch_reduction(const Op &op, int64_t n, int64_t bytes, float *out, void *workspace, void *stream) {
+qc_status launch_reduction(const Op &op, int64_t n, float *out, void *workspace, void *stream) {
     double *partials = (double *)workspace;
     hipStream_t st = (hipStream_t)stream;
     auto blocks_for = [&](int64_t chunk, int most) {
@@ -424,9 +419,13 @@ qc_status launch_reduction(const Op &op, int64_t n, int64_t bytes, float *out, v
     };
     // One launch needs the records to itself until every block that has the totals has spoiled the
     // checks: outputs that lie in the workspace are written by the second launch.
-    if (bytes <= kOneLaunchBytes && !overlap(out, Op::kOuts * sizeof(float), workspace, Op::kBytes)) {
+    if (n <= Op::kOneMost && !overlap(out, Op::kOuts * sizeof(float), workspace, Op::kBytes)) {
         constexpr int U = Op::kOneUnroll;
-        const unsigned blocks = blocks_for((int64_t)kOneThreads * U, one_launch_blocks(Op::kBytes, Op::kCount));
+        static_assert(kOneBlocks * (Op::kCount + 1) * sizeof(double) <= Op::kBytes, "room for the blocks' sums and check words");
+        // 32 blocks where each of 16 would take three chunks or more (below: latent delta of 1 MB, 16 and 32
+        // blocks, 4.3 and 4.7 us; above: variation over 8 tensors of 116508 elements 11.0 and 9.5)
+        const int64_t chunk = (int64_t)kOneThreads * U;
+        const unsigned blocks = blocks_for(chunk, n / Op::kElems < 3 * 16 * chunk ? 16 : kOneBlocks);
         reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks), dim3(kOneThreads), 0, st>>>(op, n, partials, out, next_nonce());
         return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
     }
@@ -439,7 +438,7 @@ qc_status launch_reduction(const Op &op, int64_t n, int64_t bytes, float *out, v
 
 template <int COUNT>
 qc_status launch_variation(const float *cur, const PrevList &prevs, int64_t n, float *out, void *workspace, void *stream) {
-    return launch_reduction(VariationOp<COUNT>{cur, prevs}, n, 4 * n * (COUNT + 1), out, workspace, stream);
+    return launch_reduction(VariationOp<COUNT>{cur, prevs}, n, out, workspace, stream);
 }
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -460,7 +459,7 @@ extern "C" qc_status qc_latent_delta(const float *cur, const float *prev, int64_
     if (!aligned(cur, 16) || !aligned(prev, 16) || !aligned(out3, 4) || !aligned(workspace, 256))
         return QC_ERR_INVALID_ARG;
     if (workspace_bytes < qc_latent_delta_workspace_bytes(n)) return QC_ERR_WORKSPACE;
-    return launch_reduction(DeltaOp{cur, prev}, n, 8 * n, out3, workspace, stream);
+    return launch_reduction(DeltaOp{cur, prev}, n, out3, workspace, stream);
 }
 
 // ---- qc_latent_delta for callers that cannot allocate ---------------------------------------
@@ -512,9 +511,9 @@ extern "C" qc_status qc_layer_similarity(const void *a, const void *b, qc_dtype 
         return QC_ERR_INVALID_ARG;
     if (workspace_bytes < qc_layer_similarity_workspace_bytes(n)) return QC_ERR_WORKSPACE;
     if (dt == QC_BF16)
-        return launch_reduction(SimilarityOp<uint16_t>{(const uint16_t *)a, (const uint16_t *)b}, n, 4 * n, out4,
+        return launch_reduction(SimilarityOp<uint16_t>{(const uint16_t *)a, (const uint16_t *)b}, n, out4,
                                 workspace, stream);
-    return launch_reduction(SimilarityOp<float>{(const float *)a, (const float *)b}, n, 8 * n, out4, workspace, stream);
+    return launch_reduction(SimilarityOp<float>{(const float *)a, (const float *)b}, n, out4, workspace, stream);
 }
 
 extern "C" size_t qc_frame_gradient_norm_workspace_bytes(int64_t frames, int64_t inner) {
@@ -532,8 +531,8 @@ extern "C" qc_status qc_frame_gradient_norm(const void *m, qc_dtype dt, int64_t 
     if (workspace_bytes < qc_frame_gradient_norm_workspace_bytes(frames, inner)) return QC_ERR_WORKSPACE;
     const int64_t n = (frames - 1) * inner;  // number of differences
     if (dt == QC_BF16)
-        return launch_reduction(GradientOp<uint16_t>{(const uint16_t *)m, inner}, n, 2 * n, out2, workspace, stream);
-    return launch_reduction(GradientOp<float>{(const float *)m, inner}, n, 4 * n, out2, workspace, stream);
+        return launch_reduction(GradientOp<uint16_t>{(const uint16_t *)m, inner}, n, out2, workspace, stream);
+    return launch_reduction(GradientOp<float>{(const float *)m, inner}, n, out2, workspace, stream);
 }
 
 extern "C" size_t qc_cumulative_variation_workspace_bytes(int64_t n, int count) {

@@ -1,5 +1,7 @@
 """The kernels' own edges: sizes at which a dispatch rule changes sides or a tile is partly filled,
 against the CPU oracle (codes, scales and integer sums bit for bit)."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -118,10 +120,11 @@ def test_qlinear_ragged_rows_beyond_the_last_level_cache():
     run_linear_case(random_x(rng, M, K, "bf16"), W, None, 8, "none", "bf16", check_acc=False)
 
 
-@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 170 * 4096, 170 * 4096 + 5, (12 << 20) // 8, (12 << 20) // 8 + 1])
+@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 16 * 4096, 16 * 4096 + 5, 48 * 4096 - 1, 48 * 4096, 1 << 19, (1 << 19) + 1, 170 * 4096 + 5,
+                               (12 << 20) // 8, (12 << 20) // 8 + 1])
 def test_reductions_on_both_sides_of_the_one_launch_form(n):
-    """Up to 12 MB of input the block that sees all partial sums finishes (170 blocks at most, one pass
-    of 4096 elements each, more above); beyond that a second launch does.  The workspace holds
+    """Up to 524288 elements the block that sees all partial sums finishes (16 blocks at most, 32 from
+    196608 elements on); beyond that a second launch does.  The workspace holds
     arbitrary bytes, then what the call before left in it."""
     rng = np.random.default_rng(n)
     cur, prev = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
@@ -157,11 +160,12 @@ def test_reductions_into_their_own_workspace():
                 assert torch.allclose(call(workspace=ws, **{out: inside}).cpu(), want, rtol=1e-6, atol=0), (out, at)
 
 
+@pytest.mark.parametrize("large", [False, True])
 @pytest.mark.parametrize("count", [1, 4, 5, 7, 8])
-def test_one_launch_variation_fills_its_workspace(count):
-    """256 blocks, or 227 with eight distances, on a workspace of exactly the stated size with guard
-    bytes behind it."""
-    n = (12 << 20) // (4 * (count + 1))
+def test_variation_stays_in_its_workspace(count, large):
+    """As many elements as the one-launch form takes, and two launches with 256 blocks or nearly, on a
+    workspace of exactly the stated size with guard bytes behind it."""
+    n = (12 << 20) // (4 * (count + 1)) if large else 5 << 15
     rng = np.random.default_rng(count)
     cur = rng.standard_normal(n).astype(np.float32)
     prevs = rng.standard_normal((count, n)).astype(np.float32)
@@ -171,6 +175,28 @@ def test_one_launch_variation_fills_its_workspace(count):
     got = qc.cumulative_variation_t(dev(cur), [dev(p) for p in prevs], workspace=buf[:size]).cpu().numpy()
     assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
     assert bool((buf[size:] == 0x5a).all())
+
+
+@pytest.mark.parametrize("extra", [0, 1, 9])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
+    """The largest inputs of the one-launch form and the smallest beyond it, ragged ones among them."""
+    rng = np.random.default_rng(extra)
+    size = 4 if dtype == "f32" else 2
+    n = (5 << 19) // size + extra
+    a, b = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
+    m = rng.standard_normal((2, (3 << 20) // size + extra)).astype(np.float32)
+    if dtype == "bf16":
+        a, b, m = (synth.to_bf16_bits(t) for t in (a, b, m))
+    for _ in range(2):
+        got = qc.layer_similarity_t(dev(a), dev(b)).cpu().numpy()
+        ref = np.asarray(oracle.layer_similarity(a, b), np.float64)
+        assert np.all(np.abs(got[1:3] - ref[1:3]) <= 1e-5 * np.abs(ref[1:3]))
+        # <a, b> of independent inputs is small against its terms: their rounding is what it is off by
+        assert abs(got[0] - ref[0]) <= 1e-5 * math.sqrt(ref[1] * ref[2]) and abs(got[3] - ref[3]) <= 1e-5
+        got = qc.frame_gradient_norm_t(dev(m)).cpu().numpy()
+        ref = np.asarray(oracle.frame_gradient(m), np.float64)
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
 
 
 def test_one_launch_reductions_replay_from_a_graph():
