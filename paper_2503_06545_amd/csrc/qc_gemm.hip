@@ -68,7 +68,7 @@ struct GemmArgs {
     int group_m;    // token tiles per patch of the block -> tile map (ring kernel)
     bool resident;  // run the kernel that keeps the weight tile in LDS
     bool half;      // ring kernel: tiles of 128 tokens
-    bool keep_output;  // ring kernel, f32 output: stores through the caches
+    bool keep_output;  // ring kernel, f32 output: the kernel that stores through the caches
     bool stream_edges; // bf16 output: non-temporal stores also for rows and tiles that are not whole
 };
 
@@ -111,8 +111,10 @@ __device__ inline void store_piece(T *p, V v) {
 // Epilogue of one wavefront's tile of 16 MI tokens x 128 channels: registers -> Y.  Lane (c = lane % 16, h = lane / 16)
 // of MFMA tile (i, t) holds, in register r, token m_wave + 16 i + 4 h + r and channel
 // 128 nt + 8 c + t.  sx64 / cx64: the tile's token scales / corrections, lds_sw / lds_bs /
-// lds_rs: the channel tile's 128 scales, biases and code sums, all in LDS.
-template <int BITS, int OUT, int EPI, bool ASYM, bool MAY_KEEP, int MI>
+// lds_rs: the channel tile's 128 scales, biases and code sums, all in LDS.  KEEP: interior tiles
+// through the caches; a parameter of the kernel, because two copies of the straight-line path under a
+// condition are merged by the compiler, which then drops the non-temporal hint of the one.
+template <int BITS, int OUT, int EPI, bool ASYM, bool KEEP, int MI>
 __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArgs &a, int64_t m_wave, int nt,
                                                 int lane, const float *sx64, const float *cx64,
                                                 const float *lds_sw, const float *lds_bs, const float *lds_rs) {
@@ -239,14 +241,13 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
     };
     if (!interior && OUT == QC_OUT_BF16 && a.stream_edges) write_tile(std::true_type{}, std::bool_constant<OUT != QC_OUT_BF16>{});
     else if (!interior) write_tile(std::true_type{}, std::true_type{});
-    else if (MAY_KEEP && a.keep_output) write_tile(std::false_type{}, std::bool_constant<MAY_KEEP>{});
-    else write_tile(std::false_type{}, std::false_type{});
+    else write_tile(std::false_type{}, std::bool_constant<KEEP>{});
 }
 
 // ASYM: the activation codes are the unsigned codes of the asymmetric quantizer minus a shift h
 // (128 for 8-bit codes, else 0; Section 3.1 Eq. (3)-(4) as printed).  With c[m] = h - z[m] the dequantized activation
 // is sx (code + c), so the epilogue adds c[m] * sum_k qw[n, k] to the accumulator.
-template <int BITS, int OUT, int EPI, bool ASYM, int MI>
+template <int BITS, int OUT, int EPI, bool ASYM, bool KEEP, int MI>
 __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     using L = StageLayout<BITS>;
     constexpr int TM = 4 * 16 * MI;   // tokens of the block, 16 MI of them a wavefront's
@@ -458,19 +459,29 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     }
 
     // ---- epilogue: registers -> Y --------------------------------------------------------
-    store_wave_tile<BITS, OUT, EPI, ASYM, OUT == QC_OUT_F32>(acc, a, (int64_t)mt * TM + wave * (16 * MI), nt, lane,
+    store_wave_tile<BITS, OUT, EPI, ASYM, KEEP>(acc, a, (int64_t)mt * TM + wave * (16 * MI), nt, lane,
                                            lds_sx + wave * (16 * MI), lds_cx + wave * (16 * MI), lds_sw, lds_bs, lds_rs);
 }
 
 template <int BITS, int OUT, int EPI, bool ASYM>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
-    ring_gemm<BITS, OUT, EPI, ASYM, 4>(a);
+    ring_gemm<BITS, OUT, EPI, ASYM, false, 4>(a);
 }
 
 // tiles of 128 tokens x 128 channels: see ring_half_height()
 template <int BITS, int OUT, int EPI, bool ASYM>
 __global__ __launch_bounds__(kThreads, 3) void gemm_half_kernel(GemmArgs a) {
-    ring_gemm<BITS, OUT, EPI, ASYM, 2>(a);
+    ring_gemm<BITS, OUT, EPI, ASYM, false, 2>(a);
+}
+
+// both with f32 output stored through the caches: see keep_f32_output()
+template <int BITS, int EPI, bool ASYM>
+__global__ __launch_bounds__(kThreads, 2) void gemm_cached_kernel(GemmArgs a) {
+    ring_gemm<BITS, QC_OUT_F32, EPI, ASYM, true, 4>(a);
+}
+template <int BITS, int EPI, bool ASYM>
+__global__ __launch_bounds__(kThreads, 3) void gemm_half_cached_kernel(GemmArgs a) {
+    ring_gemm<BITS, QC_OUT_F32, EPI, ASYM, true, 2>(a);
 }
 
 // ---- the same GEMM with the weight tile resident in LDS (short reductions) ---------------------
@@ -714,8 +725,16 @@ hipError_t launch_variant(const GemmArgs &args, hipStream_t stream) {
     // variant needs no set-up call and can be captured into a graph like any other
     static_assert(kLds <= 64 * 1024, "dynamic LDS beyond the default limit needs an attribute");
     const int blocks = args.m_tiles * args.n_tiles;
-    if (args.half) gemm_half_kernel<BITS, OUT, EPI, ASYM><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
-    else gemm_kernel<BITS, OUT, EPI, ASYM><<<dim3((unsigned)blocks), dim3(kThreads), kLds, stream>>>(args);
+    const dim3 grid((unsigned)blocks), block(kThreads);
+    if constexpr (OUT == QC_OUT_F32) {
+        if (args.keep_output) {
+            if (args.half) gemm_half_cached_kernel<BITS, EPI, ASYM><<<grid, block, kLds, stream>>>(args);
+            else gemm_cached_kernel<BITS, EPI, ASYM><<<grid, block, kLds, stream>>>(args);
+            return hipGetLastError();
+        }
+    }
+    if (args.half) gemm_half_kernel<BITS, OUT, EPI, ASYM><<<grid, block, kLds, stream>>>(args);
+    else gemm_kernel<BITS, OUT, EPI, ASYM><<<grid, block, kLds, stream>>>(args);
     return hipGetLastError();
 }
 
@@ -781,13 +800,19 @@ static bool ring_half_height(int m_tiles, int n_tiles) {
 }
 
 // 32-bit output: non-temporal stores write it to memory at once, ordinary ones into the last-level
-// cache, where the next layer finds it, if it fits there and is not so small that writing back the L2s
-// at the end of the launch weighs more.  Measured with N = 3456, K = 1152 (MB of output: us non-temporal,
-// ordinary): 14: 16.3 17.4, 21: 18.2 19.7, 28: 22.7 21.2, 113: 66.0 54.6, 226: 113 98, 331: 153 145,
-// 453 (the resident kernel): 173 203.  bf16 output is up to 9 % slower with ordinary stores.
-static bool keep_f32_output(int64_t M, int64_t N) {
-    const int64_t bytes = 4 * M * N;
-    return bytes >= (int64_t)24 << 20 && bytes <= (int64_t)256 << 20;
+// cache, where the next layer finds it.  Ordinary ones win from 24 MB on, 15 MB with tiles of half the
+// height (below, writing back the L2s at the end of the launch weighs more; half the height, K = 1152,
+// N = 384, 9.8 MB 10.0 10.5, 15.8 MB 14.9 14.0) while output and codes fit the cache together; past that they push
+// out codes that the next tiles need, unless the codes are few.  us, non-temporal and ordinary, K = 1152,
+// N = 1152: output of 18 MB 17.3 18.6, 21 MB 19.3 19.5, 26 MB 21.8 20.4, 127 MB 70 63, with codes 239 MB
+// 91 85, 262 MB 99.6 99.2, 318 MB 119 120, 412 MB 140 156; N = 3456 (an eighth in codes): output of 223
+// MB 112 102, 297 MB 150 136, 398 MB 186 167; K = 2304, N = 640: with codes 242 MB 96 90, 365 MB 123 138;
+// K = 4608, N = 1152: 254 MB 142 140, 320 MB 176 178, 383 MB 202 217; K = 192, N = 1152: 400 MB 176 93.
+// bf16 output is up to 9 % slower with ordinary stores.
+static bool keep_f32_output(int64_t M, int64_t N, int64_t K, bool half) {
+    constexpr int64_t MB = 1 << 20;
+    const int64_t out = 4 * M * N, codes = M * round_up(K, kKAlign);
+    return out >= (half ? 15 : 24) * MB && (out + codes <= 256 * MB || (8 * codes <= out && out <= 400 * MB));
 }
 
 // Rows of bf16 that are no multiple of 16 B long, and partly filled tiles: through the caches while the
@@ -830,7 +855,7 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     // 557 us with 8-bit weights, no difference at M = 65536 or with 4-bit weights).
     args.half = !args.resident && ring_half_height(args.m_tiles, args.n_tiles);
     if (args.half) args.m_tiles = (int)((M + kTileM / 2 - 1) / (kTileM / 2));
-    args.keep_output = keep_f32_output(M, N);
+    args.keep_output = keep_f32_output(M, N, K, args.half);
     args.stream_edges = stream_bf16_edges(M, N);
     args.group_m = args.n_tiles > 16 ? 8 : (args.KF >= 36 ? 3 : 2);
     if (x_corr && w_rowsum)
