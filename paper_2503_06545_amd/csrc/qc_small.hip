@@ -394,13 +394,21 @@ hipError_t launch_bits(int tile, int src, const SmallArgs &a, hipStream_t stream
     }
 }
 
+// Tiles with a channel below N.  A group of 128 channels is cut into tiles of NF = channels / 16 of every
+// eight (channel 8 c + t belongs to tile t / NF), so all tiles of a last group with 8 channels are live.
+int64_t live_channel_tiles(int64_t N, int channels) {
+    const int64_t nf = channels / 16, per_group = 8 / nf, last = (N % kTileN + nf - 1) / nf;
+    return N / kTileN * per_group + (last < per_group ? last : per_group);
+}
+
 // The smallest tile that leaves at most one block per CU, -1 if none does.  Measured, K = 1152
 // (blocks of a tile: us): 128 x 1152: 16 x 32 tiles 288: 5.4, 32 x 32 tiles 144: 4.1; 256 x 1152: 32 x 32
 // 288: 6.0, 32 x 64 144: 5.5; 512 x 1152: 32 x 64 288: 8.7, 64 x 64 144: 6.7; 1000 x 1152: 64 x 64 288:
-// 12.0, the ring kernel 9.1.
+// 12.0, the ring kernel 9.1.  Narrow outputs, whose channel tiles are all live: 8192 x 32: 32 x 32 1024:
+// 24.0, 64 x 64 256 (not fused): 17.4; 16384 x 64: 64 x 64 512: 23.6, the ring kernel 18.1.
 int pick_tile(int64_t M, int64_t N) {
     for (int t = 0; t < kTileCount; ++t) {
-        const int64_t mt = (M + kTiles[t].tokens - 1) / kTiles[t].tokens, nt = (N + kTiles[t].channels - 1) / kTiles[t].channels;
+        const int64_t mt = (M + kTiles[t].tokens - 1) / kTiles[t].tokens, nt = live_channel_tiles(N, kTiles[t].channels);
         if (mt <= kCus && nt <= kCus && mt * nt <= kCus) return t;
     }
     return -1;

@@ -66,3 +66,13 @@ def test_which_problems_take_the_resident_kernel():
     assert qc.qc_debug_gemm_kernel(131072, 2304, 4608, 8) == 1
     assert qc.qc_debug_gemm_kernel(131072, 2305, 4608, 4) == 0      # odd K with 4 bits
     assert qc.qc_debug_gemm_kernel(0, 1152, 4608, 8) == 0
+
+
+def test_which_problems_take_the_few_token_kernel():
+    """While tiles of 64 x 64 leave at most one block per CU.  A group of 128 channels is cut by every
+    eighth: both of its 64-channel tiles have a channel of the output as soon as five do."""
+    for N, tiles in ((1, 1), (4, 1), (5, 2), (32, 2), (64, 2), (128, 2), (129, 3), (132, 3), (133, 4), (1152, 18)):
+        most = 64 * (256 // tiles)
+        for K in (64, 1152, 4608):
+            assert qc.qc_debug_gemm_kernel(most, K, N, 8) == 3, (N, K)
+            assert qc.qc_debug_gemm_kernel(most + 1, K, N, 8) != 3, (N, K)

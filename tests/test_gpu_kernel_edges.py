@@ -41,7 +41,7 @@ def test_row_quantizers_at_the_edges_of_their_column_slices(M, K, dtype):
 @pytest.mark.parametrize("M,K,N", [
     (1, 16, 1), (2, 9216, 40), (3, 6144, 33), (16, 1536, 4100), (16, 1552, 70), (17, 1152, 128), (31, 1280, 2050),
     (32, 1296, 100), (33, 192, 4100), (100, 1152, 4100), (255, 320, 2048), (256, 64, 2050), (512, 208, 2047),
-    (1024, 64, 1024), (1025, 64, 1024), (300, 1000, 131)])
+    (1024, 64, 1024), (1025, 64, 1024), (300, 1000, 131), (1024, 64, 64), (1000, 320, 4), (1001, 1000, 132)])
 def test_qlinear_on_few_tokens_at_the_edges_of_its_tiles(M, K, N, bits):
     """Both sides of every change of tile (16 x 32, 32 x 32, 32 x 64, 64 x 64, then the ring kernel),
     of the longest rows the one-launch form takes (16 tokens: K = 1536, 32: 1280) and of row counts
