@@ -42,15 +42,29 @@ __device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0
 //   get(i)         element i of the lane, i = 0 .. 15 in that order, widened to float
 //   gather_codes() turns dwords of four codes each, in that order, into the 16 codes of one unit of
 //                  16 consecutive columns; lane sub gets unit unit_of(sub) of the eight.
-//   absmax_into()  folds the elements' magnitudes into a running maximum, absmax_value() reads it.
-//                  For bf16 it stays two packed 16-bit patterns (magnitudes order like their bit
-//                  patterns): one v_and and one v_pk_max_u16 for two elements, and nothing widened
-//                  that the compiler would then keep in registers up to the cast.
+//   absmax_into()  folds the elements' magnitudes into a running maximum, absmax_value() reads it; a NaN
+//                  is passed over, like by fmaxf, so that it spoils no code but its own.
+//                  For bf16 it stays two packed 16-bit patterns (Bf16Max): nothing is widened that the
+//                  compiler would then keep in registers up to the cast.
 //   load_ragged()  the same for a K that is no multiple of 16: rows at any alignment (the hardware takes
 //                  16 B loads at any address), the row's last, partial piece element by element, zeros
 //                  past it
 template <typename XT>
 struct Group;
+
+// The largest magnitude of bf16 patterns, two at a time.  A pattern doubled is its magnitude without the
+// sign, and magnitudes order like their patterns; 0xff more and infinity is the largest number of 16 bits,
+// while every NaN wraps round to less than a zero's 0xff and loses to anything.  One v_pk_mad_u16 and one
+// v_pk_max_u16 for two elements.
+struct Bf16Max {
+    u16x2 m = {0xff, 0xff};
+    __device__ void fold(uint32_t two_patterns) {
+        u16x2 twice = {2, 2};
+        asm("" : "+s"(twice));   // a constant the compiler does not see: it would make two instructions of it, a shift and an add
+        m = __builtin_elementwise_max(m, (u16x2)(__builtin_bit_cast(u16x2, two_patterns) * twice + u16x2{0xff, 0xff}));
+    }
+    __device__ float value() const { return __uint_as_float((uint32_t)(((m.x > m.y ? m.x : m.y) - 0xff) >> 1) << 16); }
+};
 
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // 16 B at any element
 
@@ -155,17 +169,14 @@ struct Group<uint16_t> {  // bf16 bit patterns
         const uint32_t s0 = dpp_xor1(odd ? w[0] : w[2]), s1 = dpp_xor1(odd ? w[1] : w[3]);
         return odd ? make_uint4(s0, s1, w[2], w[3]) : make_uint4(w[0], w[1], s0, s1);
     }
-    typedef u16x2 Max;
+    typedef Bf16Max Max;
     __device__ void absmax_into(Max &m) const {
         const uint32_t w[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[i] & 0x7fff7fffu));
+        for (int i = 0; i < 8; ++i) m.fold(w[i]);
     }
-    static __device__ Max no_max() { return u16x2{0, 0}; }
-    static __device__ float absmax_value(Max m) {
-        return __uint_as_float((uint32_t)(m.x > m.y ? m.x : m.y) << 16);
-    }
+    static __device__ Max no_max() { return {}; }
+    static __device__ float absmax_value(const Max &m) { return m.value(); }
 };
 
 // 16 consecutive elements of one row, widened to float by get().
@@ -219,7 +230,7 @@ __device__ inline float quotient(float x, float s, float r) {
 // Four quotients of the symmetric quantizer -> four int8 codes in one dword.  No clamp: with s =
 // RN(a / qmax) and |x| <= a the quotient is at most qmax (1 + 2^-22), which rounds to qmax.  Adding
 // 1.5 * 2^23 rounds to an integer (ties to even) and leaves its two's complement low byte in the
-// low byte of the float.
+// low byte of the float.  A NaN gets some byte as its code.
 __device__ inline uint32_t codes4(float q0, float q1, float q2, float q3) {
     const float magic = 12582912.0f;
     const uint32_t y0 = __float_as_uint(q0 + magic), y1 = __float_as_uint(q1 + magic);

@@ -84,7 +84,7 @@ struct TensorMaxLoad {
 
 // The slabs' maxima: at most one block of 1024 threads per CU, four 16 B loads in flight per lane
 // (64 KiB per CU; with 256 threads and one load the pass ran at 2.3 TB/s: 32768 x 1152 bf16 33 us).
-// bf16 magnitudes are compared as packed bit patterns, see Group.
+// bf16 magnitudes are compared as packed bit patterns, see Bf16Max.
 constexpr int kSlabThreads = 1024;
 constexpr int kSlabUnroll = 4;
 
@@ -95,16 +95,14 @@ __global__ __launch_bounds__(kSlabThreads) void tensor_absmax_kernel(const XT *_
     constexpr int kPer = 16 / (int)sizeof(XT);  // elements per 16 B load
     const int64_t nv = n / kPer;
     const int64_t stride = (int64_t)gridDim.x * kSlabThreads * kSlabUnroll;
-    u16x2 packed = {0, 0};
+    Bf16Max packed;
     float a = 0.0f;
     auto fold = [&](const uint4 &v) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if constexpr (sizeof(XT) == 2)
-                packed = __builtin_elementwise_max(packed, __builtin_bit_cast(u16x2, w[j] & 0x7fff7fffu));
-            else
-                a = fmaxf(a, fabsf(__uint_as_float(w[j])));
+            if constexpr (sizeof(XT) == 2) packed.fold(w[j]);
+            else a = fmaxf(a, fabsf(__uint_as_float(w[j])));
         }
     };
     for (int64_t base = (int64_t)blockIdx.x * kSlabThreads * kSlabUnroll + threadIdx.x; base < nv; base += stride) {
@@ -122,7 +120,7 @@ __global__ __launch_bounds__(kSlabThreads) void tensor_absmax_kernel(const XT *_
         if constexpr (sizeof(XT) == 2) a = fmaxf(a, fabsf(__uint_as_float((uint32_t)t << 16)));
         else a = fmaxf(a, fabsf(t));
     }
-    if constexpr (sizeof(XT) == 2) a = fmaxf(a, Group<XT>::absmax_value(packed));
+    if constexpr (sizeof(XT) == 2) a = fmaxf(a, packed.value());
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) a = fmaxf(a, __shfl_xor(a, d));
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = a;

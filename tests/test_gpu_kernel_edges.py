@@ -249,6 +249,41 @@ def test_tensor_scale_at_the_edges_of_its_slabs(M, K, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tensor", [False, True])
+@pytest.mark.parametrize("M,K", [(2, 1152), (64, 1000), (9, 2048), (9, 2064), (5, 6160), (3, 9216), (40, 1009)])
+def test_nan_spoils_no_code_but_its_own(M, K, tensor, dtype):
+    """A NaN beside the largest magnitude of its row: the scales and all other codes are those of the
+    input with zeros in the NaNs' place, in the row kernels, their ragged form, the one-launch linear
+    and the pass for the tensor's maximum."""
+    rng = np.random.default_rng(M * 13 + K)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    cols = rng.integers(0, K // 2, M) * 2
+    x[np.arange(M), cols + 1] = -30.0 - np.arange(M)
+    x = synth.to_bf16_bits(x) if dtype == "bf16" else x.view(np.uint32)
+    nans = np.array([0x7fc0, 0xffff, 0x7f81, 0xffc0], np.uint32)[np.arange(M) % 4] << (0 if dtype == "bf16" else 16)
+    clean, bad = x.copy(), x.copy()
+    clean[np.arange(M), cols] = 0
+    bad[np.arange(M), cols] = nans.astype(x.dtype)
+    if dtype == "f32":
+        clean, bad = clean.view(np.float32), bad.view(np.float32)
+    q_ref, s_ref = oracle.quant_act_tensor(clean) if tensor else oracle.quant_act(clean)
+    s_ref = np.broadcast_to(np.asarray(s_ref, np.float32), (M,))
+    here = np.zeros((M, K), bool)
+    here[np.arange(M), cols] = True
+
+    pw = qc.pack_weight_t(dev((rng.standard_normal((40, K)) * 0.02).astype(np.float32)), 8)
+    make, call = ((qc.qlinear_tensor_workspace_t, qc.qlinear_tensor_t) if tensor else (qc.qlinear_workspace_t, qc.qlinear_t))
+    ws = make(M, K, 40)
+    call(dev(bad), pw, workspace=ws)
+    qx, sx = qc.debug_workspace_act_t(ws, M, K)
+    assert bits_equal(sx.cpu().numpy(), s_ref) and np.array_equal(qx.cpu().numpy()[~here], q_ref[~here])
+    if K % 16 == 0:
+        qx, sx = qc.quant_act_tensor_t(dev(bad)) if tensor else qc.quant_act_t(dev(bad))
+        assert bits_equal(np.broadcast_to(sx.cpu().numpy(), (M,)), s_ref)
+        assert np.array_equal(qx.cpu().numpy()[~here], q_ref[~here])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("M,K", [(3, 1), (37, 7), (9, 127), (9, 129), (4099, 1000), (9, 2049), (5, 6145), (3, 9215), (2, 9217)])
 def test_ragged_rows_in_the_fragment_layout(M, K, dtype):
     """Row lengths that are no multiple of 16: rows at every alignment, partial last pieces, both sides
