@@ -6,21 +6,20 @@
 //
 // HBM-bound where they are large, bound by launches and dependent round trips where they are small,
 // hence two forms of one kernel:
-//   * Two launches: at most one block per CU (256), every lane with its next chunk's loads in flight
-//     while it sums the present one; a second, single-block launch adds the blocks' partial sums.
+//   * Two launches: at most one block per CU (256); a second, single-block launch adds the blocks'
+//     partial sums.
 //   * One launch, for small tensors: 16 or 32 blocks at most, of which the one that sees all partial
 //     sums finishes the job (finish_here() says how, without a counter that somebody would have to
-//     clear).  What it saves is a launch, 3 us of host time; what it costs on the GPU are the device
-//     fence of each block and the blocks' reading of each other's records, which grow with the number
-//     of blocks (frame gradient of 2 MB: 16 blocks 5.3 us, 32 4.6, 128 8.5; two launches 4.3).
-//     Each operation's limit (kOneMost) lies where one launch takes 1.5 us more on the GPU than two,
-//     half of what it saves the host.  us per call in a graph, two launches and one, warm and, behind
-//     the bar, cold inputs; from the host back to back it is 10.3 and 7.3 for all of them:
-//       latent delta     0.5 MB 4.7 4.1 | 6.0 4.6   1 MB 4.6 4.3 | 6.0 5.1   4 MB 4.8 5.4 | 6.3 6.6   8 MB 5.9 7.8 | 6.5 9.0
-//       similarity bf16  0.5 MB 4.7 4.6 | 5.2 5.1   1 MB 4.7 5.1 | 5.3 5.6   4 MB 4.8 6.3 | 5.6 7.2   8 MB 5.1 7.9 | 6.2 9.7
-//       frame gradient   0.5 MB 4.2 3.9 | 4.7 4.4   1 MB 4.3 4.5 | 4.8 4.8   2 MB 4.3 4.6 | 4.9 5.2   4 MB 4.3 5.6 | 6.3 8.6
-//       variation over 1, 3, 8 tensors of 65536 elements 3.6 4.6 7.7, 3.7 4.6 8.0 | 4.1 5.5 9.1, 4.3 5.5 9.0;
-//       of 262144 3.7 5.2 9.0, 4.4 6.4 11 | 4.4 5.7 9.4, 5.2 7.0 13
+//     clear).  What it saves is a launch, 3 us of host time (calls from the host back to back 10 and 7
+//     us); what it costs on the GPU are the device fence of each block, the blocks' reading of each
+//     other's records, and, with the size, that 32 blocks read what 256 would.  Each operation's limit
+//     (kOneMost) lies where that is some 1 us, for the similarity 2.  us per call in a graph, two launches
+//     and one, warm and, behind the bar, cold inputs:
+//       latent delta     0.5 MB 4.5 3.9 | 5.7 4.4   1 MB 4.3 4.1 | 6.0 5.2   2 MB 4.5 4.9 | 5.8 5.5   4 MB 5.2 6.7 | 6.1 6.7
+//       similarity bf16  0.5 MB 4.3 4.2 | 4.7 4.7   1 MB 4.5 4.6 | 4.8 5.5   2.5 MB 4.6 5.7 | 5.1 6.6   5 MB 4.6 6.4 | 5.5 8.2
+//       frame gradient   0.5 MB 4.1 3.9 | 4.2 4.2   1 MB 4.0 4.6 | 4.3 4.8   1.5 MB 4.0 4.8 | 4.5 5.4   3 MB 4.1 5.5 | 4.7 6.3
+//       variation over 1, 3, 8 tensors of 65536 elements 3.5 4.1 6.7, 3.7 4.4 7.8 | 4.0 5.1 8.2, 4.5 5.3 8.2;
+//       of 163840 3.5 4.3 6.8, 4.4 5.8 9.0 | 4.1 5.5 8.4, 5.5 6.5 9.7
 #include <atomic>
 
 #include "qc_device.h"
@@ -63,7 +62,9 @@ __device__ inline double wave_sum(double v) {
 }
 
 // Block-wide sums of COUNT values, in a fixed order; the result is valid in wavefront 0.  sh holds
-// COUNT * (THREADS / 64) doubles and may be reused after the next barrier.
+// COUNT * (THREADS / 64) doubles and may be reused after the next barrier.  (The wavefronts' sums are
+// added one after the other by every lane of wavefront 0: a second wave_sum over them took up to 1.4 us
+// longer per reduction, variation over 8 tensors 7.8 us instead of 6.4.)
 template <int THREADS, int COUNT>
 __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -75,7 +76,11 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
     __syncthreads();
     if (wave == 0) {
 #pragma unroll
-        for (int c = 0; c < COUNT; ++c) v[c] = wave_sum(lane < THREADS / 64 ? sh[COUNT * lane + c] : 0.0);
+        for (int c = 0; c < COUNT; ++c) {
+            v[c] = sh[c];
+#pragma unroll
+            for (int w = 1; w < THREADS / 64; ++w) v[c] += sh[COUNT * w + c];
+        }
     }
 }
 
@@ -137,6 +142,7 @@ __device__ inline bool finish_here(double (&v)[COUNT], uint64_t *records, uint64
 //   kThreads, kUnroll    launch shape of the two-launch form: threads, packs in flight per lane
 //   kOneUnroll, kBytes   packs in flight in the one-launch form (512 threads); the workspace
 //   kOneMost, kOuts      elements up to which that form is taken (see the top); floats of output
+//   kSlabs               how the blocks share the packs (see reduce_kernel)
 //   Regs, load, add      what a pack occupies, how it is read and summed
 //   tail                 one element past the last whole pack
 //   finish               totals -> outputs
@@ -199,8 +205,9 @@ __device__ inline float widen(uint16_t v) { return __uint_as_float((uint32_t)v <
 // sum|cur - prev|, sum|prev| -> both and their ratio
 struct DeltaOp {
     static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOuts = 3;
+    static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kDeltaBytes;
-    static constexpr int64_t kOneMost = 1 << 19;
+    static constexpr int64_t kOneMost = 3 << 17;
     const float *cur, *prev;
     struct Regs { float4 a, b; };
     __device__ void load(Regs &r, int64_t i) const { r.a = stream4f(cur + 4 * i); r.b = stream4f(prev + 4 * i); }
@@ -222,8 +229,10 @@ struct DeltaOp {
 // <a, b>, <a, a>, <b, b> -> all three and the cosine
 template <typename T>
 struct SimilarityOp {
-    // (1024 threads, 4 packs: 48.3 us on two bf16 tensors of 65536 x 1152; 512 and 2: 47.1)
-    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 2, kOneUnroll = 2, kOuts = 4;
+    // us for 1024 threads and 4 packs, 512 and 2, 512 and 4: bf16, 2 x 2 million elements 5.7 5.0 5.4, 2 x 8.4
+    // million 8.5 9.0 7.9, 2 x 75 million, cold, 54 48.6 50.6; binary32, 2 x 4.2 million 7.7 8.4 7.7
+    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 4, kOneUnroll = 2, kOuts = 4;
+    static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kSimilarityBytes;
     static constexpr int64_t kOneMost = (5 << 19) / sizeof(T);
     const T *a, *b;
@@ -265,10 +274,15 @@ struct SimilarityOp {
 // its elements only (the hardware takes 16 B loads at any address).
 template <typename T>
 struct GradientOp {
-    // 16 elements a lane in the two-launch form (bf16, 2 MB: 4.2 us; 32 a lane 4.8)
-    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 16 / kElems, kOneUnroll = 2, kOuts = 2;
+    // us with chunks of 2 packs a lane, slabs per block; of 16 elements a lane, every 256th chunk; of 8
+    // elements a lane, every 256th chunk (the last two read much of the map twice: the CU that has read
+    // the frame before is another one).  binary32, 16.8 and 31 million elements, frames of 1288 12.7
+    // 20.6, 17.4 33, 14.0 23; of 4096 12.9 20.8, 14.8 25, 17.3 30; of 16384 17.2 28, 22 38, 22 38.  bf16, 16.8
+    // and 31 million, frames of 1288 7.1 12.6, 7.6 13.2, 9.1 13.7; of 8192 7.6 13.1, 10.8 17.0, 12.7 20.4.
+    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 2, kOneUnroll = 2, kOuts = 2;
+    static constexpr bool kSlabs = true;
     static constexpr size_t kBytes = kGradientBytes;
-    static constexpr int64_t kOneMost = (3 << 20) / sizeof(T);
+    static constexpr int64_t kOneMost = (1 << 20) / sizeof(T);
     const T *m;
     int64_t inner;
     struct Regs { Pack<T> x, y; };
@@ -303,8 +317,9 @@ template <int COUNT>
 struct VariationOp {
     // two wavefronts per SIMD: room for 2 x 2 (COUNT + 1) float4 per lane
     static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1, kOuts = COUNT + 1;
+    static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kVariationBytes;
-    static constexpr int64_t kOneMost = 5 << 15;
+    static constexpr int64_t kOneMost = 3 << 15;
     const float *cur;
     PrevList prevs;
     struct Regs { float4 a, b[COUNT]; };
@@ -332,50 +347,46 @@ struct VariationOp {
     }
 };
 
-// A block takes contiguous chunks of THREADS * U packs, consecutive lanes consecutive packs, and
-// strides over the tensors by the grid; a chunk's loads are in flight while the one before is summed.
+// A block reads chunks of THREADS * U packs, consecutive lanes consecutive packs, all of a chunk's loads
+// ahead of the first use: those at first, first + step, .. below `end`, of which the last may be partial.
+//   kSlabs false   every gridDim.x-th chunk of the tensors
+//   kSlabs true    one stretch of `slab` packs, a slab per block: where what a chunk reads overlaps the
+//                  chunk after it, both are read through the same caches
+// (Loading a chunk while the one before is summed gains nothing, at 16 wavefronts per CU, and the longer
+// code costs the small calls 0.2 us; so did a division to count the chunks.)
 template <typename Op, int THREADS, int U, bool ONE_LAUNCH>
-__global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, double *__restrict__ partials,
+__global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, int64_t slab, double *__restrict__ partials,
                                                          float *__restrict__ out, uint64_t nonce) {
     constexpr int C = Op::kCount;
     __shared__ double sh[C * (THREADS / 64)];
     const int64_t packs = n / Op::kElems;
     constexpr int64_t kChunk = (int64_t)THREADS * U;
-    const int64_t base0 = (int64_t)blockIdx.x * kChunk + threadIdx.x, stride = (int64_t)gridDim.x * kChunk;
     double s[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) s[c] = 0.0;
-    auto load = [&](typename Op::Regs (&r)[U], int64_t base) {
+    int64_t first = (int64_t)blockIdx.x * kChunk, end = packs, step = (int64_t)gridDim.x * kChunk;
+    if constexpr (Op::kSlabs) {
+        first = (int64_t)blockIdx.x * slab;
+        end = first + slab < packs ? first + slab : packs;
+        step = kChunk;
+    }
+    int64_t base = first + threadIdx.x;
+    typename Op::Regs r[U];
+    for (; first + kChunk <= end; first += step, base += step) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) op.load(r[u], base + u * THREADS);
+#pragma unroll
+        for (int u = 0; u < U; ++u) op.add(r[u], s);
+    }
+    if (first < end) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = base + u * THREADS;
-            op.load(r[u], i < packs ? i : packs - 1);   // a valid pack either way
+            op.load(r[u], i < end ? i : end - 1);   // a valid pack either way
         }
-    };
-    auto add = [&](const typename Op::Regs (&r)[U], int64_t base) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (base + u * THREADS < packs) op.add(r[u], s);
-    };
-    const int64_t first = (int64_t)blockIdx.x * kChunk;   // uniform over the block
-    if (first < packs) {
-        const int64_t chunks = (packs - first + stride - 1) / stride;
-        typename Op::Regs a[U], b[U];
-        load(a, base0);
-        int64_t k = 0;
-        for (; k + 2 < chunks; k += 2) {
-            load(b, base0 + (k + 1) * stride);
-            add(a, base0 + k * stride);
-            load(a, base0 + (k + 2) * stride);
-            add(b, base0 + (k + 1) * stride);
-        }
-        if (k + 1 < chunks) {
-            load(b, base0 + (k + 1) * stride);
-            add(a, base0 + k * stride);
-            add(b, base0 + (k + 1) * stride);
-        } else {
-            add(a, base0 + k * stride);
-        }
+            if (base + u * THREADS < end) op.add(r[u], s);
     }
     if (blockIdx.x == 0 && threadIdx.x < (int)(n - packs * Op::kElems)) op.tail(packs * Op::kElems + threadIdx.x, s);
     block_sum<THREADS, C>(s, sh);
@@ -418,20 +429,23 @@ qc_status launch_reduction(const Op &op, int64_t n, float *out, void *workspace,
         const int64_t b = (n / Op::kElems + chunk - 1) / chunk;
         return (unsigned)(b < 1 ? 1 : b > most ? most : b);
     };
+    auto slab_for = [&](unsigned blocks) {   // whole wavefronts
+        return round_up((n / Op::kElems + blocks - 1) / blocks, 64);
+    };
     // One launch needs the records to itself until every block that has the totals has spoiled the
     // checks: outputs that lie in the workspace are written by the second launch.
     if (n <= Op::kOneMost && !overlap(out, Op::kOuts * sizeof(float), workspace, Op::kBytes)) {
         constexpr int U = Op::kOneUnroll;
         static_assert(kOneBlocks * (Op::kCount + 1) * sizeof(double) <= Op::kBytes, "room for the blocks' sums and check words");
-        // 32 blocks where each of 16 would take three chunks or more (below: latent delta of 1 MB, 16 and 32
-        // blocks, 4.3 and 4.7 us; above: variation over 8 tensors of 116508 elements 11.0 and 9.5)
+        // 32 blocks where each of 16 would take three chunks or more (latent delta, cold, 16 and 32 blocks:
+        // 1 MB 5.2 5.2, 2 MB 6.3 5.5)
         const int64_t chunk = (int64_t)kOneThreads * U;
         const unsigned blocks = blocks_for(chunk, n / Op::kElems < 3 * 16 * chunk ? 16 : kOneBlocks);
-        reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks), dim3(kOneThreads), 0, st>>>(op, n, partials, out, next_nonce());
+        reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks), dim3(kOneThreads), 0, st>>>(op, n, slab_for(blocks), partials, out, next_nonce());
         return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
     }
     const unsigned blocks = blocks_for((int64_t)Op::kThreads * Op::kUnroll, kMaxBlocks);
-    reduce_kernel<Op, Op::kThreads, Op::kUnroll, false><<<dim3(blocks), dim3(Op::kThreads), 0, st>>>(op, n, partials, nullptr, 0);
+    reduce_kernel<Op, Op::kThreads, Op::kUnroll, false><<<dim3(blocks), dim3(Op::kThreads), 0, st>>>(op, n, slab_for(blocks), partials, nullptr, 0);
     if (hipGetLastError() != hipSuccess) return QC_ERR_DEVICE;
     final_kernel<Op><<<dim3(1), dim3(kFinalThreads), 0, st>>>(partials, (int)blocks, out);
     return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;

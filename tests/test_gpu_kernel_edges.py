@@ -120,10 +120,10 @@ def test_qlinear_ragged_rows_beyond_the_last_level_cache():
     run_linear_case(random_x(rng, M, K, "bf16"), W, None, 8, "none", "bf16", check_acc=False)
 
 
-@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 16 * 4096, 16 * 4096 + 5, 48 * 4096 - 1, 48 * 4096, 1 << 19, (1 << 19) + 1, 170 * 4096 + 5,
+@pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 16 * 4096, 16 * 4096 + 5, 48 * 4096 - 1, 48 * 4096, 3 << 17, (3 << 17) + 1, 1 << 19, (1 << 19) + 1, 170 * 4096 + 5,
                                (12 << 20) // 8, (12 << 20) // 8 + 1])
 def test_reductions_on_both_sides_of_the_one_launch_form(n):
-    """Up to 524288 elements the block that sees all partial sums finishes (16 blocks at most, 32 from
+    """Up to 393216 elements the block that sees all partial sums finishes (16 blocks at most, 32 from
     196608 elements on); beyond that a second launch does.  The workspace holds
     arbitrary bytes, then what the call before left in it."""
     rng = np.random.default_rng(n)
@@ -165,7 +165,7 @@ def test_reductions_into_their_own_workspace():
 def test_variation_stays_in_its_workspace(count, large):
     """As many elements as the one-launch form takes, and two launches with 256 blocks or nearly, on a
     workspace of exactly the stated size with guard bytes behind it."""
-    n = (12 << 20) // (4 * (count + 1)) if large else 5 << 15
+    n = (12 << 20) // (4 * (count + 1)) if large else 3 << 15
     rng = np.random.default_rng(count)
     cur = rng.standard_normal(n).astype(np.float32)
     prevs = rng.standard_normal((count, n)).astype(np.float32)
@@ -185,7 +185,7 @@ def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
     size = 4 if dtype == "f32" else 2
     n = (5 << 19) // size + extra
     a, b = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
-    m = rng.standard_normal((2, (3 << 20) // size + extra)).astype(np.float32)
+    m = rng.standard_normal((2, (1 << 20) // size + extra)).astype(np.float32)
     if dtype == "bf16":
         a, b, m = (synth.to_bf16_bits(t) for t in (a, b, m))
     for _ in range(2):
@@ -197,6 +197,20 @@ def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
         got = qc.frame_gradient_norm_t(dev(m)).cpu().numpy()
         ref = np.asarray(oracle.frame_gradient(m), np.float64)
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("frames,inner", [(2, 1), (1, 4099), (3, 5), (17, 4096), (300, 5461), (1025, 1024), (40, 40001), (2049, 1288), (4097, 1027)])
+def test_frame_gradient_slabs(frames, inner, dtype):
+    """The blocks share the map in stretches of whole wavefronts' packs: fewer packs than a stretch, last
+    stretches that are partial or empty, whole chunks and remainders, frames at every alignment."""
+    rng = np.random.default_rng(frames * 7 + inner)
+    m = rng.standard_normal((frames, inner)).astype(np.float32)
+    if dtype == "bf16":
+        m = synth.to_bf16_bits(m)
+    got = qc.frame_gradient_norm_t(dev(m)).cpu().numpy()
+    ref = np.asarray(oracle.frame_gradient(m), np.float64)
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
 
 
 def test_one_launch_reductions_replay_from_a_graph():
