@@ -456,17 +456,22 @@ __global__ __launch_bounds__(kGenericThreads) void quant_rows_generic_kernel(
     }
 }
 
-// Measured with bf16 input, the GEMM that follows included.  While input and codes fit the cache
-// together, ordinary accesses are the fastest (M = 16384, QKV: 68 us against 72 with non-temporal
-// loads; M = 65536, fc1: the same).  Beyond that non-temporal loads leave the codes in the cache for
-// the GEMM (M = 131072, K = 1152: quantization 80 -> 69 us, QKV whole 562 -> 502 us), also while the
-// codes alone are somewhat larger than the cache (302 MB of codes, fc2 with 4-bit weights: 418 us
-// plain, 403 with non-temporal loads, 409 with non-temporal stores as well).  With twice the cache in
-// codes nothing is left of them to find, and non-temporal stores win too (604 MB, fc2: 852 -> 836 us).
+// Measured with the GEMM that follows included.  While input and codes fit the cache together, ordinary
+// accesses are the fastest (M = 16384, QKV: 68 us against 72 with non-temporal loads; M = 65536, fc1: the
+// same).  Beyond that non-temporal loads leave the codes in the cache for the GEMM (M = 131072, K = 1152:
+// quantization 80 -> 69 us, QKV whole 562 -> 502 us), also while the codes alone are a little larger than
+// the cache (bf16, 1152 channels, 270 MB of codes, K = 1152: 415 us, with non-temporal stores as well 471;
+// 302 MB, K = 4608: 424 and 419).  With more codes little of them is left to find, and non-temporal
+// stores win too (340 MB, K = 1152: 586 and 556; 500 MB, K = 4608: 697 and 698).  Past that size there is
+// nothing to keep X out of the cache for either: rows that are no whole lines, of which non-temporal
+// loads fetch the shared lines twice, are loaded ordinarily (340 MB, K = 1200: 641 and 627 us, K = 3952: 513
+// and 493; while the codes are to be kept non-temporal loads are the better ones here too, 220 MB, K =
+// 1200: 426 and 346).
 int cache_policy(int64_t M, int64_t K, size_t x_elem_bytes) {
     constexpr int64_t kLastLevelCache = (int64_t)256 << 20;
     const int64_t codes = M * K, input = codes * (int64_t)x_elem_bytes;
-    if (codes > kLastLevelCache * 3 / 2) return kStreamBoth;
+    const bool whole_lines = K * (int64_t)x_elem_bytes % 128 == 0;
+    if (codes > kLastLevelCache * 9 / 8) return whole_lines ? kStreamBoth : kStreamStores;
     return input + codes > kLastLevelCache ? kStreamLoads : kCachePlain;
 }
 
@@ -493,6 +498,7 @@ void with_row_variant(int64_t M, int64_t K, size_t x_elem_bytes, F &&f) {
     const int upt = units_per_lane(M, K), policy = cache_policy(M, K, x_elem_bytes);
     auto with_policy = [&](auto u) {
         if (policy == kStreamBoth) f(std::integral_constant<int, kStreamBoth>{}, u);
+        else if (policy == kStreamStores) f(std::integral_constant<int, kStreamStores>{}, u);
         else if (policy == kStreamLoads) f(std::integral_constant<int, kStreamLoads>{}, u);
         else f(std::integral_constant<int, kCachePlain>{}, u);
     };
