@@ -515,8 +515,13 @@ hipError_t launch_typed(const XT *X, int64_t M, int64_t K, int8_t *qx, uint8_t *
     if (rot) {
         if (!vec || K % rot) return hipErrorInvalidValue;  // the entry points reject these first
         with_row_variant(M, K, sizeof(XT), [&](auto pol, auto upt) {
-            // plain loads: a lane's 16 consecutive elements make every load touch lines in part
-            quant_rows_rot_kernel<XT, decltype(pol)::value & kStreamStores, decltype(upt)::value>
+            // A lane's 16 consecutive elements make every load touch lines in part.  Non-temporally that costs
+            // binary32 more than the GEMM gains from the codes in the cache (131072 x 1152 to 1152, 3456, 4608
+            // channels: 340, 609, 737 us, ordinarily 311, 626, 776), bf16 less (225, 495, 621 and 264, 575, 732);
+            // where the codes are too many to stay there, there is nothing to gain.
+            constexpr int kPol = decltype(pol)::value;
+            constexpr int P = kPol == kStreamLoads && sizeof(XT) == 2 ? kStreamLoads : kPol & kStreamStores;
+            quant_rows_rot_kernel<XT, P, decltype(upt)::value>
                 <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
                     X, M, K, qx, qx_tiled, KF, x_scale, qmax, rot);
         });
