@@ -1,6 +1,9 @@
 """The kernels' own edges: sizes at which a dispatch rule changes sides or a tile is partly filled,
 against the CPU oracle (codes, scales and integer sums bit for bit)."""
 import math
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -9,7 +12,7 @@ import torch
 import oracle
 from paper_2503_06545_amd import binding as qc
 from paper_2503_06545_amd import synth
-from test_gpu_parity import bits_equal, dev, random_x, run_asym_case, run_linear_case
+from test_gpu_parity import RTOL, assert_outputs_close, bits_equal, dev, host_f64, random_x, run_asym_case, run_linear_case
 
 pytestmark = pytest.mark.gpu
 
@@ -110,6 +113,79 @@ def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
     run_linear_case(x, W, b, bits, "gelu_tanh", "bf16")
     run_linear_case(x, W, None, bits, "none", "f32", check_acc=False)
     run_asym_case(x, W, b, bits, "gelu_erf", "bf16")
+
+
+def full_height(M, N):
+    """Whether the ring kernel takes tiles of 256 tokens (of 128 otherwise)."""
+    tiles = -(-M // 256) * -(-N // 128)
+    return not (2 * tiles <= 256 or 256 < tiles <= 332)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("kernel,M,N", [("half", 1100, 1000 + r) for r in range(8)] + [("full", 2200, 2048 + r) for r in range(8)]
+                         + [("half", 5700, 1536), ("full", 4300, 1920)]   # f32: through the caches; half the height has no smaller
+                         + [("resident", 32700, 3448 + r) for r in (0, 1, 4, 7)] + [("full", 262145, 513)])
+def test_qlinear_many_tiles_stay_inside_their_output(kernel, M, N, bits):
+    """Every remainder of N by 8 in the kernels for more than a few tokens, all types of output, rows that are
+    no multiple of 16 B beyond the cache's size too: every row against the oracle's (they repeat), nothing
+    written on either side of Y."""
+    K, period = 64, 251
+    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == (2 if kernel == "resident" else 1)
+    assert kernel == "resident" or full_height(M, N) == (kernel == "full")
+    rng = np.random.default_rng(100 * N + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    x = random_x(rng, period, K, "bf16")
+    qw, sw = oracle.quant_weight(W, bits)
+    ref = oracle.qlinear(x, qw, sw, b, 0, 8)
+    X = dev(x).repeat(-(-M // period), 1)[:M].contiguous()
+    pw, pad = qc.pack_weight_t(dev(W), bits), 4096
+    for out, t, fill in (("bf16", torch.bfloat16, -7.0), ("f32", torch.float32, -7.0), ("i32", torch.int32, -7)):
+        if M * N > 1 << 27 and out != "bf16":
+            continue
+        buf = torch.full((M * N + 2 * pad,), fill, dtype=t, device="cuda")
+        Y = qc.qlinear_t(X, pw, None if out == "i32" else dev(b), "none", out, Y=buf[pad:pad + M * N].view(M, N))
+        torch.cuda.synchronize()
+        if out == "i32":
+            assert np.array_equal(Y[:period].cpu().numpy(), ref["acc"])
+        else:
+            want = oracle.bf16_bits_to_f64(oracle.round_bf16_bits(ref["y"])) if out == "bf16" else ref["y"]
+            assert_outputs_close(host_f64(Y[:period]), want, RTOL[out])
+        assert torch.equal(Y[period:], Y[:-period])
+        assert bool((buf[:pad] == fill).all()) and bool((buf[pad + M * N:] == fill).all())
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N", [(1100, 1001), (2200, 2050)])
+@pytest.mark.parametrize("K", [200, 1000, 1160])
+def test_qlinear_ring_kernel_ragged_k_with_a_poisoned_workspace(K, M, N, bits):
+    """K no multiple of 16 or of the stage: what the quantizer leaves unwritten of the last columns meets
+    zero weights, at both tile heights."""
+    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    rng = np.random.default_rng(K + M + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    qw, _ = oracle.quant_weight(W, bits)
+    pw = qc.pack_weight_t(dev(W), bits)
+    for dtype in ("bf16", "f32"):
+        x = random_x(rng, M, K, dtype)
+        ws = qc.qlinear_workspace_t(M, K, N)
+        ws.fill_(0x7f)
+        acc = qc.qlinear_t(dev(x), pw, None, "none", "i32", workspace=ws)
+        assert np.array_equal(acc.cpu().numpy(), oracle.gemm_i32(oracle.quant_act(x)[0], qw))
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N", [(1100, 4608, 1000), (2200, 4608, 2050), (1100, 2304, 1003), (2200, 1152, 2049)])
+def test_qlinear_ring_kernel_long_reductions(M, K, N, bits):
+    """Both tile heights at the reductions they are taken for, symmetric, rotated and asymmetric codes."""
+    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    rng = np.random.default_rng(M + K + N + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    x = random_x(rng, M, K, "bf16")
+    run_linear_case(x, W, b, bits, "gelu_tanh", "bf16")
+    run_linear_case(x, W, b, bits, "none", "f32", rot_block=64, act_bits=6)
+    run_asym_case(x, W, b, bits, "gelu_erf", "f32")
 
 
 def test_qlinear_ragged_rows_beyond_the_last_level_cache():
@@ -220,10 +296,12 @@ def test_one_launch_reductions_replay_from_a_graph():
     n, inner = 65536, 4099
     a, b = (torch.from_numpy(rng.standard_normal(n).astype(np.float32)).cuda() for _ in range(2))
     m = torch.from_numpy(rng.standard_normal((16, inner)).astype(np.float32)).cuda()
-    ws = [torch.empty(16384, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    # the graph's workspaces are the graph's alone: between two replays nothing else writes a record there
+    # that would take the place of the earlier replay's
+    graphs, eager = ([torch.randint(0, 256, (16384,), dtype=torch.uint8, device="cuda") for _ in range(4)] for _ in range(2))
     outs = [torch.zeros(k, device="cuda") for k in (3, 4, 2, 4)]
 
-    def step():
+    def step(ws, outs):
         qc.latent_delta_t(a, b, workspace=ws[0], out3=outs[0])
         qc.layer_similarity_t(a, b, workspace=ws[1], out4=outs[1])
         qc.frame_gradient_norm_t(m, workspace=ws[2], out2=outs[2])
@@ -232,20 +310,49 @@ def test_one_launch_reductions_replay_from_a_graph():
     graph = torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
     with torch.cuda.graph(graph):
-        step()
-    for k in range(4):
+        step(graphs, outs)
+    for k in range(6):
         a.copy_(torch.from_numpy(rng.standard_normal(n).astype(np.float32)))
         m.mul_(1.0 + k)
-        graph.replay()
-        torch.cuda.synchronize()
-        got = [o.clone() for o in outs]
         for o in outs:
             o.zero_()
-        step()
+        graph.replay()
         torch.cuda.synchronize()
-        assert all(torch.equal(x, y) for x, y in zip(got, outs)), k
+        want = [torch.zeros_like(o) for o in outs]
+        step(eager, want)
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(outs, want)), k
         ref = np.asarray(oracle.latent_delta(a.cpu().numpy(), b.cpu().numpy()), np.float64)
-        assert np.all(np.abs(got[0].cpu().numpy() - ref) <= 1e-5 * np.abs(ref))
+        assert np.all(np.abs(outs[0].cpu().numpy() - ref) <= 1e-5 * np.abs(ref))
+
+
+def test_few_token_kernel_with_much_lds_captured_first():
+    """The 64 x 64 tile sums its wavefronts in 70 KB of LDS, which its first launch has to ask for: also
+    when that launch is being captured, in a process that has launched nothing of it yet."""
+    here = os.path.dirname(os.path.abspath(__file__))
+    code = f"import sys; sys.path[:0] = [{os.path.dirname(here)!r}, {here!r}]; import test_gpu_kernel_edges as t; t.capture_the_largest_tile()"
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=100)
+
+
+def capture_the_largest_tile():
+    M, K, N = 1000, 192, 1000
+    assert qc.qc_debug_gemm_kernel(M, K, N, 8) == 3
+    rng = np.random.default_rng(64)
+    x = dev(random_x(rng, M, K, "bf16"))
+    for bits in (8, 4):
+        pw = qc.pack_weight_t(dev((rng.standard_normal((N, K)) * 0.02).astype(np.float32)), bits)
+        ws, Y = qc.qlinear_workspace_t(M, K, N), torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            qc.qlinear_t(x, pw, workspace=ws, Y=Y)
+        for _ in range(3):
+            Y.fill_(0)
+            ws.fill_(0)
+            graph.replay()
+            torch.cuda.synchronize()
+            got = Y.clone()
+            assert torch.equal(got, qc.qlinear_t(x, pw))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
