@@ -378,9 +378,9 @@ class Bench:
         return self.x_dev[key][:case.M]
 
     def gemm_kernel_name(self, case):
-        """Which of the GEMM's two kernels the library takes for this layer."""
+        """Which of the GEMM's kernels the library takes for this layer."""
         which = self.qc.qc_debug_gemm_kernel(case.M, case.K, case.N, case.bits)
-        return "gemm_resident_kernel" if which == 2 else "gemm_kernel"
+        return {1: "gemm_kernel", 2: "gemm_resident_kernel", 3: "small_kernel"}[which]
 
     def check(self, st):
         if st != self.qc.QC_OK:

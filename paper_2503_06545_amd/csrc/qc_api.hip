@@ -228,7 +228,7 @@ extern "C" qc_status qc_qlinear_gemm(const void *workspace, size_t workspace_byt
     const uint8_t *base = (const uint8_t *)workspace;
     return device_status(launch_gemm(base + ws.scale_bytes, (const float *)base,
                                      (const uint8_t *)packed, w_scale, bias, Y, M, N, K, bits, epi,
-                                     ydt, nullptr, nullptr, kGemmAuto, (hipStream_t)stream));
+                                     ydt, nullptr, nullptr, (hipStream_t)stream));
 }
 
 extern "C" qc_status qc_qlinear_act_bits(const void *X, qc_dtype xdt, int64_t M, int64_t K,
@@ -307,7 +307,7 @@ extern "C" qc_status qc_qlinear_asym_gemm(const void *workspace, size_t workspac
     return device_status(launch_gemm(base + ws.codes_offset, (const float *)base,
                                      (const uint8_t *)packed, w_scale, bias, Y, M, N, K, bits, epi,
                                      ydt, (const float *)(base + ws.corr_offset), w_row_sums,
-                                     kGemmAuto, (hipStream_t)stream));
+                                     (hipStream_t)stream));
 }
 
 extern "C" qc_status qc_qlinear_asym(const void *X, qc_dtype xdt, int64_t M, int64_t K,

@@ -828,13 +828,12 @@ static bool stream_bf16_edges(int64_t M, int64_t N) { return 2 * M * N > (int64_
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                        int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
-                       const int32_t *w_rowsum, GemmKernel which, hipStream_t stream) {
-    if (which == kGemmResident && !gemm_resident_fits(K, bits)) return hipErrorInvalidValue;
-    if (which == kGemmSmall || (which == kGemmAuto && gemm_small_chosen(M, N)))
+                       const int32_t *w_rowsum, hipStream_t stream) {
+    if (gemm_small_chosen(M, N))
         return launch_gemm_small(x_tiled, x_scale, w_packed, w_scale, bias, Y, M, N, K, bits, epi, ydt, x_corr,
                                  w_rowsum, stream);
     GemmArgs args;
-    args.resident = which == kGemmResident || (which == kGemmAuto && gemm_resident_chosen(M, N, K, bits));
+    args.resident = gemm_resident_chosen(M, N, K, bits);
     args.x_tiled = x_tiled;
     args.x_scale = x_scale;
     args.x_corr = x_corr;

@@ -237,7 +237,8 @@ __host__ __device__ inline int resident_block_rounds(int b, int nb, int n_tiles,
     return n;
 }
 
-enum GemmKernel { kGemmAuto = 0, kGemmRing = 1, kGemmResident = 2, kGemmSmall = 3 };
+// what qc_debug_gemm_kernel returns
+enum GemmKernel { kGemmRing = 1, kGemmResident = 2, kGemmSmall = 3 };
 // whether a 128-channel weight tile of this reduction length fits the resident kernel's LDS
 bool gemm_resident_fits(int64_t K, int bits);
 // whether launch_gemm picks the resident kernel for this problem by itself
@@ -260,6 +261,6 @@ hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, f
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                        int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
-                       const int32_t *w_rowsum, GemmKernel which, hipStream_t stream);
+                       const int32_t *w_rowsum, hipStream_t stream);
 
 }  // namespace qc

@@ -451,14 +451,15 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
     return bits == 8 ? launch_bits<8>(tile, kCodes, a, stream) : launch_bits<4>(tile, kCodes, a, stream);
 }
 
-// What limits the fused form, beyond the tile: the columns a thread holds and LDS.
+// What limits the fused form, beyond the tile: the columns a thread holds.  They bound its codes in LDS too,
+// 16 B per unit of 16 columns and live row and 16 B of padding per unit: at most 81 KiB, with one row of
+// 40960 columns, far below kLdsMost.
 bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K) {
     const int tile = pick_tile(M, N);
     if (tile < 0 || kTiles[tile].upt == 0) return false;
     const int rp_log2 = live_rows_log2(M, kTiles[tile].tokens);
     const int64_t columns = (int64_t)kTiles[tile].upt * kUnit * (kThreads >> rp_log2);
-    const int64_t lds = round_up(K, kKAlign) / kFragK * 4 * quarter_stride(rp_log2);
-    return K <= columns && lds <= kLdsMost - 1024;
+    return K <= columns;
 }
 
 hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale,

@@ -326,6 +326,23 @@ def test_one_launch_reductions_replay_from_a_graph():
         assert np.all(np.abs(outs[0].cpu().numpy() - ref) <= 1e-5 * np.abs(ref))
 
 
+@pytest.mark.parametrize("M,K,N", [(1, 40960, 8224), (1, 40961, 8224), (1, 24576, 100), (2, 20480, 8224), (16, 1536, 8192), (32, 1280, 16384)])
+def test_qlinear_on_few_tokens_with_the_longest_rows(M, K, N):
+    """The longest rows the one-launch form takes, which need the most LDS (81 KB), against quantization and
+    GEMM as two calls."""
+    assert qc.qc_debug_gemm_kernel(M, K, N, 8) == 3
+    X = torch.randn(M, K, device="cuda").bfloat16()
+    pw = qc.pack_weight_t(torch.randn(N, K, device="cuda"), 8)
+    ws = qc.qlinear_workspace_t(M, K, N)
+    got = qc.qlinear_t(X, pw, None, "none", "i32", workspace=ws)
+    want, stream = torch.empty_like(got), torch.cuda.current_stream().cuda_stream
+    ws.fill_(0x7f)
+    assert qc.qc_qlinear_quant(X.data_ptr(), qc.QC_BF16, M, K, ws.data_ptr(), ws.numel(), stream) == qc.QC_OK
+    assert qc.qc_qlinear_gemm(ws.data_ptr(), ws.numel(), M, K, pw.blob.data_ptr(), pw.scale.data_ptr(), 8, N, None,
+                              qc.QC_EPI_NONE, want.data_ptr(), qc.QC_OUT_I32_ACC, stream) == qc.QC_OK
+    assert torch.equal(got, want)
+
+
 def test_few_token_kernel_with_much_lds_captured_first():
     """The 64 x 64 tile sums its wavefronts in 70 KB of LDS, which its first launch has to ask for: also
     when that launch is being captured, in a process that has launched nothing of it yet."""
