@@ -12,7 +12,9 @@
  *   - Data pointers must be 16-byte aligned.
  *   - Errors are return codes.  Argument errors are found before anything is
  *     launched, so a failed call has no side effect.  NaN / Inf in inputs are not
- *     detected; results are then unspecified.
+ *     detected; results are then unspecified.  (A NaN among activations that are quantized
+ *     symmetrically and without rotation leaves all scales, and every code but its own, what
+ *     they are with a zero in its place.)
  *
  * Quantizer (Section 3.1, Eq. (3) and Eq. (4) of the paper, in symmetric signed
  * form; Section 4.1 "Quantization Scheme": per-channel weights, activation scales
@@ -268,13 +270,13 @@ qc_status qc_debug_workspace_act(const void *workspace, int64_t M, int64_t K, in
                                  float *x_scale, void *stream);
 
 /* Test hooks for the GEMM stage, host only (no device is touched).  The GEMM (Section 4.1
- * "Hardware Implementation") exists as three kernels: one for outputs too small to fill the chip,
+ * "Hardware Implementation") exists in three designs: one for outputs too small to fill the chip,
  * which splits the reduction inside a block, one that streams the weight tile of a block through
- * a ring in LDS, the other keeps a whole 128-channel weight tile resident in LDS and is taken for
+ * a ring in LDS (with tiles of 256 or of 128 tokens), the other keeps a whole 128-channel weight tile resident in LDS and is taken for
  * short reductions (K <= 1152 with 8-bit weights, <= 2304 with 4-bit ones) on problems large
  * enough for its static schedule.
- *   qc_debug_gemm_kernel    which one qc_qlinear_gemm takes for (M, K, N, bits): 1 the ring,
- *                           2 the resident one, 3 the one for few tokens, 0 if the shape is
+ *   qc_debug_gemm_kernel    which one qc_qlinear_gemm takes for (M, K, N, bits): 1 the ring, of
+ *                           either height, 2 the resident one, 3 the one for few tokens, 0 if the shape is
  *                           unsupported
  *   qc_debug_gemm_schedule  the rounds of block `block` (0 .. 255) of the resident kernel for an
  *                           [M, N] output, in the order the block runs them: pairs[2 i] is the
@@ -309,8 +311,9 @@ qc_status qc_latent_delta(const float *cur, const float *prev, int64_t n, float 
  *   n          at most QC_LATENT_DELTA_STATIC_MAX_N, else UNSUPPORTED
  * All calls on one GPU share the array: two calls that overlap in time on one GPU (different
  * streams) race and give undefined results; calls on one stream are ordered by the stream.
- * Nothing has to be cleared between calls: every partial sum the combine reads is written by
- * the same call first.  Other arguments and errors as for qc_latent_delta (no WORKSPACE). */
+ * Nothing has to be cleared between calls: a partial sum counts only if it fits a 64-bit check
+ * word made of it and of a number that no other call of the process has, or, for larger n, is
+ * written by the call's first launch before the second reads it.  Other arguments and errors as for qc_latent_delta (no WORKSPACE). */
 #define QC_LATENT_DELTA_STATIC_MAX_N ((int64_t)1 << 30)
 qc_status qc_latent_delta_static(const float *cur, const float *prev, int64_t n, float *out3,
                                  void *stream);
@@ -331,8 +334,8 @@ qc_status qc_layer_similarity(const void *a, const void *b, qc_dtype dt, int64_t
  * Section 3.2 HLC, Eq. (5), second factor.  The paper names this factor without defining it;
  * this library takes the forward difference along the frame axis and the Euclidean norm:
  *   g[f, j] = m[f+1, j] - m[f, j]  (f < frames-1),   out2 = { sum g^2, sqrt(sum g^2) }.
- *   m          device, [frames, inner] of `dt` (float or bf16), dense.  inner a multiple of 8
- *              takes the vectorised path; any inner >= 1 is accepted.  frames = 1 gives zeros.
+ *   m          device, [frames, inner] of `dt` (float or bf16), dense, any inner >= 1.
+ *              frames = 1 gives zeros.
  *   out2       device, float [2]
  *   workspace  device, >= qc_frame_gradient_norm_workspace_bytes(frames, inner) bytes, 256-byte
  *              aligned, contents irrelevant on entry

@@ -227,11 +227,12 @@ struct DeltaOp {
 };
 
 // <a, b>, <a, a>, <b, b> -> all three and the cosine
-template <typename T>
+// THREADS: us for 1024 and 512 threads: binary32, 2 x 0.65 million elements 6.2 4.6, 2 x 2 million 6.5 5.9, 2 x 4.2
+// million 7.0 7.7, 2 x 8 million 12.0 13.4, 2 x 24 million 29.5 31.1; bf16, 2 x 2 million 5.7 5.4, 2 x 8.4 million
+// 8.5 7.9, 2 x 75 million, cold, 54 50.6.
+template <typename T, int THREADS = 512>
 struct SimilarityOp {
-    // us for 1024 threads and 4 packs, 512 and 2, 512 and 4: bf16, 2 x 2 million elements 5.7 5.0 5.4, 2 x 8.4
-    // million 8.5 9.0 7.9, 2 x 75 million, cold, 54 48.6 50.6; binary32, 2 x 4.2 million 7.7 8.4 7.7
-    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = 512, kUnroll = 4, kOneUnroll = 2, kOuts = 4;
+    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = THREADS, kUnroll = 4, kOneUnroll = 2, kOuts = 4;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kSimilarityBytes;
     static constexpr int64_t kOneMost = (5 << 19) / sizeof(T);
@@ -508,7 +509,8 @@ extern "C" qc_status qc_latent_delta_static(const float *cur, const float *prev,
     if (n > QC_LATENT_DELTA_STATIC_MAX_N) return QC_ERR_UNSUPPORTED;
     void *ws = nullptr;
     if (qc_status st = static_scratch(&ws); st != QC_OK) return st;
-    // every partial pair the second launch reads is written by the first: nothing to clear
+    // nothing to clear: one launch rejects by their check words what earlier calls left there, and of two the
+    // second reads only what the first has written
     return qc_latent_delta(cur, prev, n, out3, ws, kStaticScratchBytes, stream);
 }
 
@@ -528,6 +530,8 @@ extern "C" qc_status qc_layer_similarity(const void *a, const void *b, qc_dtype 
     if (dt == QC_BF16)
         return launch_reduction(SimilarityOp<uint16_t>{(const uint16_t *)a, (const uint16_t *)b}, n, out4,
                                 workspace, stream);
+    if (n > 1 << 21)
+        return launch_reduction(SimilarityOp<float, 1024>{(const float *)a, (const float *)b}, n, out4, workspace, stream);
     return launch_reduction(SimilarityOp<float>{(const float *)a, (const float *)b}, n, out4, workspace, stream);
 }
 

@@ -22,9 +22,11 @@
 // permutation makes a lane's eight tiles eight consecutive channels, so 16 lanes store 128
 // consecutive channels of one token at a time.  The 16x16x64 form of the MFMA is used because
 // the chip holds a higher clock on it than on the 32x32x32 form under its power cap (measured:
-// 4.1 against 3.4 POP/s on random operands, registers only).  The output is written with
-// non-temporal stores: it is not read again by this kernel and would otherwise push the operand
-// panels out of the L2.
+// 4.1 against 3.4 POP/s on random operands, registers only).  Whole tiles of bf16 and int32 output
+// are written with non-temporal stores: the output is not read again by this kernel and would
+// otherwise push the operand panels out of the L2.  Float output that the last-level cache can hold,
+// partly filled tiles and rows that are no multiple of 16 B go through the caches (keep_f32_output(),
+// stream_bf16_edges()).
 #include <type_traits>
 
 #include "qc_device.h"

@@ -253,6 +253,16 @@ def test_variation_stays_in_its_workspace(count, large):
     assert bool((buf[size:] == 0x5a).all())
 
 
+@pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1, 3_698_757, 256 * 16384 + 5])
+def test_similarity_on_both_sides_of_its_change_of_threads(n):
+    rng = np.random.default_rng(n)
+    a = rng.standard_normal(n).astype(np.float32)
+    b = (a + 0.5 * rng.standard_normal(n)).astype(np.float32)
+    got = qc.layer_similarity_t(dev(a), dev(b)).cpu().numpy()
+    ref = np.asarray(oracle.layer_similarity(a, b), np.float64)
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+
+
 @pytest.mark.parametrize("extra", [0, 1, 9])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
