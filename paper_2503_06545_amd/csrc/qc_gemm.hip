@@ -810,14 +810,15 @@ static bool ring_half_height(int m_tiles, int n_tiles) {
 // 91 85, 262 MB 99.6 99.2, 318 MB 119 120, 412 MB 140 156; N = 3456 (an eighth in codes): output of 223
 // MB 112 102, 297 MB 150 136, 398 MB 186 167; K = 2304, N = 640: with codes 242 MB 96 90, 365 MB 123 138;
 // K = 4608, N = 1152: 254 MB 142 140, 320 MB 176 178, 383 MB 202 217; K = 192, N = 1152: 400 MB 176 93.
-// GELU (erf) leaves non-temporal stores the time to drain, and ordinary ones win from 60 MB on only: 27 MB 23.3
-// 25.1, 46 MB 30.2 32.6, 53 MB 34.2 35.2, 69 MB 53.8 46.5; half the height, N = 3456, 41 MB 26.0 27.7.
+// GELU (erf) leaves non-temporal stores the time to drain, and ordinary ones win from 60 MB on only and up to 192 MB
+// with the codes: 27 MB 23.3 25.1, 46 MB 30.2 32.6, 53 MB 34.2 35.2, 69 MB 53.8 46.5, with codes 193 MB 89.9 88.2;
+// K = 1824, with codes 204 MB 116 127; half the height, N = 3456, 41 MB 26.0 27.7.
 // bf16 output is up to 9 % slower with ordinary stores.
 static bool keep_f32_output(int64_t M, int64_t N, int64_t K, bool half, qc_epilogue epi) {
     constexpr int64_t MB = 1 << 20;
     const int64_t out = 4 * M * N, codes = M * round_up(K, kKAlign);
-    const int64_t from = epi == QC_EPI_GELU_ERF ? 60 : half ? 15 : 24;
-    return out >= from * MB && (out + codes <= 256 * MB || (8 * codes <= out && out <= 400 * MB));
+    const int64_t from = epi == QC_EPI_GELU_ERF ? 60 : half ? 15 : 24, most = epi == QC_EPI_GELU_ERF ? 192 : 256;
+    return out >= from * MB && (out + codes <= most * MB || (8 * codes <= out && out <= 400 * MB));
 }
 
 // Rows of bf16 that are no multiple of 16 B long, and partly filled tiles: through the caches while the
