@@ -1,7 +1,8 @@
 // The decision reductions: latent change (Section 3.2 HLC, Eq. (5)), cosine similarity of two feature
 // tensors (Section 3.3 SRAP, Eq. (9)), inter-frame gradient norm (second factor of Eq. (5)) and
 // cumulative variation over the previous steps (Eq. (11)).  Each is one pass over its tensors with a
-// deterministic result: groups of four terms are summed in binary32, everything after that in
+// deterministic result: groups of four terms are summed in binary32 (the frame gradient's squares in
+// binary64, which costs 0.4 us of 6.9 on 16 million bf16 elements in the caches and less elsewhere), everything after that in
 // binary64 and in an order that does not depend on scheduling.
 //
 // HBM-bound where they are large, bound by launches and dependent round trips where they are small,
@@ -291,18 +292,18 @@ struct GradientOp {
     __device__ void add(const Regs &r, double (&s)[kCount]) const {
 #pragma unroll
         for (int g = 0; g < kElems / 4; ++g) {
-            float p = 0.f;
+            double p = 0.0;
 #pragma unroll
             for (int e = 4 * g; e < 4 * g + 4; ++e) {
-                const float d = r.y.get(e) - r.x.get(e);
-                p = fmaf(d, d, p);
+                const double d = (double)(r.y.get(e) - r.x.get(e));
+                p = fma(d, d, p);
             }
-            s[0] += (double)p;
+            s[0] += p;
         }
     }
     __device__ void tail(int64_t j, double (&s)[kCount]) const {
         const float d = widen(m[inner + j]) - widen(m[j]);
-        s[0] += (double)(d * d);
+        s[0] += (double)d * (double)d;
     }
     __device__ static void finish(const double (&s)[kCount], float *out) {
         out[0] = (float)s[0];

@@ -299,6 +299,21 @@ def test_frame_gradient_slabs(frames, inner, dtype):
     assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("frames,inner", [(2, 4), (2, 7), (3, 5), (2, 33), (16, 4099)])
+def test_frame_gradient_is_rounded_once(frames, inner, dtype):
+    """The squares of the binary32 differences are exact in binary64 and summed there: the result is off by
+    its rounding to 32 bits, 2^-24 at most (and some 2^-52 for each term)."""
+    for seed in range(20):
+        m = np.random.default_rng(seed).standard_normal((frames, inner)).astype(np.float32)
+        if dtype == "bf16":
+            bits = synth.to_bf16_bits(m)
+            m = oracle.bf16_bits_to_f64(bits).astype(np.float32)
+        got = float(qc.frame_gradient_norm_t(dev(bits if dtype == "bf16" else m))[0])
+        d = (m[1:] - m[:-1]).astype(np.float64)
+        assert abs(got - float((d * d).sum())) <= (2.0 ** -24 + 1e-10) * float((d * d).sum())
+
+
 def test_one_launch_reductions_replay_from_a_graph():
     """A replayed launch carries the same arguments as the time before, the number that marks its
     partial sums included: every replay has to form its result from its own inputs."""
