@@ -227,56 +227,70 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
 // Each block of `rot` consecutive columns (16, 32, 64 or 128) is multiplied by the Walsh-Hadamard
 // matrix of that size before the absmax and the cast, as a butterfly network in binary32 with
 // the strides in ascending order: one rounding per output and stage, so the bits do not depend
-// on which lane does which butterfly.  With the lane layout above, the 8 lanes of a row hold one
-// aligned run of 128 columns per register unit: strides 1..8 are butterflies inside a lane's 16
-// values, strides 16, 32, 64 pair lanes sub ^ 1, sub ^ 2, sub ^ 4 (DPP moves, no LDS).
-
-__device__ inline float dpp_quad_xor1(float v) {  // lane ^ 1: quad_perm [1, 0, 3, 2]
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
-}
-__device__ inline float dpp_quad_xor2(float v) {  // lane ^ 2: quad_perm [2, 3, 0, 1]
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
-}
-__device__ inline float dpp_xor4(float v) {
-    // lanes 0-3 and 8-11 of a row of 16 take lane + 4 (row_shl:4, banks 0 and 2), the others
-    // lane - 4 (row_shr:4, banks 1 and 3)
-    int t = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x104, 0xF, 0x5, false);
-    t = __builtin_amdgcn_update_dpp(t, __float_as_int(v), 0x114, 0xF, 0xA, false);
-    return __int_as_float(t);
-}
+// on which lane does which butterfly.  The rows are loaded as in quant_rows_kernel, whole lines per
+// instruction, so a group of 128 columns lies over eight lanes in pieces of E = 16 B: the strides below
+// E and those of 8 E or more are butterflies between a lane's own values, the three between them pair
+// lanes.
+//
+// A butterfly across lanes is one v_fmac_f32 with a DPP operand: own + sign * other.  It leaves the
+// upper lane of a pair with minus its output, which every later stage carries along unchanged; the
+// quotient takes the sign out again, because x / s and (-x) / (-s) are the same operations on the same
+// magnitudes.  DPP reaches lanes sub ^ 1, ^ 2 and ^ 7 in one move, not ^ 4; so the lane takes the piece
+// `label` of the eight, which differs in bit 2 alone between lanes sub and sub ^ 7.
+// 65536 x 1152 bf16, blocks of 128, with a move and an fma (two moves for the third stage) and 16
+// consecutive columns a lane: 52.7 us; this form 38.3 (binary32 72.1 and 60.0).
+// (One asm block per stage: the compiler leaves the DPP move and the fma apart.  A DPP operand may be read two
+// wait states after a VALU instruction has written it, hence the s_nop; inside the block no
+// instruction reads what another has written.)
+#define QC_BUTTERFLY(i, how) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " how " row_mask:0xf bank_mask:0xf\n\t"
+#define QC_BUTTERFLIES(f, sign, how)                                                                          \
+    asm volatile("s_nop 1\n\t"                                                                               \
+        QC_BUTTERFLY(0, how) QC_BUTTERFLY(1, how) QC_BUTTERFLY(2, how) QC_BUTTERFLY(3, how)                   \
+        QC_BUTTERFLY(4, how) QC_BUTTERFLY(5, how) QC_BUTTERFLY(6, how) QC_BUTTERFLY(7, how)                   \
+        QC_BUTTERFLY(8, how) QC_BUTTERFLY(9, how) QC_BUTTERFLY(10, how) QC_BUTTERFLY(11, how)                 \
+        QC_BUTTERFLY(12, how) QC_BUTTERFLY(13, how) QC_BUTTERFLY(14, how) QC_BUTTERFLY(15, how)               \
+        : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]),     \
+          "+v"(f[8]), "+v"(f[9]), "+v"(f[10]), "+v"(f[11]), "+v"(f[12]), "+v"(f[13]), "+v"(f[14]), "+v"(f[15]) \
+        : "v"(sign))
+static_assert(kUnit == 16, "a stage's elements are written out");
+__device__ inline void butterflies_xor1(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "quad_perm:[1,0,3,2]"); }
+__device__ inline void butterflies_xor2(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "quad_perm:[2,3,0,1]"); }
+__device__ inline void butterflies_xor7(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "row_half_mirror"); }
+#undef QC_BUTTERFLIES
+#undef QC_BUTTERFLY
 
 template <typename XT, int POLICY, int UPT>
 __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, int8_t *__restrict__ qx,
     uint8_t *__restrict__ qx_tiled, int64_t KF, float *__restrict__ x_scale, float qmax, int rot) {
     __shared__ float slice_max[kMaxSlices<UPT>][kRowsPerBlock];
-    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, slices = blockDim.x >> 6;
+    constexpr int E = 16 / (int)sizeof(XT);   // consecutive columns of a lane's pieces
+    const int lane = threadIdx.x & 63, slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slices = blockDim.x >> 6;
     const int sub = lane % kLanesPerRow, row_in_block = lane / kLanesPerRow;
+    const int label = sub < 4 ? sub : sub ^ 3;
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + row_in_block;
     const int units = (int)(K / kUnit);
     const bool live = row < M;
     const XT *xrow = X + (live ? row : 0) * K;
 
-    Unit<XT> u[UPT];
+    Group<XT> u[UPT];
 #pragma unroll
-    for (int i = 0; i < UPT; ++i) {
-        const int ui = slice * (UPT * kLanesPerRow) + i * kLanesPerRow + sub;
-        if (live && ui < units) u[i].template load<(POLICY & kStreamLoads) != 0>(xrow + (int64_t)ui * kUnit);
-        else u[i].zero();
-    }
+    for (int i = 0; i < UPT; ++i)
+        u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, label);
 
-    // +1 for the lane that holds the lower half of a cross-lane pair, -1 for the upper one:
-    // fma(sign, own, other) is own + other below and other - own above, one rounding either way
-    const float sg1 = (sub & 1) ? -1.0f : 1.0f, sg2 = (sub & 2) ? -1.0f : 1.0f,
-                sg4 = (sub & 4) ? -1.0f : 1.0f;
+    const float sg1 = (label & 1) ? -1.0f : 1.0f, sg2 = (label & 2) ? -1.0f : 1.0f, sg4 = (label & 4) ? -1.0f : 1.0f;
     float f[UPT][kUnit];
     float a = 0.0f;
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) f[i][e] = u[i].get(e);
+        if ((slice * UPT + i + 1) * kGroup > (int)K) {   // columns past the row's end, whole blocks of them: not its last piece again, but zeros
 #pragma unroll
-        for (int h = 1; h < kUnit; h <<= 1)
+            for (int e = 0; e < kUnit; ++e)
+                if ((slice * UPT + i) * kGroup + e / E * (kLanesPerRow * E) + E * label >= (int)K) f[i][e] = 0.0f;
+        }
+        auto own_lane = [&](int h) {   // butterflies between elements h apart
 #pragma unroll
             for (int j = 0; j < kUnit; ++j)
                 if ((j & h) == 0) {
@@ -284,17 +298,21 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
                     f[i][j] = lo + hi;
                     f[i][j + h] = lo - hi;
                 }
-        if (rot >= 32) {
-#pragma unroll
-            for (int e = 0; e < kUnit; ++e) f[i][e] = fmaf(sg1, f[i][e], dpp_quad_xor1(f[i][e]));
-        }
-        if (rot >= 64) {
-#pragma unroll
-            for (int e = 0; e < kUnit; ++e) f[i][e] = fmaf(sg2, f[i][e], dpp_quad_xor2(f[i][e]));
-        }
-        if (rot >= 128) {
-#pragma unroll
-            for (int e = 0; e < kUnit; ++e) f[i][e] = fmaf(sg4, f[i][e], dpp_xor4(f[i][e]));
+        };
+        own_lane(1);
+        own_lane(2);
+        if constexpr (E == 8) {   // strides 1 2 4 | 8 16 32 | 64
+            own_lane(4);
+            butterflies_xor1(f[i], sg1);
+            if (rot >= 32) butterflies_xor2(f[i], sg2);
+            if (rot >= 64) butterflies_xor7(f[i], sg4);
+            if (rot >= 128) own_lane(8);
+        } else {                  // strides 1 2 | 4 8 16 | 32 64
+            butterflies_xor1(f[i], sg1);
+            butterflies_xor2(f[i], sg2);
+            if (rot >= 32) butterflies_xor7(f[i], sg4);
+            if (rot >= 64) own_lane(4);
+            if (rot >= 128) own_lane(8);
         }
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) a = fmaxf(a, fabsf(f[i][e]));
@@ -311,19 +329,26 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     const float r = 1.0f / s;  // correctly rounded
     if (live && sub == 0 && slice == 0) x_scale[row] = s;
     if (!live) return;
+    // minus for the lanes that an odd number of the stages across lanes has negated
+    float sign = sg1;
+    if (rot >= 32 || E == 4) sign *= sg2;
+    if (rot >= (E == 8 ? 64 : 32)) sign *= sg4;
+    const float ss = sign * s, sr = sign * r;
 
     int8_t *out_rows = qx ? qx + row * K : nullptr;
     uint8_t *out_tiled = qx_tiled ? qx_tiled + act_frag_offset(row, 0, KF) : nullptr;
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
-        const int ui = slice * (UPT * kLanesPerRow) + i * kLanesPerRow + sub;
-        if (ui >= units) continue;
+        const int ui0 = (slice * UPT + i) * kLanesPerRow;   // first unit of the group
+        if (ui0 >= units) break;                            // the same for all lanes
         uint32_t w[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
-            w[d] = codes4(quotient(f[i][4 * d + 0], s, r), quotient(f[i][4 * d + 1], s, r),
-                          quotient(f[i][4 * d + 2], s, r), quotient(f[i][4 * d + 3], s, r));
-        const uint4 out = make_uint4(w[0], w[1], w[2], w[3]);
+            w[d] = codes4(quotient(f[i][4 * d + 0], ss, sr), quotient(f[i][4 * d + 1], ss, sr),
+                          quotient(f[i][4 * d + 2], ss, sr), quotient(f[i][4 * d + 3], ss, sr));
+        const uint4 out = Group<XT>::gather_codes(w, label);
+        const int ui = ui0 + Group<XT>::unit_of(label);
+        if (ui >= units) continue;
         if (out_rows) store16<(POLICY & kStreamStores) != 0>(out_rows + (int64_t)ui * kUnit, out);
         if (out_tiled)
             store16<(POLICY & kStreamStores) != 0>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, out);
@@ -515,12 +540,7 @@ hipError_t launch_typed(const XT *X, int64_t M, int64_t K, int8_t *qx, uint8_t *
     if (rot) {
         if (!vec || K % rot) return hipErrorInvalidValue;  // the entry points reject these first
         with_row_variant(M, K, sizeof(XT), [&](auto pol, auto upt) {
-            // A lane's 16 consecutive elements make every load touch lines in part.  Non-temporally that costs
-            // binary32 more than the GEMM gains from the codes in the cache (131072 x 1152 to 1152, 3456, 4608
-            // channels: 340, 609, 737 us, ordinarily 311, 626, 776), bf16 less (225, 495, 621 and 264, 575, 732);
-            // where the codes are too many to stay there, there is nothing to gain.
-            constexpr int kPol = decltype(pol)::value;
-            constexpr int P = kPol == kStreamLoads && sizeof(XT) == 2 ? kStreamLoads : kPol & kStreamStores;
+            constexpr int P = decltype(pol)::value;
             quant_rows_rot_kernel<XT, P, decltype(upt)::value>
                 <<<row_grid(M), row_block(K, decltype(upt)::value), 0, stream>>>(
                     X, M, K, qx, qx_tiled, KF, x_scale, qmax, rot);

@@ -40,6 +40,24 @@ def test_row_quantizers_at_the_edges_of_their_column_slices(M, K, dtype):
         assert bits_equal(sr.cpu().numpy(), r_ref[1]) and np.array_equal(qr.cpu().numpy(), r_ref[0])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,rot_block", [(1, 16, 16), (9, 32, 32), (3, 64, 64), (9, 144, 16), (8, 160, 32), (7, 192, 64),
+                                           (9, 2016, 32), (3, 2112, 64), (2, 4640, 32), (2, 6208, 64), (1, 9184, 32)])
+def test_rotated_rows_that_end_within_a_group(M, K, rot_block, dtype):
+    """A group of 128 columns that the row fills in part: what lies past the row takes no part in the maximum,
+    although the row's last elements, here its largest, are loaded in its place; with one, three
+    and nine groups a lane."""
+    rng = np.random.default_rng(M * 10007 + K + rot_block)
+    x = random_x(rng, M, K, "f32")
+    x[:, -rot_block:] = 0.0
+    x[:, -4:] = 100.0 * rng.standard_normal((M, 4))
+    if dtype == "bf16":
+        x = synth.to_bf16_bits(x.astype(np.float32))
+    q_ref, s_ref = oracle.quant_act_rot(x, rot_block, 8)
+    qx, sx = qc.quant_act_t(dev(x), 8, rot_block)
+    assert bits_equal(sx.cpu().numpy(), s_ref) and np.array_equal(qx.cpu().numpy(), q_ref)
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N", [
     (1, 16, 1), (2, 9216, 40), (3, 6144, 33), (16, 1536, 4100), (16, 1552, 70), (17, 1152, 128), (31, 1280, 2050),
