@@ -26,7 +26,7 @@ constexpr int kGenericThreads = 256;
 // last-level cache in front of HBM holds 256 MiB, and what the pass leaves in it decides whether
 // the GEMM that follows finds the codes there.
 enum CachePolicy {
-    kCachePlain = 0,    // input and codes both fit: ordinary loads and stores
+    kCachePlain = 0,    // input and codes fit with room to spare: ordinary loads and stores
     kStreamLoads = 1,   // non-temporal loads of X
     kStreamStores = 2,  // non-temporal stores of the codes
     kStreamBoth = 3,
@@ -481,10 +481,16 @@ __global__ __launch_bounds__(kGenericThreads) void quant_rows_generic_kernel(
     }
 }
 
-// Measured with the GEMM that follows included.  While input and codes fit the cache together, ordinary
-// accesses are the fastest (M = 16384, QKV: 68 us against 72 with non-temporal loads; M = 65536, fc1: the
-// same).  Beyond that non-temporal loads leave the codes in the cache for the GEMM (M = 131072, K = 1152:
-// quantization 80 -> 69 us, QKV whole 562 -> 502 us), also while the codes alone are a little larger than
+// Measured with the GEMM that follows included.  While input and codes leave room in the cache, ordinary
+// accesses are the fastest (M = 16384, QKV: 68 us against 72 with non-temporal loads).  From 160 MB of them on what
+// else is on its way through the cache counts, the output of this call and of the one before and an input that
+// another kernel has just written, and non-temporal loads leave the codes there for the GEMM (us per call, ordinary
+// and non-temporal loads, the same input again and again | four inputs, workspaces and outputs in turn | inputs
+// written just before by another kernel, its time included: 216 MB, K = 1152, N = 4608, GELU 343 350 | 390 351 |
+// 393 389, N = 3456 236 245 | 264 248 | 290 286; 162 MB, N = 3456 191 196 | 193 190 | 238 225, K = 4608, N =
+// 1152 79 82 | 81 81 | 124 114; 130 MB, K = 4608, asymmetric 72 74 | 73 75 | 103 102; 108 MB, N = 3456 129
+// 128 | 128 132 | 155 153).  Far beyond, M = 131072, K = 1152, they take the quantization from 80 to 69 us and
+// QKV whole from 562 to 502 us, also while the codes alone are a little larger than
 // the cache (bf16, 1152 channels, 270 MB of codes, K = 1152: 415 us, with non-temporal stores as well 471;
 // 302 MB, K = 4608: 424 and 419).  With more codes little of them is left to find, and non-temporal
 // stores win too (340 MB, K = 1152: 586 and 556; 500 MB, K = 4608: 697 and 698).  Past that size there is
@@ -497,7 +503,7 @@ int cache_policy(int64_t M, int64_t K, size_t x_elem_bytes) {
     const int64_t codes = M * K, input = codes * (int64_t)x_elem_bytes;
     const bool whole_lines = K * (int64_t)x_elem_bytes % 128 == 0;
     if (codes > kLastLevelCache * 9 / 8) return whole_lines ? kStreamBoth : kStreamStores;
-    return input + codes > kLastLevelCache ? kStreamLoads : kCachePlain;
+    return input + codes > kLastLevelCache * 5 / 8 ? kStreamLoads : kCachePlain;
 }
 
 // Units per lane of the row kernels.  One unit, a wavefront per 128 columns, where a block of 16
