@@ -272,11 +272,11 @@ qc_status qc_debug_workspace_act(const void *workspace, int64_t M, int64_t K, in
 /* Test hooks for the GEMM stage, host only (no device is touched).  The GEMM (Section 4.1
  * "Hardware Implementation") exists in three designs: one for outputs too small to fill the chip,
  * which splits the reduction inside a block, one that streams the weight tile of a block through
- * a ring in LDS (with tiles of 256 or of 128 tokens), the other keeps a whole 128-channel weight tile resident in LDS and is taken for
- * short reductions (K <= 1152 with 8-bit weights, <= 2304 with 4-bit ones) on problems large
- * enough for its static schedule.
+ * a ring in LDS (with tiles of 256, 192 or 128 tokens), the other keeps a whole 128-channel weight tile resident in
+ * LDS and is taken for short reductions (K <= 1152 with 8-bit weights, <= 2304 with 4-bit ones) on problems large
+ * enough for its static schedule (with GELU not always: the ring then takes some of them).
  *   qc_debug_gemm_kernel    which one qc_qlinear_gemm takes for (M, K, N, bits): 1 the ring, of
- *                           either height, 2 the resident one, 3 the one for few tokens, 0 if the shape is
+ *                           any height, 2 the resident one (without GELU), 3 the one for few tokens, 0 if the shape is
  *                           unsupported
  *   qc_debug_gemm_schedule  the rounds of block `block` (0 .. 255) of the resident kernel for an
  *                           [M, N] output, in the order the block runs them: pairs[2 i] is the

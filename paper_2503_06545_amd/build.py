@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqc.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["qc_api.hip", "qc_quant.hip", "qc_pack.hip", "qc_gemm.hip", "qc_small.hip", "qc_delta.hip"]
+SOURCES = ["qc_api.hip", "qc_quant.hip", "qc_pack.hip", "qc_gemm.hip", "qc_gemm_w8.hip", "qc_gemm_w4.hip", "qc_small.hip", "qc_delta.hip"]
 ROOFS_SRC = os.path.join(ROOT, "bench", "qc_roofs.hip")
 ROOFS = os.path.join(ROOT, "bench", "qc_roofs")  # stand-alone roofline micro-benchmark
 RESOURCE_REPORT = os.path.join(OBJ_DIR, "kernel_resources.txt")
@@ -54,7 +54,7 @@ def _compile(src: str):
     # harmless complaint about the device-only feature flag
     other, keep = [], True
     for line in r.stderr.splitlines():
-        if "packed-fp32-ops" in line:
+        if "packed-fp32-ops" in line or line.startswith("In file included from"):
             continue
         if re.search(r"(remark|warning|error|note): ", line) or re.match(r"\d+ (warning|error)s? generated", line):
             keep = "remark: " not in line and "packed-fp32-ops" not in line and " generated" not in line

@@ -206,6 +206,30 @@ def test_qlinear_ring_kernel_long_reductions(M, K, N, bits):
     run_asym_case(x, W, b, bits, "gelu_erf", "f32")
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N", [(4033, 64, 1152), (4081, 192, 1146), (4097, 400, 1151), (4225, 64, 1152), (4225, 208, 1025),
+                                   (4352, 64, 1148), (9843, 64, 1156)])
+def test_qlinear_ring_kernel_on_tiles_of_192_tokens(M, K, N, bits):
+    """The height between the two, whose wavefronts of 48 tokens begin and end inside the panels of 64 the
+    codes lie in: last tiles of 1, 49 and 65 live tokens, one that ends past the padded tokens (4225),
+    and nothing written on either side of Y."""
+    rng = np.random.default_rng(M + K + N + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    x = random_x(rng, M, K, "bf16")
+    run_linear_case(x, W, b, bits, "gelu_tanh", "bf16")
+    run_linear_case(x, W, None, bits, "gelu_erf", "f32", check_acc=False)
+    run_asym_case(x, W, b, bits, "none", "bf16")
+    pw, pad = qc.pack_weight_t(dev(W), bits), 4096
+    for out, t in (("bf16", torch.bfloat16), ("f32", torch.float32)):
+        want = qc.qlinear_t(dev(x), pw, dev(b), "none", out)
+        buf = torch.full((M * N + 2 * pad,), -7.0, dtype=t, device="cuda")
+        got = qc.qlinear_t(dev(x), pw, dev(b), "none", out, Y=buf[pad:pad + M * N].view(M, N))
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        assert bool((buf[:pad] == -7.0).all()) and bool((buf[pad + M * N:] == -7.0).all())
+
+
 def test_qlinear_ragged_rows_beyond_the_last_level_cache():
     """bf16 output of more than 256 MB whose rows are no multiple of 16 B: non-temporal stores at any alignment."""
     M, K, N = 262145, 64, 513

@@ -47,7 +47,7 @@ def wide_stores(tmp_path_factory):
     return found
 
 
-@pytest.mark.parametrize("kernel,rows", [("gemm_kernel", 16), ("gemm_half_kernel", 8)])
+@pytest.mark.parametrize("kernel,rows", [("gemm_kernel", 16), ("gemm_mid_kernel", 12), ("gemm_half_kernel", 8)])
 def test_ring_kernels_hold_both_kinds_of_store(wide_stores, kernel, rows):
     """A wavefront stores `rows` rows per lane, two pieces each in 32 bits and one in bf16, on a path for
     whole tiles, non-temporally, and on one for the others: through the caches, for bf16 either way."""
@@ -60,7 +60,7 @@ def test_ring_kernels_hold_both_kinds_of_store(wide_stores, kernel, rows):
     assert seen == 2 * (3 * 2 + 3 * 2 + 1)   # weights x (f32: epilogue, zero point; bf16; int32)
 
 
-@pytest.mark.parametrize("kernel,rows", [("gemm_cached_kernel", 16), ("gemm_half_cached_kernel", 8)])
+@pytest.mark.parametrize("kernel,rows", [("gemm_cached_kernel", 16), ("gemm_mid_cached_kernel", 12), ("gemm_half_cached_kernel", 8)])
 def test_ring_kernels_that_keep_their_output_store_through_the_caches(wide_stores, kernel, rows):
     mine = {name: counts for name, counts in wide_stores.items() if f"{len(kernel)}{kernel}I" in name}
     assert len(mine) == 2 * 3 * 2 and all(counts == [4 * rows, 0] for counts in mine.values())
