@@ -46,9 +46,11 @@ __device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0
 //                  is passed over, like by fmaxf, so that it spoils no code but its own.
 //                  For bf16 it stays two packed 16-bit patterns (Bf16Max): nothing is widened that the
 //                  compiler would then keep in registers up to the cast.
-//   load_ragged()  the same for a K that is no multiple of 16: rows at any alignment (the hardware takes
-//                  16 B loads at any address), the row's last, partial piece element by element, zeros
-//                  past it
+//   load_ragged()  the same for a K that is no multiple of 16 (16 B or more): rows at any alignment (the hardware
+//                  takes 16 B loads at any address).  The piece that holds the row's end is loaded so that it ends
+//                  there, and settle_ragged(), after all loads, moves it down to its place, zeros following.
+//                  (Its elements loaded one by one, each load waited for, in order: us 4099 x 1000 bf16 4.7 4.4, 30000 x 1156 bf16
+//                  23.3 18.5, f32 39.7 30.4.)
 template <typename XT>
 struct Group;
 
@@ -68,6 +70,21 @@ struct Bf16Max {
 
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // 16 B at any element
 
+// a piece moved down by 1 .. 7 halfwords, zeros from above
+__device__ inline uint4 move_down(uint4 v, int halfwords) {
+    if (halfwords & 4) v = make_uint4(v.z, v.w, 0, 0);
+    if (halfwords & 2) v = make_uint4(v.y, v.z, v.w, 0);
+    if (halfwords & 1) v = make_uint4(v.x >> 16 | v.y << 16, v.y >> 16 | v.z << 16, v.z >> 16 | v.w << 16, v.w >> 16);
+    return v;
+}
+
+template <int CTRL>
+__device__ inline float dpp_max(float v) {
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false)));
+}
+// the maximum of eight consecutive lanes, in each of them (quad_perm [1, 0, 3, 2], [2, 3, 0, 1], row_half_mirror)
+__device__ inline float max_of_eight(float v) { return dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(v))); }
+
 // the dword of lane ^ 1 (quad_perm [1, 0, 3, 2])
 __device__ inline uint32_t dpp_xor1(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false); }
 // the dword of lane ^ 2 (quad_perm [2, 3, 0, 1])
@@ -85,18 +102,21 @@ struct Group<float> {
         }
     }
     __device__ void load_ragged(const float *xrow, int col0, int K, int sub) {
+        const int most = K - 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int col = col0 + 32 * j + 4 * sub;
-            v[j] = make_uint4(0, 0, 0, 0);
-            if (col + 4 <= K) {
-                const u32x4_any t = *reinterpret_cast<const u32x4_any *>(xrow + col);
-                v[j] = make_uint4(t.x, t.y, t.z, t.w);
-            } else if (col < K) {
-                const uint32_t *p = reinterpret_cast<const uint32_t *>(xrow + col);
-                v[j].x = p[0];
-                if (col + 1 < K) v[j].y = p[1];
-                if (col + 2 < K) v[j].z = p[2];
+            const u32x4_any t = *reinterpret_cast<const u32x4_any *>(xrow + (col < most ? col : most));
+            v[j] = make_uint4(t.x, t.y, t.z, t.w);
+        }
+    }
+    __device__ void settle_ragged(int col0, int K, int sub) {
+        const int most = K - 4;
+        if (col0 + 128 > K) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int past = col0 + 32 * j + 4 * sub - most;   // elements of the piece past the row's end
+                if (past > 0 && past < 4) v[j] = move_down(v[j], 2 * past);
             }
         }
     }
@@ -141,19 +161,21 @@ struct Group<uint16_t> {  // bf16 bit patterns
         }
     }
     __device__ void load_ragged(const uint16_t *xrow, int col0, int K, int sub) {
+        const int most = K - 8;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int col = col0 + 64 * j + 8 * sub;
-            v[j] = make_uint4(0, 0, 0, 0);
-            if (col + 8 <= K) {
-                const u32x4_any t = *reinterpret_cast<const u32x4_any *>(xrow + col);
-                v[j] = make_uint4(t.x, t.y, t.z, t.w);
-            } else if (col < K) {
-                uint32_t w[4] = {0, 0, 0, 0};
+            const u32x4_any t = *reinterpret_cast<const u32x4_any *>(xrow + (col < most ? col : most));
+            v[j] = make_uint4(t.x, t.y, t.z, t.w);
+        }
+    }
+    __device__ void settle_ragged(int col0, int K, int sub) {
+        const int most = K - 8;
+        if (col0 + 128 > K) {
 #pragma unroll
-                for (int e = 0; e < 7; ++e)
-                    if (col + e < K) w[e / 2] |= (uint32_t)xrow[col + e] << (16 * (e % 2));
-                v[j] = make_uint4(w[0], w[1], w[2], w[3]);
+            for (int j = 0; j < 2; ++j) {
+                const int past = col0 + 64 * j + 8 * sub - most;
+                if (past > 0 && past < 8) v[j] = move_down(v[j], past);
             }
         }
     }

@@ -51,11 +51,6 @@ struct TensorMax {
 
 constexpr int kMaxSlabs = 256;
 
-template <int CTRL>
-__device__ inline float dpp_max(float v) {
-    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false)));
-}
-
 // A wavefront asks for the partial maxima in one load, before its rows, and combines them with DPP
 // moves and four readlanes afterwards (a chain of shuffles through LDS cost 4 us of 24 at
 // 32768 x 1152, every wavefront doing it).
@@ -174,6 +169,10 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
         if constexpr (RAGGED) u[i].load_ragged(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
         else u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
     }
+    if constexpr (RAGGED) {
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) u[i].settle_ragged((slice * UPT + i) * kGroup, (int)K, sub);
+    }
 
     float a = 0.0f;
     if (TENSOR) {  // one scale for the whole tensor: its absmax was reduced beforehand
@@ -183,8 +182,7 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
 #pragma unroll
         for (int i = 0; i < UPT; ++i) u[i].absmax_into(running);
         a = Group<XT>::absmax_value(running);
-#pragma unroll
-        for (int d = 1; d < kLanesPerRow; d <<= 1) a = fmaxf(a, __shfl_xor(a, d));
+        a = max_of_eight(a);
         if (slices > 1) {  // uniform over the block
             if (sub == 0) slice_max[slice][row_in_block] = a;
             __syncthreads();
@@ -317,8 +315,7 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) a = fmaxf(a, fabsf(f[i][e]));
     }
-#pragma unroll
-    for (int d = 1; d < kLanesPerRow; d <<= 1) a = fmaxf(a, __shfl_xor(a, d));
+    a = max_of_eight(a);
     if (slices > 1) {  // uniform over the block
         if (sub == 0) slice_max[slice][row_in_block] = a;
         __syncthreads();
@@ -554,9 +551,9 @@ hipError_t launch_typed(const XT *X, int64_t M, int64_t K, int8_t *qx, uint8_t *
         return hipGetLastError();
     }
     // Rows of any other length: the same kernels when only the fragment layout is wanted (4099 x 1000
-    // bf16: 12.2 us with a wavefront per row and byte stores); row-major codes of ragged rows, and rows
-    // longer than 9216, take the generic one.
-    const bool ragged = !vec && !qx && K <= (int64_t)kUnitsMost * kUnit;
+    // bf16: 12.2 us with a wavefront per row and byte stores); row-major codes of ragged rows, rows of less than 16 B and
+    // rows longer than 9216 take the generic one.
+    const bool ragged = !vec && !qx && K <= (int64_t)kUnitsMost * kUnit && K * (int64_t)sizeof(XT) >= 16;
     if (!vec && !ragged) {
         const int64_t blocks = (M + 3) / 4;
         quant_rows_generic_kernel<XT><<<dim3((unsigned)blocks), dim3(kGenericThreads), 0, stream>>>(

@@ -2,20 +2,20 @@
 // 256 x 128 to fill the chip, so what bounds the call is latency - the number of launches, each
 // wavefront's chain of loads - and how many CUs pull the weights at once.
 //
-// A block of 8 wavefronts computes a tile of 16 or 32 or 64 tokens x 32 or 64 channels.  The
+// small_kernel: a block of 8 wavefronts computes a tile of 16 or 32 or 64 tokens x 32 or 64 channels.  The
 // wavefronts split the reduction (64-k stages dealt round-robin), load their operand fragments
 // straight into registers, all of them ahead of the first use when K is short, and add their partial
 // sums through LDS: exact, the sums are integers.  The smallest tile that gives at most one block per
 // CU is taken: a second block on a CU only adds to what the CU has to load, and a single CU gets
 // about 35 B/clk from beyond its L2 (every launch starts with that L2 invalid).
 //
-// For per-token quantization the whole linear is one launch: each block quantizes its token tile into
-// LDS itself, redundantly over the channel tiles (that is cheap while there are few), and the blocks
+// fused_kernel: for per-token quantization the whole linear is one launch: each block quantizes its token tile into
+// LDS itself, redundantly over the channel tiles (that is cheap while there are few tokens in a tile), and the blocks
 // of the first channel tile leave codes and scales in the workspace as the two-launch path does.
 //
-// Measured, K = 1152, W8, GPU time of quantization + GEMM: 2 tokens x 6912 channels 4.7 + 8.2 -> 5.1
-// us, 64 x 1152 2.8 + 8.8 -> 5.5 us, 256 x 1152 2.8 + 8.8 -> 7.8 us; K = 4608: 2 x 1152 5.0 + 24.1 ->
-// 6.1 us, 256 x 1152 4.2 + 25.0 -> 4.2 + 8.5 us (a 256-token tile there walks 72 stages alone).
+// Measured, K = 1152, W8, GPU time of quantization + GEMM on full tiles, and in one launch: 2 tokens x 6912 channels
+// 4.7 + 8.2 -> 4.9 us, 64 x 1152 2.8 + 8.8 -> 5.2 us, 256 x 1152 2.8 + 8.8 -> 6.7 us; K = 4608: 2 x 1152 5.0 + 24.1 ->
+// 5.7 us, 256 x 1152 4.2 + 25.0 -> 4.2 + 8.5 us in two (a 256-token tile there walks 72 stages alone).
 #include <atomic>
 
 #include "qc_device.h"
@@ -30,11 +30,9 @@ constexpr int kGroup = 128;   // columns that eight lanes quantize per step
 constexpr int kWaves = kThreads / 64;
 constexpr int kLdsMost = 150 * 1024;
 
-enum Source { kCodes = 0, kFusedBf16 = 1, kFusedF32 = 2 };
-
 struct SmallArgs {
-    const void *X;          // fused quantizer: the activations
-    uint8_t *x_tiled;       // the workspace's codes: read (kCodes) or written (fused)
+    const void *X;          // fused_kernel: the activations
+    uint8_t *x_tiled;       // the workspace's codes: read (small_kernel) or written (fused_kernel)
     float *x_scale;
     const float *x_corr;    // asymmetric activations only, with w_rowsum
     const int32_t *w_rowsum;
@@ -44,38 +42,31 @@ struct SmallArgs {
     void *Y;
     int64_t M, N, K;
     int KF, m_tiles, n_tiles;
-    int rp_log2;            // fused: rows of a tile that can be live, rounded up to a power of two
+    int rows, groups;       // fused_kernel: rows of a tile that can be live, groups of 128 columns in a row
+    uint32_t inv_groups;    // 2^20 / groups, rounded up
     float qmax;
     int epi, out;
 };
 
-// LDS: [ token scales: TM ][ wavefront maxima: 8 ][ codes, later partial sums: WK x TM x LD int32 ]
+// partial sums of small_kernel in LDS: WK x TM x kLd int32
 template <int MI, int NF, int WN>
 struct Layout {
     static constexpr int kTM = 16 * MI;
     static constexpr int kWK = kWaves / WN;
     static constexpr int kLd = 16 * NF + 4;   // 4 rows apart = 16 banks apart: conflict-free
     static constexpr int kSums = kWK * kTM * kLd * 4;
-    static constexpr int kSumsAt = (kTM * 4 + kWaves * 4 + 15) / 16 * 16;
 };
-// bytes between the 16-k quarters of a stage in the fused kernel's code tile: 16 B per row and 16 B
-// of padding, so that the quarters a row's units go to fall into different banks
-__host__ __device__ inline int quarter_stride(int rp_log2) { return (16 << rp_log2) + 16; }
 
-// MI x 16 tokens by NF x 16 channels per block; WN wavefront columns, kWaves / WN ways over K; a
-// register ring of D stages.  UPT: groups of 128 columns a thread quantizes (fused only).
-template <int BITS, int MI, int NF, int WN, int D, int SRC, int UPT>
+// MI x 16 tokens by NF x 16 channels per block, codes from the workspace; WN wavefront columns, kWaves / WN
+// ways over K; a register ring of D stages.
+template <int BITS, int MI, int NF, int WN, int D>
 __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
     using L = Layout<MI, NF, WN>;
     constexpr int TM = L::kTM, WK = L::kWK, NFW = NF / WN;
     constexpr int NW = BITS == 8 ? NFW : NFW / 2;             // 1 KiB weight pieces per stage and wavefront
     constexpr int kStageBytes = BITS == 8 ? 8192 : 4096;
-    constexpr bool FUSED = SRC != kCodes;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    float *const lds_sx = reinterpret_cast<float *>(lds);
-    float *const lds_max = lds_sx + TM;
-    uint8_t *const codes = lds + L::kSumsAt;
-    int *const sums = reinterpret_cast<int *>(codes);
+    int *const sums = reinterpret_cast<int *>(lds);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -92,24 +83,6 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
     if ((int64_t)G * kTileN + t0 >= a.N) return;   // no live channel in this tile
 
     const int KF = a.KF;
-    typedef typename std::conditional<SRC == kFusedF32, float, uint16_t>::type XT;
-    Group<XT> u[FUSED ? UPT : 1];
-    const int tpr_log2 = 9 - a.rp_log2, tpr = 1 << tpr_log2;   // threads per row, 8 or more
-    const int row = tid >> tpr_log2, sub = lane & 7;
-    const int group0 = (tid & (tpr - 1)) >> 3, groups_per_step = tpr >> 3;
-    const bool live = m0 + row < a.M;
-    if constexpr (FUSED) {
-        const XT *xrow = reinterpret_cast<const XT *>(a.X) + (live ? m0 + row : m0) * a.K;
-        if (a.K % kUnit == 0) {
-#pragma unroll
-            for (int i = 0; i < UPT; ++i)
-                u[i].template load<false>(xrow, (group0 + i * groups_per_step) * kGroup, (int)a.K, sub);
-        } else {
-#pragma unroll
-            for (int i = 0; i < UPT; ++i) u[i].load_ragged(xrow, (group0 + i * groups_per_step) * kGroup, (int)a.K, sub);
-        }
-    }
-
     // what the epilogue needs, requested first: a thread keeps one column of channels, n0 .. n0 + NF - 1,
     // and the tokens tid / 16 + 32 j
     constexpr int kRows = TM < 32 ? 1 : TM / 32;
@@ -127,10 +100,10 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {   // padded to a multiple of 256 tokens
-        sx[j] = FUSED ? 0.0f : a.x_scale[m0 + (em + 32 * j) % TM];
+        sx[j] = a.x_scale[m0 + (em + 32 * j) % TM];
         cx[j] = 0.0f;
     }
-    if (!FUSED && a.x_corr) {
+    if (a.x_corr) {
 #pragma unroll
         for (int t = 0; t < NF; ++t)
             rs[t] = (float)a.w_rowsum[n0 + t < a.N ? n0 + t : a.N - 1] * (BITS == 4 ? 16.0f : 1.0f);
@@ -144,7 +117,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
 
     // weights of this wavefront: stages wk, wk + WK, ..; a register ring of D of them
     v4i w[D][NW];
-    v4i x[FUSED ? 1 : D][MI];
+    v4i x[D][MI];
     const uint8_t *const wbase = a.w_codes + (int64_t)G * KF * kStageBytes +
                                  (BITS == 8 ? t0 + wn * NFW : (t0 + wn * NFW) / 2) * kFragBytes + lane * 16;
     const uint8_t *const xbase = a.x_tiled + (m0 / kWaveM) * (int64_t)KF * (4 * kFragBytes) +
@@ -154,55 +127,12 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
         const uint8_t *p = wbase + (int64_t)sc * kStageBytes;
 #pragma unroll
         for (int j = 0; j < NW; ++j) w[d][j] = *reinterpret_cast<const v4i *>(p + j * kFragBytes);
-        if constexpr (!FUSED) {
-            const uint8_t *q = xbase + (int64_t)sc * (4 * kFragBytes);
+        const uint8_t *q = xbase + (int64_t)sc * (4 * kFragBytes);
 #pragma unroll
-            for (int i = 0; i < MI; ++i) x[d][i] = *reinterpret_cast<const v4i *>(q + i * kFragBytes);
-        }
+        for (int i = 0; i < MI; ++i) x[d][i] = *reinterpret_cast<const v4i *>(q + i * kFragBytes);
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) request(wk + d * WK, d);
-
-    const int qs = quarter_stride(a.rp_log2);
-    if constexpr (FUSED) {
-        auto running = Group<XT>::no_max();
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) u[i].absmax_into(running);
-        float amax = Group<XT>::absmax_value(running);
-        for (int d = 1; d < tpr && d < 64; d <<= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
-        if (tpr > 64) {   // a row spans several wavefronts
-            if (lane == 0) lds_max[wave] = amax;
-            __syncthreads();
-            const int first = row << (tpr_log2 - 6);
-            for (int j = 0; j < tpr / 64; ++j) amax = fmaxf(amax, lds_max[first + j]);
-        }
-        const float s = scale_of(amax, a.qmax);
-        const float r = 1.0f / s;  // correctly rounded
-        const bool keep = nt == 0 && live;   // one block per token tile leaves the codes in the workspace
-        if ((tid & (tpr - 1)) == 0) {
-            lds_sx[row] = s;
-            if (keep) a.x_scale[m0 + row] = s;
-        }
-        uint8_t *out_tiled = a.x_tiled + act_frag_offset(m0 + row, 0, KF);
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) {
-            const int g = group0 + i * groups_per_step;
-            if (g * kGroup >= (int)a.K) break;   // the same for the eight lanes of a group
-            uint32_t q[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-                q[d] = codes4(quotient(u[i].get(4 * d + 0), s, r), quotient(u[i].get(4 * d + 1), s, r),
-                              quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r));
-            const uint4 o = Group<XT>::gather_codes(q, sub);
-            const int ui = g * 8 + Group<XT>::unit_of(sub);
-            if (ui * kUnit >= (int)a.K) continue;
-            *reinterpret_cast<uint4 *>(codes + ui * qs + row * 16) = o;   // unit = quarter of a stage
-            if (keep) store16<false>(out_tiled + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, o);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kRows; ++j) sx[j] = lds_sx[(em + 32 * j) % TM];
-    }
 
     v4i acc[MI][NFW];
 #pragma unroll
@@ -210,13 +140,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
 #pragma unroll
         for (int t = 0; t < NFW; ++t) acc[i][t] = v4i{0, 0, 0, 0};
 
-    const uint8_t *const xl = codes + h * qs;
-    const int rmask = (1 << a.rp_log2) - 1;
-    auto multiply = [&](int s, int d) {   // stage s, in ring slot d
-        v4i xa[MI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-            xa[i] = FUSED ? *reinterpret_cast<const v4i *>(xl + s * 4 * qs + ((16 * i + c) & rmask) * 16) : x[FUSED ? 0 : d][i];
+    auto multiply = [&](int d) {   // the stage in ring slot d
 #pragma unroll
         for (int t = 0; t < NFW; ++t) {
             v4i wt;
@@ -232,7 +156,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
             }
 #pragma unroll
             for (int i = 0; i < MI; ++i)
-                acc[i][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[i], wt, acc[i][t], 0, 0, 0);
+                acc[i][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x[d][i], wt, acc[i][t], 0, 0, 0);
         }
     };
     // Stages wk, wk + WK, ..: the loads are unconditional wherever there are any (past the end they
@@ -241,24 +165,23 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
     for (; s + (2 * D - 1) * WK < KF; s += D * WK) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            multiply(s + d * WK, d);
+            multiply(d);
             request(s + (d + D) * WK, d);
         }
     }
     if (s + D * WK < KF) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            multiply(s + d * WK, d);
+            multiply(d);
             request(s + (d + D) * WK, d);
         }
         s += D * WK;
     }
 #pragma unroll
     for (int d = 0; d < D; ++d)
-        if (s + d * WK < KF) multiply(s + d * WK, d);
+        if (s + d * WK < KF) multiply(d);
 
     // the wavefronts' partial sums meet in LDS (integers: exact in any order)
-    if constexpr (FUSED) __syncthreads();   // in the place of the codes
     int *const mine = sums + wk * TM * L::kLd + (4 * h) * L::kLd + wn * NFW * 16 + c;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -292,7 +215,7 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
 #pragma unroll
         for (int t = 0; t < NF; ++t) {
             float af = (float)raw[t];
-            if (!FUSED && a.x_corr) af = fmaf(cx[j], rs[t], af);
+            if (a.x_corr) af = fmaf(cx[j], rs[t], af);
             y[t] = fmaf(af * sx[j], sw[t], bs[t]);
         }
         if (a.epi == QC_EPI_GELU_TANH) {
@@ -327,6 +250,254 @@ __global__ __launch_bounds__(kThreads, 2) void small_kernel(SmallArgs a) {
     }
 }
 
+// ---- quantization and GEMM in one launch -------------------------------------------------------
+// A block of 8 or 16 wavefronts quantizes its tokens into LDS, redundantly over the channel tiles, and multiplies:
+// 16 MI tokens by 16 NF channels, the wavefronts NF / 2 across the channels (two fragments each) and WK ways over
+// K.  What bounds it is a chain - the activations' way from memory, the maximum, the cast, the products,
+// the sums' way through LDS - and on more than a few tokens the cast itself, six vector instructions an
+// element on one CU for as many elements as the tile has tokens.  Hence
+//   * tiles of few tokens and many channels, 16 x 128 rather than 32 x 64: half as much to cast for the same
+//     number of blocks;
+//   * rows dealt to the threads in pairs (row, group of 128 columns), eight lanes a pair, so that a row of 9
+//     groups wastes nothing; what a wavefront has no pair for it skips;
+//   * 16 wavefronts where there is much to cast: a SIMD with two issues an instruction every 5.4 clocks, with
+//     four every 4; they take longer to start;
+//   * all arguments in one load, all loads of activations and (up to K = 1152) weights ahead of the first use.
+// us per call in a graph, with 512 threads, tiles of 16 x 32 to 32 x 64 and a power of two of threads per row, and so:
+// 2 x 1152 x 6912 5.7 4.9, 1 x 1152 x 1152 4.8 4.0, 64 x 1152 x 1152 5.7 5.2, 256 x 1152 x 1152 bf16 8.7 6.7, f32 9.5
+// 7.2, 100 x 1152 x 4608 GELU 10.8 6.8, 256 x 1154 x 1152 11.7 7.2, 8 x 4608 x 4608 11.4 9.1.
+constexpr int kStepsMost = 3;   // of 8 pairs per wavefront and step
+
+// bytes between the 16-k quarters of a stage in the code tile: 16 B per row and 16 B of padding, so that
+// the quarters a row's units go to fall into different banks
+__host__ __device__ inline int quarter_stride(int rows) { return 16 * rows + 16; }
+
+// LDS: [ row maxima: TM ][ token scales: TM ][ their reciprocals: TM ][ partial sums: WK x TM x kLd int32 ][ codes ]
+template <int MI, int NF, int WAVES>
+struct FusedLayout {
+    static constexpr int kTM = 16 * MI;
+    static constexpr int kWN = NF / 2, kWK = WAVES / kWN;
+    static constexpr int kLt = 20;              // between the columns of two fragments
+    static constexpr int kLd = NF * kLt + 4;    // four rows 16 banks apart
+    static constexpr int kSumsAt = 3 * kTM * 4;
+    static constexpr int kCodesAt = kSumsAt + kWK * kTM * kLd * 4;
+};
+
+template <int BITS, typename XT, int MI, int NF, int WAVES, int STEPS>
+__global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
+    using L = FusedLayout<MI, NF, WAVES>;
+    constexpr int TM = L::kTM, WK = L::kWK, kPairs = 8 * WAVES;   // pairs cast per step
+    constexpr int NW = BITS == 8 ? 2 : 1;       // 1 KiB weight pieces per stage and wavefront
+    constexpr int D = WK == 16 ? 2 : WK == 8 ? 3 : 5;   // stages in flight: all of K = 1152
+    constexpr int kStageBytes = BITS == 8 ? 8192 : 4096;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    uint32_t *const row_max = reinterpret_cast<uint32_t *>(lds);
+    float *const lds_s = reinterpret_cast<float *>(lds) + TM, *const lds_r = lds_s + TM;
+    int *const sums = reinterpret_cast<int *>(lds + L::kSumsAt);
+    uint8_t *const codes = lds + L::kCodesAt;
+    // all arguments in one go: fetched where they are first needed, they are three round trips
+    asm volatile("" ::"s"(a.X), "s"(a.x_tiled), "s"(a.x_scale), "s"(a.w_codes), "s"(a.w_scale), "s"(a.bias), "s"(a.Y), "s"(a.M),
+                 "s"(a.N), "s"(a.K), "s"(a.KF), "s"(a.m_tiles), "s"(a.n_tiles), "s"(a.rows), "s"(a.groups), "s"(a.inv_groups), "s"(a.qmax), "s"(a.epi), "s"(a.out));
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, h = lane >> 4;
+    const int wk = wave % WK, wn = wave / WK;
+
+    // block b runs on XCD b % 8: the blocks of one XCD take consecutive tiles, token tile fastest, so
+    // that they share weight tiles in its L2
+    const int nb = a.m_tiles * a.n_tiles, b = blockIdx.x;
+    const int v = (b % 8) * (nb / 8) + ((b % 8) < nb % 8 ? (b % 8) : nb % 8) + b / 8;
+    const int mt = v % a.m_tiles, nt = v / a.m_tiles;
+    const int64_t m0 = (int64_t)mt * TM;
+    const int G = nt / (8 / NF), t0 = nt % (8 / NF) * NF;
+    if ((int64_t)G * kTileN + t0 >= a.N) return;   // no live channel in this tile
+    if (tid < TM) row_max[tid] = 0;
+
+    const int K = (int)a.K, KF = a.KF, pairs = a.rows * a.groups;
+    const int sub = lane & 7, p0 = tid >> 3;
+    Group<XT> u[STEPS];
+    int row[STEPS], col0[STEPS];
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        if (i > 0 && wave * 8 + i * kPairs >= pairs) continue;   // uniform over the wavefront
+        const int p = p0 + i * kPairs < pairs ? p0 + i * kPairs : pairs - 1;
+        row[i] = (int)((uint32_t)p * a.inv_groups >> 20);
+        col0[i] = (p - row[i] * a.groups) * kGroup;
+        const int64_t m = m0 + row[i] < a.M ? m0 + row[i] : a.M - 1;
+        const XT *xrow = reinterpret_cast<const XT *>(a.X) + m * a.K;
+        u[i].load_ragged(xrow, col0[i], K, sub);
+    }
+
+    // weights of this wavefront: stages wk, wk + WK, ..; a register ring of D of them
+    v4i w[D][NW];
+    const uint8_t *const wbase = a.w_codes + (int64_t)G * KF * kStageBytes + (t0 + 2 * wn) * (BITS == 8 ? kFragBytes : kFragBytes / 2);
+    auto request = [&](int s, int d) {
+        const uint8_t *p = wbase + (int64_t)(s < KF ? s : KF - 1) * kStageBytes;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) w[d][j] = *reinterpret_cast<const v4i *>(p + j * kFragBytes + lane * 16);
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) request(wk + d * WK, d);
+
+    // what the epilogue needs: a thread keeps two channels, n0 and n0 + 1, and one or two tokens
+    constexpr int JT = NF / 2, kRowsPerPass = 64 * WAVES / (16 * JT);
+    const int ej = tid % JT, ec = tid / JT % 16, em = tid / (16 * JT);
+    const int64_t n0 = (int64_t)G * kTileN + 8 * ec + t0 + 2 * ej;
+    const int64_t na = n0 < a.N ? n0 : a.N - 1, nb2 = n0 + 1 < a.N ? n0 + 1 : a.N - 1;
+    float sw0 = a.w_scale[na], sw1 = a.w_scale[nb2], bs0 = 0.0f, bs1 = 0.0f;
+    if (a.bias) { bs0 = a.bias[na]; bs1 = a.bias[nb2]; }
+
+    // the maximum of each row, over the lanes of its pairs
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the zeros above are there; the loads stay in flight
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        if (i > 0 && wave * 8 + i * kPairs >= pairs) continue;
+        if (K % kUnit) u[i].settle_ragged(col0[i], K, sub);
+        auto running = Group<XT>::no_max();
+        u[i].absmax_into(running);
+        const float m = max_of_eight(Group<XT>::absmax_value(running));   // no NaN, not negative: ordered like its bits
+        if (sub == 0) atomicMax(row_max + row[i], __float_as_uint(m));
+    }
+    __syncthreads();
+    const bool first_tile = nt == 0;   // one block per token tile leaves codes and scales in the workspace
+    float s1 = 0.0f, r1 = 0.0f;
+    if constexpr (STEPS > 1) {
+        if (tid < a.rows) {
+            const float s = scale_of(__uint_as_float(row_max[tid]), a.qmax);
+            lds_s[tid] = s;
+            lds_r[tid] = 1.0f / s;   // correctly rounded
+            if (first_tile && m0 + tid < a.M) a.x_scale[m0 + tid] = s;
+        }
+        __syncthreads();
+    } else {
+        s1 = scale_of(__uint_as_float(row_max[row[0]]), a.qmax);
+        r1 = 1.0f / s1;
+        if (sub == 0 && col0[0] == 0 && p0 < pairs) {
+            lds_s[row[0]] = s1;
+            if (first_tile && m0 + row[0] < a.M) a.x_scale[m0 + row[0]] = s1;
+        }
+    }
+    const int qs = quarter_stride(a.rows);
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        if (i > 0 && wave * 8 + i * kPairs >= pairs) continue;
+        const float s = STEPS > 1 ? lds_s[row[i]] : s1, r = STEPS > 1 ? lds_r[row[i]] : r1;
+        uint32_t q[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            q[d] = codes4(quotient(u[i].get(4 * d + 0), s, r), quotient(u[i].get(4 * d + 1), s, r),
+                          quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r));
+        const uint4 o = Group<XT>::gather_codes(q, sub);
+        const int ui = col0[i] / kUnit + Group<XT>::unit_of(sub);   // unit = quarter of a stage
+        if (p0 + i * kPairs < pairs && ui * kUnit < K) {
+            *reinterpret_cast<uint4 *>(codes + ui * qs + row[i] * 16) = o;
+            if (first_tile && m0 + row[i] < a.M)
+                store16<false>(a.x_tiled + act_frag_offset(m0 + row[i], 0, KF) + (int64_t)(ui >> 2) * (4 * kFragBytes) + (ui & 3) * 256, o);
+        }
+    }
+    __syncthreads();
+
+    v4i acc[MI][2];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[i][t] = v4i{0, 0, 0, 0};
+    const uint8_t *xl[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) xl[i] = codes + h * qs + (16 * i + c < a.rows ? 16 * i + c : a.rows - 1) * 16;
+    auto multiply = [&](int s, int d) {   // stage s, in ring slot d
+        v4i wt[2];
+        if constexpr (BITS == 8) {
+            wt[0] = w[d][0];
+            wt[1] = w[d][1];
+        } else {
+            const v4i unit = w[d][0];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const uint32_t v0 = (uint32_t)unit[2 * t], v1 = (uint32_t)unit[2 * t + 1];
+                wt[t][0] = (int)((v0 << 4) & 0xF0F0F0F0u);
+                wt[t][1] = (int)(v0 & 0xF0F0F0F0u);
+                wt[t][2] = (int)((v1 << 4) & 0xF0F0F0F0u);
+                wt[t][3] = (int)(v1 & 0xF0F0F0F0u);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const v4i xa = *reinterpret_cast<const v4i *>(xl[i] + s * 4 * qs);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[i][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, wt[t], acc[i][t], 0, 0, 0);
+        }
+    };
+    int s = wk;
+    for (; s + (2 * D - 1) * WK < KF; s += D * WK) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(s + d * WK, d);
+            request(s + (d + D) * WK, d);
+        }
+    }
+    if (s + D * WK < KF) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(s + d * WK, d);
+            request(s + (d + D) * WK, d);
+        }
+        s += D * WK;
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (s + d * WK < KF) multiply(s + d * WK, d);
+
+    // the wavefronts' partial sums meet in LDS (integers: exact in any order)
+    int *const mine = sums + (wk * TM + 4 * h) * L::kLd + 2 * wn * L::kLt + c;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) mine[(16 * i + q) * L::kLd + t * L::kLt] = acc[i][t][q];
+    __syncthreads();
+
+    if (BITS == 4) { sw0 *= 0.0625f; sw1 *= 0.0625f; }   // operands carry codes times 16
+    for (int m = em; m < TM && m0 + m < a.M && n0 < a.N; m += kRowsPerPass) {
+        int raw0 = 0, raw1 = 0;
+#pragma unroll
+        for (int k = 0; k < WK; ++k) {
+            const int *p = sums + (k * TM + m) * L::kLd + 2 * ej * L::kLt + ec;
+            raw0 += p[0];
+            raw1 += p[L::kLt];
+        }
+        const bool both = n0 + 1 < a.N;   // stored in one piece, at any alignment of Y's elements
+        const int64_t at = (m0 + m) * a.N + n0;
+        if (a.out == QC_OUT_I32_ACC) {
+            int32_t *y = reinterpret_cast<int32_t *>(a.Y) + at;
+            y[0] = BITS == 4 ? raw0 >> 4 : raw0;   // exact: multiples of 16
+            if (both) y[1] = BITS == 4 ? raw1 >> 4 : raw1;
+            continue;
+        }
+        const float sx = lds_s[m];
+        float y[2] = {fmaf((float)raw0 * sx, sw0, bs0), fmaf((float)raw1 * sx, sw1, bs1)};
+        if (a.epi == QC_EPI_GELU_TANH) {
+            y[0] = gelu_tanh_f(y[0]);
+            y[1] = gelu_tanh_f(y[1]);
+        } else if (a.epi == QC_EPI_GELU_ERF) {
+            y[0] = gelu_erf_f(y[0]);
+            y[1] = gelu_erf_f(y[1]);
+        }
+        if (a.out == QC_OUT_F32) {
+            float *o = reinterpret_cast<float *>(a.Y) + at;
+            if (both) __builtin_memcpy(o, y, sizeof(y));
+            else o[0] = y[0];
+        } else {
+            uint16_t *o = reinterpret_cast<uint16_t *>(a.Y) + at;
+            const uint32_t pk = pack_bf16x2(y[0], y[1]);
+            if (both) __builtin_memcpy(o, &pk, sizeof(pk));
+            else o[0] = (uint16_t)(pk & 0xffffu);
+        }
+    }
+}
+
 // A kernel may use 64 KiB of LDS without asking; this asks for more, once per kernel and device.
 hipError_t allow_lds(const void *kernel, std::atomic<uint64_t> &asked) {
     int device = 0;
@@ -339,58 +510,32 @@ hipError_t allow_lds(const void *kernel, std::atomic<uint64_t> &asked) {
     return hipSuccess;
 }
 
-int live_rows_log2(int64_t M, int tile) {   // rows of a tile that can be live, as a power of two
-    int r = 0;
-    while ((1 << r) < tile && (1 << r) < M) ++r;
-    return r;
-}
-
-template <int BITS, int MI, int NF, int WN, int D, int SRC, int UPT>
+template <int BITS, int MI, int NF, int WN, int D>
 hipError_t launch_tile(SmallArgs a, hipStream_t stream) {
     using L = Layout<MI, NF, WN>;
     a.m_tiles = (int)((a.M + L::kTM - 1) / L::kTM);
     a.n_tiles = (int)(round_up(a.N, kTileN) / kTileN) * (8 / NF);
-    a.rp_log2 = live_rows_log2(a.M, L::kTM);
-    const size_t codes = SRC != kCodes ? (size_t)a.KF * 4 * quarter_stride(a.rp_log2) : 0;
-    const size_t lds = L::kSumsAt + (codes > (size_t)L::kSums ? codes : (size_t)L::kSums);
-    if (lds > 64 * 1024) {
+    if (L::kSums > 64 * 1024) {
         static std::atomic<uint64_t> asked{0};
-        if (hipError_t e = allow_lds((const void *)small_kernel<BITS, MI, NF, WN, D, SRC, UPT>, asked); e != hipSuccess) return e;
+        if (hipError_t e = allow_lds((const void *)small_kernel<BITS, MI, NF, WN, D>, asked); e != hipSuccess) return e;
     }
-    small_kernel<BITS, MI, NF, WN, D, SRC, UPT>
-        <<<dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(kThreads), lds, stream>>>(a);
+    small_kernel<BITS, MI, NF, WN, D><<<dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(kThreads), L::kSums, stream>>>(a);
     return hipGetLastError();
 }
 
-// The tiles, smallest first: tokens, channels, and for the fused form how many groups of 128 columns
-// a thread may hold.  The 64-token tile is not fused: its blocks would spend longer on the
-// redundant quantization than a launch of its own takes (512 x 1152: 11.2 against 2.9 + 6.7 us).
-struct TileShape { int tokens, channels, upt; };
-constexpr TileShape kTiles[] = {{16, 32, 3}, {32, 32, 5}, {32, 64, 5}, {64, 64, 0}};
+// The tiles of small_kernel, smallest first: tokens and channels.
+struct TileShape { int tokens, channels; };
+constexpr TileShape kTiles[] = {{16, 32}, {32, 32}, {32, 64}, {64, 64}};
 constexpr int kTileCount = 4;
 constexpr int kCus = 256;
 
 template <int BITS>
-hipError_t launch_bits(int tile, int src, const SmallArgs &a, hipStream_t stream) {
-    if (src == kCodes) {
-        switch (tile) {
-            case 0: return launch_tile<BITS, 1, 2, 1, 4, kCodes, 1>(a, stream);
-            case 1: return launch_tile<BITS, 2, 2, 1, 4, kCodes, 1>(a, stream);
-            case 2: return launch_tile<BITS, 2, 4, 2, 4, kCodes, 1>(a, stream);
-            default: return launch_tile<BITS, 4, 4, 2, 3, kCodes, 1>(a, stream);
-        }
-    }
-    if (src == kFusedBf16) {
-        switch (tile) {
-            case 0: return launch_tile<BITS, 1, 2, 1, 4, kFusedBf16, kTiles[0].upt>(a, stream);
-            case 1: return launch_tile<BITS, 2, 2, 1, 4, kFusedBf16, kTiles[1].upt>(a, stream);
-            default: return launch_tile<BITS, 2, 4, 2, 4, kFusedBf16, kTiles[2].upt>(a, stream);
-        }
-    }
+hipError_t launch_bits(int tile, const SmallArgs &a, hipStream_t stream) {
     switch (tile) {
-        case 0: return launch_tile<BITS, 1, 2, 1, 4, kFusedF32, kTiles[0].upt>(a, stream);
-        case 1: return launch_tile<BITS, 2, 2, 1, 4, kFusedF32, kTiles[1].upt>(a, stream);
-        default: return launch_tile<BITS, 2, 4, 2, 4, kFusedF32, kTiles[2].upt>(a, stream);
+        case 0: return launch_tile<BITS, 1, 2, 1, 4>(a, stream);
+        case 1: return launch_tile<BITS, 2, 2, 1, 4>(a, stream);
+        case 2: return launch_tile<BITS, 2, 4, 2, 4>(a, stream);
+        default: return launch_tile<BITS, 4, 4, 2, 3>(a, stream);
     }
 }
 
@@ -406,12 +551,72 @@ int64_t live_channel_tiles(int64_t N, int channels) {
 // 288: 6.0, 32 x 64 144: 5.5; 512 x 1152: 32 x 64 288: 8.7, 64 x 64 144: 6.7; 1000 x 1152: 64 x 64 288:
 // 12.0, the ring kernel 9.1.  Narrow outputs, whose channel tiles are all live: 8192 x 32: 32 x 32 1024:
 // 24.0, 64 x 64 256 (not fused): 17.4; 16384 x 64: 64 x 64 512: 23.6, the ring kernel 18.1.
+bool one_block_per_cu(int64_t M, int64_t N, TileShape t) {
+    const int64_t mt = (M + t.tokens - 1) / t.tokens, nt = live_channel_tiles(N, t.channels);
+    return mt <= kCus && nt <= kCus && mt * nt <= kCus;
+}
 int pick_tile(int64_t M, int64_t N) {
-    for (int t = 0; t < kTileCount; ++t) {
-        const int64_t mt = (M + kTiles[t].tokens - 1) / kTiles[t].tokens, nt = live_channel_tiles(N, kTiles[t].channels);
-        if (mt <= kCus && nt <= kCus && mt * nt <= kCus) return t;
+    for (int t = 0; t < kTileCount; ++t)
+        if (one_block_per_cu(M, N, kTiles[t])) return t;
+    return -1;
+}
+
+// The same for fused_kernel, -1 if two launches are the better or the only way: the smallest tile again, with eight
+// wavefronts while each lane has at most three pairs of a row and a group to cast.  us in a graph, 8 and 16
+// wavefronts: 2 x 1152 x 6912 4.9 6.3, 64 x 1152 x 1152 5.2 6.1, 128 x 1152 x 1152 (16 x 64) 5.6 5.9, 200 x 640 x 1152
+// 4.8 5.8, 256 x 1152 x 1152 (16 x 128) 6.9 6.7.  Tiles of 32 tokens, two launches and one: 512 x 1152 x 1152
+// 10.9 9.8, 700 tokens 11.0 10.3, K = 1536, 600 tokens 11.2 12.1: up to nine groups a row.
+struct FusedShape { TileShape tile; int waves, pairs; };   // pairs: most pairs of a row and a group that it is taken for
+constexpr FusedShape kFusedShapes[] = {{{16, 32}, 8, 192}, {{16, 32}, 16, 384}, {{16, 64}, 8, 192},
+                                        {{16, 64}, 16, 384}, {{16, 128}, 16, 384}, {{32, 128}, 16, 288}};
+constexpr int kFusedShapeCount = 6;
+int pick_fused_shape(int64_t M, int64_t N, int64_t K) {
+    if (K < 8 || K > QC_MAX_K) return -1;   // a row of less than 16 B has no whole piece to load
+    for (int i = 0; i < kFusedShapeCount; ++i) {
+        const FusedShape &f = kFusedShapes[i];
+        if (!one_block_per_cu(M, N, f.tile)) continue;
+        const int64_t rows = M < f.tile.tokens ? M : f.tile.tokens;
+        if (rows * ((K + kGroup - 1) / kGroup) <= f.pairs) return i;
     }
     return -1;
+}
+
+template <int BITS, typename XT, int MI, int NF, int WAVES, int STEPS>
+hipError_t launch_fused_steps(const SmallArgs &a, size_t lds, hipStream_t stream) {
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> asked{0};
+        if (hipError_t e = allow_lds((const void *)fused_kernel<BITS, XT, MI, NF, WAVES, STEPS>, asked); e != hipSuccess) return e;
+    }
+    fused_kernel<BITS, XT, MI, NF, WAVES, STEPS><<<dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(64 * WAVES), lds, stream>>>(a);
+    return hipGetLastError();
+}
+
+template <int BITS, typename XT, int MI, int NF, int WAVES>
+hipError_t launch_fused(SmallArgs a, hipStream_t stream) {
+    using L = FusedLayout<MI, NF, WAVES>;
+    a.m_tiles = (int)((a.M + L::kTM - 1) / L::kTM);
+    a.n_tiles = (int)(round_up(a.N, kTileN) / kTileN) * (8 / NF);
+    a.rows = (int)(a.M < L::kTM ? a.M : L::kTM);
+    a.groups = (int)((a.K + kGroup - 1) / kGroup);
+    a.inv_groups = ((1u << 20) + a.groups - 1) / a.groups;   // exact for pairs below 384
+    // 384 groups at most, so that the codes, 16 B per unit of 16 columns and row and 16 B of padding per unit, take
+    // 96 KiB at most, with one row, and less than kLdsMost together with the sums
+    const size_t lds = L::kCodesAt + (size_t)a.KF * 4 * quarter_stride(a.rows);
+    if (lds > (size_t)kLdsMost) return hipErrorInvalidValue;
+    return a.rows * a.groups <= 8 * WAVES ? launch_fused_steps<BITS, XT, MI, NF, WAVES, 1>(a, lds, stream)
+                                          : launch_fused_steps<BITS, XT, MI, NF, WAVES, kStepsMost>(a, lds, stream);
+}
+
+template <int BITS, typename XT>
+hipError_t launch_fused_shape(int shape, const SmallArgs &a, hipStream_t stream) {
+    switch (shape) {
+        case 0: return launch_fused<BITS, XT, 1, 2, 8>(a, stream);
+        case 1: return launch_fused<BITS, XT, 1, 2, 16>(a, stream);
+        case 2: return launch_fused<BITS, XT, 1, 4, 8>(a, stream);
+        case 3: return launch_fused<BITS, XT, 1, 4, 16>(a, stream);
+        case 4: return launch_fused<BITS, XT, 1, 8, 16>(a, stream);
+        default: return launch_fused<BITS, XT, 2, 8, 16>(a, stream);
+    }
 }
 
 SmallArgs small_args(uint8_t *x_tiled, float *x_scale, const uint8_t *w_packed, const float *w_scale,
@@ -448,30 +653,22 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
         a.x_corr = x_corr;
         a.w_rowsum = w_rowsum;
     }
-    return bits == 8 ? launch_bits<8>(tile, kCodes, a, stream) : launch_bits<4>(tile, kCodes, a, stream);
+    return bits == 8 ? launch_bits<8>(tile, a, stream) : launch_bits<4>(tile, a, stream);
 }
 
-// What limits the fused form, beyond the tile: the columns a thread holds.  They bound its codes in LDS too,
-// 16 B per unit of 16 columns and live row and 16 B of padding per unit: at most 81 KiB, with one row of
-// 40960 columns, far below kLdsMost.
-bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K) {
-    const int tile = pick_tile(M, N);
-    if (tile < 0 || kTiles[tile].upt == 0) return false;
-    const int rp_log2 = live_rows_log2(M, kTiles[tile].tokens);
-    const int64_t columns = (int64_t)kTiles[tile].upt * kUnit * (kThreads >> rp_log2);
-    return K <= columns;
-}
+bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K) { return pick_fused_shape(M, N, K) >= 0; }
 
 hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale,
                                 const uint8_t *w_packed, const float *w_scale, const float *bias, void *Y,
                                 int64_t M, int64_t N, int64_t K, int act_bits, int bits, qc_epilogue epi,
                                 qc_out ydt, hipStream_t stream) {
-    if (!qlinear_small_chosen(M, N, K)) return hipErrorInvalidValue;
+    const int shape = pick_fused_shape(M, N, K);
+    if (shape < 0) return hipErrorInvalidValue;
     SmallArgs a = small_args(x_tiled, x_scale, w_packed, w_scale, bias, Y, M, N, K, epi, ydt);
     a.X = X;
     a.qmax = (float)((1 << (act_bits - 1)) - 1);
-    const int src = xdt == QC_BF16 ? kFusedBf16 : kFusedF32, tile = pick_tile(M, N);
-    return bits == 8 ? launch_bits<8>(tile, src, a, stream) : launch_bits<4>(tile, src, a, stream);
+    if (xdt == QC_BF16) return bits == 8 ? launch_fused_shape<8, uint16_t>(shape, a, stream) : launch_fused_shape<4, uint16_t>(shape, a, stream);
+    return bits == 8 ? launch_fused_shape<8, float>(shape, a, stream) : launch_fused_shape<4, float>(shape, a, stream);
 }
 
 }  // namespace qc

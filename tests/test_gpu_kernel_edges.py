@@ -104,6 +104,23 @@ def test_qlinear_on_few_tokens_over_its_own_input(M, K, N, shift, dtype):
 
 
 @pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N", [
+    (3, 8, 40), (5, 7, 33), (13, 10, 200), (16, 1530, 70), (16, 1538, 70), (16, 3070, 95), (16, 3074, 40), (1, 24580, 33),
+    (2, 24570, 1), (17, 1152, 4100), (48, 1538, 2050), (130, 1000, 1282), (144, 1540, 1282), (250, 1152, 2049), (256, 3068, 2046),
+    (272, 1030, 1920), (257, 1152, 4081), (700, 1152, 1281), (505, 1154, 2033), (519, 1151, 1921)])
+def test_qlinear_in_one_launch_at_the_edges_of_its_shapes(M, K, N, bits):
+    """Every tile of the one-launch form, both counts of wavefronts, one step of pairs of a row and a group and
+    three, the longest rows each takes and one group more; ragged rows of any remainder, of less
+    than 16 B too, row counts that are no power of two, a last tile with one live row and odd channels."""
+    rng = np.random.default_rng(M * 31 + K * 7 + N + bits)
+    K += K % 2 if bits == 4 else 0
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    run_linear_case(random_x(rng, M, K, "bf16"), W, b, bits, "gelu_tanh", "bf16")
+    run_linear_case(random_x(rng, M, K, "f32"), W, None, bits, "none", "f32", act_bits=6)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("N", [129, 130, 132, 136])
 def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
     """The kernel that streams its weights, whose smallest problems are larger than the few-token
