@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libqc.so")
@@ -375,7 +376,8 @@ def qc_prune_probability(S, tau_low, tau_high, p_base) -> float:
 
 # What the tensor helpers cost on the host decides how long the small calls take, so the module is
 # looked up once, the stream is read as a number instead of through a Stream object, and the helpers
-# of the per-step calls go to the C entry directly: the linear of 2 tokens 8.95 -> 6.22 us.
+# of the per-step calls go to the C entry directly: the linear of 2 tokens 8.95 -> 6.22 us.  Where torch is
+# imported before this module they are replaced by native ones (end of this file).
 _torch_module = None
 
 
@@ -670,3 +672,37 @@ def qlinear_tensor_t(X, pw: PackedWeight, bias=None, epi="none", out="bf16", wor
                              OUT[out], workspace.data_ptr(), workspace.numel(), _stream()),
            "qc_qlinear_tensor")
     return Y
+
+
+# ---- the per-step helpers as native functions ----------------------------------------------------
+
+_PER_STEP = ("qlinear_t", "qlinear_asym_t", "qlinear_tensor_t", "latent_delta_t", "layer_similarity_t",
+             "frame_gradient_norm_t", "cumulative_variation_t")
+
+
+def _entries():
+    """The addresses of the C entries behind _PER_STEP, in that order, and of the rotated linear."""
+    names = ("qc_qlinear_act_bits", "qc_qlinear_asym", "qc_qlinear_tensor", "qc_latent_delta", "qc_layer_similarity",
+             "qc_frame_gradient_norm", "qc_cumulative_variation", "qc_qlinear_rot")
+    return tuple(ctypes.cast(getattr(lib(), n), ctypes.c_void_p).value for n in names)
+
+
+def _use_native_helpers() -> None:
+    """Replace the per-step helpers by those of _qc_torch (csrc/qc_torch.cpp), which do the same and hand what is
+    out of the ordinary to the ones above.  The module is linked against torch's libraries, so it is left alone
+    where torch has not been imported; where it is not built the helpers above serve."""
+    if "torch" not in sys.modules:
+        return
+    try:
+        from . import _qc_torch
+    except ImportError:
+        return
+    helpers = globals()
+    _python_helpers.update((n, helpers[n]) for n in _PER_STEP)
+    _qc_torch.setup(_entries, _check, tuple(_python_helpers[n] for n in _PER_STEP))
+    for n in _PER_STEP:
+        helpers[n] = getattr(_qc_torch, n)
+
+
+_python_helpers = {}   # those replaced
+_use_native_helpers()

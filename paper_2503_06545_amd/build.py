@@ -22,6 +22,8 @@ OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["qc_api.hip", "qc_quant.hip", "qc_pack.hip", "qc_gemm.hip", "qc_gemm_w8.hip", "qc_gemm_w4.hip", "qc_small.hip", "qc_delta.hip"]
 ROOFS_SRC = os.path.join(ROOT, "bench", "qc_roofs.hip")
 ROOFS = os.path.join(ROOT, "bench", "qc_roofs")  # stand-alone roofline micro-benchmark
+TORCH_SRC = os.path.join(CSRC, "qc_torch.cpp")   # the per-step tensor helpers, host code
+TORCH_LIB = os.path.join(HERE, "_qc_torch.so")
 RESOURCE_REPORT = os.path.join(OBJ_DIR, "kernel_resources.txt")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -68,18 +70,32 @@ def _compile(src: str):
     return obj, [(src,) + k for k in _resources(r.stderr)]
 
 
+def _compile_torch(_=None) -> str:
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    lib = os.path.join(base, "lib")
+    includes = [os.path.join(ROOT, "include"), os.path.join(base, "include"), "/opt/rocm/include", sysconfig.get_paths()["include"],
+                os.path.join(base, "include", "torch", "csrc", "api", "include")]
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    *("-I" + i for i in includes), TORCH_SRC, "-o", TORCH_LIB, "-L" + lib, "-ltorch_python", "-lc10",
+                    "-lc10_hip", "-Wl,-rpath," + lib], check=True)
+    return TORCH_LIB
+
+
 def _compile_roofs(_=None) -> str:
     subprocess.run([HIPCC, *FLAGS, ROOFS_SRC, "-o", ROOFS], check=True, stderr=subprocess.DEVNULL)
     return ROOFS
 
 
 def build(verbose: bool = True) -> str:
-    """Always recompiles every source, relinks libqc.so and rebuilds the qc_roofs program."""
+    """Always recompiles every source, relinks libqc.so and rebuilds _qc_torch.so and the qc_roofs program."""
     os.makedirs(OBJ_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as pool:
-        roofs = pool.submit(_compile_roofs)
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 2)) as pool:
+        others = [pool.submit(_compile_roofs), pool.submit(_compile_torch)]
         results = list(pool.map(_compile, SOURCES))
-        roofs.result()
+        for other in others:
+            other.result()
     objs = [o for o, _ in results]
     kernels = [k for _, ks in results for k in ks]
     with open(RESOURCE_REPORT, "w") as f:
