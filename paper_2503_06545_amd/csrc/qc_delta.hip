@@ -9,18 +9,20 @@
 // hence two forms of one kernel:
 //   * Two launches: at most one block per CU (256); a second, single-block launch adds the blocks'
 //     partial sums.
-//   * One launch, for small tensors: 16 or 32 blocks at most, of which the one that sees all partial
+//   * One launch, for small tensors: at most 128 blocks, of which the one that sees all partial
 //     sums finishes the job (finish_here() says how, without a counter that somebody would have to
-//     clear).  What it saves is a launch, 3 us of host time (calls from the host back to back 10 and 7
-//     us); what it costs on the GPU are the device fence of each block, the blocks' reading of each
-//     other's records, and, with the size, that 32 blocks read what 256 would.  Each operation's limit
-//     (kOneMost) lies where that is some 1 us, for the similarity 2.  us per call in a graph, two launches
-//     and one, warm and, behind the bar, cold inputs:
-//       latent delta     0.5 MB 4.5 3.9 | 5.7 4.4   1 MB 4.3 4.1 | 6.0 5.2   2 MB 4.5 4.9 | 5.8 5.5   4 MB 5.2 6.7 | 6.1 6.7
-//       similarity bf16  0.5 MB 4.3 4.2 | 4.7 4.7   1 MB 4.5 4.6 | 4.8 5.5   2.5 MB 4.6 5.7 | 5.1 6.6   5 MB 4.6 6.4 | 5.5 8.2
-//       frame gradient   0.5 MB 4.1 3.9 | 4.2 4.2   1 MB 4.0 4.6 | 4.3 4.8   1.5 MB 4.0 4.8 | 4.5 5.4   3 MB 4.1 5.5 | 4.7 6.3
-//       variation over 1, 3, 8 tensors of 65536 elements 3.5 4.1 6.7, 3.7 4.4 7.8 | 4.0 5.1 8.2, 4.5 5.3 8.2;
-//       of 163840 3.5 4.3 6.8, 4.4 5.8 9.0 | 4.1 5.5 8.4, 5.5 6.5 9.7
+//     clear).  What it saves is a launch, 3 us of host time (a call takes 4.1 and 7.1 us there); what it costs on
+//     the GPU are the device fence of each block, the blocks' reading of each other's records, and, with
+//     the size, that fewer blocks read.  Two chunks a block (one from five earlier tensors on), 16 blocks at least while there are as many
+//     chunks: with 32 blocks at most it took 5.6 instead of 5.3 us for a latent delta of 390000 elements, 7.7
+//     instead of 6.6 for a similarity of 1.2 million.  Each operation's limit (kOneMost) lies where it costs
+//     some 0.5 us more than two launches, for the similarity 1.  us per call in a graph, four sets of inputs in
+//     turn, two launches and one:
+//       latent delta     65536 4.5 3.7   300000 5.4 4.6   500000 5.7 5.6   700000 6.0 6.3   1 million 6.2 7.4
+//       similarity bf16  100000 4.8 4.0   300000 4.7 4.7   600000 5.4 5.6   1.3 million 5.6 6.5   1.7 million 5.4 7.4
+//       frame gradient   binary32 65536 4.1 3.4   250000 4.2 4.2   400000 4.0 5.1; bf16 500000 4.4 4.5   900000 4.2 5.5
+//       variation over 1, 3, 8 tensors of 65536 elements 4.0 5.2 8.0, 3.6 4.4 6.9; of 97000 4.0 5.2 8.3, 3.9 5.0
+//       7.5; of 150000 3.6 4.9 8.0, 4.4 5.3 8.9
 #include <atomic>
 
 #include "qc_device.h"
@@ -28,11 +30,11 @@
 namespace qc {
 namespace {
 
-constexpr int kFinalThreads = 256;  // the second launch: one partial sum tuple per thread
+constexpr int kFinalThreads = 64;   // the second launch
 constexpr int kMaxBlocks = 256;     // two launches: one block per CU
 constexpr int kOneThreads = 512;    // one launch
-constexpr int kOneBlocks = 32;
-static_assert(kFinalThreads >= kMaxBlocks && kOneBlocks <= 64, "a thread, a lane per block in the combine");
+constexpr int kOneFew = 16, kOneBlocks = 128;
+static_assert(kMaxBlocks % kFinalThreads == 0 && kOneBlocks % 64 == 0, "whole wavefronts of blocks in the combines");
 
 // the workspaces: a double per sum and block of the two-launch form
 constexpr size_t kDeltaBytes = kMaxBlocks * 2 * sizeof(double), kSimilarityBytes = kMaxBlocks * 3 * sizeof(double);
@@ -85,7 +87,7 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
     }
 }
 
-// The one-launch form's end.  v: this block's sums, valid in wavefront 0.  Every block publishes its
+// The one-launch form's end, for the first wavefront alone: v holds this block's sums.  Every block publishes its
 // sums and a check word, a 64-bit hash of the launch's nonce and the sums, with device-scope stores,
 // passes a sequentially consistent fence, and then reads everybody's.  A block's sums count once they
 // fit their check.  Words of a record half written or left by something else fit it with a probability
@@ -93,47 +95,59 @@ __device__ inline void block_sum(double (&v)[COUNT], double *sh) {
 // graph, is not there, because a launch clears its checks before it ends.  The block whose stores come
 // last sees all records: at least one block finds everything present, forms the totals (every block
 // that does forms the same ones) and clears the checks.  Nobody waits for anybody.  Returns whether
-// this block has the totals in v (wavefront 0).
-__device__ inline uint64_t mix(uint64_t hash, uint64_t bits) {
-    hash = (hash ^ bits) * 0x9E3779B97F4A7C15ull;   // odd: a bijection of hash ^ bits
-    return hash ^ (hash >> 32);
+// this block has the totals in v.
+// The check is a sum of one term per word, each a bijection of the word under a nonce of its own, so that
+// the multiplications do not wait for each other.
+__device__ inline uint64_t term_of(uint64_t nonce, int c, uint64_t bits) {
+    const uint64_t t = ((nonce + (uint64_t)c * 0xD1B54A32D192ED03ull) ^ bits) * 0x9E3779B97F4A7C15ull;
+    return t ^ (t >> 32);
 }
 
 template <int COUNT>
 __device__ inline bool finish_here(double (&v)[COUNT], uint64_t *records, uint64_t nonce) {
     constexpr int kWords = COUNT + 1;
-    const int tid = threadIdx.x, blocks = gridDim.x;
-    if (tid == 0) {
-        uint64_t *r = records + kWords * blockIdx.x, check = nonce;
+    const int lane = threadIdx.x, blocks = gridDim.x;
+    if (lane == 0) {
+        uint64_t *r = records + kWords * blockIdx.x, check = 0;
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
             const uint64_t bits = (uint64_t)__double_as_longlong(v[c]);
             __hip_atomic_store(r + c, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            check = mix(check, bits);
+            check += term_of(nonce, c, bits);
         }
-        __hip_atomic_store(r + COUNT, check, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");   // the stores before anybody's loads below
+        // 0 is what a cleared check holds
+        __hip_atomic_store(r + COUNT, check ? check : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
-    bool present = true;
-    if (tid < 64) {
-        uint64_t *r = records + kWords * (tid < blocks ? tid : 0), word[kWords];
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");   // the stores before anybody's loads below
+    constexpr int kPer = kOneBlocks / 64;   // records a lane reads
+    uint64_t word[kPer][kWords];
 #pragma unroll
-        for (int c = 0; c < kWords; ++c) word[c] = __hip_atomic_load(r + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint64_t check = nonce;
+    for (int i = 0; i < kPer; ++i) {
+        const int b = lane + 64 * i;
+        if (i > 0 && 64 * i >= blocks) break;   // uniform
+#pragma unroll
+        for (int c = 0; c < kWords; ++c)
+            word[i][c] = __hip_atomic_load(records + kWords * (b < blocks ? b : 0) + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    bool present = true;
+#pragma unroll
+    for (int c = 0; c < COUNT; ++c) v[c] = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        if (i > 0 && 64 * i >= blocks) break;
+        uint64_t check = 0;
 #pragma unroll
         for (int c = 0; c < COUNT; ++c) {
-            check = mix(check, word[c]);
-            v[c] = tid < blocks ? __longlong_as_double((long long)word[c]) : 0.0;
+            check += term_of(nonce, c, word[i][c]);
+            v[c] += lane + 64 * i < blocks ? __longlong_as_double((long long)word[i][c]) : 0.0;
         }
-        present = check == word[COUNT];
+        present = present && (check ? check : 1) == word[i][COUNT];
     }
-    if (!__syncthreads_and(present)) return false;
-    if (tid < 64) {
-        if (tid < blocks) __hip_atomic_store(records + kWords * tid + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!__all(present)) return false;
+    for (int b = lane; b < blocks; b += 64)
+        __hip_atomic_store(records + kWords * b + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int c = 0; c < COUNT; ++c) v[c] = wave_sum(v[c]);
-    }
+    for (int c = 0; c < COUNT; ++c) v[c] = wave_sum(v[c]);
     return true;
 }
 
@@ -142,6 +156,7 @@ __device__ inline bool finish_here(double (&v)[COUNT], uint64_t *records, uint64
 //   kCount, kElems       sums it keeps; elements per pack
 //   kThreads, kUnroll    launch shape of the two-launch form: threads, packs in flight per lane
 //   kOneUnroll, kBytes   packs in flight in the one-launch form (512 threads); the workspace
+//   kOneChunks           chunks a block takes there beyond 16 blocks
 //   kOneMost, kOuts      elements up to which that form is taken (see the top); floats of output
 //   kSlabs               how the blocks share the packs (see reduce_kernel)
 //   Regs, load, add      what a pack occupies, how it is read and summed
@@ -205,10 +220,10 @@ __device__ inline float widen(uint16_t v) { return __uint_as_float((uint32_t)v <
 
 // sum|cur - prev|, sum|prev| -> both and their ratio
 struct DeltaOp {
-    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOuts = 3;
+    static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOneChunks = 2, kOuts = 3;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kDeltaBytes;
-    static constexpr int64_t kOneMost = 3 << 17;
+    static constexpr int64_t kOneMost = 3 << 18;
     const float *cur, *prev;
     struct Regs { float4 a, b; };
     __device__ void load(Regs &r, int64_t i) const { r.a = stream4f(cur + 4 * i); r.b = stream4f(prev + 4 * i); }
@@ -233,7 +248,7 @@ struct DeltaOp {
 // 8.5 7.9, 2 x 75 million, cold, 54 50.6.
 template <typename T, int THREADS = 512>
 struct SimilarityOp {
-    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = THREADS, kUnroll = 4, kOneUnroll = 2, kOuts = 4;
+    static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = THREADS, kUnroll = 4, kOneUnroll = 2, kOneChunks = 2, kOuts = 4;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kSimilarityBytes;
     static constexpr int64_t kOneMost = (5 << 19) / sizeof(T);
@@ -281,7 +296,7 @@ struct GradientOp {
     // the frame before is another one).  binary32, 16.8 and 31 million elements, frames of 1288 12.7
     // 20.6, 17.4 33, 14.0 23; of 4096 12.9 20.8, 14.8 25, 17.3 30; of 16384 17.2 28, 22 38, 22 38.  bf16, 16.8
     // and 31 million, frames of 1288 7.1 12.6, 7.6 13.2, 9.1 13.7; of 8192 7.6 13.1, 10.8 17.0, 12.7 20.4.
-    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 2, kOneUnroll = 2, kOuts = 2;
+    static constexpr int kCount = 1, kElems = Pack<T>::kElems, kThreads = 1024, kUnroll = 2, kOneUnroll = 2, kOneChunks = 2, kOuts = 2;
     static constexpr bool kSlabs = true;
     static constexpr size_t kBytes = kGradientBytes;
     static constexpr int64_t kOneMost = (1 << 20) / sizeof(T);
@@ -318,10 +333,10 @@ struct PrevList { const float *p[QC_MAX_PREV]; };
 template <int COUNT>
 struct VariationOp {
     // two wavefronts per SIMD: room for 2 x 2 (COUNT + 1) float4 per lane
-    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1, kOuts = COUNT + 1;
+    static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1, kOneChunks = COUNT > 4 ? 1 : 2, kOuts = COUNT + 1;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kVariationBytes;
-    static constexpr int64_t kOneMost = 3 << 15;
+    static constexpr int64_t kOneMost = 1 << 17;
     const float *cur;
     PrevList prevs;
     struct Regs { float4 a, b[COUNT]; };
@@ -393,6 +408,7 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, int64
     if (blockIdx.x == 0 && threadIdx.x < (int)(n - packs * Op::kElems)) op.tail(packs * Op::kElems + threadIdx.x, s);
     block_sum<THREADS, C>(s, sh);
     if constexpr (ONE_LAUNCH) {
+        if (threadIdx.x >= 64) return;
         if (finish_here(s, reinterpret_cast<uint64_t *>(partials), nonce) && threadIdx.x == 0)
             Op::finish(s, out);
     } else if (threadIdx.x == 0) {
@@ -401,16 +417,25 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, int64
     }
 }
 
-// one block: fixed-order combine of the partial sums
+// one wavefront: fixed-order combine of the partial sums, four blocks' a lane
 template <typename Op>
 __global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__restrict__ partials, int count,
                                                               float *__restrict__ out) {
-    constexpr int C = Op::kCount;
-    __shared__ double sh[C * (kFinalThreads / 64)];
-    double s[C];
+    constexpr int C = Op::kCount, kPer = kMaxBlocks / kFinalThreads;
+    double p[kPer][C], s[C];
 #pragma unroll
-    for (int c = 0; c < C; ++c) s[c] = (int)threadIdx.x < count ? partials[C * threadIdx.x + c] : 0.0;
-    block_sum<kFinalThreads, C>(s, sh);
+    for (int i = 0; i < kPer; ++i) {
+        const int b = (int)threadIdx.x + kFinalThreads * i;
+#pragma unroll
+        for (int c = 0; c < C; ++c) p[i][c] = partials[C * (b < count ? b : 0) + c];
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        s[c] = 0.0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) s[c] += (int)threadIdx.x + kFinalThreads * i < count ? p[i][c] : 0.0;
+        s[c] = wave_sum(s[c]);
+    }
     if (threadIdx.x == 0) Op::finish(s, out);
 }
 
@@ -439,10 +464,8 @@ qc_status launch_reduction(const Op &op, int64_t n, float *out, void *workspace,
     if (n <= Op::kOneMost && !overlap(out, Op::kOuts * sizeof(float), workspace, Op::kBytes)) {
         constexpr int U = Op::kOneUnroll;
         static_assert(kOneBlocks * (Op::kCount + 1) * sizeof(double) <= Op::kBytes, "room for the blocks' sums and check words");
-        // 32 blocks where each of 16 would take three chunks or more (latent delta, cold, 16 and 32 blocks:
-        // 1 MB 5.2 5.2, 2 MB 6.3 5.5)
         const int64_t chunk = (int64_t)kOneThreads * U;
-        const unsigned blocks = blocks_for(chunk, n / Op::kElems < 3 * 16 * chunk ? 16 : kOneBlocks);
+        const unsigned few = blocks_for(chunk, kOneFew), more = blocks_for(chunk * Op::kOneChunks, kOneBlocks), blocks = few > more ? few : more;
         reduce_kernel<Op, kOneThreads, U, true><<<dim3(blocks), dim3(kOneThreads), 0, st>>>(op, n, slab_for(blocks), partials, out, next_nonce());
         return hipGetLastError() == hipSuccess ? QC_OK : QC_ERR_DEVICE;
     }

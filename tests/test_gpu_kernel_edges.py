@@ -275,6 +275,31 @@ def test_reductions_on_both_sides_of_the_one_launch_form(n):
     assert np.all(np.abs(other - ref) <= 1e-5 * np.abs(ref))
 
 
+@pytest.mark.parametrize("n", [32 * 4096, 32 * 4096 + 1, 128 * 4096, 128 * 4096 + 5, 3 << 18, (3 << 18) + 1])
+def test_latent_delta_in_one_launch_of_many_blocks(n):
+    """More blocks than a wavefront has lanes, whose records a lane reads in two goes: 16, 17, 64, 65 and 96 blocks, then two
+    launches."""
+    rng = np.random.default_rng(n)
+    cur, prev = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
+    ref = np.asarray(oracle.latent_delta(cur, prev), np.float64)
+    ws = torch.randint(0, 256, (qc.qc_latent_delta_workspace_bytes(n),), dtype=torch.uint8, device="cuda")
+    for _ in range(4):
+        got = qc.latent_delta_t(dev(cur), dev(prev), workspace=ws).cpu().numpy()
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+
+
+@pytest.mark.parametrize("count", [1, 4, 5, 8])
+@pytest.mark.parametrize("n", [32 * 2048 + 3, 1 << 17, (1 << 17) + 1])
+def test_variation_on_both_sides_of_its_one_launch_form(n, count):
+    rng = np.random.default_rng(n + count)
+    cur, prevs = rng.standard_normal(n).astype(np.float32), [rng.standard_normal(n).astype(np.float32) for _ in range(count)]
+    ref = np.asarray(oracle.cumulative_variation(cur, prevs), np.float64)
+    ws = torch.randint(0, 256, (qc.qc_cumulative_variation_workspace_bytes(n, count),), dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        got = qc.cumulative_variation_t(dev(cur), [dev(p) for p in prevs], workspace=ws).cpu().numpy()
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+
+
 def test_reductions_into_their_own_workspace():
     """Outputs inside the workspace, at its start or at the check word of a block's record, are what
     outputs elsewhere are: no block may spoil a check that is an output by then.  (The two forms add the
