@@ -376,8 +376,8 @@ def qc_prune_probability(S, tau_low, tau_high, p_base) -> float:
 
 # What the tensor helpers cost on the host decides how long the small calls take, so the module is
 # looked up once, the stream is read as a number instead of through a Stream object, and the helpers
-# of the per-step calls go to the C entry directly: the linear of 2 tokens 8.95 -> 6.22 us.  Where torch is
-# imported before this module they are replaced by native ones (end of this file).
+# of the per-step calls go to the C entry directly: the linear of 2 tokens 8.95 -> 6.22 us.  Once torch is
+# there they are replaced by native ones (end of this file).
 _torch_module = None
 
 
@@ -386,6 +386,7 @@ def _torch():
     if _torch_module is None:
         import torch
         _torch_module = torch
+        _use_native_helpers()
     return _torch_module
 
 
@@ -687,11 +688,15 @@ def _entries():
     return tuple(ctypes.cast(getattr(lib(), n), ctypes.c_void_p).value for n in names)
 
 
+_python_helpers = {}   # those replaced
+
+
 def _use_native_helpers() -> None:
     """Replace the per-step helpers by those of _qc_torch (csrc/qc_torch.cpp), which do the same and hand what is
-    out of the ordinary to the ones above.  The module is linked against torch's libraries, so it is left alone
-    where torch has not been imported; where it is not built the helpers above serve."""
-    if "torch" not in sys.modules:
+    out of the ordinary to the ones above.  The module is linked against torch's libraries, so this waits until
+    torch has been imported, before this module or by the first helper that is called; where it is
+    not built the helpers above serve."""
+    if _python_helpers or "torch" not in sys.modules:
         return
     try:
         from . import _qc_torch
@@ -704,5 +709,4 @@ def _use_native_helpers() -> None:
         helpers[n] = getattr(_qc_torch, n)
 
 
-_python_helpers = {}   # those replaced
 _use_native_helpers()

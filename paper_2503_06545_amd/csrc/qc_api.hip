@@ -145,6 +145,14 @@ qc_status qlinear_quant_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, A
                                           (hipStream_t)stream));
 }
 
+// Whether quantization and GEMM go out as one launch.  Y may lie over X: in two launches X has been read when the
+// GEMM writes; in one launch the blocks that write Y run beside others that still read X.
+bool one_launch(const void *X, qc_dtype xdt, const void *Y, qc_out ydt, int64_t M, int64_t K, int64_t N, QuantScheme scheme) {
+    const size_t x_bytes = (size_t)M * (size_t)K * (xdt == QC_BF16 ? 2 : 4);
+    const size_t y_bytes = (size_t)M * (size_t)N * (ydt == QC_OUT_BF16 ? 2 : 4);
+    return qlinear_small_chosen(M, N, K, xdt, scheme) && !overlap(X, x_bytes, Y, y_bytes);
+}
+
 qc_status qlinear_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, ActQuant how,
                       const void *packed, const float *w_scale, int bits, int64_t N,
                       const float *bias, qc_epilogue epi, void *Y, qc_out ydt, void *workspace,
@@ -157,15 +165,12 @@ qc_status qlinear_any(const void *X, qc_dtype xdt, int64_t M, int64_t K, ActQuan
     QC_TRY(check_gemm_supported(M, K, N, bits));
     const ActWorkspace ws = act_workspace(M, K);
     if (workspace_bytes < ws.total_bytes) return QC_ERR_WORKSPACE;
-    // Y may lie over X: in two launches X has been read when the GEMM writes.  In one launch the blocks
-    // that write Y run beside others that still read X.
-    const size_t x_bytes = (size_t)M * (size_t)K * (xdt == QC_BF16 ? 2 : 4);
-    const size_t y_bytes = (size_t)M * (size_t)N * (ydt == QC_OUT_BF16 ? 2 : 4);
-    if (how.rot_block == 0 && qlinear_small_chosen(M, N, K) && !overlap(X, x_bytes, Y, y_bytes)) {
+    const QuantScheme scheme = how.rot_block ? kQuantRotated : kQuantToken;
+    if (one_launch(X, xdt, Y, ydt, M, K, N, scheme)) {
         uint8_t *base = (uint8_t *)workspace;
-        return device_status(launch_qlinear_small(X, xdt, base + ws.scale_bytes, (float *)base,
-                                                  (const uint8_t *)packed, w_scale, bias, Y, M, N, K,
-                                                  how.act_bits, bits, epi, ydt, (hipStream_t)stream));
+        return device_status(launch_qlinear_small(X, xdt, base + ws.scale_bytes, (float *)base, nullptr,
+                                                  (const uint8_t *)packed, w_scale, nullptr, bias, Y, M, N, K, scheme,
+                                                  how.act_bits, how.rot_block, bits, epi, ydt, (hipStream_t)stream));
     }
     QC_TRY(qlinear_quant_any(X, xdt, M, K, how, workspace, workspace_bytes, stream));
     return qc_qlinear_gemm(workspace, workspace_bytes, M, K, packed, w_scale, bits, N, bias, epi, Y,
@@ -322,6 +327,13 @@ extern "C" qc_status qc_qlinear_asym(const void *X, qc_dtype xdt, int64_t M, int
     QC_TRY(check_quant_supported(M, K, act_bits, true, 0));
     QC_TRY(check_gemm_supported(M, K, N, bits));
     if (workspace_bytes < act_workspace_asym(M, K).total_bytes) return QC_ERR_WORKSPACE;
+    if (one_launch(X, xdt, Y, ydt, M, K, N, kQuantAsym)) {
+        const ActWorkspaceAsym ws = act_workspace_asym(M, K);
+        uint8_t *base = (uint8_t *)workspace;
+        return device_status(launch_qlinear_small(X, xdt, base + ws.codes_offset, (float *)base, (float *)(base + ws.corr_offset),
+                                                  (const uint8_t *)packed, w_scale, w_row_sums, bias, Y, M, N, K, kQuantAsym,
+                                                  act_bits, 0, bits, epi, ydt, (hipStream_t)stream));
+    }
     QC_TRY(qc_qlinear_asym_quant(X, xdt, M, K, act_bits, workspace, workspace_bytes, stream));
     return qc_qlinear_asym_gemm(workspace, workspace_bytes, M, K, packed, w_scale, w_row_sums, bits,
                                 N, bias, epi, Y, ydt, stream);
@@ -366,6 +378,10 @@ extern "C" qc_status qc_qlinear_tensor(const void *X, qc_dtype xdt, int64_t M, i
     // [ the workspace of qc_qlinear ][ slab maxima ]: the first part is what qc_qlinear_gemm and
     // qc_debug_workspace_act read, with the one scale repeated for every token
     uint8_t *base = (uint8_t *)workspace;
+    if (one_launch(X, xdt, Y, ydt, M, K, N, kQuantTensor))
+        return device_status(launch_qlinear_small(X, xdt, base + ws.scale_bytes, (float *)base, nullptr,
+                                                  (const uint8_t *)packed, w_scale, nullptr, bias, Y, M, N, K, kQuantTensor,
+                                                  act_bits, 0, bits, epi, ydt, (hipStream_t)stream));
     QC_TRY(device_status(launch_quant_act_tensor(X, xdt, M, K, nullptr, base + ws.scale_bytes, ws.KF,
                                                  (float *)base, false,
                                                  (float *)(base + ws.total_bytes), act_bits,

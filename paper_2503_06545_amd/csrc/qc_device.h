@@ -82,6 +82,11 @@ template <int CTRL>
 __device__ inline float dpp_max(float v) {
     return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false)));
 }
+template <int CTRL>
+__device__ inline float dpp_min(float v) {
+    return fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false)));
+}
+__device__ inline float min_of_eight(float v) { return dpp_min<0x141>(dpp_min<0x4E>(dpp_min<0xB1>(v))); }
 // the maximum of eight consecutive lanes, in each of them (quad_perm [1, 0, 3, 2], [2, 3, 0, 1], row_half_mirror)
 __device__ inline float max_of_eight(float v) { return dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(v))); }
 
@@ -263,6 +268,104 @@ __device__ inline uint32_t codes4(float q0, float q1, float q2, float q3) {
 }
 
 __device__ inline float scale_of(float absmax, float qmax) { return fmaxf(absmax, kAbsmaxFloor) / qmax; }
+
+// Four quotients of the asymmetric quantizer -> four bytes in one dword: clamp(rne(q) + off, cmin, cmax).
+__device__ inline uint32_t asym_codes4(float q0, float q1, float q2, float q3, float off, float cmin, float cmax) {
+    const float magic = 12582912.0f;  // 1.5 * 2^23: the sum's low byte is the integer's low byte
+    const float q[4] = {q0, q1, q2, q3};
+    uint32_t y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = __float_as_uint(__builtin_amdgcn_fmed3f(rintf(q[e]) + off, cmin, cmax) + magic);
+    return __builtin_amdgcn_perm(y[1], y[0], 0x0c0c0400u) | __builtin_amdgcn_perm(y[3], y[2], 0x04000c0cu);
+}
+
+// ---- rotation of a group of 128 columns (Section 3.2 AIGQ (1)) ------------------------------------
+// Each block of `rot` consecutive columns (16, 32, 64 or 128) is multiplied by the Walsh-Hadamard
+// matrix of that size before the absmax and the cast, as a butterfly network in binary32 with
+// the strides in ascending order: one rounding per output and stage, so the bits do not depend
+// on which lane does which butterfly.  The rows are loaded as in quant_rows_kernel, whole lines per
+// instruction, so a group of 128 columns lies over eight lanes in pieces of E = 16 B: the strides below
+// E and those of 8 E or more are butterflies between a lane's own values, the three between them pair
+// lanes.
+//
+// A butterfly across lanes is one v_fmac_f32 with a DPP operand: own + sign * other.  It leaves the
+// upper lane of a pair with minus its output, which every later stage carries along unchanged; the
+// quotient takes the sign out again, because x / s and (-x) / (-s) are the same operations on the same
+// magnitudes.  DPP reaches lanes sub ^ 1, ^ 2 and ^ 7 in one move, not ^ 4; so the lane takes the piece
+// `label` of the eight, which differs in bit 2 alone between lanes sub and sub ^ 7.
+// 65536 x 1152 bf16, blocks of 128, with a move and an fma (two moves for the third stage) and 16
+// consecutive columns a lane: 52.7 us; this form 38.3 (binary32 72.1 and 60.0).
+// (One asm block per stage: the compiler leaves the DPP move and the fma apart.  A DPP operand may be read two
+// wait states after a VALU instruction has written it, hence the s_nop; inside the block no
+// instruction reads what another has written.)
+#define QC_BUTTERFLY(i, how) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " how " row_mask:0xf bank_mask:0xf\n\t"
+#define QC_BUTTERFLIES(f, sign, how)                                                                          \
+    asm volatile("s_nop 1\n\t"                                                                               \
+        QC_BUTTERFLY(0, how) QC_BUTTERFLY(1, how) QC_BUTTERFLY(2, how) QC_BUTTERFLY(3, how)                   \
+        QC_BUTTERFLY(4, how) QC_BUTTERFLY(5, how) QC_BUTTERFLY(6, how) QC_BUTTERFLY(7, how)                   \
+        QC_BUTTERFLY(8, how) QC_BUTTERFLY(9, how) QC_BUTTERFLY(10, how) QC_BUTTERFLY(11, how)                 \
+        QC_BUTTERFLY(12, how) QC_BUTTERFLY(13, how) QC_BUTTERFLY(14, how) QC_BUTTERFLY(15, how)               \
+        : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]),     \
+          "+v"(f[8]), "+v"(f[9]), "+v"(f[10]), "+v"(f[11]), "+v"(f[12]), "+v"(f[13]), "+v"(f[14]), "+v"(f[15]) \
+        : "v"(sign))
+static_assert(kUnit == 16, "a stage's elements are written out");
+__device__ inline void butterflies_xor1(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "quad_perm:[1,0,3,2]"); }
+__device__ inline void butterflies_xor2(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "quad_perm:[2,3,0,1]"); }
+__device__ inline void butterflies_xor7(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "row_half_mirror"); }
+#undef QC_BUTTERFLIES
+#undef QC_BUTTERFLY
+
+// Lane sub's piece of the eight, which the rotated forms use in the place of sub.
+__device__ inline int rotation_label(int sub) { return sub < 4 ? sub : sub ^ 3; }
+
+template <typename XT>
+struct Rotation {
+    static constexpr int E = 16 / (int)sizeof(XT);   // consecutive columns of a lane's pieces
+    int rot, label;
+    float sg1, sg2, sg4;
+    __device__ Rotation(int rot_, int label_)
+        : rot(rot_), label(label_), sg1(label_ & 1 ? -1.0f : 1.0f), sg2(label_ & 2 ? -1.0f : 1.0f), sg4(label_ & 4 ? -1.0f : 1.0f) {}
+    static __device__ void own_lane(float (&f)[kUnit], int h) {   // butterflies between elements h apart
+#pragma unroll
+        for (int j = 0; j < kUnit; ++j)
+            if ((j & h) == 0) {
+                const float lo = f[j], hi = f[j + h];
+                f[j] = lo + hi;
+                f[j + h] = lo - hi;
+            }
+    }
+    // f: the group's columns col0 .. of a row of K, widened.  Columns past the row's end, whole blocks of them, are
+    // not the row's last piece again, as loaded, but zeros.
+    __device__ void apply(float (&f)[kUnit], int col0, int K) const {
+        if (col0 + 128 > K) {
+#pragma unroll
+            for (int e = 0; e < kUnit; ++e)
+                if (col0 + e / E * (8 * E) + E * label >= K) f[e] = 0.0f;
+        }
+        own_lane(f, 1);
+        own_lane(f, 2);
+        if constexpr (E == 8) {   // strides 1 2 4 | 8 16 32 | 64
+            own_lane(f, 4);
+            butterflies_xor1(f, sg1);
+            if (rot >= 32) butterflies_xor2(f, sg2);
+            if (rot >= 64) butterflies_xor7(f, sg4);
+            if (rot >= 128) own_lane(f, 8);
+        } else {                  // strides 1 2 | 4 8 16 | 32 64
+            butterflies_xor1(f, sg1);
+            butterflies_xor2(f, sg2);
+            if (rot >= 32) butterflies_xor7(f, sg4);
+            if (rot >= 64) own_lane(f, 4);
+            if (rot >= 128) own_lane(f, 8);
+        }
+    }
+    // minus for the lanes that an odd number of the stages across lanes has negated
+    __device__ float sign() const {
+        float sign = sg1;
+        if (rot >= 32 || E == 4) sign *= sg2;
+        if (rot >= (E == 8 ? 64 : 32)) sign *= sg4;
+        return sign;
+    }
+};
 
 __device__ inline float gelu_tanh_f(float y) {
     // 0.5 y (1 + tanh(u)) = y / (1 + exp(-2u)),  u = sqrt(2/pi) (y + 0.044715 y^3)

@@ -252,11 +252,14 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
                              const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                              int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
                              const int32_t *w_rowsum, hipStream_t stream);
-bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K);
-hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale,
-                                const uint8_t *w_packed, const float *w_scale, const float *bias, void *Y,
-                                int64_t M, int64_t N, int64_t K, int act_bits, int bits, qc_epilogue epi,
-                                qc_out ydt, hipStream_t stream);
+// how a linear quantizes its activations
+enum QuantScheme { kQuantToken = 0, kQuantRotated = 1, kQuantAsym = 2, kQuantTensor = 3 };
+bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K, qc_dtype xdt, QuantScheme scheme);
+// x_corr, w_rowsum: asymmetric only; rot_block: rotated only
+hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale, float *x_corr,
+                                const uint8_t *w_packed, const float *w_scale, const int32_t *w_rowsum, const float *bias,
+                                void *Y, int64_t M, int64_t N, int64_t K, QuantScheme scheme, int act_bits, int rot_block,
+                                int bits, qc_epilogue epi, qc_out ydt, hipStream_t stream);
 
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,

@@ -222,50 +222,15 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
 
 // ---- rotation fused into the quantization (Section 3.2 AIGQ (1); Section 4.1 "Hardware
 // Implementation") -----------------------------------------------------------------------------
-// Each block of `rot` consecutive columns (16, 32, 64 or 128) is multiplied by the Walsh-Hadamard
-// matrix of that size before the absmax and the cast, as a butterfly network in binary32 with
-// the strides in ascending order: one rounding per output and stage, so the bits do not depend
-// on which lane does which butterfly.  The rows are loaded as in quant_rows_kernel, whole lines per
-// instruction, so a group of 128 columns lies over eight lanes in pieces of E = 16 B: the strides below
-// E and those of 8 E or more are butterflies between a lane's own values, the three between them pair
-// lanes.
-//
-// A butterfly across lanes is one v_fmac_f32 with a DPP operand: own + sign * other.  It leaves the
-// upper lane of a pair with minus its output, which every later stage carries along unchanged; the
-// quotient takes the sign out again, because x / s and (-x) / (-s) are the same operations on the same
-// magnitudes.  DPP reaches lanes sub ^ 1, ^ 2 and ^ 7 in one move, not ^ 4; so the lane takes the piece
-// `label` of the eight, which differs in bit 2 alone between lanes sub and sub ^ 7.
-// 65536 x 1152 bf16, blocks of 128, with a move and an fma (two moves for the third stage) and 16
-// consecutive columns a lane: 52.7 us; this form 38.3 (binary32 72.1 and 60.0).
-// (One asm block per stage: the compiler leaves the DPP move and the fma apart.  A DPP operand may be read two
-// wait states after a VALU instruction has written it, hence the s_nop; inside the block no
-// instruction reads what another has written.)
-#define QC_BUTTERFLY(i, how) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " how " row_mask:0xf bank_mask:0xf\n\t"
-#define QC_BUTTERFLIES(f, sign, how)                                                                          \
-    asm volatile("s_nop 1\n\t"                                                                               \
-        QC_BUTTERFLY(0, how) QC_BUTTERFLY(1, how) QC_BUTTERFLY(2, how) QC_BUTTERFLY(3, how)                   \
-        QC_BUTTERFLY(4, how) QC_BUTTERFLY(5, how) QC_BUTTERFLY(6, how) QC_BUTTERFLY(7, how)                   \
-        QC_BUTTERFLY(8, how) QC_BUTTERFLY(9, how) QC_BUTTERFLY(10, how) QC_BUTTERFLY(11, how)                 \
-        QC_BUTTERFLY(12, how) QC_BUTTERFLY(13, how) QC_BUTTERFLY(14, how) QC_BUTTERFLY(15, how)               \
-        : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]),     \
-          "+v"(f[8]), "+v"(f[9]), "+v"(f[10]), "+v"(f[11]), "+v"(f[12]), "+v"(f[13]), "+v"(f[14]), "+v"(f[15]) \
-        : "v"(sign))
-static_assert(kUnit == 16, "a stage's elements are written out");
-__device__ inline void butterflies_xor1(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "quad_perm:[1,0,3,2]"); }
-__device__ inline void butterflies_xor2(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "quad_perm:[2,3,0,1]"); }
-__device__ inline void butterflies_xor7(float (&f)[kUnit], float sign) { QC_BUTTERFLIES(f, sign, "row_half_mirror"); }
-#undef QC_BUTTERFLIES
-#undef QC_BUTTERFLY
-
+// see rotate_group() (qc_device.h)
 template <typename XT, int POLICY, int UPT>
 __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     const XT *__restrict__ X, int64_t M, int64_t K, int8_t *__restrict__ qx,
     uint8_t *__restrict__ qx_tiled, int64_t KF, float *__restrict__ x_scale, float qmax, int rot) {
     __shared__ float slice_max[kMaxSlices<UPT>][kRowsPerBlock];
-    constexpr int E = 16 / (int)sizeof(XT);   // consecutive columns of a lane's pieces
     const int lane = threadIdx.x & 63, slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slices = blockDim.x >> 6;
     const int sub = lane % kLanesPerRow, row_in_block = lane / kLanesPerRow;
-    const int label = sub < 4 ? sub : sub ^ 3;
+    const int label = rotation_label(sub);
     const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + row_in_block;
     const int units = (int)(K / kUnit);
     const bool live = row < M;
@@ -276,42 +241,14 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     for (int i = 0; i < UPT; ++i)
         u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, label);
 
-    const float sg1 = (label & 1) ? -1.0f : 1.0f, sg2 = (label & 2) ? -1.0f : 1.0f, sg4 = (label & 4) ? -1.0f : 1.0f;
+    const Rotation<XT> rotation(rot, label);
     float f[UPT][kUnit];
     float a = 0.0f;
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) f[i][e] = u[i].get(e);
-        if ((slice * UPT + i + 1) * kGroup > (int)K) {   // columns past the row's end, whole blocks of them: not its last piece again, but zeros
-#pragma unroll
-            for (int e = 0; e < kUnit; ++e)
-                if ((slice * UPT + i) * kGroup + e / E * (kLanesPerRow * E) + E * label >= (int)K) f[i][e] = 0.0f;
-        }
-        auto own_lane = [&](int h) {   // butterflies between elements h apart
-#pragma unroll
-            for (int j = 0; j < kUnit; ++j)
-                if ((j & h) == 0) {
-                    const float lo = f[i][j], hi = f[i][j + h];
-                    f[i][j] = lo + hi;
-                    f[i][j + h] = lo - hi;
-                }
-        };
-        own_lane(1);
-        own_lane(2);
-        if constexpr (E == 8) {   // strides 1 2 4 | 8 16 32 | 64
-            own_lane(4);
-            butterflies_xor1(f[i], sg1);
-            if (rot >= 32) butterflies_xor2(f[i], sg2);
-            if (rot >= 64) butterflies_xor7(f[i], sg4);
-            if (rot >= 128) own_lane(8);
-        } else {                  // strides 1 2 | 4 8 16 | 32 64
-            butterflies_xor1(f[i], sg1);
-            butterflies_xor2(f[i], sg2);
-            if (rot >= 32) butterflies_xor7(f[i], sg4);
-            if (rot >= 64) own_lane(4);
-            if (rot >= 128) own_lane(8);
-        }
+        rotation.apply(f[i], (slice * UPT + i) * kGroup, (int)K);
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) a = fmaxf(a, fabsf(f[i][e]));
     }
@@ -326,10 +263,7 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     const float r = 1.0f / s;  // correctly rounded
     if (live && sub == 0 && slice == 0) x_scale[row] = s;
     if (!live) return;
-    // minus for the lanes that an odd number of the stages across lanes has negated
-    float sign = sg1;
-    if (rot >= 32 || E == 4) sign *= sg2;
-    if (rot >= (E == 8 ? 64 : 32)) sign *= sg4;
+    const float sign = rotation.sign();
     const float ss = sign * s, sr = sign * r;
 
     int8_t *out_rows = qx ? qx + row * K : nullptr;
@@ -386,11 +320,8 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_asym_kernel(
             hi = fmaxf(hi, u[i].get(e));
         }
     }
-#pragma unroll
-    for (int d = 1; d < kLanesPerRow; d <<= 1) {
-        lo = fminf(lo, __shfl_xor(lo, d));
-        hi = fmaxf(hi, __shfl_xor(hi, d));
-    }
+    lo = min_of_eight(lo);
+    hi = max_of_eight(hi);
     if (slices > 1) {  // uniform over the block
         if (sub == 0) { slice_lo[slice][row_in_block] = lo; slice_hi[slice][row_in_block] = hi; }
         __syncthreads();
@@ -411,7 +342,6 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_asym_kernel(
     // clamp(rne(q) + z, 0, levels) - shift = clamp(rne(q) + (z - shift), -shift, levels - shift)
     const float off = shifted ? z - shift : z;
     const float cmin = shifted ? -shift : 0.0f, cmax = shifted ? levels - shift : levels;
-    const float magic = 12582912.0f;  // 1.5 * 2^23: the sum's low byte is the integer's low byte
 
     uint8_t *out_rows = qx ? qx + row * K : nullptr;
     uint8_t *out_tiled = qx_tiled ? qx_tiled + act_frag_offset(row, 0, KF) : nullptr;
@@ -422,13 +352,8 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_asym_kernel(
         uint32_t w[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            uint32_t y[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = rintf(quotient(u[i].get(4 * d + e), s, r)) + off;
-                y[e] = __float_as_uint(__builtin_amdgcn_fmed3f(v, cmin, cmax) + magic);
-            }
-            w[d] = __builtin_amdgcn_perm(y[1], y[0], 0x0c0c0400u) | __builtin_amdgcn_perm(y[3], y[2], 0x04000c0cu);
+            w[d] = asym_codes4(quotient(u[i].get(4 * d + 0), s, r), quotient(u[i].get(4 * d + 1), s, r),
+                               quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r), off, cmin, cmax);
         }
         const uint4 out = Group<XT>::gather_codes(w, sub);
         const int ui = ui0 + Group<XT>::unit_of(sub);

@@ -9,7 +9,7 @@
 // CU is taken: a second block on a CU only adds to what the CU has to load, and a single CU gets
 // about 35 B/clk from beyond its L2 (every launch starts with that L2 invalid).
 //
-// fused_kernel: for per-token quantization the whole linear is one launch: each block quantizes its token tile into
+// fused_kernel: the whole linear is one launch: each block quantizes its token tile into
 // LDS itself, redundantly over the channel tiles (that is cheap while there are few tokens in a tile), and the blocks
 // of the first channel tile leave codes and scales in the workspace as the two-launch path does.
 //
@@ -34,7 +34,7 @@ struct SmallArgs {
     const void *X;          // fused_kernel: the activations
     uint8_t *x_tiled;       // the workspace's codes: read (small_kernel) or written (fused_kernel)
     float *x_scale;
-    const float *x_corr;    // asymmetric activations only, with w_rowsum
+    float *x_corr;          // asymmetric activations only, with w_rowsum: read (small_kernel) or written
     const int32_t *w_rowsum;
     const uint8_t *w_codes;
     const float *w_scale;
@@ -44,8 +44,8 @@ struct SmallArgs {
     int KF, m_tiles, n_tiles;
     int rows, groups;       // fused_kernel: rows of a tile that can be live, groups of 128 columns in a row
     uint32_t inv_groups;    // 2^20 / groups, rounded up
-    float qmax;
-    int epi, out;
+    float qmax, shift;      // fused_kernel: largest code; asymmetric: largest unsigned one and what is subtracted from it
+    int rot, epi, out;
 };
 
 // partial sums of small_kernel in LDS: WK x TM x kLd int32
@@ -272,32 +272,41 @@ constexpr int kStepsMost = 3;   // of 8 pairs per wavefront and step
 // the quarters a row's units go to fall into different banks
 __host__ __device__ inline int quarter_stride(int rows) { return 16 * rows + 16; }
 
-// LDS: [ row maxima: TM ][ token scales: TM ][ their reciprocals: TM ][ partial sums: WK x TM x kLd int32 ][ codes ]
+// a float as a number that orders like it, and back
+__device__ inline uint32_t ordered(float v) {
+    const uint32_t b = __float_as_uint(v);
+    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+}
+__device__ inline float from_ordered(uint32_t u) { return __uint_as_float(u ^ (((u >> 31) - 1) | 0x80000000u)); }
+
+// LDS: [ row maxima: TM ][ row minima: TM ][ token scales: TM ][ their reciprocals: TM ][ corrections: TM ]
+// [ partial sums: WK x TM x kLd int32 ][ codes ]
 template <int MI, int NF, int WAVES>
 struct FusedLayout {
     static constexpr int kTM = 16 * MI;
     static constexpr int kWN = NF / 2, kWK = WAVES / kWN;
     static constexpr int kLt = 20;              // between the columns of two fragments
     static constexpr int kLd = NF * kLt + 4;    // four rows 16 banks apart
-    static constexpr int kSumsAt = 3 * kTM * 4;
+    static constexpr int kSumsAt = 5 * kTM * 4;
     static constexpr int kCodesAt = kSumsAt + kWK * kTM * kLd * 4;
 };
 
-template <int BITS, typename XT, int MI, int NF, int WAVES, int STEPS>
+template <int BITS, typename XT, int MI, int NF, int WAVES, int STEPS, int SCHEME>
 __global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
     using L = FusedLayout<MI, NF, WAVES>;
     constexpr int TM = L::kTM, WK = L::kWK, kPairs = 8 * WAVES;   // pairs cast per step
     constexpr int NW = BITS == 8 ? 2 : 1;       // 1 KiB weight pieces per stage and wavefront
-    constexpr int D = WK == 16 ? 2 : WK == 8 ? 3 : 5;   // stages in flight: all of K = 1152
+    constexpr int D = WK == 16 ? 2 : WK == 8 ? 3 : SCHEME == kQuantToken ? 5 : 4;   // stages in flight: all of K = 1152, or what registers allow
     constexpr int kStageBytes = BITS == 8 ? 8192 : 4096;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     uint32_t *const row_max = reinterpret_cast<uint32_t *>(lds);
-    float *const lds_s = reinterpret_cast<float *>(lds) + TM, *const lds_r = lds_s + TM;
+    uint32_t *const row_min = row_max + TM;
+    float *const lds_s = reinterpret_cast<float *>(lds) + 2 * TM, *const lds_r = lds_s + TM, *const lds_c = lds_r + TM;
     int *const sums = reinterpret_cast<int *>(lds + L::kSumsAt);
     uint8_t *const codes = lds + L::kCodesAt;
     // all arguments in one go: fetched where they are first needed, they are three round trips
     asm volatile("" ::"s"(a.X), "s"(a.x_tiled), "s"(a.x_scale), "s"(a.w_codes), "s"(a.w_scale), "s"(a.bias), "s"(a.Y), "s"(a.M),
-                 "s"(a.N), "s"(a.K), "s"(a.KF), "s"(a.m_tiles), "s"(a.n_tiles), "s"(a.rows), "s"(a.groups), "s"(a.inv_groups), "s"(a.qmax), "s"(a.epi), "s"(a.out));
+                 "s"(a.N), "s"(a.K), "s"(a.KF), "s"(a.m_tiles), "s"(a.n_tiles), "s"(a.rows), "s"(a.groups), "s"(a.inv_groups), "s"(a.qmax), "s"(a.epi), "s"(a.out), "s"(a.rot), "s"(a.shift), "s"(a.x_corr), "s"(a.w_rowsum));
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -312,10 +321,13 @@ __global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
     const int64_t m0 = (int64_t)mt * TM;
     const int G = nt / (8 / NF), t0 = nt % (8 / NF) * NF;
     if ((int64_t)G * kTileN + t0 >= a.N) return;   // no live channel in this tile
-    if (tid < TM) row_max[tid] = 0;
+    if (tid < TM) {
+        row_max[tid] = 0;
+        if (SCHEME == kQuantAsym) row_min[tid] = 0xffffffffu;
+    }
 
     const int K = (int)a.K, KF = a.KF, pairs = a.rows * a.groups;
-    const int sub = lane & 7, p0 = tid >> 3;
+    const int sub = lane & 7, p0 = tid >> 3, piece = SCHEME == kQuantRotated ? rotation_label(sub) : sub;
     Group<XT> u[STEPS];
     int row[STEPS], col0[STEPS];
 #pragma unroll
@@ -326,7 +338,7 @@ __global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
         col0[i] = (p - row[i] * a.groups) * kGroup;
         const int64_t m = m0 + row[i] < a.M ? m0 + row[i] : a.M - 1;
         const XT *xrow = reinterpret_cast<const XT *>(a.X) + m * a.K;
-        u[i].load_ragged(xrow, col0[i], K, sub);
+        u[i].load_ragged(xrow, col0[i], K, piece);
     }
 
     // weights of this wavefront: stages wk, wk + WK, ..; a register ring of D of them
@@ -347,27 +359,101 @@ __global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
     const int64_t na = n0 < a.N ? n0 : a.N - 1, nb2 = n0 + 1 < a.N ? n0 + 1 : a.N - 1;
     float sw0 = a.w_scale[na], sw1 = a.w_scale[nb2], bs0 = 0.0f, bs1 = 0.0f;
     if (a.bias) { bs0 = a.bias[na]; bs1 = a.bias[nb2]; }
+    int rs0 = 0, rs1 = 0;
+    if (SCHEME == kQuantAsym) { rs0 = a.w_rowsum[na]; rs1 = a.w_rowsum[nb2]; }
 
     // the maximum of each row, over the lanes of its pairs
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the zeros above are there; the loads stay in flight
+    const Rotation<XT> rotation(a.rot, piece);
+    float f[SCHEME == kQuantRotated ? STEPS : 1][kUnit];
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
         if (i > 0 && wave * 8 + i * kPairs >= pairs) continue;
-        if (K % kUnit) u[i].settle_ragged(col0[i], K, sub);
-        auto running = Group<XT>::no_max();
-        u[i].absmax_into(running);
-        const float m = max_of_eight(Group<XT>::absmax_value(running));   // no NaN, not negative: ordered like its bits
-        if (sub == 0) atomicMax(row_max + row[i], __float_as_uint(m));
+        if (K % kUnit) u[i].settle_ragged(col0[i], K, piece);
+        if constexpr (SCHEME == kQuantAsym) {
+            float lo = __builtin_inff(), hi = -__builtin_inff();
+#pragma unroll
+            for (int e = 0; e < kUnit; ++e) {
+                lo = fminf(lo, u[i].get(e));
+                hi = fmaxf(hi, u[i].get(e));
+            }
+            lo = min_of_eight(lo);
+            hi = max_of_eight(hi);
+            if (sub == 0) {
+                atomicMin(row_min + row[i], ordered(lo));
+                atomicMax(row_max + row[i], ordered(hi));
+            }
+        } else {
+            float m = 0.0f;
+            if constexpr (SCHEME == kQuantRotated) {
+#pragma unroll
+                for (int e = 0; e < kUnit; ++e) f[i][e] = u[i].get(e);
+                rotation.apply(f[i], col0[i], K);
+#pragma unroll
+                for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(f[i][e]));
+            } else {
+                auto running = Group<XT>::no_max();
+                u[i].absmax_into(running);
+                m = Group<XT>::absmax_value(running);
+            }
+            m = max_of_eight(m);   // no NaN, not negative: ordered like its bits
+            if (sub == 0) atomicMax(row_max + (SCHEME == kQuantTensor ? 0 : row[i]), __float_as_uint(m));
+        }
+    }
+    if constexpr (SCHEME == kQuantTensor) {
+        if (a.m_tiles > 1) {   // the rows of the other tiles: every block reads the whole tensor
+            constexpr int kPer = 16 / (int)sizeof(XT);
+            const XT *const X = reinterpret_cast<const XT *>(a.X);
+            const int n = (int)(a.M * a.K), nv = n / kPer;
+            Bf16Max packed;
+            float m = 0.0f;
+            for (int base = tid; base < nv; base += 64 * WAVES * 4) {
+                uint4 piece4[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {   // past the end the last piece again: the same maximum
+                    const int at = base + 64 * WAVES * k;
+                    piece4[k] = reinterpret_cast<const uint4 *>(X)[at < nv ? at : nv - 1];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t word[4] = {piece4[k].x, piece4[k].y, piece4[k].z, piece4[k].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (sizeof(XT) == 2) packed.fold(word[e]);
+                        else m = fmaxf(m, fabsf(__uint_as_float(word[e])));
+                    }
+                }
+            }
+            if (tid < n - nv * kPer) {
+                if constexpr (sizeof(XT) == 2) m = fmaxf(m, fabsf(__uint_as_float((uint32_t)X[nv * kPer + tid] << 16)));
+                else m = fmaxf(m, fabsf(X[nv * kPer + tid]));
+            }
+            if constexpr (sizeof(XT) == 2) m = fmaxf(m, packed.value());
+            m = max_of_eight(m);
+            if (sub == 0) atomicMax(row_max, __float_as_uint(m));
+        }
     }
     __syncthreads();
     const bool first_tile = nt == 0;   // one block per token tile leaves codes and scales in the workspace
     float s1 = 0.0f, r1 = 0.0f;
-    if constexpr (STEPS > 1) {
+    if constexpr (STEPS > 1 || SCHEME != kQuantToken) {
         if (tid < a.rows) {
-            const float s = scale_of(__uint_as_float(row_max[tid]), a.qmax);
+            const bool keep = first_tile && m0 + tid < a.M;
+            float s, r;
+            if constexpr (SCHEME == kQuantAsym) {
+                const float lo = from_ordered(row_min[tid]), hi = from_ordered(row_max[tid]);
+                s = fmaxf(hi - lo, kAbsmaxFloor) / a.qmax;
+                r = 1.0f / s;   // correctly rounded
+                const float corr = a.shift - -rintf(quotient(lo, s, r));   // minus the zero point
+                lds_c[tid] = corr;
+                if (keep) a.x_corr[m0 + tid] = corr;
+            } else {
+                s = scale_of(__uint_as_float(row_max[SCHEME == kQuantTensor ? 0 : tid]), a.qmax);
+                r = 1.0f / s;   // correctly rounded
+            }
             lds_s[tid] = s;
-            lds_r[tid] = 1.0f / s;   // correctly rounded
-            if (first_tile && m0 + tid < a.M) a.x_scale[m0 + tid] = s;
+            lds_r[tid] = r;
+            if (keep) a.x_scale[m0 + tid] = s;
         }
         __syncthreads();
     } else {
@@ -382,14 +468,29 @@ __global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
         if (i > 0 && wave * 8 + i * kPairs >= pairs) continue;
-        const float s = STEPS > 1 ? lds_s[row[i]] : s1, r = STEPS > 1 ? lds_r[row[i]] : r1;
+        constexpr bool kTable = STEPS > 1 || SCHEME != kQuantToken;
+        float s = kTable ? lds_s[row[i]] : s1, r = kTable ? lds_r[row[i]] : r1;
         uint32_t q[4];
+        if constexpr (SCHEME == kQuantAsym) {
+            const float off = -lds_c[row[i]], cmin = -a.shift, cmax = a.qmax - a.shift;
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
-            q[d] = codes4(quotient(u[i].get(4 * d + 0), s, r), quotient(u[i].get(4 * d + 1), s, r),
-                          quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r));
-        const uint4 o = Group<XT>::gather_codes(q, sub);
-        const int ui = col0[i] / kUnit + Group<XT>::unit_of(sub);   // unit = quarter of a stage
+            for (int d = 0; d < 4; ++d)
+                q[d] = asym_codes4(quotient(u[i].get(4 * d + 0), s, r), quotient(u[i].get(4 * d + 1), s, r),
+                                   quotient(u[i].get(4 * d + 2), s, r), quotient(u[i].get(4 * d + 3), s, r), off, cmin, cmax);
+        } else {
+            if constexpr (SCHEME == kQuantRotated) {
+                const float sign = rotation.sign();
+                s *= sign;
+                r *= sign;
+            }
+            auto get = [&](int e) { return SCHEME == kQuantRotated ? f[SCHEME == kQuantRotated ? i : 0][e] : u[i].get(e); };
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+                q[d] = codes4(quotient(get(4 * d + 0), s, r), quotient(get(4 * d + 1), s, r),
+                              quotient(get(4 * d + 2), s, r), quotient(get(4 * d + 3), s, r));
+        }
+        const uint4 o = Group<XT>::gather_codes(q, piece);
+        const int ui = col0[i] / kUnit + Group<XT>::unit_of(piece);   // unit = quarter of a stage
         if (p0 + i * kPairs < pairs && ui * kUnit < K) {
             *reinterpret_cast<uint4 *>(codes + ui * qs + row[i] * 16) = o;
             if (first_tile && m0 + row[i] < a.M)
@@ -477,7 +578,12 @@ __global__ __launch_bounds__(64 * WAVES) void fused_kernel(SmallArgs a) {
             continue;
         }
         const float sx = lds_s[m];
-        float y[2] = {fmaf((float)raw0 * sx, sw0, bs0), fmaf((float)raw1 * sx, sw1, bs1)};
+        float f0 = (float)raw0, f1 = (float)raw1;
+        if constexpr (SCHEME == kQuantAsym) {
+            f0 = fmaf(lds_c[m], (float)rs0 * (BITS == 4 ? 16.0f : 1.0f), f0);
+            f1 = fmaf(lds_c[m], (float)rs1 * (BITS == 4 ? 16.0f : 1.0f), f1);
+        }
+        float y[2] = {fmaf(f0 * sx, sw0, bs0), fmaf(f1 * sx, sw1, bs1)};
         if (a.epi == QC_EPI_GELU_TANH) {
             y[0] = gelu_tanh_f(y[0]);
             y[1] = gelu_tanh_f(y[1]);
@@ -565,33 +671,41 @@ int pick_tile(int64_t M, int64_t N) {
 // wavefronts while each lane has at most three pairs of a row and a group to cast.  us in a graph, 8 and 16
 // wavefronts: 2 x 1152 x 6912 4.9 6.3, 64 x 1152 x 1152 5.2 6.1, 128 x 1152 x 1152 (16 x 64) 5.6 5.9, 200 x 640 x 1152
 // 4.8 5.8, 256 x 1152 x 1152 (16 x 128) 6.9 6.7.  Tiles of 32 tokens, two launches and one: 512 x 1152 x 1152
-// 10.9 9.8, 700 tokens 11.0 10.3, K = 1536, 600 tokens 11.2 12.1: up to nine groups a row.
-struct FusedShape { TileShape tile; int waves, pairs; };   // pairs: most pairs of a row and a group that it is taken for
-constexpr FusedShape kFusedShapes[] = {{{16, 32}, 8, 192}, {{16, 32}, 16, 384}, {{16, 64}, 8, 192},
-                                        {{16, 64}, 16, 384}, {{16, 128}, 16, 384}, {{32, 128}, 16, 288}};
+// 10.9 9.8, 700 tokens 11.0 10.3, K = 1536, 600 tokens 11.2 12.1: up to nine groups a row.  The other quantizers, in two
+// launches (one scale for the tensor: three) and one, rotated, asymmetric, tensor: 2 x 1152 x 6912 8.0 5.1, 7.7 5.0, 8.8
+// 4.8; 64 x 1152 x 1152 7.6 6.1, 7.3 5.8, 8.9 7.5; 256 x 1152 x 1152 10.1 7.2, 10.4 7.1.
+struct FusedShape { TileShape tile; int waves, pairs; bool all_schemes; };   // pairs: most pairs of a row and a group that it is taken for
+constexpr FusedShape kFusedShapes[] = {{{16, 32}, 8, 192, true},   {{16, 32}, 16, 384, false}, {{16, 64}, 8, 192, true},
+                                       {{16, 64}, 16, 384, false}, {{16, 128}, 16, 384, true}, {{32, 128}, 16, 288, false}};
 constexpr int kFusedShapeCount = 6;
-int pick_fused_shape(int64_t M, int64_t N, int64_t K) {
+constexpr int64_t kTensorMost = 320 << 10;   // bytes of X that every block may read for one scale for the tensor: 115 x 1152 x 3456 11.5 9.3 us
+int pick_fused_shape(int64_t M, int64_t N, int64_t K, size_t x_elem_bytes, QuantScheme scheme) {
     if (K < 8 || K > QC_MAX_K) return -1;   // a row of less than 16 B has no whole piece to load
-    for (int i = 0; i < kFusedShapeCount; ++i) {
+    if (scheme == kQuantAsym && !quant_vector_path(K)) return -1;
+    int tile = 0;   // the smallest that gives at most one block per CU
+    while (tile < kFusedShapeCount && !one_block_per_cu(M, N, kFusedShapes[tile].tile)) ++tile;
+    for (int i = tile; i < kFusedShapeCount; ++i) {
         const FusedShape &f = kFusedShapes[i];
-        if (!one_block_per_cu(M, N, f.tile)) continue;
+        if (f.tile.tokens != kFusedShapes[tile].tile.tokens || f.tile.channels != kFusedShapes[tile].tile.channels) break;
+        if (scheme != kQuantToken && !f.all_schemes) continue;
+        if (scheme == kQuantTensor && M > f.tile.tokens && M * K * (int64_t)x_elem_bytes > kTensorMost) continue;
         const int64_t rows = M < f.tile.tokens ? M : f.tile.tokens;
         if (rows * ((K + kGroup - 1) / kGroup) <= f.pairs) return i;
     }
     return -1;
 }
 
-template <int BITS, typename XT, int MI, int NF, int WAVES, int STEPS>
+template <int BITS, typename XT, int MI, int NF, int WAVES, int STEPS, int SCHEME>
 hipError_t launch_fused_steps(const SmallArgs &a, size_t lds, hipStream_t stream) {
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> asked{0};
-        if (hipError_t e = allow_lds((const void *)fused_kernel<BITS, XT, MI, NF, WAVES, STEPS>, asked); e != hipSuccess) return e;
+        if (hipError_t e = allow_lds((const void *)fused_kernel<BITS, XT, MI, NF, WAVES, STEPS, SCHEME>, asked); e != hipSuccess) return e;
     }
-    fused_kernel<BITS, XT, MI, NF, WAVES, STEPS><<<dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(64 * WAVES), lds, stream>>>(a);
+    fused_kernel<BITS, XT, MI, NF, WAVES, STEPS, SCHEME><<<dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(64 * WAVES), lds, stream>>>(a);
     return hipGetLastError();
 }
 
-template <int BITS, typename XT, int MI, int NF, int WAVES>
+template <int BITS, typename XT, int MI, int NF, int WAVES, int SCHEME>
 hipError_t launch_fused(SmallArgs a, hipStream_t stream) {
     using L = FusedLayout<MI, NF, WAVES>;
     a.m_tiles = (int)((a.M + L::kTM - 1) / L::kTM);
@@ -603,19 +717,36 @@ hipError_t launch_fused(SmallArgs a, hipStream_t stream) {
     // 96 KiB at most, with one row, and less than kLdsMost together with the sums
     const size_t lds = L::kCodesAt + (size_t)a.KF * 4 * quarter_stride(a.rows);
     if (lds > (size_t)kLdsMost) return hipErrorInvalidValue;
-    return a.rows * a.groups <= 8 * WAVES ? launch_fused_steps<BITS, XT, MI, NF, WAVES, 1>(a, lds, stream)
-                                          : launch_fused_steps<BITS, XT, MI, NF, WAVES, kStepsMost>(a, lds, stream);
+    if constexpr (SCHEME == kQuantToken) {   // (the others: three steps whatever the rows)
+        if (a.rows * a.groups <= 8 * WAVES) return launch_fused_steps<BITS, XT, MI, NF, WAVES, 1, SCHEME>(a, lds, stream);
+    }
+    return launch_fused_steps<BITS, XT, MI, NF, WAVES, kStepsMost, SCHEME>(a, lds, stream);
+}
+
+template <int BITS, typename XT, int SCHEME>
+hipError_t launch_fused_scheme(int shape, const SmallArgs &a, hipStream_t stream) {
+    switch (shape) {
+        case 0: return launch_fused<BITS, XT, 1, 2, 8, SCHEME>(a, stream);
+        case 2: return launch_fused<BITS, XT, 1, 4, 8, SCHEME>(a, stream);
+        case 4: return launch_fused<BITS, XT, 1, 8, 16, SCHEME>(a, stream);
+    }
+    if constexpr (SCHEME == kQuantToken) {
+        switch (shape) {
+            case 1: return launch_fused<BITS, XT, 1, 2, 16, SCHEME>(a, stream);
+            case 3: return launch_fused<BITS, XT, 1, 4, 16, SCHEME>(a, stream);
+            default: return launch_fused<BITS, XT, 2, 8, 16, SCHEME>(a, stream);
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int BITS, typename XT>
-hipError_t launch_fused_shape(int shape, const SmallArgs &a, hipStream_t stream) {
-    switch (shape) {
-        case 0: return launch_fused<BITS, XT, 1, 2, 8>(a, stream);
-        case 1: return launch_fused<BITS, XT, 1, 2, 16>(a, stream);
-        case 2: return launch_fused<BITS, XT, 1, 4, 8>(a, stream);
-        case 3: return launch_fused<BITS, XT, 1, 4, 16>(a, stream);
-        case 4: return launch_fused<BITS, XT, 1, 8, 16>(a, stream);
-        default: return launch_fused<BITS, XT, 2, 8, 16>(a, stream);
+hipError_t launch_fused_shape(int shape, QuantScheme scheme, const SmallArgs &a, hipStream_t stream) {
+    switch (scheme) {
+        case kQuantToken: return launch_fused_scheme<BITS, XT, kQuantToken>(shape, a, stream);
+        case kQuantRotated: return launch_fused_scheme<BITS, XT, kQuantRotated>(shape, a, stream);
+        case kQuantAsym: return launch_fused_scheme<BITS, XT, kQuantAsym>(shape, a, stream);
+        default: return launch_fused_scheme<BITS, XT, kQuantTensor>(shape, a, stream);
     }
 }
 
@@ -650,25 +781,32 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
     SmallArgs a = small_args(const_cast<uint8_t *>(x_tiled), const_cast<float *>(x_scale), w_packed, w_scale,
                              bias, Y, M, N, K, epi, ydt);   // kCodes reads both
     if (x_corr && w_rowsum) {
-        a.x_corr = x_corr;
+        a.x_corr = const_cast<float *>(x_corr);
         a.w_rowsum = w_rowsum;
     }
     return bits == 8 ? launch_bits<8>(tile, a, stream) : launch_bits<4>(tile, a, stream);
 }
 
-bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K) { return pick_fused_shape(M, N, K) >= 0; }
+bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K, qc_dtype xdt, QuantScheme scheme) {
+    return pick_fused_shape(M, N, K, xdt == QC_BF16 ? 2 : 4, scheme) >= 0;
+}
 
-hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale,
-                                const uint8_t *w_packed, const float *w_scale, const float *bias, void *Y,
-                                int64_t M, int64_t N, int64_t K, int act_bits, int bits, qc_epilogue epi,
-                                qc_out ydt, hipStream_t stream) {
-    const int shape = pick_fused_shape(M, N, K);
+hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale, float *x_corr,
+                                const uint8_t *w_packed, const float *w_scale, const int32_t *w_rowsum, const float *bias,
+                                void *Y, int64_t M, int64_t N, int64_t K, QuantScheme scheme, int act_bits, int rot_block,
+                                int bits, qc_epilogue epi, qc_out ydt, hipStream_t stream) {
+    const int shape = pick_fused_shape(M, N, K, xdt == QC_BF16 ? 2 : 4, scheme);
     if (shape < 0) return hipErrorInvalidValue;
     SmallArgs a = small_args(x_tiled, x_scale, w_packed, w_scale, bias, Y, M, N, K, epi, ydt);
     a.X = X;
-    a.qmax = (float)((1 << (act_bits - 1)) - 1);
-    if (xdt == QC_BF16) return bits == 8 ? launch_fused_shape<8, uint16_t>(shape, a, stream) : launch_fused_shape<4, uint16_t>(shape, a, stream);
-    return bits == 8 ? launch_fused_shape<8, float>(shape, a, stream) : launch_fused_shape<4, float>(shape, a, stream);
+    a.x_corr = x_corr;
+    a.w_rowsum = w_rowsum;
+    a.qmax = (float)(scheme == kQuantAsym ? (1 << act_bits) - 1 : (1 << (act_bits - 1)) - 1);
+    a.shift = (float)asym_code_shift(act_bits);
+    a.rot = rot_block;
+    if (xdt == QC_BF16)
+        return bits == 8 ? launch_fused_shape<8, uint16_t>(shape, scheme, a, stream) : launch_fused_shape<4, uint16_t>(shape, scheme, a, stream);
+    return bits == 8 ? launch_fused_shape<8, float>(shape, scheme, a, stream) : launch_fused_shape<4, float>(shape, scheme, a, stream);
 }
 
 }  // namespace qc

@@ -120,6 +120,49 @@ def test_qlinear_in_one_launch_at_the_edges_of_its_shapes(M, K, N, bits):
     run_linear_case(random_x(rng, M, K, "f32"), W, None, bits, "none", "f32", act_bits=6)
 
 
+@pytest.mark.parametrize("scheme", ["token", "rot16", "rot32", "rot64", "rot128", "asym", "tensor"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,N,bits,act_bits", [
+    (1, 128, 33, 8, 8), (3, 384, 40, 4, 6), (16, 1536, 100, 8, 8), (16, 1664, 70, 4, 8), (13, 1152, 4099, 8, 4), (17, 1152, 2050, 4, 8),
+    (130, 640, 1282, 8, 6), (48, 2944, 2049, 8, 8), (256, 1152, 1153, 8, 8), (250, 3072, 1200, 4, 4), (300, 512, 1792, 8, 8), (64, 144, 1000, 8, 8)])
+def test_one_launch_and_two_are_the_same_for_every_quantizer(scheme, dtype, M, K, N, bits, act_bits):
+    """Codes, scales, corrections and outputs, bit for bit: a Y that begins in X's last bytes has the quantizer and
+    the GEMM go out one after the other."""
+    rot = int(scheme[3:]) if scheme.startswith("rot") else 0
+    if rot and K % rot:
+        rot = 16
+    rng = np.random.default_rng(M * 31 + K * 7 + N + act_bits)
+    x = dev(random_x(rng, M, K, dtype))
+    pw = qc.pack_weight_t(dev((rng.standard_normal((N, K)) * 0.02).astype(np.float32)), bits, rot)
+    bias, sums = dev((rng.standard_normal(N) * 0.01).astype(np.float32)), qc.weight_row_sums_t(pw)
+    make = {"asym": qc.qlinear_asym_workspace_t, "tensor": qc.qlinear_tensor_workspace_t}.get(scheme, qc.qlinear_workspace_t)
+
+    def call(X, Y, workspace, **kw):
+        if scheme == "asym":
+            return qc.qlinear_asym_t(X, pw, sums, bias, workspace=workspace, Y=Y, act_bits=act_bits, **kw)
+        if scheme == "tensor":
+            return qc.qlinear_tensor_t(X, pw, bias, workspace=workspace, Y=Y, act_bits=act_bits, **kw)
+        return qc.qlinear_t(X, pw, bias, workspace=workspace, Y=Y, act_bits=act_bits, rot_block=rot, **kw)
+
+    for out, t, epi in (("bf16", torch.bfloat16, "gelu_tanh"), ("f32", torch.float32, "none"), ("f32", torch.float32, "gelu_erf")):
+        got, left = [], []
+        for over in (False, True):
+            x_bytes = x.numel() * x.element_size()
+            at = (x_bytes + 15) // 16 * 16 - 16 if over else (x_bytes + 255) // 256 * 256
+            buf = torch.zeros(at + M * N * 4 + 256, dtype=torch.uint8, device="cuda")
+            X = buf[:x_bytes].view(x.dtype).view(M, K)
+            X.copy_(x)
+            Y = buf[at:at + M * N * torch.empty(0, dtype=t).element_size()].view(t).view(M, N)
+            ws = make(M, K, N)
+            ws.fill_(0x7f)
+            call(X, Y, ws, epi=epi, out=out)
+            got.append(Y.clone())
+            left.append(qc.debug_workspace_act_asym_t(ws, M, K, act_bits) if scheme == "asym" else qc.debug_workspace_act_t(ws, M, K))
+        assert torch.equal(*got)
+        for a, b in zip(*left):
+            assert torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a, b.view(torch.int32) if b.dtype == torch.float32 else b)
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("N", [129, 130, 132, 136])
 def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):

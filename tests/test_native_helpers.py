@@ -6,6 +6,7 @@ import torch
 
 from paper_2503_06545_amd import binding as qc
 
+qc._use_native_helpers()   # binding may have been imported before torch
 REPLACED = sorted(qc._python_helpers)
 
 
