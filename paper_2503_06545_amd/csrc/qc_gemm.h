@@ -33,6 +33,7 @@ struct GemmArgs {
     int group_m;    // token tiles per patch of the block -> tile map (ring kernel)
     bool resident;  // run the kernel that keeps the weight tile in LDS
     int height;     // ring kernel: 4, 3 or 2 blocks of 16 tokens per wavefront
+    bool split;     // ring kernel, height 4 or 2: two groups of wavefronts, half of the reduction each
     bool keep_output;  // ring kernel, f32 output: the kernel that stores through the caches
     bool stream_edges; // bf16 output: non-temporal stores also for rows and tiles that are not whole
 };

@@ -82,6 +82,23 @@ static int ring_height(int64_t M, int n_tiles, int64_t K, qc_epilogue epi) {
     return best;
 }
 
+// Tiles of which a CU gets one at most leave its SIMDs a wavefront each, which waits out every load, unpacking and
+// barrier on its own.  Eight wavefronts in two groups, each with half of the reduction, cover each other's waits and
+// add their sums up through LDS at the end, which the reduction has to be worth.  Ring kernel, and so, us:
+// 4 bit, tiles of 128 tokens, K = 4608: 96 25.3 18.8, 256 26.0 20.0; K = 1152: 96 8.9 7.8, 256 9.9 9.1; K = 768 7.1 6.6; but
+// K = 384 5.0 5.2.  4 bit, tiles of 256: K = 4608: 144 28.4 25.6, 256 39.0 31.8; K = 2304: 144 16.6 16.1; but K = 1536
+// 12.5 12.7.  8 bit, tiles of 128 (nothing to unpack): K = 4608: 96 17.5 15.6, 144 18.8 17.1; K = 2304: 126 10.9 10.5;
+// but K = 1536 8.7 8.8, and 256 tiles K = 2304 12.6 13.1, K = 6144 25.9 26.6.  With two tiles of 128 or 256 to a CU the two
+// hide each other's waits and the exchange is lost: 8192 x 4608 x 1152, 288 tiles of 256, 41.9 52.6.
+// The split kernels have no form that keeps f32 output in the caches: where tiles of 256 should, it takes K = 4608 (7168 x 4608 x
+// 1152 41.5 38.2, but 4096 x 2304 x 2048 24.3 28.2).  Height of the tiles to split, 0: none.
+static int split_height(int64_t M, int n_tiles, int KF, int bits) {
+    const int64_t half = (M + 2 * kWaveM - 1) / (2 * kWaveM) * n_tiles, full = (M + kTileM - 1) / kTileM * n_tiles;
+    if (bits == 8) return half <= 160 && KF >= 36 ? 2 : 0;
+    if (half <= kCus) return KF >= 12 ? 2 : 0;
+    return full <= kCus && KF >= 36 ? 4 : 0;
+}
+
 // 32-bit output: non-temporal stores write it to memory at once, ordinary ones into the last-level
 // cache, where the next layer finds it.  Ordinary ones win from 24 MB on, 15 MB with lower
 // tiles (below, writing back the L2s at the end of the launch weighs more; half the height, K = 1152,
@@ -149,6 +166,9 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
         args.height = 4;
         args.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, 4, epi);
     }
+    const int split = args.resident ? 0 : split_height(M, args.n_tiles, args.KF, bits);
+    args.split = split == 2 || (split == 4 && (args.KF >= 72 || ydt != QC_OUT_F32 || !keep_f32_output(M, N, K, 4, epi)));
+    if (args.split) { args.height = split; args.keep_output = false; }
     if (args.height != 4) args.m_tiles = (int)((M + kWaveM * args.height - 1) / (kWaveM * args.height));
     args.stream_edges = stream_bf16_edges(M, N);
     args.group_m = args.n_tiles > 16 ? 8 : (args.KF >= 36 ? 3 : 2);

@@ -42,10 +42,15 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256, kSplitThreads = 2 * kThreads;
 constexpr int kStages = 3;   // both rings: weight stages in LDS (4 and 6 were measured: 1.5 % and 3 % slower) and
                              // activation stages in registers.  The half-height tile gains nothing from 6
                              // either: alone on its CU a block waits for bandwidth, not for latency.
+
+// LDS in front of the scales: the ring, or, split, two rings or what the groups exchange at a time
+template <int BITS, bool SPLIT>
+constexpr int kRingBytes = !SPLIT ? kStages * StageLayout<BITS>::kBytes
+                           : 2 * kStages * StageLayout<BITS>::kBytes > kSplitThreads * 64 ? 2 * kStages * StageLayout<BITS>::kBytes : kSplitThreads * 64;
 
 __device__ inline void lds_dma_16(const uint8_t *gsrc, uint8_t *lds_dst) {
     __builtin_amdgcn_global_load_lds(
@@ -230,7 +235,9 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
 // ASYM: the activation codes are the unsigned codes of the asymmetric quantizer minus a shift h
 // (128 for 8-bit codes, else 0; Section 3.1 Eq. (3)-(4) as printed).  With c[m] = h - z[m] the dequantized activation
 // is sx (code + c), so the epilogue adds c[m] * sum_k qw[n, k] to the accumulator.
-template <int BITS, int OUT, int EPI, bool ASYM, bool KEEP, int MI>
+// SPLIT: eight wavefronts in two groups that each walk half of the reduction, with a ring of their own, and
+// exchange sums at the end: see split_height().
+template <int BITS, int OUT, int EPI, bool ASYM, bool KEEP, int MI, bool SPLIT = false>
 __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     using L = StageLayout<BITS>;
     constexpr int TM = 4 * 16 * MI;   // tokens of the block, 16 MI of them a wavefront's
@@ -238,15 +245,19 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_of_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = SPLIT ? wave_of_block & 3 : wave_of_block, group = SPLIT ? wave_of_block >> 2 : 0;
     int mt, nt;
     tile_of_block(blockIdx.x, gridDim.x, a.m_tiles, a.n_tiles, a.group_m, mt, nt);
 
-    const int stages = a.KF;
+    // this group's stages, in whole threes: the first group has three more if they do not come out even
+    const int most = SPLIT ? 3 * ((a.KF / 3 + 1) / 2) : a.KF;
+    const int stage0 = group ? most : 0, stages = group ? a.KF - most : most;
+    uint8_t *const ring = lds + group * (kStages * L::kBytes);
     // The epilogue's scales and bias are fetched now (one value per thread) and handed round
     // through LDS after the main loop, so that the epilogue does not start with a chain of L2
     // round trips.
-    float *lds_sx = reinterpret_cast<float *>(lds + kStages * L::kBytes);  // TM token scales (room for 256)
+    float *lds_sx = reinterpret_cast<float *>(lds + kRingBytes<BITS, SPLIT>);  // TM token scales (room for 256)
     float *lds_sw = lds_sx + kTileM;                                       // 128 channel scales
     float *lds_bs = lds_sw + kTileN;                                       // 128 biases
     float *lds_cx = lds_bs + kTileN;                                       // ASYM: 256 corrections
@@ -270,10 +281,10 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     }
     // The pieces of the weight stage tile this wavefront copies HBM -> LDS, at stage 0 (a
     // stage tile is contiguous in memory).
-    const uint8_t *const wsrc = a.w_codes + (int64_t)nt * a.KF * L::kBytes + wave * FPW * kFragBytes + lane * 16;
+    const uint8_t *const wsrc = a.w_codes + ((int64_t)nt * a.KF + stage0) * L::kBytes + wave * FPW * kFragBytes + lane * 16;
     // copy the weight pieces of K stage `stage` into ring buffer `slot`
     auto issue_w = [&](int stage, int slot) {
-        uint8_t *buf = lds + slot * L::kBytes;
+        uint8_t *buf = ring + slot * L::kBytes;
 #pragma unroll
         for (int j = 0; j < FPW; ++j)
             lds_dma_16(wsrc + (int64_t)stage * L::kBytes + j * kFragBytes, buf + (wave * FPW + j) * kFragBytes);
@@ -290,7 +301,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     // panel of 64 and end in the next: an offset per fragment.  Its tile may end past the padded
     // tokens, where it reads the last fragment again and stores nothing.
     const int frag0 = min((mt * 4 + wave) * MI, a.x_frags - 1);   // first of its blocks of 16 tokens, four to a panel
-    const uint8_t *const xsrc = a.x_tiled + (int64_t)(frag0 / 4) * a.KF * (4 * kFragBytes);
+    const uint8_t *const xsrc = a.x_tiled + ((int64_t)(frag0 / 4) * a.KF + stage0) * (4 * kFragBytes);
     uint32_t xoff[MI == 3 ? 3 : 1];
     if constexpr (MI == 3) {
 #pragma unroll
@@ -338,7 +349,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     // LDS -> registers for the weight fragments.
     //   wr[h][t]: 16-channel block 4 h + t (8 bit);  wr[0][u]: nibble unit of blocks 2 u, 2 u + 1 (4 bit)
     v4i wr[2][4];
-    const uint32_t lds_lane = (uint32_t)(uintptr_t)lds + lane * 16;  // LDS byte address of this lane
+    const uint32_t lds_lane = (uint32_t)(uintptr_t)ring + lane * 16;  // LDS byte address of this lane
 #define QC_DS_READ(dst, addr, imm) \
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 #define QC_READ_W(SLOT, H)                                                           \
@@ -447,6 +458,8 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     QC_WAIT_X(0, 0);
     QC_WAIT_X(0, 1);
     QC_WAIT_X(0, 2);
+    // a barrier is for both groups, so the second meets the first at those of the stages it does not have
+    for (int s = stages; s < most; ++s) __builtin_amdgcn_s_barrier();
 #undef QC_MFMA_LOOPS
 #undef QC_CLAMP
 #undef QC_STAGE
@@ -471,8 +484,30 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &a) {
     }
 
     // ---- epilogue: registers -> Y --------------------------------------------------------
-    store_wave_tile<BITS, OUT, EPI, ASYM, KEEP>(acc, a, (int64_t)mt * TM + wave * (16 * MI), nt, lane,
-                                           lds_sx + wave * (16 * MI), lds_cx + wave * (16 * MI), lds_sw, lds_bs, lds_rs);
+    if constexpr (SPLIT) {
+        // Each group finishes half of the tokens: a wavefront hands its sums of the others to its counterpart in the other
+        // group, 4 KiB at a time, where the rings were.
+        constexpr int H = MI / 2;
+        v4i half[H][8];
+        v4i *const mine = reinterpret_cast<v4i *>(lds) + wave_of_block * 256 + lane;
+        const v4i *const theirs = reinterpret_cast<const v4i *>(lds) + (wave_of_block ^ 4) * 256 + lane;
+#pragma unroll
+        for (int i = 0; i < H; ++i)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                __syncthreads();   // the rings, or the exchange before, have been read
+#pragma unroll
+                for (int t = 0; t < 4; ++t) mine[64 * t] = group ? acc[i][4 * r + t] : acc[H + i][4 * r + t];
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < 4; ++t) half[i][4 * r + t] = (group ? acc[H + i][4 * r + t] : acc[i][4 * r + t]) + theirs[64 * t];
+            }
+        const int at = wave * (16 * MI) + group * (16 * H);
+        store_wave_tile<BITS, OUT, EPI, ASYM, KEEP>(half, a, (int64_t)mt * TM + at, nt, lane, lds_sx + at, lds_cx + at, lds_sw, lds_bs, lds_rs);
+    } else {
+        store_wave_tile<BITS, OUT, EPI, ASYM, KEEP>(acc, a, (int64_t)mt * TM + wave * (16 * MI), nt, lane,
+                                                    lds_sx + wave * (16 * MI), lds_cx + wave * (16 * MI), lds_sw, lds_bs, lds_rs);
+    }
 }
 
 template <int BITS, int OUT, int EPI, bool ASYM>
@@ -491,7 +526,17 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_half_kernel(GemmArgs a) {
     ring_gemm<BITS, OUT, EPI, ASYM, false, 2>(a);
 }
 
-// the same three with f32 output stored through the caches: see keep_f32_output()
+// two groups of four wavefronts on tiles of 128 and, with 4-bit weights, 256 tokens: see split_height()
+template <int BITS, int OUT, int EPI, bool ASYM>
+__global__ __launch_bounds__(kSplitThreads, 2) void gemm_split_half_kernel(GemmArgs a) {
+    ring_gemm<BITS, OUT, EPI, ASYM, false, 2, true>(a);
+}
+template <int OUT, int EPI, bool ASYM>
+__global__ __launch_bounds__(kSplitThreads, 2) void gemm_split_kernel(GemmArgs a) {
+    ring_gemm<4, OUT, EPI, ASYM, false, 4, true>(a);
+}
+
+// the first three with f32 output stored through the caches: see keep_f32_output()
 template <int BITS, int EPI, bool ASYM>
 __global__ __launch_bounds__(kThreads, 2) void gemm_cached_kernel(GemmArgs a) {
     ring_gemm<BITS, QC_OUT_F32, EPI, ASYM, true, 4>(a);
@@ -730,14 +775,25 @@ hipError_t launch_variant(const GemmArgs &args, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    using L = StageLayout<BITS>;
-    constexpr int kLds = kStages * L::kBytes +
+    constexpr int kLds = kRingBytes<BITS, false> +
                          (kTileM + 2 * kTileN + (ASYM ? kTileM + kTileN : 0)) * (int)sizeof(float);
     // far below the 64 KiB a kernel may use without an attribute, so the first launch of a
     // variant needs no set-up call and can be captured into a graph like any other
     static_assert(kLds <= 64 * 1024, "dynamic LDS beyond the default limit needs an attribute");
     const int blocks = args.m_tiles * args.n_tiles;
     const dim3 grid((unsigned)blocks), block(kThreads);
+    if (args.split) {
+        constexpr int kSplitLds = kLds - kRingBytes<BITS, false> + kRingBytes<BITS, true>;
+        static_assert(kSplitLds <= 64 * 1024, "dynamic LDS beyond the default limit needs an attribute");
+        if constexpr (BITS == 4) {
+            if (args.height == 4) {
+                gemm_split_kernel<OUT, EPI, ASYM><<<grid, dim3(kSplitThreads), kSplitLds, stream>>>(args);
+                return hipGetLastError();
+            }
+        }
+        gemm_split_half_kernel<BITS, OUT, EPI, ASYM><<<grid, dim3(kSplitThreads), kSplitLds, stream>>>(args);
+        return hipGetLastError();
+    }
     if constexpr (OUT == QC_OUT_F32) {
         if (args.keep_output) {
             if (args.height == 2) gemm_half_cached_kernel<BITS, EPI, ASYM><<<grid, block, kLds, stream>>>(args);

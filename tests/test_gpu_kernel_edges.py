@@ -290,6 +290,28 @@ def test_qlinear_ring_kernel_on_tiles_of_192_tokens(M, K, N, bits):
         assert bool((buf[:pad] == -7.0).all()) and bool((buf[pad + M * N:] == -7.0).all())
 
 
+@pytest.mark.parametrize("M,K,N,bits", [(1025, 768, 1152, 4), (2001, 960, 1030, 4), (2047, 720, 2045, 4), (1281, 2304, 1148, 8), (2545, 2480, 1023, 8),
+                                        (1281, 2480, 1027, 4), (3716, 2304, 1153, 4), (3841, 2480, 1146, 4)])
+def test_qlinear_ring_kernel_split_in_two_halves_of_the_reduction(M, K, N, bits):
+    """Few tiles of 128 tokens (the first six) and, with 4-bit weights, of 256: the shortest reductions it is taken for, halves
+    of the same and of different length, last tiles of 1 token, and nothing written on either side of Y."""
+    rng = np.random.default_rng(M + K + N + bits)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    b = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    x = random_x(rng, M, K, "bf16")
+    run_linear_case(x, W, b, bits, "gelu_tanh", "bf16")
+    run_linear_case(x, W, None, bits, "gelu_erf", "f32", check_acc=False)
+    run_asym_case(x, W, b, bits, "none", "bf16")
+    pw, pad = qc.pack_weight_t(dev(W), bits), 4096
+    for out, t in (("bf16", torch.bfloat16), ("f32", torch.float32)):
+        want = qc.qlinear_t(dev(x), pw, dev(b), "none", out)
+        buf = torch.full((M * N + 2 * pad,), -7.0, dtype=t, device="cuda")
+        got = qc.qlinear_t(dev(x), pw, dev(b), "none", out, Y=buf[pad:pad + M * N].view(M, N))
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        assert bool((buf[:pad] == -7.0).all()) and bool((buf[pad + M * N:] == -7.0).all())
+
+
 def test_qlinear_ragged_rows_beyond_the_last_level_cache():
     """bf16 output of more than 256 MB whose rows are no multiple of 16 B: non-temporal stores at any alignment."""
     M, K, N = 262145, 64, 513

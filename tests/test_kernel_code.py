@@ -47,7 +47,7 @@ def wide_stores(tmp_path_factory):
     return found
 
 
-@pytest.mark.parametrize("kernel,rows", [("gemm_kernel", 16), ("gemm_mid_kernel", 12), ("gemm_half_kernel", 8)])
+@pytest.mark.parametrize("kernel,rows", [("gemm_kernel", 16), ("gemm_mid_kernel", 12), ("gemm_half_kernel", 8), ("gemm_split_half_kernel", 4)])
 def test_ring_kernels_hold_both_kinds_of_store(wide_stores, kernel, rows):
     """A wavefront stores `rows` rows per lane, two pieces each in 32 bits and one in bf16, on a path for
     whole tiles, non-temporally, and on one for the others: through the caches, for bf16 either way."""
