@@ -181,8 +181,8 @@ def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
 @pytest.mark.parametrize("M,K,N", [(5505, 192, 130), (16384, 64, 129), (16385, 64, 129), (21889, 64, 257), (21249, 320, 512),
                                    (21250, 64, 511), (26001, 64, 512)])
 def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
-    """Tiles of 128 tokens up to 128 full tiles and from 257 to 332 of them, tiles of 256 otherwise; with
-    32-bit output also both kinds of store (through the caches from 24 MB on); an asymmetric one."""
+    """From a few tiles to several per CU, whose heights the launcher chooses by how they spread; with
+    32-bit output also both kinds of store (through the caches from 15 or 24 MB on); an asymmetric one."""
     assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
     rng = np.random.default_rng(M + N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
@@ -194,7 +194,7 @@ def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
 
 
 def full_height(M, N):
-    """Whether the ring kernel takes tiles of 256 tokens (of 128 otherwise)."""
+    """Whether tiles of 256 tokens spread well over the CUs, against those of 128; the launcher weighs 192 too."""
     tiles = -(-M // 256) * -(-N // 128)
     return not (2 * tiles <= 256 or 256 < tiles <= 332)
 
@@ -323,8 +323,8 @@ def test_qlinear_ragged_rows_beyond_the_last_level_cache():
 @pytest.mark.parametrize("n", [1, 4, 1023 * 4, 1024 * 4 + 1, 16 * 4096, 16 * 4096 + 5, 48 * 4096 - 1, 48 * 4096, 3 << 17, (3 << 17) + 1, 1 << 19, (1 << 19) + 1, 170 * 4096 + 5,
                                (12 << 20) // 8, (12 << 20) // 8 + 1])
 def test_reductions_on_both_sides_of_the_one_launch_form(n):
-    """Up to 393216 elements the block that sees all partial sums finishes (16 blocks at most, 32 from
-    196608 elements on); beyond that a second launch does.  The workspace holds
+    """Up to 786432 elements the block that sees all partial sums finishes (16 blocks, more of them where
+    each would have more than two chunks); beyond that a second launch does.  The workspace holds
     arbitrary bytes, then what the call before left in it."""
     rng = np.random.default_rng(n)
     cur, prev = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
