@@ -16,7 +16,8 @@
 //     the size, that fewer blocks read.  Two chunks a block (one from five earlier tensors on), 16 blocks at least while there are as many
 //     chunks: with 32 blocks at most it took 5.6 instead of 5.3 us for a latent delta of 390000 elements, 7.7
 //     instead of 6.6 for a similarity of 1.2 million.  Each operation's limit (kOneMost) lies where it costs
-//     some 0.5 us more than two launches, for the similarity 1.  us per call in a graph, four sets of inputs in
+//     no more than two launches, for the similarity up to 1 us, over inputs read again and again too (one launch for a latent delta of
+//     540000 to 715000 elements 6 to 7.4 us where two took 4.6).  us per call in a graph, four sets of inputs in
 //     turn, two launches and one:
 //       latent delta     65536 4.5 3.7   300000 5.4 4.6   500000 5.7 5.6   700000 6.0 6.3   1 million 6.2 7.4
 //       similarity bf16  100000 4.8 4.0   300000 4.7 4.7   600000 5.4 5.6   1.3 million 5.6 6.5   1.7 million 5.4 7.4
@@ -223,7 +224,7 @@ struct DeltaOp {
     static constexpr int kCount = 2, kElems = 4, kThreads = 1024, kUnroll = 4, kOneUnroll = 2, kOneChunks = 2, kOuts = 3;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kDeltaBytes;
-    static constexpr int64_t kOneMost = 3 << 18;
+    static constexpr int64_t kOneMost = 3 << 17;
     const float *cur, *prev;
     struct Regs { float4 a, b; };
     __device__ void load(Regs &r, int64_t i) const { r.a = stream4f(cur + 4 * i); r.b = stream4f(prev + 4 * i); }
@@ -336,7 +337,7 @@ struct VariationOp {
     static constexpr int kCount = COUNT, kElems = 4, kThreads = 512, kUnroll = 2, kOneUnroll = 1, kOneChunks = COUNT > 4 ? 1 : 2, kOuts = COUNT + 1;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kVariationBytes;
-    static constexpr int64_t kOneMost = 1 << 17;
+    static constexpr int64_t kOneMost = 3 << 15;
     const float *cur;
     PrevList prevs;
     struct Regs { float4 a, b[COUNT]; };
