@@ -34,14 +34,16 @@ bool gemm_resident_chosen(int64_t M, int64_t N, int64_t K, int bits) {
     return (int64_t)most * kResBlocks * 100 <= total * 104;
 }
 
-// Its one block per CU hides less of a GELU than two of the ring kernel's, which take the place of the
-// resident one for GELU (erf) (us under sustained load, ring and resident: 65536 x 1152 x 4608 375 382, 131072 x 384 x
-// 4608 483 514), and for GELU (tanh) to bf16 with 4-bit weights (131072 x 1152 x 4608 658 668) or a short
-// reduction (K = 384 374 379; K = 1152, 8-bit weights 661 629).  In bursts of a few calls the ring kernel gains 5 % more.
+// Its one block per CU hides less of a GELU, or of an output that is long for the reduction, than two of the ring kernel's,
+// which take its place for GELU (erf) (us under sustained load, ring and resident: 65536 x 1152 x 4608 375 382, 131072 x 384 x
+// 4608 483 514), for GELU (tanh) to bf16 with 4-bit weights (131072 x 1152 x 4608 658 668) or a short
+// reduction (K = 384 374 379; K = 1152, 8-bit weights 661 629), for GELU (tanh) to f32 (59454 x 1152 x 4608 416 463, 131072 x 1152 x
+// 1152 238 272, 40000 x 768 x 2304 125 137) and for f32 with a short reduction (60000 x 768 x 4608 343 390, 131072 x 768 x 2304 382
+// 422; K = 1152, 65536 x 4608, 427 403).  In bursts of a few calls the ring kernel gains 5 % more.
 static bool gemm_resident_epilogue(int64_t K, int bits, qc_epilogue epi, qc_out ydt) {
-    if (ydt == QC_OUT_I32_ACC || epi == QC_EPI_NONE) return true;
-    if (epi == QC_EPI_GELU_ERF) return false;
-    return ydt == QC_OUT_F32 || (bits == 8 && K > 768);
+    if (ydt == QC_OUT_I32_ACC) return true;
+    if (epi == QC_EPI_NONE) return ydt == QC_OUT_BF16 || K > 768;
+    return epi == QC_EPI_GELU_TANH && ydt == QC_OUT_BF16 && bits == 8 && K > 768;
 }
 
 int gemm_resident_blocks() { return kResBlocks; }
@@ -108,6 +110,9 @@ static int split_height(int64_t M, int n_tiles, int KF, int bits) {
 // 91 85, 262 MB 99.6 99.2, 318 MB 119 120, 412 MB 140 156; N = 3456 (an eighth in codes): output of 223
 // MB 112 102, 297 MB 150 136, 398 MB 186 167; K = 2304, N = 640: with codes 242 MB 96 90, 365 MB 123 138;
 // K = 4608, N = 1152: 254 MB 142 140, 320 MB 176 178, 383 MB 202 217; K = 192, N = 1152: 400 MB 176 93.
+// With K up to 576 the output is nearly all there is to move, and the caches take it at any size while it is
+// 16 times the codes: 57258 x 192 x 4608 443 207, 100000 x 384 x 2304 367 234, 150000 x 576 x 2304 496 403, 200000 x 384 x 1536 441 347; but
+// 60000 x 768 x 4608 342 351.
 // GELU (erf) leaves non-temporal stores the time to drain, and ordinary ones win from 60 MB on only and up to 192 MB
 // with the codes: 27 MB 23.3 25.1, 46 MB 30.2 32.6, 53 MB 34.2 35.2, 69 MB 53.8 46.5, with codes 193 MB 89.9 88.2;
 // K = 1824, with codes 204 MB 116 127; half the height, N = 3456, 41 MB 26.0 27.7.
@@ -116,7 +121,7 @@ static bool keep_f32_output(int64_t M, int64_t N, int64_t K, int height, qc_epil
     constexpr int64_t MB = 1 << 20;
     const int64_t out = 4 * M * N, codes = M * round_up(K, kKAlign);
     const int64_t from = epi == QC_EPI_GELU_ERF ? 60 : height == 4 ? 24 : 15, most = epi == QC_EPI_GELU_ERF ? 192 : 256;
-    return out >= from * MB && (out + codes <= most * MB || (8 * codes <= out && out <= 400 * MB));
+    return out >= from * MB && (out + codes <= most * MB || (8 * codes <= out && out <= 400 * MB) || (K <= 576 && 16 * codes <= out));
 }
 
 // Rows of bf16 that are no multiple of 16 B long, and partly filled tiles: through the caches while the
@@ -161,8 +166,11 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     args.height = args.resident ? 4 : ring_height(M, args.n_tiles, K, applied);
     args.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, args.height, epi);
     // Whole rows of 32 bits past the caches: the more blocks a CU holds the worse their stores drain (us at 256
-    // and 192 tokens: 39510 x 1152 x 4608 274 324, 105656 x 784 x 1152 210 229; of less than 40 MB the spread over the CUs counts).
-    if (args.height != 4 && ydt != QC_OUT_BF16 && N % 4 == 0 && !args.keep_output && 4 * M * N > (int64_t)40 << 20) {
+    // and 192 tokens: 39510 x 1152 x 4608 274 324, 105656 x 784 x 1152 210 229; of less than 192 MB the spread over the CUs
+    // counts: 42 MB 9149 x 4608 x 1152 58.1 49.0, 43 MB 5597 x 592 x 1920, 4 bit, 128 tokens 20.0 17.6, 29000 x 4608 x 1152 147 147).
+    // Of more than 400 MB through the caches too (250000 x 192 x 1152 287 247, 100000 x 384 x 2304, 4 bit, GELU 257 222).
+    const int64_t out32 = ydt == QC_OUT_BF16 || N % 4 ? 0 : 4 * M * N;
+    if (args.height != 4 && (out32 > (int64_t)400 << 20 || (out32 > (int64_t)192 << 20 && !args.keep_output))) {
         args.height = 4;
         args.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, 4, epi);
     }

@@ -117,7 +117,7 @@ __device__ __forceinline__ void store_wave_tile(v4i (&acc)[MI][8], const GemmArg
         // 1113 x 1152 x 2819 W4 GELU 13.9 12.0, 3000 x 1152 x 1203 10.3 9.2, f32 65536 x 1152 x 1156 135 127.
         const int cols = CHECKED ? (int)(a.N - n0 < 8 ? a.N - n0 : 8) : 8;
         const int rows = CHECKED ? (int)(a.M - m0 < 16 * MI ? a.M - m0 : 16 * MI) : 16 * MI;
-        const bool ragged = CHECKED && (int64_t)(nt + 1) * kTileN > a.N;   // uniform over the wavefront
+        const bool ragged = CHECKED && a.N % 8 && (int64_t)(nt + 1) * kTileN > a.N;   // uniform over the wavefront
         const bool four = cols & 4, two = cols & 2;
 
         float sw[8], bs[8], rs[8];
@@ -769,7 +769,7 @@ __global__ __launch_bounds__(kResThreads, 1) void gemm_resident_kernel(GemmArgs 
 template <int BITS, int OUT, int EPI, bool ASYM>
 hipError_t launch_variant(const GemmArgs &args, hipStream_t stream) {
     // the combinations gemm_resident_epilogue() lets through
-    if constexpr (EPI != QC_EPI_GELU_ERF && !(BITS == 4 && OUT == QC_OUT_BF16 && EPI == QC_EPI_GELU_TANH)) {
+    if constexpr (EPI == QC_EPI_NONE || (EPI == QC_EPI_GELU_TANH && BITS == 8 && OUT == QC_OUT_BF16)) {
         if (args.resident) {
             gemm_resident_kernel<BITS, OUT, EPI, ASYM><<<dim3(kResBlocks), dim3(kResThreads), 0, stream>>>(args);
             return hipGetLastError();
