@@ -379,10 +379,8 @@ class Bench:
 
     def gemm_kernel_name(self, case):
         """Which of the GEMM's kernels the library takes for this layer (the ring of any height: gemm_kernel)."""
-        which = self.qc.qc_debug_gemm_kernel(case.M, case.K, case.N, case.bits)
-        if which == 2 and (case.epi == "gelu_erf" or (case.epi == "gelu_tanh" and (case.bits == 4 or case.K <= 768))):
-            which = 1   # GELUs that the ring hides better, with bf16 output
-        return {1: "gemm_kernel", 2: "gemm_resident_kernel", 3: "small_kernel"}[which]
+        plan = self.qc.linear_plan(case.M, case.K, case.N, case.bits, epi=case.epi)
+        return {"ring": "gemm_kernel", "resident": "gemm_resident_kernel", "few": "small_kernel"}[plan["kernel"]]
 
     def check(self, st):
         if st != self.qc.QC_OK:

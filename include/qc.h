@@ -275,9 +275,19 @@ qc_status qc_debug_workspace_act(const void *workspace, int64_t M, int64_t K, in
  * a ring in LDS (with tiles of 256, 192 or 128 tokens), the other keeps a whole 128-channel weight tile resident in
  * LDS and is taken for short reductions (K <= 1152 with 8-bit weights, <= 2304 with 4-bit ones) on problems large
  * enough for its static schedule (with GELU not always: the ring then takes some of them).
- *   qc_debug_gemm_kernel    which one qc_qlinear_gemm takes for (M, K, N, bits): 1 the ring, of
- *                           any height, 2 the resident one (without GELU), 3 the one for few tokens, 0 if the shape is
- *                           unsupported
+ *   qc_debug_gemm_kernel    which one qc_qlinear_gemm takes for (M, K, N, bits) without activation and with bf16
+ *                           output (int32, and f32 of K > 768, the same): 1 the ring, of any height, 2 the resident
+ *                           one, 3 the one for few tokens, 0 if the shape is unsupported
+ *   qc_debug_linear_plan    what a whole linear does, its outputs not lying over its inputs.  scheme: 0 one scale per
+ *                           token, 1 the same with rotation, 2 asymmetric, 3 one scale for the tensor.  Returns 0 and
+ *                           fills plan[0 .. 5] (host memory); -1 for what the linear refuses and for bad arguments.
+ *                             0  the GEMM's kernel, numbered as above, for this epilogue and output
+ *                             1  tokens of a block's tile (resident: of a round)
+ *                             2  1 if the ring's block splits the reduction over two groups of wavefronts
+ *                             3  1 if the ring writes f32 output through the caches
+ *                             4  1 if the quantization goes out in the same launch
+ *                             5  otherwise how the quantizer reads X and writes the codes: 0 ordinary loads and
+ *                                stores, 1 non-temporal loads, 2 non-temporal stores, 3 both
  *   qc_debug_gemm_schedule  the rounds of block `block` (0 .. 255) of the resident kernel for an
  *                           [M, N] output, in the order the block runs them: pairs[2 i] is the
  *                           128-channel tile, pairs[2 i + 1] the 512-token chunk of round i.
@@ -285,6 +295,8 @@ qc_status qc_debug_workspace_act(const void *workspace, int64_t M, int64_t K, in
  *                           memory; may be NULL with cap 0); -1 for bad arguments.  Over all
  *                           blocks every (tile, chunk) appears exactly once. */
 int qc_debug_gemm_kernel(int64_t M, int64_t K, int64_t N, int bits);
+int qc_debug_linear_plan(int64_t M, int64_t K, int64_t N, qc_dtype xdt, int scheme, int bits, qc_epilogue epi, qc_out ydt,
+                         int32_t *plan);
 int qc_debug_gemm_schedule(int64_t M, int64_t N, int block, int32_t *pairs, int cap);
 
 /* ---- S5: latent change reduction ----------------------------------------------------

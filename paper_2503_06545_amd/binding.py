@@ -28,6 +28,7 @@ EXPORTS = (
     "qc_qlinear", "qc_qlinear_quant", "qc_qlinear_gemm", "qc_quant_act_bits",
     "qc_qlinear_quant_bits", "qc_qlinear_act_bits", "qc_layer_similarity_workspace_bytes",
     "qc_layer_similarity", "qc_debug_workspace_act", "qc_debug_gemm_kernel", "qc_debug_gemm_schedule",
+    "qc_debug_linear_plan",
     "qc_latent_delta",
     "qc_frame_gradient_norm_workspace_bytes", "qc_frame_gradient_norm",
     "qc_cumulative_variation_workspace_bytes", "qc_cumulative_variation",
@@ -94,6 +95,8 @@ def lib() -> ctypes.CDLL:
         L.qc_debug_workspace_act.argtypes = [vp, i64, i64, vp, vp, vp]
         L.qc_debug_gemm_kernel.restype = i32
         L.qc_debug_gemm_kernel.argtypes = [i64, i64, i64, i32]
+        L.qc_debug_linear_plan.restype = i32
+        L.qc_debug_linear_plan.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32, vp]
         L.qc_debug_gemm_schedule.restype = i32
         L.qc_debug_gemm_schedule.argtypes = [i64, i64, i32, vp, i32]
         L.qc_latent_delta.restype = i32
@@ -247,6 +250,22 @@ def gemm_schedule(M: int, N: int, block: int):
     buf = (ctypes.c_int32 * (2 * max(n, 1)))()
     qc_debug_gemm_schedule(M, N, block, ctypes.cast(buf, ctypes.c_void_p), n)
     return [(buf[2 * i], buf[2 * i + 1]) for i in range(n)]
+
+
+def qc_debug_linear_plan(M, K, N, xdt, scheme, bits, epi, ydt, plan) -> int:
+    return int(lib().qc_debug_linear_plan(M, K, N, xdt, scheme, bits, epi, ydt, plan))
+
+
+def linear_plan(M: int, K: int, N: int, bits: int = 8, x: str = "bf16", out: str = "bf16", epi: str = "none",
+                scheme: str = "token") -> dict:
+    """What a linear's launches are (host only): kernel "ring", "resident" or "few", tokens of its tiles, split, kept,
+    fused, and the quantizer's non-temporal loads and stores."""
+    plan = (ctypes.c_int32 * 6)()
+    if qc_debug_linear_plan(M, K, N, QC_BF16 if x == "bf16" else QC_F32, ("token", "rot", "asym", "tensor").index(scheme), bits,
+                            EPI[epi], OUT[out], ctypes.cast(plan, ctypes.c_void_p)) != 0:
+        raise QcError(QC_ERR_INVALID_ARG, "qc_debug_linear_plan")
+    return {"kernel": (None, "ring", "resident", "few")[plan[0]], "tokens": plan[1], "split": bool(plan[2]), "kept": bool(plan[3]),
+            "fused": bool(plan[4]), "nt_loads": bool(plan[5] & 1), "nt_stores": bool(plan[5] & 2)}
 
 
 def qc_latent_delta(cur, prev, n, out3, workspace, workspace_bytes, stream=0) -> int:

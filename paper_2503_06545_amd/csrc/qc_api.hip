@@ -404,3 +404,31 @@ extern "C" int qc_debug_gemm_schedule(int64_t M, int64_t N, int block, int32_t *
     if (m_tiles * n_tiles > 0x7fffffffLL) return -1;
     return resident_block_rounds(block, gemm_resident_blocks(), (int)n_tiles, (int)m_tiles, pairs, cap);
 }
+
+extern "C" int qc_debug_linear_plan(int64_t M, int64_t K, int64_t N, qc_dtype xdt, int scheme, int bits, qc_epilogue epi,
+                                    qc_out ydt, int32_t *plan) {
+    if (M < 1 || K < 1 || N < 1 || !plan || (xdt != QC_F32 && xdt != QC_BF16) || scheme < 0 || scheme > 3) return -1;
+    if (epi < QC_EPI_NONE || epi > QC_EPI_GELU_ERF || ydt < QC_OUT_F32 || ydt > QC_OUT_I32_ACC) return -1;
+    const QuantScheme how = (QuantScheme)scheme;
+    if (check_gemm_supported(M, K, N, bits) != QC_OK) return -1;
+    if (check_quant_supported(M, K, 8, how == kQuantAsym, how == kQuantRotated ? 16 : 0) != QC_OK) return -1;
+    plan[2] = plan[3] = plan[4] = plan[5] = 0;
+    if (qlinear_small_chosen(M, N, K, xdt, how)) {
+        plan[0] = kGemmSmall;
+        plan[1] = qlinear_small_tokens(M, N, K, xdt, how);
+        plan[4] = 1;
+        return 0;
+    }
+    plan[5] = quant_cache_policy(M, K, xdt, how);
+    if (gemm_small_chosen(M, N)) {
+        plan[0] = kGemmSmall;
+        plan[1] = gemm_small_tokens(M, N);
+        return 0;
+    }
+    const GemmChoice c = choose_gemm(M, N, K, bits, epi, ydt);
+    plan[0] = c.resident ? kGemmResident : kGemmRing;
+    plan[1] = c.resident ? kRoundTokens : kWaveM * c.height;
+    plan[2] = c.split;
+    plan[3] = c.keep_output;
+    return 0;
+}

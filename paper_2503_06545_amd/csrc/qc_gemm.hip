@@ -131,6 +131,34 @@ static bool keep_f32_output(int64_t M, int64_t N, int64_t K, int height, qc_epil
 // 227 MB 101 189, 906 MB 500 674).
 static bool stream_bf16_edges(int64_t M, int64_t N) { return 2 * M * N > (int64_t)256 << 20; }
 
+GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt) {
+    GemmChoice c{};
+    const int n_tiles = (int)(round_up(N, kTileN) / kTileN);
+    if (gemm_resident_chosen(M, N, K, bits) && gemm_resident_epilogue(K, bits, epi, ydt)) {
+        c.resident = true;
+        c.height = 4;
+        return c;
+    }
+    c.height = ring_height(M, n_tiles, K, ydt == QC_OUT_I32_ACC ? QC_EPI_NONE : epi);
+    c.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, c.height, epi);
+    // Whole rows of 32 bits past the caches: the more blocks a CU holds the worse their stores drain (us at 256
+    // and 192 tokens: 39510 x 1152 x 4608 274 324, 105656 x 784 x 1152 210 229; of less than 192 MB the spread over the CUs
+    // counts: 42 MB 9149 x 4608 x 1152 58.1 49.0, 43 MB 5597 x 592 x 1920, 4 bit, 128 tokens 20.0 17.6, 29000 x 4608 x 1152 147 147).
+    // Of more than 400 MB through the caches too (250000 x 192 x 1152 287 247, 100000 x 384 x 2304, 4 bit, GELU 257 222).
+    const int64_t out32 = ydt == QC_OUT_BF16 || N % 4 ? 0 : 4 * M * N;
+    if (c.height != 4 && (out32 > (int64_t)400 << 20 || (out32 > (int64_t)192 << 20 && !c.keep_output))) {
+        c.height = 4;
+        c.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, 4, epi);
+    }
+    const int KF = (int)(round_up(K, kKAlign) / kFragK), split = split_height(M, n_tiles, KF, bits);
+    c.split = split == 2 || (split == 4 && (KF >= 72 || ydt != QC_OUT_F32 || !keep_f32_output(M, N, K, 4, epi)));
+    if (c.split) {
+        c.height = split;
+        c.keep_output = false;
+    }
+    return c;
+}
+
 hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                        const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                        int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
@@ -138,8 +166,12 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     if (gemm_small_chosen(M, N))
         return launch_gemm_small(x_tiled, x_scale, w_packed, w_scale, bias, Y, M, N, K, bits, epi, ydt, x_corr,
                                  w_rowsum, stream);
+    const GemmChoice choice = choose_gemm(M, N, K, bits, epi, ydt);
     GemmArgs args;
-    args.resident = gemm_resident_chosen(M, N, K, bits) && gemm_resident_epilogue(K, bits, epi, ydt);
+    args.resident = choice.resident;
+    args.height = choice.height;
+    args.split = choice.split;
+    args.keep_output = choice.keep_output;
     args.x_tiled = x_tiled;
     args.x_scale = x_scale;
     args.x_corr = x_corr;
@@ -162,21 +194,6 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     // 2 is the best of 1 .. 8 at K = 1152 and 3 the best of 2 .. 6 at K = 4608 (545 against
     // 557 us with 8-bit weights, no difference at M = 65536 or with 4-bit weights).
     args.x_frags = args.m_tiles * (kTileM / kFragRows);
-    const qc_epilogue applied = ydt == QC_OUT_I32_ACC ? QC_EPI_NONE : epi;
-    args.height = args.resident ? 4 : ring_height(M, args.n_tiles, K, applied);
-    args.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, args.height, epi);
-    // Whole rows of 32 bits past the caches: the more blocks a CU holds the worse their stores drain (us at 256
-    // and 192 tokens: 39510 x 1152 x 4608 274 324, 105656 x 784 x 1152 210 229; of less than 192 MB the spread over the CUs
-    // counts: 42 MB 9149 x 4608 x 1152 58.1 49.0, 43 MB 5597 x 592 x 1920, 4 bit, 128 tokens 20.0 17.6, 29000 x 4608 x 1152 147 147).
-    // Of more than 400 MB through the caches too (250000 x 192 x 1152 287 247, 100000 x 384 x 2304, 4 bit, GELU 257 222).
-    const int64_t out32 = ydt == QC_OUT_BF16 || N % 4 ? 0 : 4 * M * N;
-    if (args.height != 4 && (out32 > (int64_t)400 << 20 || (out32 > (int64_t)192 << 20 && !args.keep_output))) {
-        args.height = 4;
-        args.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, 4, epi);
-    }
-    const int split = args.resident ? 0 : split_height(M, args.n_tiles, args.KF, bits);
-    args.split = split == 2 || (split == 4 && (args.KF >= 72 || ydt != QC_OUT_F32 || !keep_f32_output(M, N, K, 4, epi)));
-    if (args.split) { args.height = split; args.keep_output = false; }
     if (args.height != 4) args.m_tiles = (int)((M + kWaveM * args.height - 1) / (kWaveM * args.height));
     args.stream_edges = stream_bf16_edges(M, N);
     args.group_m = args.n_tiles > 16 ? 8 : (args.KF >= 36 ? 3 : 2);

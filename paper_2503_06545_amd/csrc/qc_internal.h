@@ -244,10 +244,19 @@ bool gemm_resident_fits(int64_t K, int bits);
 // whether launch_gemm picks the resident kernel for this problem by itself
 bool gemm_resident_chosen(int64_t M, int64_t N, int64_t K, int bits);
 int gemm_resident_blocks();
+// what launch_gemm decides for a problem that is not for the few-token kernel
+struct GemmChoice {
+    bool resident;      // the kernel that keeps its weight tile in LDS; otherwise the ring
+    int height;         // of the ring's tiles, in 64 tokens
+    bool split;         // two groups of wavefronts, half of the reduction each
+    bool keep_output;   // f32 output through the caches
+};
+GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt);
 
 // The kernels for few tokens (qc_small.hip).  gemm_small_chosen: launch_gemm picks them for this
 // problem by itself; qlinear_small_chosen: quantization and GEMM in one launch.
 bool gemm_small_chosen(int64_t M, int64_t N);
+int gemm_small_tokens(int64_t M, int64_t N);   // tokens of its tiles
 hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                              const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                              int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
@@ -255,6 +264,10 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
 // how a linear quantizes its activations
 enum QuantScheme { kQuantToken = 0, kQuantRotated = 1, kQuantAsym = 2, kQuantTensor = 3 };
 bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K, qc_dtype xdt, QuantScheme scheme);
+int qlinear_small_tokens(int64_t M, int64_t N, int64_t K, qc_dtype xdt, QuantScheme scheme);
+// how the activation quantizer that writes the GEMM's codes treats the caches: 0 ordinary loads and stores, 1 non-temporal
+// loads, 2 non-temporal stores, 3 both
+int quant_cache_policy(int64_t M, int64_t K, qc_dtype xdt, QuantScheme scheme);
 // x_corr, w_rowsum: asymmetric only; rot_block: rotated only
 hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale, float *x_corr,
                                 const uint8_t *w_packed, const float *w_scale, const int32_t *w_rowsum, const float *bias,

@@ -524,6 +524,11 @@ hipError_t launch_quant_act_asym(const void *X, qc_dtype xdt, int64_t M, int64_t
     return xdt == QC_BF16 ? launch((const uint16_t *)X) : launch((const float *)X);
 }
 
+int quant_cache_policy(int64_t M, int64_t K, qc_dtype xdt, QuantScheme scheme) {
+    if (scheme == kQuantTensor || !quant_vector_path(K) || units_per_lane(M, K) == 1) return kCachePlain;
+    return cache_policy(M, K, xdt == QC_BF16 ? 2 : 4);
+}
+
 bool quant_rotation_supported(int64_t K, int rot_block) {
     if (rot_block != 16 && rot_block != 32 && rot_block != 64 && rot_block != 128) return false;
     return K % rot_block == 0 && quant_vector_path(K);

@@ -772,6 +772,8 @@ SmallArgs small_args(uint8_t *x_tiled, float *x_scale, const uint8_t *w_packed, 
 
 bool gemm_small_chosen(int64_t M, int64_t N) { return pick_tile(M, N) >= 0; }
 
+int gemm_small_tokens(int64_t M, int64_t N) { return kTiles[pick_tile(M, N)].tokens; }
+
 hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const uint8_t *w_packed,
                              const float *w_scale, const float *bias, void *Y, int64_t M, int64_t N,
                              int64_t K, int bits, qc_epilogue epi, qc_out ydt, const float *x_corr,
@@ -789,6 +791,10 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
 
 bool qlinear_small_chosen(int64_t M, int64_t N, int64_t K, qc_dtype xdt, QuantScheme scheme) {
     return pick_fused_shape(M, N, K, xdt == QC_BF16 ? 2 : 4, scheme) >= 0;
+}
+
+int qlinear_small_tokens(int64_t M, int64_t N, int64_t K, qc_dtype xdt, QuantScheme scheme) {
+    return kFusedShapes[pick_fused_shape(M, N, K, xdt == QC_BF16 ? 2 : 4, scheme)].tile.tokens;
 }
 
 hipError_t launch_qlinear_small(const void *X, qc_dtype xdt, uint8_t *x_tiled, float *x_scale, float *x_corr,

@@ -76,3 +76,19 @@ def test_which_problems_take_the_few_token_kernel():
         for K in (64, 1152, 4608):
             assert qc.qc_debug_gemm_kernel(most, K, N, 8) == 3, (N, K)
             assert qc.qc_debug_gemm_kernel(most + 1, K, N, 8) != 3, (N, K)
+
+
+def test_the_plan_of_a_linear_agrees_with_the_kernel_it_takes():
+    for M, K, N, bits in ((2, 1152, 6912, 8), (1000, 64, 1000, 8), (4099, 1000, 1301, 8), (16384, 1152, 3456, 8), (131072, 1152, 3456, 4)):
+        which = {1: "ring", 2: "resident", 3: "few"}[qc.qc_debug_gemm_kernel(M, K, N, bits)]
+        assert qc.linear_plan(M, K, N, bits)["kernel"] == which
+    assert qc.linear_plan(2, 1152, 6912) == {"kernel": "few", "tokens": 16, "split": False, "kept": False, "fused": True,
+                                             "nt_loads": False, "nt_stores": False}
+    assert qc.linear_plan(65536, 1152, 4608, epi="gelu_erf")["kernel"] == "ring"      # the epilogue decides too
+    assert qc.linear_plan(131072, 1152, 3456, out="i32")["kernel"] == "resident"
+    assert qc.linear_plan(131072, 768, 4608, out="f32")["kernel"] == "ring"           # and the output's type
+    assert qc.linear_plan(1024, 4608, 1152)["split"] and qc.linear_plan(1024, 4608, 1152)["tokens"] == 128
+    assert qc.linear_plan(8192, 1152, 1152, out="f32")["kept"] and not qc.linear_plan(1200, 1152, 1152, out="f32")["kept"]
+    for bad in (dict(M=0), dict(K=0), dict(bits=3), dict(K=1153, bits=4), dict(K=1000, scheme="rot"), dict(K=1000, scheme="asym")):
+        with pytest.raises(qc.QcError):
+            qc.linear_plan(**{"M": 4096, "K": 1152, "N": 1152, **bad})
