@@ -9,16 +9,19 @@
 // hence two forms of one kernel:
 //   * Two launches: at most one block per CU (256); a second, single-block launch adds the blocks'
 //     partial sums.
-//   * One launch, for small tensors: at most 128 blocks, of which the one that sees all partial
+//   * One launch, for small tensors: at most 64 blocks, of which the one that sees all partial
 //     sums finishes the job (finish_here() says how, without a counter that somebody would have to
 //     clear).  What it saves is a launch, 3 us of host time (a call takes 4.1 and 7.1 us there); what it costs on
 //     the GPU are the device fence of each block, the blocks' reading of each other's records, and, with
 //     the size, that fewer blocks read.  Two chunks a block (one from five earlier tensors on), 16 blocks at least while there are as many
-//     chunks: with 32 blocks at most it took 5.6 instead of 5.3 us for a latent delta of 390000 elements, 7.7
-//     instead of 6.6 for a similarity of 1.2 million.  Each operation's limit (kOneMost) lies where it costs
-//     no more than two launches, for the similarity up to 1 us, over inputs read again and again too (one launch for a latent delta of
-//     540000 to 715000 elements 6 to 7.4 us where two took 4.6).  us per call in a graph, four sets of inputs in
-//     turn, two launches and one:
+//     chunks: with 32 blocks at most it took 5.6 instead of 5.3 us for a latent delta of 390000 elements, 7.5
+//     instead of 6.6 for a similarity of 1.2 million; with more than 64, whose records a lane reads in two goes, 7.3 to 7.7 instead of
+//     6.2 to 6.4 for 1.18 to 1.31 million bf16 elements read again and again.  Each operation's limit (kOneMost) lies where it costs
+//     no more than two launches, over inputs read again and again too (one launch for a latent delta of
+//     540000 to 715000 elements 6 to 7.4 us where two took 4.6; for a binary32 similarity of 400000 5.5 and 4.5, of 655360 7.1 and
+//     4.6); only for the similarity of bf16 features, which a step asks for from the host, it lies where one launch takes what
+//     the host needs for two: 6.4 us for 1.31 million, where two launches take 5.0 in a graph.  us per call in a graph,
+//     four sets of inputs in turn, two launches and one:
 //       latent delta     65536 4.5 3.7   300000 5.4 4.6   500000 5.7 5.6   700000 6.0 6.3   1 million 6.2 7.4
 //       similarity bf16  100000 4.8 4.0   300000 4.7 4.7   600000 5.4 5.6   1.3 million 5.6 6.5   1.7 million 5.4 7.4
 //       frame gradient   binary32 65536 4.1 3.4   250000 4.2 4.2   400000 4.0 5.1; bf16 500000 4.4 4.5   900000 4.2 5.5
@@ -34,8 +37,8 @@ namespace {
 constexpr int kFinalThreads = 64;   // the second launch
 constexpr int kMaxBlocks = 256;     // two launches: one block per CU
 constexpr int kOneThreads = 512;    // one launch
-constexpr int kOneFew = 16, kOneBlocks = 128;
-static_assert(kMaxBlocks % kFinalThreads == 0 && kOneBlocks % 64 == 0, "whole wavefronts of blocks in the combines");
+constexpr int kOneFew = 16, kOneBlocks = 64;
+static_assert(kMaxBlocks % kFinalThreads == 0 && kOneBlocks <= 64, "whole wavefronts of blocks, a lane per block in the combines");
 
 // the workspaces: a double per sum and block of the two-launch form
 constexpr size_t kDeltaBytes = kMaxBlocks * 2 * sizeof(double), kSimilarityBytes = kMaxBlocks * 3 * sizeof(double);
@@ -120,33 +123,17 @@ __device__ inline bool finish_here(double (&v)[COUNT], uint64_t *records, uint64
         __hip_atomic_store(r + COUNT, check ? check : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");   // the stores before anybody's loads below
-    constexpr int kPer = kOneBlocks / 64;   // records a lane reads
-    uint64_t word[kPer][kWords];
+    uint64_t *const mine = records + kWords * (lane < blocks ? lane : 0);   // the record this lane reads
+    uint64_t word[kWords], check = 0;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int b = lane + 64 * i;
-        if (i > 0 && 64 * i >= blocks) break;   // uniform
+    for (int c = 0; c < kWords; ++c) word[c] = __hip_atomic_load(mine + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int c = 0; c < kWords; ++c)
-            word[i][c] = __hip_atomic_load(records + kWords * (b < blocks ? b : 0) + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int c = 0; c < COUNT; ++c) {
+        check += term_of(nonce, c, word[c]);
+        v[c] = lane < blocks ? __longlong_as_double((long long)word[c]) : 0.0;
     }
-    bool present = true;
-#pragma unroll
-    for (int c = 0; c < COUNT; ++c) v[c] = 0.0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        if (i > 0 && 64 * i >= blocks) break;
-        uint64_t check = 0;
-#pragma unroll
-        for (int c = 0; c < COUNT; ++c) {
-            check += term_of(nonce, c, word[i][c]);
-            v[c] += lane + 64 * i < blocks ? __longlong_as_double((long long)word[i][c]) : 0.0;
-        }
-        present = present && (check ? check : 1) == word[i][COUNT];
-    }
-    if (!__all(present)) return false;
-    for (int b = lane; b < blocks; b += 64)
-        __hip_atomic_store(records + kWords * b + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!__all((check ? check : 1) == word[COUNT])) return false;
+    if (lane < blocks) __hip_atomic_store(mine + COUNT, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int c = 0; c < COUNT; ++c) v[c] = wave_sum(v[c]);
     return true;
@@ -252,7 +239,7 @@ struct SimilarityOp {
     static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = THREADS, kUnroll = 4, kOneUnroll = 2, kOneChunks = 2, kOuts = 4;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kSimilarityBytes;
-    static constexpr int64_t kOneMost = (5 << 19) / sizeof(T);
+    static constexpr int64_t kOneMost = sizeof(T) == 4 ? 9 << 15 : 5 << 18;
     const T *a, *b;
     struct Regs { Pack<T> x, y; };
     __device__ void load(Regs &r, int64_t i) const { r.x.stream(a + kElems * i); r.y.stream(b + kElems * i); }
@@ -418,7 +405,9 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, int64
     }
 }
 
-// one wavefront: fixed-order combine of the partial sums, four blocks' a lane
+// one wavefront: fixed-order combine of the partial sums, four blocks' a lane (with a thread per block, and the four wavefronts'
+// sums through LDS, us in a graph: latent delta of 4 million 6.34 6.20, frame gradient 5.30 5.20, variation over 8 tensors of 1 million
+// 8.71 8.29, similarity of 4 million 6.67 6.56; nowhere faster)
 template <typename Op>
 __global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__restrict__ partials, int count,
                                                               float *__restrict__ out) {

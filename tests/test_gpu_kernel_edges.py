@@ -428,6 +428,26 @@ def test_similarity_on_both_sides_of_its_change_of_threads(n):
     assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
 
 
+@pytest.mark.parametrize("dtype,n,one_launch", [("f32", 9 << 15, True), ("f32", (9 << 15) + 1, False), ("f32", 482354, False),
+                                                ("f32", 653550, False), ("bf16", 5 << 18, True), ("bf16", (5 << 18) + 1, False)])
+def test_similarity_in_one_launch_and_in_two(dtype, n, one_launch):
+    """Which form a size takes shows in the workspace: one launch ends with zeros in its blocks' check words, every fourth
+    of 64 at most; two leave three sums a block, none of them zero.  A used workspace and one of arbitrary bytes."""
+    rng = np.random.default_rng(n)
+    a = rng.standard_normal(n).astype(np.float32)
+    b = (a + 0.5 * rng.standard_normal(n)).astype(np.float32)
+    if dtype == "bf16":
+        a, b = synth.to_bf16_bits(a), synth.to_bf16_bits(b)
+    ref = np.asarray(oracle.layer_similarity(a, b), np.float64)
+    ws = torch.randint(1, 256, (qc.qc_layer_similarity_workspace_bytes(n),), dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        got = qc.layer_similarity_t(dev(a), dev(b), workspace=ws).cpu().numpy()
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+        checks = ws.view(torch.int64)[3:4 * 64:4].cpu()
+        zeros = int((checks == 0).sum())
+        assert zeros == min(64, -(-n // (8192 if dtype == "f32" else 16384))) if one_launch else zeros == 0
+
+
 @pytest.mark.parametrize("extra", [0, 1, 9])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
