@@ -92,3 +92,25 @@ def test_the_plan_of_a_linear_agrees_with_the_kernel_it_takes():
     for bad in (dict(M=0), dict(K=0), dict(bits=3), dict(K=1153, bits=4), dict(K=1000, scheme="rot"), dict(K=1000, scheme="asym")):
         with pytest.raises(qc.QcError):
             qc.linear_plan(**{"M": 4096, "K": 1152, "N": 1152, **bad})
+
+
+MB = 1 << 20
+
+
+@pytest.mark.parametrize("x", ["bf16", "f32"])
+@pytest.mark.parametrize("scheme", ["token", "rot", "asym"])
+def test_which_quantizers_load_past_the_caches(x, scheme):
+    """Whole lines of 128 B from 160 MB of input and codes on, other rows, whose shared lines would be fetched twice, from
+    224 MB; the codes are stored past the caches from 288 MB of them on."""
+    size = 3 if x == "bf16" else 5
+    for K, from_mb in ((1152, 160), (4608, 160), (544, 224), (1200, 224), (1552, 224), (2576, 224)):
+        if x == "f32" and K == 544:
+            continue                                   # 17 whole lines
+        for mb, loads in ((from_mb - 8, False), (from_mb + 8, True), (280, True)):
+            plan = qc.linear_plan(mb * MB // (size * K), K, 56, x=x, scheme=scheme)
+            assert plan["nt_loads"] == loads and not plan["nt_stores"], (K, mb)
+        plan = qc.linear_plan(300 * MB // K, K, 1152, x=x, scheme=scheme)
+        assert plan["nt_stores"] and plan["nt_loads"] == (from_mb == 160)
+    for M, K, N in ((105713, 544, 56), (26425, 2576, 45), (39840, 1552, 1152)):
+        assert not qc.linear_plan(M, K, N)["nt_loads"]
+    assert qc.linear_plan(65536, 1152, 4608, epi="gelu_tanh")["nt_loads"]
