@@ -58,6 +58,23 @@ def test_rotated_rows_that_end_within_a_group(M, K, rot_block, dtype):
     assert bits_equal(sx.cpu().numpy(), s_ref) and np.array_equal(qx.cpu().numpy(), q_ref)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,rot_block", [(147473, 64, 32), (73729, 128, 16), (73731, 128, 128), (36865, 256, 64), (24577, 384, 128),
+                                           (18433, 512, 16), (8, 6272, 128), (3, 9216, 16)])
+def test_rotated_rows_shorter_than_a_wavefronts_columns(M, K, rot_block, dtype):
+    """Rows on three and nine groups a lane, of which one, two, all or one of the next slice are the row's: the first and
+    the last rows against the oracle."""
+    rng = np.random.default_rng(M + K + rot_block)
+    x = random_x(rng, min(M, 40), K, dtype)
+    X = dev(x).repeat(-(-M // len(x)), 1)[:M].contiguous()
+    q_ref, s_ref = oracle.quant_act_rot(x, rot_block, 8)
+    qx, sx = qc.quant_act_t(X, 8, rot_block)
+    torch.cuda.synchronize()
+    n = len(x)
+    assert bits_equal(sx[:n].cpu().numpy(), s_ref) and np.array_equal(qx[:n].cpu().numpy(), q_ref)
+    assert torch.equal(sx[n:], sx[:-n]) and torch.equal(qx[n:], qx[:-n])
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N", [
     (1, 16, 1), (2, 9216, 40), (3, 6144, 33), (16, 1536, 4100), (16, 1552, 70), (17, 1152, 128), (31, 1280, 2050),
