@@ -56,13 +56,17 @@ constexpr int kCus = 256;
 // tiles of 256 the blocks' own chains of waits count: two tiles cost little more than one (510 against
 // 400), one of 192 saves an eighth of its quarter.  Beyond, multiplications do, 57 for each 64 tokens, and what a
 // lower tile fetches more for them (none while the reduction is short), less what the more blocks per CU hide
-// of a GELU.
+// of a GELU.  Those calls read the same codes and weights again and again.  Where these come from beyond the L2s, two tiles
+// of 128 with a long reduction lose to one of 256 what they gain otherwise (the whole linear at 256 and 128, the same operands again
+// and again | four sets in turn: 12000 x 3072 x 576 42.3 42.7 | 45.3 49.3, 6400 x 4608 x 1152 49.6 49.5 | 51.9 57.2, 6145 x 3360 x
+// 1152 39.2 38.6 | 40.3 45.8; but 6400 x 1536 x 1152 23.1 22.3 | 21.9 21.4; over 87 drawn calls +1 % | -5 %).
 static int ring_cost(int h, int64_t per_cu, int64_t K, qc_epilogue epi) {
     const bool gelu = epi != QC_EPI_NONE, brief = K <= 384, lengthy = K > 1500;
     constexpr int kFull[] = {400, 510, 680}, kMid[] = {350, 440, 540, 666}, kHalf[] = {310, 380, 450, 535, 630, 707};
     if (h == 4 && per_cu <= 3) return kFull[per_cu - 1];
     if (h == 3 && per_cu <= 4) return kMid[per_cu - 1];
-    if (h == 2 && per_cu <= 6) return kHalf[per_cu - 1] * (per_cu == 1 ? 100 : lengthy ? 105 : gelu || brief ? 95 : 100) / 100;
+    if (h == 2 && per_cu <= 6)
+        return kHalf[per_cu - 1] * (per_cu == 1 ? 100 : per_cu == 2 && K > 2000 ? 108 : lengthy ? 105 : gelu || brief ? 95 : 100) / 100;
     int more = 100;
     if (h == 3) more = lengthy ? 102 : per_cu < 12 ? 98 : 101;
     if (h == 2) more = brief ? 100 : lengthy ? 116 : gelu ? 106 : 113;

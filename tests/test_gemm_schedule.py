@@ -125,3 +125,11 @@ def test_the_longest_rows_that_are_quantized_in_the_launch_of_the_gemm(M, N, x, 
     assert not qc.linear_plan(M, most + 2, N, bits, x=x)["fused"]
     if (M, x) in ((301, "f32"), (687, "f32")):   # where the quantizer alone costs more, one launch goes on
         assert qc.linear_plan(M, 3072, N, bits, x=x, scheme="asym")["fused"]
+
+
+@pytest.mark.parametrize("bits,M,K,N,tokens", [
+    (8, 12000, 3072, 576, 256), (8, 6400, 4608, 1152, 256), (8, 1775, 4608, 4608, 256), (8, 2767, 4528, 2797, 256),   # one tile of 256 to a CU
+    (8, 6400, 1536, 1152, 128), (8, 6400, 1152, 1152, 128), (8, 5120, 4608, 1152, 192), (8, 7390, 1152, 1152, 192)])
+def test_heights_of_tiles_that_are_one_or_two_to_a_cu(bits, M, K, N, tokens):
+    plan = qc.linear_plan(M, K, N, bits)
+    assert plan["kernel"] == "ring" and not plan["split"] and plan["tokens"] == tokens
