@@ -50,61 +50,6 @@ int gemm_resident_blocks() { return kResBlocks; }
 
 constexpr int kCus = 256;
 
-// What a CU takes for `per_cu` of the ring kernel's tiles of 64 h tokens x 128 channels, in hundredths of what it
-// takes for 64 tokens of a tile of 256 that it has to itself.  Read off some 8000 calls of bf16 output drawn
-// over K = 128 .. 4608, 300 to 131072 tokens and 100 to 4608 channels, each at every height.  Up to three
-// tiles of 256 the blocks' own chains of waits count: two tiles cost little more than one (510 against
-// 400), one of 192 saves an eighth of its quarter.  Beyond, multiplications do, 57 for each 64 tokens, and what a
-// lower tile fetches more for them (none while the reduction is short), less what the more blocks per CU hide
-// of a GELU.  Those calls read the same codes and weights again and again.  Where these come from beyond the L2s, two tiles
-// of 128 with a long reduction lose to one of 256 what they gain otherwise (the whole linear at 256 and 128, the same operands again
-// and again | four sets in turn: 12000 x 3072 x 576 42.3 42.7 | 45.3 49.3, 6400 x 4608 x 1152 49.6 49.5 | 51.9 57.2, 6145 x 3360 x
-// 1152 39.2 38.6 | 40.3 45.8; but 6400 x 1536 x 1152 23.1 22.3 | 21.9 21.4; over 87 drawn calls +1 % | -5 %).
-static int ring_cost(int h, int64_t per_cu, int64_t K, qc_epilogue epi) {
-    const bool gelu = epi != QC_EPI_NONE, brief = K <= 384, lengthy = K > 1500;
-    constexpr int kFull[] = {400, 510, 680}, kMid[] = {350, 440, 540, 666}, kHalf[] = {310, 380, 450, 535, 630, 707};
-    if (h == 4 && per_cu <= 3) return kFull[per_cu - 1];
-    if (h == 3 && per_cu <= 4) return kMid[per_cu - 1];
-    if (h == 2 && per_cu <= 6)
-        return kHalf[per_cu - 1] * (per_cu == 1 ? 100 : per_cu == 2 && K > 2000 ? 108 : lengthy ? 105 : gelu || brief ? 95 : 100) / 100;
-    int more = 100;
-    if (h == 3) more = lengthy ? 102 : per_cu < 12 ? 98 : 101;
-    if (h == 2) more = brief ? 100 : lengthy ? 116 : gelu ? 106 : 113;
-    return (int)(h * (per_cu < 100000 ? per_cu : 100000) * 57 * more / 100);
-}
-
-// Height of the ring kernel's tiles in 64 tokens: the one whose tiles spread best over the CUs.  Full
-// height, full or half by the rule before, and this rule, us: K = 1152, tiles of 256 / 192 / 128 tokens:
-// 144 / 198 / 288 9.7 9.8 8.5, 351 / 468 / 693 16.3 16.3 13.6, 216 / 297 / 432 10.6 10.7 9.6; K = 4608: 198 of 192
-// tokens 27.0 27.0 23.1, 288 / 387 / 576 47.6 43.9 39.7, 351 / 468 / 693 50.7 51.3 43.5.  Over the drawn calls, the GEMM alone:
-// 4 to 6 % less time, slower by more than 3 % in 2 %.
-static int ring_height(int64_t M, int n_tiles, int64_t K, qc_epilogue epi) {
-    int best = 4, least = 0;
-    for (int h = 4; h >= 2; --h) {
-        const int64_t tiles = (M + kWaveM * h - 1) / (kWaveM * h) * n_tiles;
-        const int cost = ring_cost(h, (tiles + kCus - 1) / kCus, K, epi);
-        if (h == 4 || cost < least) { best = h; least = cost; }
-    }
-    return best;
-}
-
-// Tiles of which a CU gets one at most leave its SIMDs a wavefront each, which waits out every load, unpacking and
-// barrier on its own.  Eight wavefronts in two groups, each with half of the reduction, cover each other's waits and
-// add their sums up through LDS at the end, which the reduction has to be worth.  Ring kernel, and so, us:
-// 4 bit, tiles of 128 tokens, K = 4608: 96 25.3 18.8, 256 26.0 20.0; K = 1152: 96 8.9 7.8, 256 9.9 9.1; K = 768 7.1 6.6; but
-// K = 384 5.0 5.2.  4 bit, tiles of 256: K = 4608: 144 28.4 25.6, 256 39.0 31.8; K = 2304: 144 16.6 16.1; but K = 1536
-// 12.5 12.7.  8 bit, tiles of 128 (nothing to unpack): K = 4608: 96 17.5 15.6, 144 18.8 17.1; K = 2304: 126 10.9 10.5;
-// but K = 1536 8.7 8.8, and 256 tiles K = 2304 12.6 13.1, K = 6144 25.9 26.6.  With two tiles of 128 or 256 to a CU the two
-// hide each other's waits and the exchange is lost: 8192 x 4608 x 1152, 288 tiles of 256, 41.9 52.6.
-// The split kernels have no form that keeps f32 output in the caches: where tiles of 256 should, it takes K = 4608 (7168 x 4608 x
-// 1152 41.5 38.2, but 4096 x 2304 x 2048 24.3 28.2).  Height of the tiles to split, 0: none.
-static int split_height(int64_t M, int n_tiles, int KF, int bits) {
-    const int64_t half = (M + 2 * kWaveM - 1) / (2 * kWaveM) * n_tiles, full = (M + kTileM - 1) / kTileM * n_tiles;
-    if (bits == 8) return half <= 160 && KF >= 36 ? 2 : 0;
-    if (half <= kCus) return KF >= 12 ? 2 : 0;
-    return full <= kCus && KF >= 36 ? 4 : 0;
-}
-
 // 32-bit output: non-temporal stores write it to memory at once, ordinary ones into the last-level
 // cache, where the next layer finds it.  Ordinary ones win from 24 MB on, 15 MB with lower
 // tiles (below, writing back the L2s at the end of the launch weighs more; half the height, K = 1152,
@@ -128,6 +73,66 @@ static bool keep_f32_output(int64_t M, int64_t N, int64_t K, int height, qc_epil
     return out >= from * MB && (out + codes <= most * MB || (8 * codes <= out && out <= 400 * MB) || (K <= 576 && 16 * codes <= out));
 }
 
+// What a CU takes for `per_cu` of the ring kernel's tiles of 64 h tokens x 128 channels, in hundredths of what it
+// takes for 64 tokens of a tile of 256 that it has to itself.  Read off some 8000 calls of bf16 output drawn
+// over K = 128 .. 4608, 300 to 131072 tokens and 100 to 4608 channels, each at every height.  Up to three
+// tiles of 256 the blocks' own chains of waits count: two tiles cost little more than one (510 against
+// 400), one of 192 saves an eighth of its quarter.  Beyond, multiplications do, 57 for each 64 tokens, and what a
+// lower tile fetches more for them (none while the reduction is short), less what the more blocks per CU hide
+// of a GELU.  Those calls read the same codes and weights again and again.  Where these come from beyond the L2s, two tiles
+// of 128 with a long reduction lose to one of 256 what they gain otherwise (the whole linear at 256 and 128, the same operands again
+// and again | four sets in turn: 12000 x 3072 x 576 42.3 42.7 | 45.3 49.3, 6400 x 4608 x 1152 49.6 49.5 | 51.9 57.2, 6145 x 3360 x
+// 1152 39.2 38.6 | 40.3 45.8; but 6400 x 1536 x 1152 23.1 22.3 | 21.9 21.4; over 87 drawn calls +1 % | -5 %).
+// extra: hundredths of the cost for what ring_height() knows of the stores.
+static int ring_cost(int h, int64_t per_cu, int64_t K, qc_epilogue epi, int extra) {
+    const bool gelu = epi != QC_EPI_NONE, brief = K <= 384, lengthy = K > 1500;
+    constexpr int kFull[] = {400, 510, 680}, kMid[] = {350, 440, 540, 666}, kHalf[] = {310, 380, 450, 535, 630, 707};
+    if (h == 4 && per_cu <= 3) return kFull[per_cu - 1];
+    if (h == 3 && per_cu <= 4) return kMid[per_cu - 1] * extra / 100;
+    if (h == 2 && per_cu <= 6)
+        return kHalf[per_cu - 1] * (per_cu == 1 ? 100 : per_cu == 2 && K > 2000 ? 108 : lengthy ? 105 : gelu || brief ? 95 : 100) / 100 * extra / 100;
+    int more = 100;
+    if (h == 3) more = lengthy ? 102 : per_cu < 12 ? 98 : 101;
+    if (h == 2) more = brief ? 100 : lengthy ? 116 : gelu ? 106 : 113;
+    return (int)(h * (per_cu < 100000 ? per_cu : 100000) * 57 * more / 100 * extra / 100);
+}
+
+// Height of the ring kernel's tiles in 64 tokens: the one whose tiles spread best over the CUs.  Full
+// height, full or half by the rule before, and this rule, us: K = 1152, tiles of 256 / 192 / 128 tokens:
+// 144 / 198 / 288 9.7 9.8 8.5, 351 / 468 / 693 16.3 16.3 13.6, 216 / 297 / 432 10.6 10.7 9.6; K = 4608: 198 of 192
+// tokens 27.0 27.0 23.1, 288 / 387 / 576 47.6 43.9 39.7, 351 / 468 / 693 50.7 51.3 43.5.  Over the drawn calls, the GEMM alone:
+// 4 to 6 % less time, slower by more than 3 % in 2 %.
+// f32 output past the caches: the more blocks a CU holds the worse their stores drain (the whole linear at 256 and 128, the same
+// operands again and again | four sets in turn: 2850 x 1152 x 4608 GELU (erf) 34.1 38.3 | 28.8 34.0, 3649 x 352 x 3456 the same 23.4
+// 27.5 | 22.4 27.1, 11670 x 1152 x 1152 38.6 43.4; over 1400 drawn calls -1 % | -3 %).
+static int ring_height(int64_t M, int64_t N, int n_tiles, int64_t K, qc_epilogue epi, qc_out ydt) {
+    int best = 4, least = 0;
+    for (int h = 4; h >= 2; --h) {
+        const int64_t tiles = (M + kWaveM * h - 1) / (kWaveM * h) * n_tiles;
+        const bool streamed = ydt == QC_OUT_F32 && !keep_f32_output(M, N, K, h, epi);
+        const int cost = ring_cost(h, (tiles + kCus - 1) / kCus, K, epi, h == 2 && streamed ? 106 : 100);
+        if (h == 4 || cost < least) { best = h; least = cost; }
+    }
+    return best;
+}
+
+// Tiles of which a CU gets one at most leave its SIMDs a wavefront each, which waits out every load, unpacking and
+// barrier on its own.  Eight wavefronts in two groups, each with half of the reduction, cover each other's waits and
+// add their sums up through LDS at the end, which the reduction has to be worth.  Ring kernel, and so, us:
+// 4 bit, tiles of 128 tokens, K = 4608: 96 25.3 18.8, 256 26.0 20.0; K = 1152: 96 8.9 7.8, 256 9.9 9.1; K = 768 7.1 6.6; but
+// K = 384 5.0 5.2.  4 bit, tiles of 256: K = 4608: 144 28.4 25.6, 256 39.0 31.8; K = 2304: 144 16.6 16.1; but K = 1536
+// 12.5 12.7.  8 bit, tiles of 128 (nothing to unpack): K = 4608: 96 17.5 15.6, 144 18.8 17.1; K = 2304: 126 10.9 10.5;
+// but K = 1536 8.7 8.8, and 256 tiles K = 2304 12.6 13.1, K = 6144 25.9 26.6.  With two tiles of 128 or 256 to a CU the two
+// hide each other's waits and the exchange is lost: 8192 x 4608 x 1152, 288 tiles of 256, 41.9 52.6.
+// The split kernels have no form that keeps f32 output in the caches: where tiles of 256 should, it takes K = 4608 (7168 x 4608 x
+// 1152 41.5 38.2, but 4096 x 2304 x 2048 24.3 28.2).  Height of the tiles to split, 0: none.
+static int split_height(int64_t M, int n_tiles, int KF, int bits) {
+    const int64_t half = (M + 2 * kWaveM - 1) / (2 * kWaveM) * n_tiles, full = (M + kTileM - 1) / kTileM * n_tiles;
+    if (bits == 8) return half <= 160 && KF >= 36 ? 2 : 0;
+    if (half <= kCus) return KF >= 12 ? 2 : 0;
+    return full <= kCus && KF >= 36 ? 4 : 0;
+}
+
 // Rows of bf16 that are no multiple of 16 B long, and partly filled tiles: through the caches while the
 // output fits the last-level cache, past them beyond (N = 3460, K = 1152, ordinary and non-temporal: 113 MB
 // 72.3 78.6 us, 454 MB 333 287; N = 1156: 303 MB 286 253).  With 32-bit output a piece covers half of the
@@ -143,7 +148,7 @@ GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue ep
         c.height = 4;
         return c;
     }
-    c.height = ring_height(M, n_tiles, K, ydt == QC_OUT_I32_ACC ? QC_EPI_NONE : epi);
+    c.height = ring_height(M, N, n_tiles, K, ydt == QC_OUT_I32_ACC ? QC_EPI_NONE : epi, ydt);
     c.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, c.height, epi);
     // Whole rows of 32 bits past the caches: the more blocks a CU holds the worse their stores drain (us at 256
     // and 192 tokens: 39510 x 1152 x 4608 274 324, 105656 x 784 x 1152 210 229; of less than 192 MB the spread over the CUs

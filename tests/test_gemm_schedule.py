@@ -133,3 +133,12 @@ def test_the_longest_rows_that_are_quantized_in_the_launch_of_the_gemm(M, N, x, 
 def test_heights_of_tiles_that_are_one_or_two_to_a_cu(bits, M, K, N, tokens):
     plan = qc.linear_plan(M, K, N, bits)
     assert plan["kernel"] == "ring" and not plan["split"] and plan["tokens"] == tokens
+
+
+@pytest.mark.parametrize("M,K,N,epi,out,tokens,kept", [
+    (2850, 1152, 4608, "gelu_erf", "f32", 256, False), (3649, 352, 3456, "gelu_erf", "f32", 256, False),
+    (11670, 1152, 1152, "gelu_erf", "f32", 256, False), (2850, 1152, 4608, "gelu_erf", "bf16", 128, False),
+    (800, 1152, 4608, "none", "f32", 128, False), (10535, 1152, 1152, "gelu_tanh", "f32", 128, True)])
+def test_heights_of_tiles_whose_f32_output_goes_past_the_caches(M, K, N, epi, out, tokens, kept):
+    plan = qc.linear_plan(M, K, N, epi=epi, out=out)
+    assert (plan["kernel"], plan["tokens"], plan["kept"]) == ("ring", tokens, kept)
