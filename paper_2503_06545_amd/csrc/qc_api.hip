@@ -425,7 +425,7 @@ extern "C" int qc_debug_linear_plan(int64_t M, int64_t K, int64_t N, qc_dtype xd
         plan[1] = gemm_small_tokens(M, N);
         return 0;
     }
-    const GemmChoice c = choose_gemm(M, N, K, bits, epi, ydt);
+    const GemmChoice c = choose_gemm(M, N, K, bits, epi, ydt, how == kQuantAsym);
     plan[0] = c.resident ? kGemmResident : kGemmRing;
     plan[1] = c.resident ? kRoundTokens : kWaveM * c.height;
     plan[2] = c.split;

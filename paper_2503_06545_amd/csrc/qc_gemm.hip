@@ -83,7 +83,7 @@ static bool keep_f32_output(int64_t M, int64_t N, int64_t K, int height, qc_epil
 // of 128 with a long reduction lose to one of 256 what they gain otherwise (the whole linear at 256 and 128, the same operands again
 // and again | four sets in turn: 12000 x 3072 x 576 42.3 42.7 | 45.3 49.3, 6400 x 4608 x 1152 49.6 49.5 | 51.9 57.2, 6145 x 3360 x
 // 1152 39.2 38.6 | 40.3 45.8; but 6400 x 1536 x 1152 23.1 22.3 | 21.9 21.4; over 87 drawn calls +1 % | -5 %).
-// extra: hundredths of the cost for what ring_height() knows of the stores.
+// extra: hundredths of the cost for what ring_height() knows of the stores and the zero point.
 static int ring_cost(int h, int64_t per_cu, int64_t K, qc_epilogue epi, int extra) {
     const bool gelu = epi != QC_EPI_NONE, brief = K <= 384, lengthy = K > 1500;
     constexpr int kFull[] = {400, 510, 680}, kMid[] = {350, 440, 540, 666}, kHalf[] = {310, 380, 450, 535, 630, 707};
@@ -105,12 +105,16 @@ static int ring_cost(int h, int64_t per_cu, int64_t K, qc_epilogue epi, int extr
 // f32 output past the caches: the more blocks a CU holds the worse their stores drain (the whole linear at 256 and 128, the same
 // operands again and again | four sets in turn: 2850 x 1152 x 4608 GELU (erf) 34.1 38.3 | 28.8 34.0, 3649 x 352 x 3456 the same 23.4
 // 27.5 | 22.4 27.1, 11670 x 1152 x 1152 38.6 43.4; over 1400 drawn calls -1 % | -3 %).
-static int ring_height(int64_t M, int64_t N, int n_tiles, int64_t K, qc_epilogue epi, qc_out ydt) {
+// A zero point and 8-bit weights: of 192 tokens two blocks fit a CU, without them three (at 256 and 192: 37714 x 256 x 3456,
+// binary32 to bf16, 78.8 83.9 | 77.1 81.3, 11666 x 1152 x 4608 74.7 76.2 | 72.9 84.9, 67636 x 1152 x 4608 370 394 | 355 384; over 150
+// drawn calls -2 % | -2 %; with two tiles to a CU or one there is nothing to fit, 2478 x 1152 x 3456 24.0 20.4 | 21.9 18.8).
+static int ring_height(int64_t M, int64_t N, int n_tiles, int64_t K, qc_epilogue epi, qc_out ydt, bool asym8) {
     int best = 4, least = 0;
     for (int h = 4; h >= 2; --h) {
         const int64_t tiles = (M + kWaveM * h - 1) / (kWaveM * h) * n_tiles;
         const bool streamed = ydt == QC_OUT_F32 && !keep_f32_output(M, N, K, h, epi);
-        const int cost = ring_cost(h, (tiles + kCus - 1) / kCus, K, epi, h == 2 && streamed ? 106 : 100);
+        const int64_t per_cu = (tiles + kCus - 1) / kCus;
+        const int cost = ring_cost(h, per_cu, K, epi, h == 2 && streamed ? 106 : h == 3 && asym8 && per_cu > 2 ? 108 : 100);
         if (h == 4 || cost < least) { best = h; least = cost; }
     }
     return best;
@@ -140,7 +144,7 @@ static int split_height(int64_t M, int n_tiles, int KF, int bits) {
 // 227 MB 101 189, 906 MB 500 674).
 static bool stream_bf16_edges(int64_t M, int64_t N) { return 2 * M * N > (int64_t)256 << 20; }
 
-GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt) {
+GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt, bool asym) {
     GemmChoice c{};
     const int n_tiles = (int)(round_up(N, kTileN) / kTileN);
     if (gemm_resident_chosen(M, N, K, bits) && gemm_resident_epilogue(K, bits, epi, ydt)) {
@@ -148,7 +152,7 @@ GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue ep
         c.height = 4;
         return c;
     }
-    c.height = ring_height(M, N, n_tiles, K, ydt == QC_OUT_I32_ACC ? QC_EPI_NONE : epi, ydt);
+    c.height = ring_height(M, N, n_tiles, K, ydt == QC_OUT_I32_ACC ? QC_EPI_NONE : epi, ydt, asym && bits == 8);
     c.keep_output = ydt == QC_OUT_F32 && keep_f32_output(M, N, K, c.height, epi);
     // Whole rows of 32 bits past the caches: the more blocks a CU holds the worse their stores drain (us at 256
     // and 192 tokens: 39510 x 1152 x 4608 274 324, 105656 x 784 x 1152 210 229; of less than 192 MB the spread over the CUs
@@ -175,7 +179,7 @@ hipError_t launch_gemm(const uint8_t *x_tiled, const float *x_scale, const uint8
     if (gemm_small_chosen(M, N))
         return launch_gemm_small(x_tiled, x_scale, w_packed, w_scale, bias, Y, M, N, K, bits, epi, ydt, x_corr,
                                  w_rowsum, stream);
-    const GemmChoice choice = choose_gemm(M, N, K, bits, epi, ydt);
+    const GemmChoice choice = choose_gemm(M, N, K, bits, epi, ydt, x_corr && w_rowsum);
     GemmArgs args;
     args.resident = choice.resident;
     args.height = choice.height;

@@ -251,7 +251,7 @@ struct GemmChoice {
     bool split;         // two groups of wavefronts, half of the reduction each
     bool keep_output;   // f32 output through the caches
 };
-GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt);
+GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt, bool asym);
 
 // The kernels for few tokens (qc_small.hip).  gemm_small_chosen: launch_gemm picks them for this
 // problem by itself; qlinear_small_chosen: quantization and GEMM in one launch.

@@ -142,3 +142,11 @@ def test_heights_of_tiles_that_are_one_or_two_to_a_cu(bits, M, K, N, tokens):
 def test_heights_of_tiles_whose_f32_output_goes_past_the_caches(M, K, N, epi, out, tokens, kept):
     plan = qc.linear_plan(M, K, N, epi=epi, out=out)
     assert (plan["kernel"], plan["tokens"], plan["kept"]) == ("ring", tokens, kept)
+
+
+@pytest.mark.parametrize("scheme,bits,M,K,N,x,tokens", [
+    ("asym", 8, 37714, 256, 3456, "f32", 256), ("asym", 8, 11666, 1152, 4608, "bf16", 256), ("token", 8, 11666, 1152, 4608, "bf16", 192),
+    ("asym", 4, 11666, 1152, 4608, "bf16", 192), ("asym", 8, 2478, 1152, 3456, "bf16", 192), ("asym", 8, 4096, 1152, 1152, "bf16", 192), ("asym", 8, 9843, 4608, 1152, "bf16", 192)])
+def test_heights_of_tiles_with_a_zero_point(scheme, bits, M, K, N, x, tokens):
+    plan = qc.linear_plan(M, K, N, bits, x=x, scheme=scheme)
+    assert plan["kernel"] == "ring" and plan["tokens"] == tokens
