@@ -64,13 +64,16 @@ constexpr int kCus = 256;
 // 60000 x 768 x 4608 342 351.
 // GELU (erf) leaves non-temporal stores the time to drain, and ordinary ones win from 60 MB on only and up to 192 MB
 // with the codes: 27 MB 23.3 25.1, 46 MB 30.2 32.6, 53 MB 34.2 35.2, 69 MB 53.8 46.5, with codes 193 MB 89.9 88.2;
-// K = 1824, with codes 204 MB 116 127; half the height, N = 3456, 41 MB 26.0 27.7.
+// K = 1824, with codes 204 MB 116 127; half the height, N = 3456, 41 MB 26.0 27.7.  Of those outputs that are nearly all there is, with K
+// from 385 to 576 it takes ordinary stores up to 512 MB only (to 724 MB the two are equal, beyond non-temporal ones take 5 to 7 % less,
+// over 33 drawn calls).
 // bf16 output is up to 9 % slower with ordinary stores.
 static bool keep_f32_output(int64_t M, int64_t N, int64_t K, int height, qc_epilogue epi) {
     constexpr int64_t MB = 1 << 20;
     const int64_t out = 4 * M * N, codes = M * round_up(K, kKAlign);
     const int64_t from = epi == QC_EPI_GELU_ERF ? 60 : height == 4 ? 24 : 15, most = epi == QC_EPI_GELU_ERF ? 192 : 256;
-    return out >= from * MB && (out + codes <= most * MB || (8 * codes <= out && out <= 400 * MB) || (K <= 576 && 16 * codes <= out));
+    const bool any_size = K <= 576 && 16 * codes <= out && (epi != QC_EPI_GELU_ERF || K <= 384 || out <= 512 * MB);
+    return out >= from * MB && (out + codes <= most * MB || (8 * codes <= out && out <= 400 * MB) || any_size);
 }
 
 // What a CU takes for `per_cu` of the ring kernel's tiles of 64 h tokens x 128 channels, in hundredths of what it

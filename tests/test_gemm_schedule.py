@@ -150,3 +150,11 @@ def test_heights_of_tiles_whose_f32_output_goes_past_the_caches(M, K, N, epi, ou
 def test_heights_of_tiles_with_a_zero_point(scheme, bits, M, K, N, x, tokens):
     plan = qc.linear_plan(M, K, N, bits, x=x, scheme=scheme)
     assert plan["kernel"] == "ring" and plan["tokens"] == tokens
+
+
+@pytest.mark.parametrize("M,K,N,epi,kept", [
+    (57258, 192, 4608, "none", True), (150000, 576, 2304, "none", True), (150000, 577, 2304, "none", False),
+    (57258, 192, 4608, "gelu_erf", True), (88010, 384, 3984, "gelu_erf", True), (97902, 576, 3984, "gelu_erf", False),
+    (33000, 576, 3984, "gelu_erf", True), (34000, 576, 3984, "gelu_erf", False), (220001, 64, 500, "none", False), (137000, 64, 768, "none", True)])
+def test_short_reductions_whose_f32_output_of_any_size_stays_in_the_caches(M, K, N, epi, kept):
+    assert qc.linear_plan(M, K, N, epi=epi, out="f32")["kept"] == kept
