@@ -39,10 +39,11 @@ bool gemm_resident_chosen(int64_t M, int64_t N, int64_t K, int bits) {
 // 4608 483 514), for GELU (tanh) to bf16 with 4-bit weights (131072 x 1152 x 4608 658 668) or a short
 // reduction (K = 384 374 379; K = 1152, 8-bit weights 661 629), for GELU (tanh) to f32 (59454 x 1152 x 4608 416 463, 131072 x 1152 x
 // 1152 238 272, 40000 x 768 x 2304 125 137) and for f32 with a short reduction (60000 x 768 x 4608 343 390, 131072 x 768 x 2304 382
-// 422; K = 1152, 65536 x 4608, 427 403).  In bursts of a few calls the ring kernel gains 5 % more.
-static bool gemm_resident_epilogue(int64_t K, int bits, qc_epilogue epi, qc_out ydt) {
+// 422; K = 1152, 65536 x 4608, 427 403; with a zero point and 8-bit weights only up to K = 576: 81720 x
+// 768 x 3456 420 348, 90440 x 688 x 3984 547 487).  In bursts of a few calls the ring kernel gains 5 % more.
+static bool gemm_resident_epilogue(int64_t K, int bits, qc_epilogue epi, qc_out ydt, bool asym) {
     if (ydt == QC_OUT_I32_ACC) return true;
-    if (epi == QC_EPI_NONE) return ydt == QC_OUT_BF16 || K > 768;
+    if (epi == QC_EPI_NONE) return ydt == QC_OUT_BF16 || K > (asym && bits == 8 ? 576 : 768);
     return epi == QC_EPI_GELU_TANH && ydt == QC_OUT_BF16 && bits == 8 && K > 768;
 }
 
@@ -150,7 +151,7 @@ static bool stream_bf16_edges(int64_t M, int64_t N) { return 2 * M * N > (int64_
 GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, int bits, qc_epilogue epi, qc_out ydt, bool asym) {
     GemmChoice c{};
     const int n_tiles = (int)(round_up(N, kTileN) / kTileN);
-    if (gemm_resident_chosen(M, N, K, bits) && gemm_resident_epilogue(K, bits, epi, ydt)) {
+    if (gemm_resident_chosen(M, N, K, bits) && gemm_resident_epilogue(K, bits, epi, ydt, asym)) {
         c.resident = true;
         c.height = 4;
         return c;

@@ -158,3 +158,10 @@ def test_heights_of_tiles_with_a_zero_point(scheme, bits, M, K, N, x, tokens):
     (33000, 576, 3984, "gelu_erf", True), (34000, 576, 3984, "gelu_erf", False), (220001, 64, 500, "none", False), (137000, 64, 768, "none", True)])
 def test_short_reductions_whose_f32_output_of_any_size_stays_in_the_caches(M, K, N, epi, kept):
     assert qc.linear_plan(M, K, N, epi=epi, out="f32")["kept"] == kept
+
+
+@pytest.mark.parametrize("scheme,bits,M,K,N,kernel", [("asym", 8, 81720, 768, 3456, "resident"), ("asym", 8, 90440, 688, 3984, "resident"),
+                                                      ("asym", 8, 81720, 576, 3456, "ring"), ("asym", 4, 81720, 768, 3456, "ring"),
+                                                      ("token", 8, 81720, 768, 3456, "ring"), ("token", 8, 81720, 784, 3456, "resident")])
+def test_which_short_reductions_with_f32_output_keep_their_weights_resident(scheme, bits, M, K, N, kernel):
+    assert qc.linear_plan(M, K, N, bits, out="f32", scheme=scheme)["kernel"] == kernel
