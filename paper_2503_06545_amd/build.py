@@ -89,13 +89,14 @@ def _compile_roofs(_=None) -> str:
 
 
 def build(verbose: bool = True) -> str:
-    """Always recompiles every source, relinks libqc.so and rebuilds _qc_torch.so and the qc_roofs program."""
+    """Always recompiles every source, relinks libqc.so and rebuilds _qc_torch.so and the qc_roofs program.  libqc.so
+    needs neither torch's headers nor g++: without them _qc_torch.so is left out, and binding.py's own helpers serve."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 2)) as pool:
-        others = [pool.submit(_compile_roofs), pool.submit(_compile_torch)]
+        roofs, helpers = pool.submit(_compile_roofs), pool.submit(_compile_torch)
         results = list(pool.map(_compile, SOURCES))
-        for other in others:
-            other.result()
+        roofs.result()
+        no_helpers = helpers.exception()
     objs = [o for o, _ in results]
     kernels = [k for _, ks in results for k in ks]
     with open(RESOURCE_REPORT, "w") as f:
@@ -106,6 +107,10 @@ def build(verbose: bool = True) -> str:
         raise RuntimeError("kernels that use scratch memory (register spills), or no resource "
                            f"report at all: {spilled}")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], check=True)
+    if no_helpers is not None:
+        if os.path.exists(TORCH_LIB):
+            os.unlink(TORCH_LIB)   # of other sources
+        print(f"warning: {TORCH_LIB} not built, calls take longer on the host: {no_helpers!r}", file=sys.stderr)
     # which sources the library was built from: the tree travels to the GPU machine without its
     # history, so the benchmark reads the commit from this stamp
     git = subprocess.run(["git", "-C", ROOT, "describe", "--always", "--dirty", "--abbrev=12"],
