@@ -726,6 +726,10 @@ def _use_native_helpers() -> None:
     _qc_torch.setup(_entries, _check, tuple(_python_helpers[n] for n in _PER_STEP))
     for n in _PER_STEP:
         helpers[n] = getattr(_qc_torch, n)
+        helpers[n].__module__ = __name__   # pickled as this module's, whose import sets them up
 
 
+for _name in _PER_STEP:   # a helper taken from here before torch was imported is pickled under a name of its own
+    globals()["_python_" + _name] = globals()[_name]
+    globals()[_name].__qualname__ = "_python_" + _name
 _use_native_helpers()

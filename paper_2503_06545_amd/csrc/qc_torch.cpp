@@ -348,16 +348,18 @@ PyObject *setup(PyObject *module, PyObject *args) {
     Py_RETURN_NONE;
 }
 
-#define QC_METHOD(name, signature) \
-    {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL | METH_KEYWORDS, #name signature "\n--\n\n"}
+#define QC_METHOD(name, signature, ...) \
+    {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL | METH_KEYWORDS, #name signature "\n--\n\n" __VA_ARGS__}
 PyMethodDef methods[] = {
     QC_METHOD(qlinear_t, "($module, X, pw, bias=None, epi='none', out='bf16', workspace=None, Y=None, act_bits=8, rot_block=0)"),
     QC_METHOD(qlinear_asym_t, "($module, X, pw, row_sums, bias=None, epi='none', out='bf16', workspace=None, Y=None, act_bits=8)"),
     QC_METHOD(qlinear_tensor_t, "($module, X, pw, bias=None, epi='none', out='bf16', workspace=None, Y=None, act_bits=8)"),
     QC_METHOD(latent_delta_t, "($module, cur, prev, workspace=None, out3=None)"),
     QC_METHOD(layer_similarity_t, "($module, a, b, workspace=None, out4=None)"),
-    QC_METHOD(frame_gradient_norm_t, "($module, m, workspace=None, out2=None)"),
-    QC_METHOD(cumulative_variation_t, "($module, cur, prevs, workspace=None, out=None)"),
+    QC_METHOD(frame_gradient_norm_t, "($module, m, workspace=None, out2=None)",
+              "m: [frames, ...] float32 or bfloat16, contiguous -> device float [2]."),
+    QC_METHOD(cumulative_variation_t, "($module, cur, prevs, workspace=None, out=None)",
+              "cur float32 [n], prevs a list of float32 tensors of the same size -> device float\n[len(prevs) + 1]."),
     {"setup", setup, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

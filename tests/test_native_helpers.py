@@ -1,5 +1,9 @@
 """The per-step tensor helpers as native functions: the arguments, results and errors of the Python ones they replace."""
 import inspect
+import os
+import pickle
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -23,6 +27,28 @@ def test_all_are_replaced_under_their_signatures():
         native, python = inspect.signature(getattr(qc, n)), inspect.signature(qc._python_helpers[n])
         assert [(p.name, p.default, p.kind) for p in native.parameters.values()] == [
             (p.name, p.default, p.kind) for p in python.parameters.values()]
+
+
+@pytest.mark.parametrize("before", ["", "import torch; ", "from paper_2503_06545_amd.binding import qlinear_t; import torch; "])
+def test_a_pickled_helper_works_in_another_process(before):
+    """What was pickled here, or by a program that took the helpers from the module before it imported torch, is called
+    in a process that has imported nothing yet."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    for n in REPLACED:
+        f = getattr(qc, n)
+        assert f.__doc__ == (inspect.getdoc(qc._python_helpers[n]) or None) and pickle.loads(pickle.dumps(f)) is f
+        assert pickle.loads(pickle.dumps(qc._python_helpers[n])) is qc._python_helpers[n]
+    code = f"""
+import sys, pickle
+sys.path.insert(0, {root!r})
+{before}
+for f in pickle.loads({pickle.dumps([getattr(qc, n) for n in REPLACED] + [qc._python_helpers[n] for n in REPLACED])!r}):
+    try:
+        f(1, 2, 3)
+    except Exception as e:
+        assert type(e) is AttributeError, repr(e)
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=100)
 
 
 class NoPointer(torch.Tensor):
