@@ -1,4 +1,4 @@
-// Device helpers shared by the quantization and the GEMM translation units: 16-element units of an
+// Device helpers shared by the quantization and the GEMM translation units: groups of 128 columns of an
 // activation row, the quantizer's exact quotient and cast, the epilogue's activations.
 #pragma once
 
@@ -48,7 +48,8 @@ __device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0
 //                  compiler would then keep in registers up to the cast.
 //   load_ragged()  the same for a K that is no multiple of 16 (16 B or more): rows at any alignment (the hardware
 //                  takes 16 B loads at any address).  The piece that holds the row's end is loaded so that it ends
-//                  there, and settle_ragged(), after all loads, moves it down to its place, zeros following.
+//                  there, and settle_ragged(), after all loads, moves it down to its place, zeros following; pieces wholly past
+//                  the end stay copies of the last one, as with load().
 //                  (Its elements loaded one by one, each load waited for, in order: us 4099 x 1000 bf16 4.7 4.4, 30000 x 1156 bf16
 //                  23.3 18.5, f32 39.7 30.4.)
 template <typename XT>
@@ -204,48 +205,6 @@ struct Group<uint16_t> {  // bf16 bit patterns
     }
     static __device__ Max no_max() { return {}; }
     static __device__ float absmax_value(const Max &m) { return m.value(); }
-};
-
-// 16 consecutive elements of one row, widened to float by get().
-template <typename XT>
-struct Unit;
-
-template <>
-struct Unit<float> {
-    float4 v[4];
-    template <bool NT>
-    __device__ void load(const float *p) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint4 w = load16<NT>(p + 4 * i);
-            v[i] = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w));
-        }
-    }
-    __device__ void zero() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __device__ float get(int i) const {
-        const float4 &f = v[i >> 2];
-        switch (i & 3) { case 0: return f.x; case 1: return f.y; case 2: return f.z; default: return f.w; }
-    }
-};
-
-template <>
-struct Unit<uint16_t> {  // bf16 bit patterns
-    uint4 v[2];
-    template <bool NT>
-    __device__ void load(const uint16_t *p) {
-        v[0] = load16<NT>(p);
-        v[1] = load16<NT>(p + 8);
-    }
-    __device__ void zero() { v[0] = v[1] = make_uint4(0, 0, 0, 0); }
-    __device__ float get(int i) const {
-        const uint4 &u = v[i >> 3];
-        uint32_t w;
-        switch ((i >> 1) & 3) { case 0: w = u.x; break; case 1: w = u.y; break; case 2: w = u.z; break; default: w = u.w; }
-        return (i & 1) ? bf16_hi(w) : bf16_lo(w);
-    }
 };
 
 // RN(x / s) from r = RN(1 / s): product, exact residual, one correction.

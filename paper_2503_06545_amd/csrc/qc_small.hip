@@ -788,7 +788,7 @@ hipError_t launch_gemm_small(const uint8_t *x_tiled, const float *x_scale, const
     const int tile = pick_tile(M, N);
     if (tile < 0) return hipErrorInvalidValue;
     SmallArgs a = small_args(const_cast<uint8_t *>(x_tiled), const_cast<float *>(x_scale), w_packed, w_scale,
-                             bias, Y, M, N, K, epi, ydt);   // kCodes reads both
+                             bias, Y, M, N, K, epi, ydt);   // small_kernel only reads both
     if (x_corr && w_rowsum) {
         a.x_corr = const_cast<float *>(x_corr);
         a.w_rowsum = w_rowsum;
