@@ -721,7 +721,8 @@ hipError_t launch_fused(SmallArgs a, hipStream_t stream) {
     a.groups = (int)((a.K + kGroup - 1) / kGroup);
     a.inv_groups = ((1u << 20) + a.groups - 1) / a.groups;   // exact for pairs below 384
     // 384 groups at most, so that the codes, 16 B per unit of 16 columns and row and 16 B of padding per unit, take
-    // 96 KiB at most, with one row, and less than kLdsMost together with the sums
+    // 96 KiB at most, with one row, and less than kLdsMost together with the sums (140 KiB on tiles of 16 x 32)
+    static_assert(MI > 1 || L::kCodesAt + 96 * 1024 <= kLdsMost, "the longest rows fit");
     const size_t lds = L::kCodesAt + (size_t)a.KF * 4 * quarter_stride(a.rows);
     if (lds > (size_t)kLdsMost) return hipErrorInvalidValue;
     if constexpr (SCHEME == kQuantToken) {   // (the others: three steps whatever the rows)

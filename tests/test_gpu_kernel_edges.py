@@ -17,6 +17,12 @@ from test_gpu_parity import RTOL, assert_outputs_close, bits_equal, dev, host_f6
 pytestmark = pytest.mark.gpu
 
 
+def kernel_of(M, K, N, bits, **which):
+    """The GEMM kernel a linear takes: "few", "resident" or "ring" with its tile's tokens, "split" and "kept"."""
+    plan = qc.linear_plan(M, K, N, bits, **which)
+    return plan["kernel"] + (f" {plan['tokens']}" if plan["kernel"] == "ring" else "") + " split" * plan["split"] + " kept" * plan["kept"]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("M,K", [(1, 16), (9, 112), (8, 128), (7, 144), (9, 2032), (9, 2048), (9, 2064),
                                  (5, 6144), (5, 6160), (4609, 2048), (4610, 2048)])
@@ -81,9 +87,8 @@ def test_rotated_rows_shorter_than_a_wavefronts_columns(M, K, rot_block, dtype):
     (32, 1296, 100), (33, 192, 4100), (100, 1152, 4100), (255, 320, 2048), (256, 64, 2050), (512, 208, 2047),
     (1024, 64, 1024), (1025, 64, 1024), (300, 1000, 131), (1024, 64, 64), (1000, 320, 4), (1001, 1000, 132)])
 def test_qlinear_on_few_tokens_at_the_edges_of_its_tiles(M, K, N, bits):
-    """Both sides of every change of tile (16 x 32, 32 x 32, 32 x 64, 64 x 64, then the ring kernel),
-    of the longest rows the one-launch form takes (16 tokens: K = 1536, 32: 1280) and of row counts
-    below a power of two; every quantizer, every output type, channel counts of every store width."""
+    """Both sides of every change of tile (16 x 32, 32 x 32, 32 x 64, 64 x 64, then the ring kernel), in one launch
+    and in two, row counts below a power of two; every quantizer, every output type, channel counts of every store width."""
     rng = np.random.default_rng(M * 31 + K * 7 + N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -183,10 +188,10 @@ def test_one_launch_and_two_are_the_same_for_every_quantizer(scheme, dtype, M, K
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("N", [129, 130, 132, 136])
 def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
-    """The kernel that streams its weights, whose smallest problems are larger than the few-token
-    kernel's: partial tiles in both directions, channel counts of every store width."""
+    """The kernel that streams its weights, on tiles of 192 tokens: partial tiles in both directions, channel counts of
+    every store width."""
     M, K = 16421, 64
-    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    assert kernel_of(M, K, N, bits, out="f32") == kernel_of(M, K, N, bits, epi="gelu_tanh") == "ring 192"
     rng = np.random.default_rng(100 * bits + N)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -195,12 +200,17 @@ def test_qlinear_ring_kernel_on_ragged_tokens_and_channels(N, bits):
 
 
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("M,K,N", [(5505, 192, 130), (16384, 64, 129), (16385, 64, 129), (21889, 64, 257), (21249, 320, 512),
-                                   (21250, 64, 511), (26001, 64, 512)])
-def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
+@pytest.mark.parametrize("M,K,N,bf16,f32,asym", [
+    (5505, 192, 130, "ring 128", "ring 128", "ring 128"), (16384, 64, 129, "ring 128", "ring 128", "ring 128"),
+    (16385, 64, 129, "ring 192", "ring 192", "ring 192"), (21889, 64, 257, "ring 128", "ring 128 kept", "ring 128"),
+    (21249, 320, 512, "ring 128", "ring 128 kept", "ring 128"), (21250, 64, 511, "ring 128", "ring 128 kept", "ring 128"),
+    (26001, 64, 512, "ring 128", "ring 128 kept", "ring 128"), (7501, 400, 1156, "ring 128", "ring 192 kept", "ring 128"),
+    (16300, 448, 1003, "ring 128", "ring 256 kept", "ring 128"), (25001, 2064, 129, "ring 256", "ring 256", "ring 256")])
+def test_qlinear_ring_kernel_at_every_tile_height(M, K, N, bf16, f32, asym, bits):
     """From a few tiles to several per CU, whose heights the launcher chooses by how they spread; with
     32-bit output also both kinds of store (through the caches from 15 or 24 MB on); an asymmetric one."""
-    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    assert kernel_of(M, K, N, bits, epi="gelu_tanh") == bf16 and kernel_of(M, K, N, bits, out="f32") == f32
+    assert kernel_of(M, K, N, bits, epi="gelu_erf", scheme="asym") == asym
     rng = np.random.default_rng(M + N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -210,23 +220,22 @@ def test_qlinear_ring_kernel_at_both_tile_heights(M, K, N, bits):
     run_asym_case(x, W, b, bits, "gelu_erf", "bf16")
 
 
-def full_height(M, N):
-    """Whether tiles of 256 tokens spread well over the CUs, against those of 128; the launcher weighs 192 too."""
-    tiles = -(-M // 256) * -(-N // 128)
-    return not (2 * tiles <= 256 or 256 < tiles <= 332)
-
-
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("kernel,M,N", [("half", 1100, 1000 + r) for r in range(8)] + [("full", 2200, 2048 + r) for r in range(8)]
-                         + [("half", 5700, 1536), ("full", 4300, 1920)]   # f32: through the caches; half the height has no smaller
-                         + [("resident", 32700, 3448 + r) for r in (0, 1, 4, 7)] + [("full", 262145, 513)])
-def test_qlinear_many_tiles_stay_inside_their_output(kernel, M, N, bits):
-    """Every remainder of N by 8 in the kernels for more than a few tokens, all types of output, rows that are
-    no multiple of 16 B beyond the cache's size too: every row against the oracle's (they repeat), nothing
-    written on either side of Y."""
-    K, period = 64, 251
-    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == (2 if kernel == "resident" else 1)
-    assert kernel == "resident" or full_height(M, N) == (kernel == "full")
+@pytest.mark.parametrize("M,K,N,bf16,f32,i32", [(1100, 64, 1000 + r, "ring 128", "ring 128", "ring 128") for r in range(8)]
+                         + [(2200, 64, 2048 + r, "ring 192", "ring 192 kept", "ring 192") for r in range(8)]
+                         + [(25000, 2064, 129 + r, "ring 256", "ring 256", "ring 256") for r in range(8)]
+                         + [(16300, 448, 1000 + r, "ring 256", "ring 256 kept", "ring 256") for r in range(8)]
+                         + [(5700, 64, 1536, "ring 128", "ring 128 kept", "ring 128"), (4300, 64, 1920, "ring 128", "ring 128 kept", "ring 128")]
+                         + [(32700, 64, 3448 + r, "resident", "ring 256 kept" if r % 4 == 0 else "ring 128 kept", "resident") for r in (0, 1, 4, 7)]
+                         + [(16300, 832, 6896 + r, "resident", "resident", "resident") for r in (0, 3)]
+                         + [(262145, 64, 513, "ring 192", None, None), (137000, 448, 1003, "ring 256", None, None)])   # bf16 of more than 256 MB
+def test_qlinear_many_tiles_stay_inside_their_output(M, K, N, bf16, f32, i32, bits):
+    """Every remainder of N by 8 in the kernels for more than a few tokens, at every height of the ring's tiles, all types of
+    output and both kinds of store, rows that are no multiple of 16 B beyond the cache's size too: every row against the
+    oracle's (they repeat), nothing written on either side of Y."""
+    period = 251
+    for out, kernel in (("bf16", bf16), ("f32", f32), ("i32", i32)):
+        assert kernel is None or kernel_of(M, K, N, bits, out=out) == kernel
     rng = np.random.default_rng(100 * N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -235,8 +244,8 @@ def test_qlinear_many_tiles_stay_inside_their_output(kernel, M, N, bits):
     ref = oracle.qlinear(x, qw, sw, b, 0, 8)
     X = dev(x).repeat(-(-M // period), 1)[:M].contiguous()
     pw, pad = qc.pack_weight_t(dev(W), bits), 4096
-    for out, t, fill in (("bf16", torch.bfloat16, -7.0), ("f32", torch.float32, -7.0), ("i32", torch.int32, -7)):
-        if M * N > 1 << 27 and out != "bf16":
+    for out, t, fill, kernel in (("bf16", torch.bfloat16, -7.0, bf16), ("f32", torch.float32, -7.0, f32), ("i32", torch.int32, -7, i32)):
+        if kernel is None:
             continue
         buf = torch.full((M * N + 2 * pad,), fill, dtype=t, device="cuda")
         Y = qc.qlinear_t(X, pw, None if out == "i32" else dev(b), "none", out, Y=buf[pad:pad + M * N].view(M, N))
@@ -251,12 +260,13 @@ def test_qlinear_many_tiles_stay_inside_their_output(kernel, M, N, bits):
 
 
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("M,N", [(1100, 1001), (2200, 2050)])
+@pytest.mark.parametrize("M,N", [(1100, 1001), (2200, 2050), (50000, 129)])
 @pytest.mark.parametrize("K", [200, 1000, 1160])
 def test_qlinear_ring_kernel_ragged_k_with_a_poisoned_workspace(K, M, N, bits):
     """K no multiple of 16 or of the stage: what the quantizer leaves unwritten of the last columns meets
-    zero weights, at both tile heights."""
-    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+    zero weights, at several tile heights and in both halves of a split reduction."""
+    wanted = {1100: ("ring 128 split" if bits == 4 and K > 200 else "ring 128"), 2200: "ring 192", 50000: "ring 128" if K == 200 else "ring 256"}[M]
+    assert kernel_of(M, K, N, bits, out="i32") == wanted
     rng = np.random.default_rng(K + M + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     qw, _ = oracle.quant_weight(W, bits)
@@ -270,10 +280,13 @@ def test_qlinear_ring_kernel_ragged_k_with_a_poisoned_workspace(K, M, N, bits):
 
 
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("M,K,N", [(1100, 4608, 1000), (2200, 4608, 2050), (1100, 2304, 1003), (2200, 1152, 2049)])
-def test_qlinear_ring_kernel_long_reductions(M, K, N, bits):
-    """Both tile heights at the reductions they are taken for, symmetric, rotated and asymmetric codes."""
-    assert qc.qc_debug_gemm_kernel(M, K, N, bits) == 1
+@pytest.mark.parametrize("M,K,N,w8,w4", [(1100, 4608, 1000, "ring 128 split", "ring 128 split"), (2200, 4608, 2050, "ring 192", "ring 256 split"),
+                                         (1100, 2304, 1003, "ring 128 split", "ring 128 split"), (2200, 1152, 2049, "ring 192", "ring 192"),
+                                         (6500, 2304, 899, "ring 256", "ring 256 split")])
+def test_qlinear_ring_kernel_long_reductions(M, K, N, w8, w4, bits):
+    """Every tile height at the reductions it is taken for, split and whole, symmetric, rotated and asymmetric codes."""
+    for which in (dict(epi="gelu_tanh"), dict(out="f32", scheme="rot"), dict(out="f32", epi="gelu_erf", scheme="asym")):
+        assert kernel_of(M, K, N, bits, **which).replace(" kept", "") == (w8 if bits == 8 else w4)
     rng = np.random.default_rng(M + K + N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -285,11 +298,13 @@ def test_qlinear_ring_kernel_long_reductions(M, K, N, bits):
 
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N", [(4033, 64, 1152), (4081, 192, 1146), (4097, 400, 1151), (4225, 64, 1152), (4225, 208, 1025),
-                                   (4352, 64, 1148), (9843, 64, 1156)])
+                                   (4352, 64, 1148)])
 def test_qlinear_ring_kernel_on_tiles_of_192_tokens(M, K, N, bits):
     """The height between the two, whose wavefronts of 48 tokens begin and end inside the panels of 64 the
     codes lie in: last tiles of 1, 49 and 65 live tokens, one that ends past the padded tokens (4225),
     and nothing written on either side of Y."""
+    assert kernel_of(M, K, N, bits, epi="gelu_tanh") == kernel_of(M, K, N, bits, scheme="asym") == "ring 192"
+    assert kernel_of(M, K, N, bits, epi="gelu_erf", out="f32") == "ring 192" and kernel_of(M, K, N, bits, out="f32") == "ring 192 kept"
     rng = np.random.default_rng(M + K + N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -312,6 +327,9 @@ def test_qlinear_ring_kernel_on_tiles_of_192_tokens(M, K, N, bits):
 def test_qlinear_ring_kernel_split_in_two_halves_of_the_reduction(M, K, N, bits):
     """Few tiles of 128 tokens (the first six) and, with 4-bit weights, of 256: the shortest reductions it is taken for, halves
     of the same and of different length, last tiles of 1 token, and nothing written on either side of Y."""
+    kernel = f"ring {128 if M < 3000 else 256} split"
+    assert kernel_of(M, K, N, bits, epi="gelu_tanh") == kernel_of(M, K, N, bits, scheme="asym") == kernel
+    assert kernel_of(M, K, N, bits, epi="gelu_erf", out="f32") == kernel_of(M, K, N, bits, out="f32") == kernel
     rng = np.random.default_rng(M + K + N + bits)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     b = (rng.standard_normal(N) * 0.01).astype(np.float32)
@@ -337,16 +355,19 @@ def test_qlinear_ragged_rows_beyond_the_last_level_cache():
     run_linear_case(random_x(rng, M, K, "bf16"), W, None, 8, "none", "bf16", check_acc=False)
 
 
-@pytest.mark.parametrize("N,epi", [(500, "gelu_tanh"), (501, "none")])
-def test_qlinear_f32_output_of_any_size_through_the_caches(N, epi):
-    """A short reduction whose f32 output of more than 400 MB stays on its way through the caches: every row
-    against the oracle's (they repeat)."""
-    M, K, period = 220001, 64, 251
+@pytest.mark.parametrize("M,N,epi,kernel", [(220001, 500, "gelu_tanh", "ring 256"), (220001, 501, "none", "ring 192"),
+                                            (136701, 768, "gelu_tanh", "ring 256 kept"), (136701, 769, "none", "ring 256 kept"),
+                                            (136701, 771, "gelu_erf", "ring 256 kept"), (138001, 764, "none", "ring 256")])
+def test_qlinear_f32_output_of_any_size_through_the_caches(M, N, epi, kernel):
+    """A short reduction whose f32 output of more than 400 MB stays on its way through the caches, where it is 16 times
+    the codes, and on both sides of that: every row against the oracle's (they repeat)."""
+    K, period = 64, 251
+    assert 4 * M * N > 400 << 20 and kernel_of(M, K, N, 8, epi=epi, out="f32") == kernel
     rng = np.random.default_rng(N)
     W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
     x = random_x(rng, period, K, "bf16")
     qw, sw = oracle.quant_weight(W, 8)
-    ref = oracle.qlinear(x, qw, sw, np.zeros(N, np.float32), oracle.EPI_GELU_TANH if epi == "gelu_tanh" else oracle.EPI_NONE, 8)
+    ref = oracle.qlinear(x, qw, sw, np.zeros(N, np.float32), {"none": oracle.EPI_NONE, "gelu_tanh": oracle.EPI_GELU_TANH, "gelu_erf": oracle.EPI_GELU_ERF}[epi], 8)
     Y = qc.qlinear_t(dev(x).repeat(-(-M // period), 1)[:M].contiguous(), qc.pack_weight_t(dev(W), 8), None, epi, "f32")
     torch.cuda.synchronize()
     assert_outputs_close(host_f64(Y[:period]), ref["y"], RTOL["f32"])
@@ -375,8 +396,7 @@ def test_reductions_on_both_sides_of_the_one_launch_form(n):
 
 @pytest.mark.parametrize("n", [32 * 4096, 32 * 4096 + 1, 3 << 17, (3 << 17) + 1, 128 * 4096, 3 << 18])
 def test_latent_delta_in_one_launch_of_many_blocks(n):
-    """More blocks than a wavefront has lanes, whose records a lane reads in two goes, then two
-    launches."""
+    """Up to the 48 blocks that the largest input of the one-launch form has, then two launches."""
     rng = np.random.default_rng(n)
     cur, prev = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
     ref = np.asarray(oracle.latent_delta(cur, prev), np.float64)
@@ -471,7 +491,7 @@ def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
     """The largest inputs of the one-launch form and the smallest beyond it, ragged ones among them."""
     rng = np.random.default_rng(extra)
     size = 4 if dtype == "f32" else 2
-    n = (5 << 19) // size + extra
+    n = (9 << 15 if dtype == "f32" else 5 << 18) + extra
     a, b = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
     m = rng.standard_normal((2, (1 << 20) // size + extra)).astype(np.float32)
     if dtype == "bf16":
@@ -553,11 +573,13 @@ def test_one_launch_reductions_replay_from_a_graph():
         assert np.all(np.abs(outs[0].cpu().numpy() - ref) <= 1e-5 * np.abs(ref))
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 40960, 8224), (1, 40961, 8224), (1, 24576, 100), (2, 20480, 8224), (16, 1536, 8192), (32, 1280, 16384)])
-def test_qlinear_on_few_tokens_with_the_longest_rows(M, K, N):
-    """The longest rows the one-launch form takes, which need the most LDS (81 KB), against quantization and
-    GEMM as two calls."""
-    assert qc.qc_debug_gemm_kernel(M, K, N, 8) == 3
+@pytest.mark.parametrize("M,K,N,fused", [(1, 49152, 100, True), (1, 49154, 100, False), (1, 49152, 8224, True), (1, 49154, 8224, False),
+                                         (1, 49152, 16500, True), (2, 24576, 100, True), (2, 24578, 8224, False), (1, 40960, 8224, True),
+                                         (1, 40961, 8224, True), (1, 24576, 100, True), (2, 20480, 8224, True), (16, 1536, 8192, True), (32, 1280, 16384, True)])
+def test_qlinear_on_few_tokens_with_the_longest_rows(M, K, N, fused):
+    """The longest rows the one-launch form takes on tiles of 32, 64 and 128 channels, which need the most LDS (140 KiB), and
+    the shortest that it does not, against quantization and GEMM as two calls."""
+    assert qc.linear_plan(M, K, N)["fused"] == fused
     X = torch.randn(M, K, device="cuda").bfloat16()
     pw = qc.pack_weight_t(torch.randn(N, K, device="cuda"), 8)
     ws = qc.qlinear_workspace_t(M, K, N)

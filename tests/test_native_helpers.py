@@ -51,11 +51,28 @@ for f in pickle.loads({pickle.dumps([getattr(qc, n) for n in REPLACED] + [qc._py
     subprocess.run([sys.executable, "-c", code], check=True, timeout=100)
 
 
+@pytest.fixture
+def handed_on():
+    """The calls that the native helpers hand on to the Python ones, by name."""
+    from paper_2503_06545_amd import _qc_torch
+    seen = []
+
+    def recorded(n):
+        def helper(*args, **kwargs):
+            seen.append(n)
+            return qc._python_helpers[n](*args, **kwargs)
+        return helper
+
+    _qc_torch.setup(qc._entries, qc._check, tuple(recorded(n) for n in qc._PER_STEP))
+    yield seen
+    _qc_torch.setup(qc._entries, qc._check, tuple(qc._python_helpers[n] for n in qc._PER_STEP))
+
+
 class NoPointer(torch.Tensor):
     """A subclass: the Python helper's business."""
 
 
-def test_what_is_refused_is_refused_alike():
+def test_what_is_refused_is_refused_alike(handed_on):
     x, w = torch.zeros(2, 16, dtype=torch.bfloat16), torch.zeros(512, dtype=torch.uint8)
     pw, ws, y, f = qc.PackedWeight(w, torch.zeros(3), 3, 16, 8), torch.zeros(4096, dtype=torch.uint8), torch.zeros(2, 3), torch.zeros(4, 4)
     calls = [("qlinear_t", (), {}), ("qlinear_t", (x,), {}), ("qlinear_t", (x, pw), {}), ("qlinear_t", (x, pw, None, "no"), {}),
@@ -68,11 +85,15 @@ def test_what_is_refused_is_refused_alike():
              ("cumulative_variation_t", (f, [f, f]), {"workspace": ws, "out": y}), ("cumulative_variation_t", (f, f), {"workspace": ws, "out": y})]
     for name, args, kwargs in calls:
         want = outcome(qc._python_helpers[name], *args, **kwargs)
+        handed_on.clear()
         assert isinstance(want, tuple) and outcome(getattr(qc, name), *args, **kwargs) == want, (name, args, kwargs)
+        assert handed_on == [name]
 
 
 @pytest.mark.gpu
-def test_results_and_device_errors_are_those_of_the_python_helpers():
+def test_results_and_device_errors_are_those_of_the_python_helpers(handed_on):
+    """Ordinary calls are the native helpers' own, also where the library refuses them; those that leave out the workspace and the
+    output or bring tensors of another type, order or container go to the Python helpers."""
     g = torch.Generator(device="cuda").manual_seed(7)
     x = torch.randn(40, 256, generator=g, device="cuda").bfloat16()
     pw, prw = (qc.pack_weight_t(torch.randn(72, 256, generator=g, device="cuda"), 8, rot) for rot in (0, 64))
@@ -86,24 +107,30 @@ def test_results_and_device_errors_are_those_of_the_python_helpers():
         return {"workspace": torch.empty(1 << 16, dtype=torch.uint8, device="cuda"), key: torch.empty(count, device="cuda")}
 
     little = {"workspace": torch.empty(16, dtype=torch.uint8, device="cuda"), "Y": torch.empty(40, 72, device="cuda")}
-    calls = [("qlinear_t", (x, pw), lambda: dict(space(qc.qlinear_workspace_t), bias=bias, epi="gelu_tanh", act_bits=6)),
-             ("qlinear_t", (x, pw, bias), dict), ("qlinear_t", (x, prw), lambda: dict(space(qc.qlinear_workspace_t), rot_block=64)),
-             ("qlinear_asym_t", (x, pw, sums), lambda: dict(space(qc.qlinear_asym_workspace_t), bias=bias)),
-             ("qlinear_tensor_t", (x, pw), lambda: dict(space(qc.qlinear_tensor_workspace_t), epi="gelu_erf")),
-             ("latent_delta_t", (a, b), lambda: small("out3", 3)), ("latent_delta_t", (a, b), dict),
-             ("layer_similarity_t", (a, b), lambda: small("out4", 4)), ("layer_similarity_t", (x, x), lambda: small("out4", 4)),
-             ("frame_gradient_norm_t", (a,), lambda: small("out2", 2)), ("cumulative_variation_t", (a, [b, a, b]), lambda: small("out", 4)),
-             ("qlinear_t", (x, pw), lambda: little), ("qlinear_t", (x.double(), pw), lambda: space(qc.qlinear_workspace_t)),
-             ("qlinear_t", (x.t(), pw), lambda: space(qc.qlinear_workspace_t)), ("latent_delta_t", (a, b.t()), lambda: small("out3", 3)),
-             ("qlinear_t", (x, pw), lambda: dict(space(qc.qlinear_workspace_t), act_bits=5)),
-             ("cumulative_variation_t", (a, [b] * 9), lambda: small("out", 10)), ("cumulative_variation_t", (a, (b, a)), lambda: small("out", 3))]
+    own = [("qlinear_t", (x, pw), lambda: dict(space(qc.qlinear_workspace_t), bias=bias, epi="gelu_tanh", act_bits=6)),
+           ("qlinear_t", (x, prw), lambda: dict(space(qc.qlinear_workspace_t), rot_block=64)),
+           ("qlinear_t", (x, pw, None, "none", "bf16", *space(qc.qlinear_workspace_t).values()), dict),
+           ("qlinear_asym_t", (x, pw, sums), lambda: dict(space(qc.qlinear_asym_workspace_t), bias=bias)),
+           ("qlinear_tensor_t", (x, pw), lambda: dict(space(qc.qlinear_tensor_workspace_t), epi="gelu_erf")),
+           ("latent_delta_t", (a, b), lambda: small("out3", 3)), ("layer_similarity_t", (a, b), lambda: small("out4", 4)),
+           ("layer_similarity_t", (x, x), lambda: small("out4", 4)), ("frame_gradient_norm_t", (a,), lambda: small("out2", 2)),
+           ("cumulative_variation_t", (a, [b, a, b]), lambda: small("out", 4)), ("qlinear_t", (x, pw), lambda: little),
+           ("qlinear_t", (x, pw), lambda: dict(space(qc.qlinear_workspace_t), act_bits=5))]
+    others = [("qlinear_t", (x, pw, bias), dict), ("latent_delta_t", (a, b), dict), ("qlinear_t", (x.double(), pw), lambda: space(qc.qlinear_workspace_t)),
+              ("qlinear_t", (x.t(), pw), lambda: space(qc.qlinear_workspace_t)), ("latent_delta_t", (a, b.t()), lambda: small("out3", 3)),
+              ("cumulative_variation_t", (a, [b] * 9), lambda: small("out", 10)), ("cumulative_variation_t", (a, (b, a)), lambda: small("out", 3))]
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     for stream in (torch.cuda.current_stream(), side):
         with torch.cuda.stream(stream):
-            for name, args, options in calls:
+            for i, (name, args, options) in enumerate(own + others):
                 given = options()
-                want, got = outcome(qc._python_helpers[name], *args, **options()), outcome(getattr(qc, name), *args, **given)
+                want = outcome(qc._python_helpers[name], *args, **options())
+                if torch.is_tensor(want):
+                    want = want.clone()   # of the call that was given its output by position
+                handed_on.clear()
+                got = outcome(getattr(qc, name), *args, **given)
+                assert handed_on == ([] if i < len(own) else [name]), (name, given)
                 if isinstance(want, tuple):
                     assert got == want, (name, got, want)
                     continue
