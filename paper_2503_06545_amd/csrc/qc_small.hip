@@ -675,9 +675,11 @@ int pick_tile(int64_t M, int64_t N) {
 // launches (one scale for the tensor: three) and one, rotated, asymmetric, tensor: 2 x 1152 x 6912 8.0 5.1, 7.7 5.0, 8.8
 // 4.8; 64 x 1152 x 1152 7.6 6.1, 7.3 5.8, 8.9 7.5; 256 x 1152 x 1152 10.1 7.2, 10.4 7.1.
 // The longest rows on 16 x 32 tiles, the same input again and again | four in turn: 32 x 2816 x 4096 8.2 8.3 | 9.4 8.7, K = 2944 8.2 8.8
-// | 9.3 9.3, 4 bit 7.7 8.5 | 8.5 8.8: up to 22 groups on 16 rows (10 rows of 36 gain again, 0.91 of the time in two).  From 300 binary32 tokens
-// on the quantizer alone spreads over more CUs than the tiles do: 687 x 2560 x 565 13.6 13.5 | 12.9 14.0, K = 2912 14.2 15.8 | 13.2
-// 16.0, 446 x 2816 x 758 12.8 12.3 | 12.5 13.9: up to 20 groups on 16 rows there (asymmetric, where it costs more: not; 0.85 to 0.96 | 1.01 to 1.06).
+// | 9.3 9.3, 4 bit 7.7 8.5 | 8.5 8.8: up to 22 groups on 16 rows (10 rows of 36 gain again, 0.91 of the time in two).  Where
+// an XCD's L2 does not hold X beside the weights, what each of four channel tiles or more reads of it again comes from further away:
+// binary32 687 x 2560 x 565 13.6 13.5 | 12.9 14.0, K = 2912 14.2 15.8 | 13.2 16.0, 991 x 2688 x 46 11.2 13.3 | 10.3 13.5; bf16 991 x 3072 x 46 11.4
+// 11.2 | 9.7 12.4; but two or three channel tiles, 1091 x 2688 x 92, 11.5 8.9 | 10.5 10.1: up to 27 MB of it in all (asymmetric,
+// where a launch of the quantizer costs more: any; 0.85 to 0.96 | 1.01 to 1.06).
 struct FusedShape { TileShape tile; int waves, pairs; bool all_schemes; };   // pairs: most pairs of a row and a group that it is taken for
 constexpr FusedShape kFusedShapes[] = {{{16, 32}, 8, 192, true},   {{16, 32}, 16, 384, false}, {{16, 64}, 8, 192, true},
                                        {{16, 64}, 16, 384, false}, {{16, 128}, 16, 384, true}, {{32, 128}, 16, 288, false}};
@@ -695,8 +697,9 @@ int pick_fused_shape(int64_t M, int64_t N, int64_t K, size_t x_elem_bytes, Quant
         if (scheme == kQuantTensor && M > f.tile.tokens && M * K * (int64_t)x_elem_bytes > kTensorMost) continue;
         const int64_t rows = M < f.tile.tokens ? M : f.tile.tokens, groups = (K + kGroup - 1) / kGroup;
         if (rows * groups > f.pairs) continue;
-        const bool spread = M > 300 && x_elem_bytes == 4 && scheme != kQuantAsym;
-        if (rows == 16 && groups > (spread ? 20 : f.tile.channels == 32 ? 22 : 24)) continue;
+        if (rows == 16 && f.tile.channels == 32 && groups > 22) continue;
+        const int64_t x_bytes = M * K * (int64_t)x_elem_bytes, readers = live_channel_tiles(N, f.tile.channels);
+        if (scheme != kQuantAsym && readers >= 4 && x_bytes > 3 << 20 && readers * x_bytes > 27 << 20) continue;
         return i;
     }
     return -1;
