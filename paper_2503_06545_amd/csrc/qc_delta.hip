@@ -18,10 +18,10 @@
 //     instead of 6.6 for a similarity of 1.2 million; with more than 64, whose records a lane reads in two goes, 7.3 to 7.7 instead of
 //     6.2 to 6.4 for 1.18 to 1.31 million bf16 elements read again and again.  Each operation's limit (kOneMost) lies where it costs
 //     no more than two launches, over inputs read again and again too (one launch for a latent delta of
-//     540000 to 715000 elements 6 to 7.4 us where two took 4.6; for a binary32 similarity of 400000 5.5 and 4.5, of 655360 7.1 and
-//     4.6); only for the similarity of bf16 features, which a step asks for from the host, it lies where one launch takes what
-//     the host needs for two: 6.4 us for 1.31 million, where two launches take 5.0 in a graph.  us per call in a graph,
-//     four sets of inputs in turn, two launches and one:
+//     540000 to 715000 elements 6 to 7.4 us where two took 4.6).  Only the similarity's lies higher, for the calls from the
+//     host, which two launches take 7.1 us for whatever the size: binary32, in a graph and from the host, two launches and one, 400000
+//     4.5 5.5, 7.8 5.2, 524288 4.5 5.2, 7.3 6.2, 653550 5.1 6.0, 7.3 7.0; bf16, whose features a step asks for from the host, 1.31 million
+//     5.0 6.3, 7.1 6.4.  us per call in a graph, four sets of inputs in turn, two launches and one:
 //       latent delta     65536 4.5 3.7   300000 5.4 4.6   500000 5.7 5.6   700000 6.0 6.3   1 million 6.2 7.4
 //       similarity bf16  100000 4.8 4.0   300000 4.7 4.7   600000 5.4 5.6   1.3 million 5.6 6.5   1.7 million 5.4 7.4
 //       frame gradient   binary32 65536 4.1 3.4   250000 4.2 4.2   400000 4.0 5.1; bf16 500000 4.4 4.5   900000 4.2 5.5
@@ -239,7 +239,7 @@ struct SimilarityOp {
     static constexpr int kCount = 3, kElems = Pack<T>::kElems, kThreads = THREADS, kUnroll = 4, kOneUnroll = 2, kOneChunks = 2, kOuts = 4;
     static constexpr bool kSlabs = false;
     static constexpr size_t kBytes = kSimilarityBytes;
-    static constexpr int64_t kOneMost = sizeof(T) == 4 ? 9 << 15 : 5 << 18;
+    static constexpr int64_t kOneMost = sizeof(T) == 4 ? 1 << 19 : 5 << 18;
     const T *a, *b;
     struct Regs { Pack<T> x, y; };
     __device__ void load(Regs &r, int64_t i) const { r.x.stream(a + kElems * i); r.y.stream(b + kElems * i); }

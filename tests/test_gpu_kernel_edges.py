@@ -465,7 +465,7 @@ def test_similarity_on_both_sides_of_its_change_of_threads(n):
     assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
 
 
-@pytest.mark.parametrize("dtype,n,one_launch", [("f32", 9 << 15, True), ("f32", (9 << 15) + 1, False), ("f32", 482354, False),
+@pytest.mark.parametrize("dtype,n,one_launch", [("f32", 9 << 15, True), ("f32", 1 << 19, True), ("f32", (1 << 19) + 1, False), ("f32", 634887, False),
                                                 ("f32", 653550, False), ("bf16", 5 << 18, True), ("bf16", (5 << 18) + 1, False)])
 def test_similarity_in_one_launch_and_in_two(dtype, n, one_launch):
     """Which form a size takes shows in the workspace: one launch ends with zeros in its blocks' check words, every fourth
@@ -491,7 +491,7 @@ def test_one_launch_limits_of_similarity_and_gradient(dtype, extra):
     """The largest inputs of the one-launch form and the smallest beyond it, ragged ones among them."""
     rng = np.random.default_rng(extra)
     size = 4 if dtype == "f32" else 2
-    n = (9 << 15 if dtype == "f32" else 5 << 18) + extra
+    n = (1 << 19 if dtype == "f32" else 5 << 18) + extra
     a, b = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
     m = rng.standard_normal((2, (1 << 20) // size + extra)).astype(np.float32)
     if dtype == "bf16":
