@@ -415,10 +415,10 @@ __global__ __launch_bounds__(kGenericThreads) void quant_rows_generic_kernel(
 // 393 389, N = 3456 236 245 | 264 248 | 290 286; 162 MB, N = 3456 191 196 | 193 190 | 238 225, K = 4608, N =
 // 1152 79 82 | 81 81 | 124 114; 130 MB, K = 4608, asymmetric 72 74 | 73 75 | 103 102; 108 MB, N = 3456 129
 // 128 | 128 132 | 155 153).  Rows that are no whole lines, of which non-temporal loads fetch the shared lines twice, gain
-// from them only from 224 MB on, and from inputs that are not in the cache (MB of input and codes, K, N, ordinary and
+// from them only where input and codes do not fit the cache (MB of input and codes, K, N, ordinary and
 // non-temporal: 165, 544, 56 47 52 | 52 52 | 86 91; 177, 1552, 1152 103 110 | 106 111 | 144 155; 200, 1200, 64 51 58 | 63 65 | 105
-// 113; 195, 2576, 45 52 59 | 64 65 | 106 111; 200, 1552, 3456 250 257 | 251 260 | 292 307; but 245, 544, 1152 155 151 | 202 175 |
-// 216 221; 245, 1200, 1152 142 143 | 166 151 | 199 205).  With few channels of output whole lines gain as well, except from the same input
+// 113; 195, 2576, 45 52 59 | 64 65 | 106 111; 200, 1552, 3456 250 257 | 251 260 | 292 307; 245, 544, 1152 155 151 | 202 175 |
+// 216 221; 245, 1200, 1152 142 143 | 166 151 | 199 205; the quantizer alone, 245, 1168 44 54 | 55 55).  With few channels of output whole lines gain as well, except from the same input
 // again and again (165, 1152, 64 44 45 | 52 48 | 86 83; 237, 1152, 64 59 61 | 75 64 | 121 113; binary32 165, 1152, 288 48 52 | 55 50 | 97
 // 93).  Far beyond, M = 131072, K = 1152, they take the quantization from 80 to 69 us and
 // QKV whole from 562 to 502 us, also while the codes alone are a little larger than
@@ -434,7 +434,7 @@ int cache_policy(int64_t M, int64_t K, size_t x_elem_bytes) {
     const int64_t codes = M * K, input = codes * (int64_t)x_elem_bytes;
     const bool whole_lines = K * (int64_t)x_elem_bytes % 128 == 0;
     if (codes > kLastLevelCache * 9 / 8) return whole_lines ? kStreamBoth : kStreamStores;
-    return input + codes > kLastLevelCache * (whole_lines ? 5 : 7) / 8 ? kStreamLoads : kCachePlain;
+    return input + codes > kLastLevelCache * (whole_lines ? 5 : 8) / 8 ? kStreamLoads : kCachePlain;
 }
 
 // Units per lane of the row kernels.  One unit, a wavefront per 128 columns, where a block of 16

@@ -101,9 +101,9 @@ MB = 1 << 20
 @pytest.mark.parametrize("scheme", ["token", "rot", "asym"])
 def test_which_quantizers_load_past_the_caches(x, scheme):
     """Whole lines of 128 B from 160 MB of input and codes on, other rows, whose shared lines would be fetched twice, from
-    224 MB; the codes are stored past the caches from 288 MB of them on."""
+    256 MB; the codes are stored past the caches from 288 MB of them on."""
     size = 3 if x == "bf16" else 5
-    for K, from_mb in ((1152, 160), (4608, 160), (544, 224), (1200, 224), (1552, 224), (2576, 224)):
+    for K, from_mb in ((1152, 160), (4608, 160), (544, 256), (1200, 256), (1552, 256), (2576, 256)):
         if x == "f32" and K == 544:
             continue                                   # 17 whole lines
         for mb, loads in ((from_mb - 8, False), (from_mb + 8, True), (280, True)):
