@@ -679,7 +679,8 @@ int pick_tile(int64_t M, int64_t N) {
 // an XCD's L2 does not hold X beside the weights, what each of four channel tiles or more reads of it again comes from further away:
 // binary32 687 x 2560 x 565 13.6 13.5 | 12.9 14.0, K = 2912 14.2 15.8 | 13.2 16.0, 991 x 2688 x 46 11.2 13.3 | 10.3 13.5; bf16 991 x 3072 x 46 11.4
 // 11.2 | 9.7 12.4; but two or three channel tiles, 1091 x 2688 x 92, 11.5 8.9 | 10.5 10.1: up to 27 MB of it in all, asymmetric,
-// where a launch of the quantizer costs more, 34 (420 x 3024 x 1152, 43 MB, 13.8 16.3 | 13.1 15.9).
+// where a launch of the quantizer costs more, 34 (420 x 3024 x 1152, 43 MB, 13.8 16.3 | 13.1 15.9).  Tiles
+// of 32 tokens, whose rows are short, at any size (over 98 drawn calls one launch 0.88 | 1.05 of two).
 struct FusedShape { TileShape tile; int waves, pairs; bool all_schemes; };   // pairs: most pairs of a row and a group that it is taken for
 constexpr FusedShape kFusedShapes[] = {{{16, 32}, 8, 192, true},   {{16, 32}, 16, 384, false}, {{16, 64}, 8, 192, true},
                                        {{16, 64}, 16, 384, false}, {{16, 128}, 16, 384, true}, {{32, 128}, 16, 288, false}};
@@ -699,7 +700,7 @@ int pick_fused_shape(int64_t M, int64_t N, int64_t K, size_t x_elem_bytes, Quant
         if (rows * groups > f.pairs) continue;
         if (rows == 16 && f.tile.channels == 32 && groups > 22) continue;
         const int64_t x_bytes = M * K * (int64_t)x_elem_bytes, readers = live_channel_tiles(N, f.tile.channels);
-        if (readers >= 4 && x_bytes > 3 << 20 && readers * x_bytes > (scheme == kQuantAsym ? 34 : 27) << 20) continue;
+        if (f.tile.tokens == 16 && readers >= 4 && x_bytes > 3 << 20 && readers * x_bytes > (scheme == kQuantAsym ? 34 : 27) << 20) continue;
         return i;
     }
     return -1;

@@ -119,7 +119,7 @@ def test_which_quantizers_load_past_the_caches(x, scheme):
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,x,most", [(32, 4096, "bf16", 2816), (67, 1152, "f32", 2816), (10, 4096, "bf16", 4864), (1, 4096, "f32", 49152),
                                         (256, 1200, "f32", 3072), (687, 565, "f32", 2060), (687, 565, "bf16", 3072), (991, 46, "f32", 1784),
-                                        (1091, 92, "f32", 3072), (2687, 122, "f32", 3072), (100, 2048, "f32", 3072), (640, 1152, "f32", 1152)])
+                                        (1091, 92, "f32", 3072), (2687, 122, "f32", 3072), (100, 2048, "f32", 3072), (640, 1152, "f32", 1152), (800, 1152, "f32", 1152)])
 def test_the_longest_rows_that_are_quantized_in_the_launch_of_the_gemm(M, N, x, most, bits):
     assert qc.linear_plan(M, most, N, bits, x=x)["fused"]
     assert not qc.linear_plan(M, most + 2, N, bits, x=x)["fused"]
