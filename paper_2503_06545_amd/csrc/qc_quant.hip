@@ -30,6 +30,7 @@ enum CachePolicy {
     kStreamLoads = 1,   // non-temporal loads of X
     kStreamStores = 2,  // non-temporal stores of the codes
     kStreamBoth = 3,
+    kSkipPast = 4,      // with kStreamLoads: nothing is loaded for columns wholly past the row, see load_group()
 };
 
 // code = clamp(rne(x / s), -qmax, qmax): true IEEE division, then round half to even.
@@ -142,6 +143,19 @@ constexpr int kUnitsMost = 9 * kLanesPerRow * 8;  // units of the longest row: 8
 template <int UPT>
 constexpr int kMaxSlices = UPT == 9 ? 8 : 16;
 
+// Group i of the columns of a slice.  One wholly past the row loads the row's last piece once more, which does not
+// change a maximum.  Ordinary loads find that piece in the L1; non-temporal ones fetch its line again.  Under kSkipPast
+// such a group is the slice's first one over again instead, which begins inside the row (the quantizer alone, us for ordinary
+// loads, non-temporal ones and these, the same input again and again | four in turn: binary32, 195 MB of input and codes,
+// 304690 x 128 28 51 32 | 36 49 33, 81253 x 480 30 42 32 | 38 42 34; bf16, 245 MB, 182294 x 448 42 51 43 | 50 52 46.  Whole
+// linears, four in turn: 102673 x 480 x 1152 142 128 123, 183344 x 448 x 1152 227 205 198).
+template <typename XT, int POLICY, int UPT>
+__device__ inline void load_group(Group<XT> (&u)[UPT], int i, const XT *xrow, int slice, int K, int sub) {
+    const int col0 = (slice * UPT + i) * kGroup;
+    if ((POLICY & kSkipPast) != 0 && i > 0 && __builtin_amdgcn_readfirstlane(col0) >= K) u[i] = u[0];
+    else u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, col0, K, sub);
+}
+
 // TENSOR: the absmax comes from `tmax` (one scale for the whole tensor).  A template parameter
 // rather than a test of tmax.partials, so that the per-token kernel is compiled exactly as if
 // the other did not exist.  RAGGED: a K that is no multiple of 16, for the fragment layout only; the
@@ -167,7 +181,7 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_kernel(
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
         if constexpr (RAGGED) u[i].load_ragged(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
-        else u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
+        else load_group<XT, POLICY, UPT>(u, i, xrow, slice, (int)K, sub);
     }
     if constexpr (RAGGED) {
 #pragma unroll
@@ -239,7 +253,7 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_rot_kernel(
     Group<XT> u[UPT];
 #pragma unroll
     for (int i = 0; i < UPT; ++i)
-        u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, label);
+        load_group<XT, POLICY, UPT>(u, i, xrow, slice, (int)K, label);
 
     const Rotation<XT> rotation(rot, label);
     float f[UPT][kUnit];
@@ -311,7 +325,7 @@ __global__ __launch_bounds__(64 * kMaxSlices<UPT>) void quant_rows_asym_kernel(
     Group<XT> u[UPT];
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
-        u[i].template load<(POLICY & kStreamLoads) != 0>(xrow, (slice * UPT + i) * kGroup, (int)K, sub);
+        load_group<XT, POLICY, UPT>(u, i, xrow, slice, (int)K, sub);
     }
 
     float lo = __builtin_inff(), hi = -__builtin_inff();
@@ -458,10 +472,20 @@ dim3 row_block(int64_t K, int upt) {
 template <typename F>
 void with_row_variant(int64_t M, int64_t K, size_t x_elem_bytes, F &&f) {
     const int upt = units_per_lane(M, K), policy = cache_policy(M, K, x_elem_bytes);
+    // Full rows have nothing to skip and lose up to 5 % by the test (202549 x 1152 bf16 114 to 118 us).  It is worth it where
+    // a third or more of the wavefronts' columns are past the row: in binary32 K = 480 of 768 columns takes 0.82 to 0.84 of
+    // the time without it, 512 of them 0.93 to 0.96, in bf16 512 as much or more.
+    const int64_t columns = (K + 3 * kGroup - 1) / (3 * kGroup) * (3 * kGroup);
+    const bool skip = upt == 3 && 2 * columns > 3 * K;
     auto with_policy = [&](auto u) {
         if (policy == kStreamBoth) f(std::integral_constant<int, kStreamBoth>{}, u);
         else if (policy == kStreamStores) f(std::integral_constant<int, kStreamStores>{}, u);
-        else if (policy == kStreamLoads) f(std::integral_constant<int, kStreamLoads>{}, u);
+        else if (policy == kStreamLoads) {
+            if constexpr (decltype(u)::value == 3) {
+                if (skip) return f(std::integral_constant<int, kStreamLoads | kSkipPast>{}, u);
+            }
+            f(std::integral_constant<int, kStreamLoads>{}, u);
+        }
         else f(std::integral_constant<int, kCachePlain>{}, u);
     };
     if (upt == 1) f(std::integral_constant<int, kCachePlain>{}, std::integral_constant<int, 1>{});  // small: plain

@@ -81,6 +81,28 @@ def test_rotated_rows_shorter_than_a_wavefronts_columns(M, K, rot_block, dtype):
     assert torch.equal(sx[n:], sx[:-n]) and torch.equal(qx[n:], qx[:-n])
 
 
+@pytest.mark.parametrize("scheme", ["token", "rot", "asym"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 416, 448, 480, 512])
+def test_rows_streamed_without_the_columns_past_their_end(K, dtype, scheme):
+    """Non-temporal loads on rows that leave a third or more of their wavefronts' columns empty, and on the shortest that do
+    not (256, 512; of 416 binary32 is whole lines): the first rows against the oracle, the others, with a remainder of three, against those."""
+    M = (180 << 20) // ((5 if dtype == "f32" else 3) * K) // 40 * 40 + 3
+    assert qc.linear_plan(M, K, 64, x=dtype, scheme=scheme)["nt_loads"] == (K * (4 if dtype == "f32" else 2) % 128 == 0)
+    rng = np.random.default_rng(K)
+    x = random_x(rng, 40, K, dtype)
+    X = dev(x).repeat(-(-M // 40), 1)[:M].contiguous()
+    if scheme == "asym":
+        got, want = qc.quant_act_asym_t(X, 8), oracle.quant_act_asym(x, 8)
+    else:
+        rot = 32 if scheme == "rot" else 0
+        got, want = qc.quant_act_t(X, 8, rot), oracle.quant_act_rot(x, rot, 8) if rot else oracle.quant_act(x, 8)
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert np.array_equal(g[:40].cpu().numpy(), w)
+        assert torch.equal(g[40:], g[:-40])
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N", [
     (1, 16, 1), (2, 9216, 40), (3, 6144, 33), (16, 1536, 4100), (16, 1552, 70), (17, 1152, 128), (31, 1280, 2050),
