@@ -406,7 +406,7 @@ __global__ __launch_bounds__(THREADS) void reduce_kernel(Op op, int64_t n, int64
 }
 
 // one wavefront: fixed-order combine of the partial sums, four blocks' a lane (with a thread per block, and the four wavefronts'
-// sums through LDS, us in a graph: latent delta of 4 million 6.34 6.20, frame gradient 5.30 5.20, variation over 8 tensors of 1 million
+// sums through LDS, against this, us in a graph: latent delta of 4 million 6.34 6.20, frame gradient 5.30 5.20, variation over 8 tensors of 1 million
 // 8.71 8.29, similarity of 4 million 6.67 6.56; nowhere faster)
 template <typename Op>
 __global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__restrict__ partials, int count,
